@@ -128,9 +128,10 @@ typedef struct galore_ctx galore_ctx; /* opaque; OWNED by the library; host memo
 const char* galore_status_string(galore_status s);
 
 /* Workspace, in bytes, that lets one call process up to 8 consecutive tensors of the
- * list per kernel launch (transients R and N of the step, plus, for a bf16 tensor with
+ * list per kernel launch (transients R and N of the step; R up to four times, where a projection of few
+ * tiles may cut its contraction into pieces; for a bf16 tensor with
  * rows <= cols, rows a multiple of 64 and cols not a multiple of 8, a copy of G with its rows
- * padded to a multiple of 8 elements, which the projection then reads instead of G; Gram
+ * padded to a multiple of 8 elements, which the projection may then read instead of G; Gram
  * matrix, iteration blocks and reflector storage of the refresh).  Any 256-byte-aligned workspace at least as
  * large as the largest single-tensor need is accepted by galore_init; a smaller one
  * only means more, smaller launches.  What a call's transients leave free of its share of the
@@ -168,7 +169,7 @@ galore_status galore_step(galore_ctx* ctx, const galore_tensor* W, const galore_
  * the array (galore_set_concurrency and galore_set_call_overlap do not apply; pending overlapped
  * calls are joined first).
  * Limits: GALORE_ERR_WORKSPACE if one tensor's transients exceed the array (4 r max(rows, cols) bytes
- * of R plus s r max(rows, cols) of N, s = element size of W; every tensor of the LLaMA 60M ... 7B
+ * of R, up to four times where the projection may be cut into pieces (fewer than 224 tiles of 64 x 64), plus s r max(rows, cols) of N, s = element size of W; every tensor of the LLaMA 60M ... 7B
  * stacks at the paper's ranks fits); GALORE_ERR_UNIMPLEMENTED if auto_refresh is on and a tensor of
  * the call is due for a subspace refresh (t mod T == 0: the refresh needs hundreds of MB; take that
  * step with galore_step); GALORE_ERR_INVALID_ARG between galore_profile_start and _stop.  On any
@@ -209,11 +210,12 @@ galore_status galore_refresh_subspace(galore_ctx* ctx, const galore_tensor* G, i
  * sequence of calls results are bit-identical from run to run. */
 galore_status galore_set_concurrency(galore_ctx* ctx, int32_t lanes);
 
-/* Adam inside the projection (off by default; 1 = on).  When on, a bf16 tensor with fp32 moments whose
- * projection runs on the large-tile kernel gets the update block of Algorithm 2 (moments, bias correction,
- * N) computed in that GEMM's epilogue, on the accumulators: R is never written to memory and read back,
- * and the step of such a tensor is two kernels instead of three.  Other tensors (fp32, 8-bit moments,
- * shapes the large-tile kernel does not take) keep the separate Adam kernel.  Both paths evaluate the
+/* Adam inside the projection (off by default; 1 = on).  When on, a tensor with fp32 moments gets the update block of
+ * Algorithm 2 (moments, bias correction, N) computed in its projection GEMM's epilogue, on the accumulators: R is never
+ * written to memory and read back, and the step of such a tensor is two kernels instead of three.  Exceptions keep the
+ * separate Adam kernel: 8-bit moments, a projection whose contraction is cut into pieces (few tiles), a side of fewer
+ * than 8 elements.  When off, tensors that share a small launch may still take the epilogue where the library expects
+ * it to be faster.  Both paths evaluate the
  * same fp32 expression on the same R: W, M, V are bit-identical between the two settings. */
 galore_status galore_set_fused_adam(galore_ctx* ctx, int32_t on);
 

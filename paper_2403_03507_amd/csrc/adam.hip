@@ -4,6 +4,8 @@
 // are read and M, V written with non-temporal accesses (each is touched once per step and the
 // stack's moments are far larger than the caches), N is written normally because the
 // back-projection GEMM reads it next.  Measured at 7B: 0.210 -> 0.204 ms per layer set.
+#include <algorithm>
+
 #include "adam_entry.hpp"
 #include "common.hpp"
 
@@ -59,131 +61,240 @@ __global__ __launch_bounds__(256) void adam_group_kernel(const AdamGroup grp) {
   }
 }
 
-// Same update, but N is written transposed (cols x rows): the back-projection GEMM then finds
-// its contraction index contiguous in memory.  One block per 64 x 64 tile: R, M, V are read and
-// M, V written row-wise with 16-byte vectors, N goes through a padded LDS tile and leaves
-// column-wise, again as 16-byte vectors.  Ragged or unaligned tiles take an element-wise path.
 // 16-byte access to four floats that are only 4-byte aligned (rows of odd length): the compiler picks
 // the widest access the target allows at that alignment
 __device__ __forceinline__ f32x4 load4(const float* p) { f32x4 v; __builtin_memcpy(&v, p, sizeof v); return v; }
 __device__ __forceinline__ void store4(float* p, f32x4 v) { __builtin_memcpy(p, &v, sizeof v); }
 
-// RAGGED: some tile of the launch is not a full, aligned 64 x 64 tile.  The variant without that path needs 48 registers
-// per lane instead of 55 (bf16 N), which is what lets a wavefront of it share a SIMD with the two wavefronts of the
-// projection GEMM (2 x 232 of the 512 registers per lane): the Adam pass of one call then runs on the CUs that the
-// projection of the next call occupies.
-template <class TN, bool RAGGED>
+
+// The update with N transposed (cols x rows) for problems with transpose_n, the back-projection GEMM's layout for a LEFT
+// tensor, and row-wise for the others, in one launch.  One workgroup per 64 x 64 tile: R (or the slabs it is the sum of),
+// M, V are read and M, V written row-wise in 16-byte pieces at element alignment; all pieces of a thread are requested
+// before the first is used (as one piece after the other the kernel was a chain of four memory round trips per tile).
+// A transposed N goes through a padded LDS tile and leaves column-wise in 16-byte pieces as well.
+template <class TN>
+__global__ __launch_bounds__(256) void adam_tile_group_kernel(const AdamGroup grp) {
+  constexpr int TS = 64;
+  constexpr int VEC = 16 / sizeof(TN);
+  __shared__ __align__(16) TN tile[TS][TS + VEC];  // tile[j][i] = N[i][j]
+  const AdamProblem& pr = grp.p[blockIdx.y];
+  const int rows = pr.rows, cols = pr.cols, ldr = pr.ldr, slabs = pr.slabs;
+  const int64_t stride = pr.slab_stride;
+  const int tiles_c = (cols + TS - 1) / TS;
+  const int ntiles = tiles_c * ((rows + TS - 1) / TS);
+  const float beta1 = grp.beta1, beta2 = grp.beta2, eps = grp.eps;
+  const float ic1 = pr.inv_c1, ic2 = pr.inv_c2;
+  const bool tr = pr.transpose_n != 0;
+  const float* __restrict__ R = pr.R;
+  float* __restrict__ M = pr.M;
+  float* __restrict__ V = pr.V;
+  TN* __restrict__ N = static_cast<TN*>(pr.N);
+  for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
+    const int i0 = (t / tiles_c) * TS, j0 = (t % tiles_c) * TS;
+    const int j = j0 + (threadIdx.x & 15) * 4;
+    const bool whole = j + 4 <= cols;
+    const int jc = whole ? j : 0;  // lanes without a whole piece read the row's first elements and leave them alone (cols >= 4 there)
+    f32x4 g[4], m[4], v[4];
+    if (cols >= 4) {
+#pragma unroll
+      for (int ps = 0; ps < 4; ++ps) {
+        const int i = i0 + ps * 16 + (threadIdx.x >> 4), ic = i < rows ? i : rows - 1;
+        const float* Ri = R + (size_t)ic * ldr + jc;
+        g[ps] = load4(Ri);
+        m[ps] = load4(M + (size_t)ic * cols + jc);
+        v[ps] = load4(V + (size_t)ic * cols + jc);
+      }
+      for (int s = 1; s < slabs; s += 2) {  // two slabs of all pieces at a time, added in slab order
+        const float* Rs = R + s * stride;
+        const int64_t second = s + 1 < slabs ? stride : 0;
+        f32x4 x[2][4];
+#pragma unroll
+        for (int ps = 0; ps < 4; ++ps) {
+          const int i = i0 + ps * 16 + (threadIdx.x >> 4), ic = i < rows ? i : rows - 1;
+          x[0][ps] = load4(Rs + (size_t)ic * ldr + jc);
+          x[1][ps] = load4(Rs + second + (size_t)ic * ldr + jc);
+        }
+#pragma unroll
+        for (int ps = 0; ps < 4; ++ps) {
+          g[ps] += x[0][ps];
+          if (second) g[ps] += x[1][ps];
+        }
+      }
+    }
+#pragma unroll
+    for (int ps = 0; ps < 4; ++ps) {
+      const int i = i0 + ps * 16 + (threadIdx.x >> 4);
+      if (i >= rows || j >= cols) continue;
+      float n[4];
+      if (whole) {
+        f32x4 mo, vo;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          float me = m[ps][e], ve = v[ps][e];
+          n[e] = adam_entry(g[ps][e], me, ve, beta1, beta2, eps, ic1, ic2);
+          mo[e] = me; vo[e] = ve;
+        }
+        store4(M + (size_t)i * cols + j, mo);
+        store4(V + (size_t)i * cols + j, vo);
+      } else {  // the piece that straddles the end of the row
+#pragma unroll
+        for (int e = 0; e < 3; ++e) {
+          n[e] = 0.f;
+          if (j + e < cols) {
+            const float* p = R + (size_t)i * ldr + j + e;
+            float ge = *p;
+            for (int s = 1; s < slabs; ++s) ge += p[s * stride];
+            float me = M[(size_t)i * cols + j + e], ve = V[(size_t)i * cols + j + e];
+            n[e] = adam_entry(ge, me, ve, beta1, beta2, eps, ic1, ic2);
+            M[(size_t)i * cols + j + e] = me;
+            V[(size_t)i * cols + j + e] = ve;
+          }
+        }
+        n[3] = 0.f;
+      }
+      if (tr) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) tile[j - j0 + e][i - i0] = (TN)n[e];
+      } else {
+        TN o[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = (TN)n[e];
+        TN* dst = N + (size_t)i * cols + j;
+        if (whole) __builtin_memcpy(dst, o, sizeof o);
+        else
+#pragma unroll
+          for (int e = 0; e < 3; ++e)
+            if (j + e < cols) dst[e] = o[e];
+      }
+    }
+    if (tr) {
+      __syncthreads();
+      constexpr int LPR = TS / VEC;        // lanes per output row
+      constexpr int RPP = 256 / LPR;       // output rows per pass
+#pragma unroll
+      for (int ps = 0; ps < TS / RPP; ++ps) {
+        const int jj = ps * RPP + threadIdx.x / LPR, i = (threadIdx.x % LPR) * VEC;
+        if (j0 + jj >= cols || i0 + i >= rows) continue;
+        TN* dst = N + (size_t)(j0 + jj) * rows + i0 + i;
+        if (i0 + i + VEC <= rows) {
+          const uint4 o = *reinterpret_cast<const uint4*>(&tile[jj][i]);
+          __builtin_memcpy(dst, &o, sizeof o);
+        } else {
+#pragma unroll
+          for (int e = 0; e < VEC; ++e)
+            if (i0 + i + e < rows) dst[e] = tile[jj][i + e];
+        }
+      }
+      __syncthreads();
+    }
+  }
+}
+
+// Transposing variant for launches whose tiles are all full and aligned (every LEFT tensor of a large stack) and whose R is
+// one matrix: R, M, V row-wise with 16-byte non-temporal accesses, one 16-element trip of a thread at a time.  48 registers
+// per lane (bf16 N), which is what lets a wavefront of it share a SIMD with the two wavefronts of the projection GEMM
+// (2 x 232 of the 512 registers per lane): the Adam pass of one call then runs on the CUs that the projection of the next
+// call occupies.
+template <class TN>
 __global__ __launch_bounds__(256) void adam_transpose_group_kernel(const AdamGroup grp) {
   constexpr int TS = 64;
   constexpr int VEC = 16 / sizeof(TN);          // N elements per 16 bytes
   __shared__ __align__(16) TN tile[TS][TS + VEC];  // tile[j][i] = N[i][j]
   const AdamProblem& pr = grp.p[blockIdx.y];
   const int rows = pr.rows, cols = pr.cols, ldr = pr.ldr;
-  const int tiles_c = (cols + TS - 1) / TS;
-  const int ntiles = tiles_c * ((rows + TS - 1) / TS);
+  const int tiles_c = cols / TS;
+  const int ntiles = tiles_c * (rows / TS);
   const float beta1 = grp.beta1, beta2 = grp.beta2, eps = grp.eps;
   const float ic1 = pr.inv_c1, ic2 = pr.inv_c2;
   const float* __restrict__ R = pr.R;
   float* __restrict__ M = pr.M;
   float* __restrict__ V = pr.V;
   TN* __restrict__ N = static_cast<TN*>(pr.N);
-  const bool cols4 = cols % 4 == 0 && ldr % 4 == 0 && ((reinterpret_cast<uintptr_t>(R) | reinterpret_cast<uintptr_t>(M) | reinterpret_cast<uintptr_t>(V)) & 15) == 0;
-  const bool aligned = rows % VEC == 0;  // rows of N^T stay 16-byte aligned; R, M, V rows may be of any length
   for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
     const int i0 = (t / tiles_c) * TS, j0 = (t % tiles_c) * TS;
-    const bool full = aligned && i0 + TS <= rows && j0 + TS <= cols;
-    if (full) {
-      // tile origin as a (wave-uniform) pointer, in-tile offsets in 32 bits: fewer address registers per lane
-      const float* __restrict__ Rt = R + ((size_t)i0 * ldr + j0);
-      float* __restrict__ Mt = M + ((size_t)i0 * cols + j0);
-      float* __restrict__ Vt = V + ((size_t)i0 * cols + j0);
+    // tile origin as a (wave-uniform) pointer, in-tile offsets in 32 bits: fewer address registers per lane
+    const float* __restrict__ Rt = R + ((size_t)i0 * ldr + j0);
+    float* __restrict__ Mt = M + ((size_t)i0 * cols + j0);
+    float* __restrict__ Vt = V + ((size_t)i0 * cols + j0);
 #pragma unroll 1
-      for (int ps = 0; ps < 4; ++ps) {
-        const int i = ps * 16 + (threadIdx.x >> 4), j = (threadIdx.x & 15) * 4;
-        const int idx = i * cols + j;
-        const int ridx = i * ldr + j;
-        f32x4 g, m, v;
-        if (cols4) {
-          g = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(Rt + ridx));
-          m = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(Mt + idx));
-          v = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(Vt + idx));
-        } else {
-          g = load4(Rt + ridx); m = load4(Mt + idx); v = load4(Vt + idx);
-        }
+    for (int ps = 0; ps < 4; ++ps) {
+      const int i = ps * 16 + (threadIdx.x >> 4), j = (threadIdx.x & 15) * 4;
+      const int idx = i * cols + j;
+      const int ridx = i * ldr + j;
+      const f32x4 g = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(Rt + ridx));
+      f32x4 m = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(Mt + idx));
+      f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(Vt + idx));
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          float me = m[e], ve = v[e];
-          tile[j + e][i] = (TN)adam_entry(g[e], me, ve, beta1, beta2, eps, ic1, ic2);
-          m[e] = me; v[e] = ve;
-        }
-        if (cols4) {
-          __builtin_nontemporal_store(m, reinterpret_cast<f32x4*>(Mt + idx));
-          __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(Vt + idx));
-        } else {
-          store4(Mt + idx, m);
-          store4(Vt + idx, v);
-        }
+      for (int e = 0; e < 4; ++e) {
+        float me = m[e], ve = v[e];
+        tile[j + e][i] = (TN)adam_entry(g[e], me, ve, beta1, beta2, eps, ic1, ic2);
+        m[e] = me; v[e] = ve;
       }
-      __syncthreads();
-      constexpr int LPR = TS / VEC;        // lanes per output row
-      constexpr int RPP = 256 / LPR;       // output rows per pass
-#pragma unroll
-      for (int ps = 0; ps < TS / RPP; ++ps) {
-        const int j = ps * RPP + threadIdx.x / LPR, i = (threadIdx.x % LPR) * VEC;
-        *reinterpret_cast<uint4*>(N + (size_t)(j0 + j) * rows + i0 + i) = *reinterpret_cast<const uint4*>(&tile[j][i]);
-      }
-      __syncthreads();
-    } else if constexpr (RAGGED) {
-      for (int e = threadIdx.x; e < TS * TS; e += 256) {
-        const int i = e / TS, j = e % TS;
-        if (i0 + i < rows && j0 + j < cols) {
-          const size_t idx = (size_t)(i0 + i) * cols + j0 + j;
-          float me = M[idx], ve = V[idx];
-          const float n = adam_entry(R[(size_t)(i0 + i) * ldr + j0 + j], me, ve, beta1, beta2, eps, ic1, ic2);
-          M[idx] = me; V[idx] = ve;
-          N[(size_t)(j0 + j) * rows + i0 + i] = (TN)n;
-        }
-      }
+      __builtin_nontemporal_store(m, reinterpret_cast<f32x4*>(Mt + idx));
+      __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(Vt + idx));
     }
+    __syncthreads();
+    constexpr int LPR = TS / VEC;        // lanes per output row
+    constexpr int RPP = 256 / LPR;       // output rows per pass
+#pragma unroll
+    for (int ps = 0; ps < TS / RPP; ++ps) {
+      const int j = ps * RPP + threadIdx.x / LPR, i = (threadIdx.x % LPR) * VEC;
+      *reinterpret_cast<uint4*>(N + (size_t)(j0 + j) * rows + i0 + i) = *reinterpret_cast<const uint4*>(&tile[j][i]);
+    }
+    __syncthreads();
   }
 }
 
+// A launch whose problems are all streams of full, aligned tiles and large enough to be bound by HBM goes to the lean
+// kernels, one launch per orientation; everything else runs as one launch of the tile kernel.  ENTRIES_LEAN below.
 hipError_t launch_adam_group(const AdamGroup& g, DType n_dtype, hipStream_t stream) {
   if (g.count <= 0) return hipSuccess;
   if (g.count > kMaxGroup) return hipErrorInvalidValue;
-  for (int i = 0; i < g.count; ++i)  // padded rows of R are a feature of the transposing kernel only
-    if (g.p[i].ldr < g.p[i].cols || (!g.p[0].transpose_n && g.p[i].ldr != g.p[i].cols)) return hipErrorInvalidValue;
-  if (g.p[0].transpose_n) {
+  constexpr int64_t ENTRIES_LEAN = (int64_t)4 << 20;
+  AdamGroup lean[2] = {}, rest{};
+  int64_t entries = 0;
+  for (int i = 0; i < g.count; ++i) entries += g.p[i].count;
+  for (AdamGroup* x : {&lean[0], &lean[1], &rest}) { x->beta1 = g.beta1; x->beta2 = g.beta2; x->eps = g.eps; }
+  for (int i = 0; i < g.count; ++i) {
+    const AdamProblem& p = g.p[i];
+    if (p.rows < 1 || p.cols < 1) continue;
+    if (p.ldr < p.cols || (!p.transpose_n && p.ldr != p.cols)) return hipErrorInvalidValue;  // padded rows of R only with transpose_n
+    const bool aligned = ((reinterpret_cast<uintptr_t>(p.R) | reinterpret_cast<uintptr_t>(p.M) | reinterpret_cast<uintptr_t>(p.V) | reinterpret_cast<uintptr_t>(p.N)) & 15) == 0 && p.ldr % 4 == 0;
+    const bool full = !p.transpose_n || (p.rows % 64 == 0 && p.cols % 64 == 0);
+    AdamGroup& to = entries >= ENTRIES_LEAN && aligned && full && p.slabs <= 1 ? lean[p.transpose_n ? 1 : 0] : rest;
+    to.p[to.count++] = p;
+  }
+  if (lean[1].count > 0) {
     int64_t maxtiles = 0;
-    for (int i = 0; i < g.count; ++i) {
-      const int64_t t = (int64_t)((g.p[i].rows + 63) / 64) * ((g.p[i].cols + 63) / 64);
-      maxtiles = t > maxtiles ? t : maxtiles;
-    }
-    if (maxtiles == 0) return hipSuccess;
-    const dim3 grid((unsigned)(maxtiles > 4096 ? 4096 : maxtiles), (unsigned)g.count);
-    // every tile of every problem full and 16-byte aligned on the N side: the lean variant
-    bool ragged = false;
-    for (int i = 0; i < g.count; ++i) ragged = ragged || g.p[i].rows % 64 != 0 || g.p[i].cols % 64 != 0;
-    if (n_dtype == DType::BF16) {
-      if (ragged) hipLaunchKernelGGL((adam_transpose_group_kernel<__bf16, true>), grid, dim3(256), 0, stream, g);
-      else hipLaunchKernelGGL((adam_transpose_group_kernel<__bf16, false>), grid, dim3(256), 0, stream, g);
-    } else {
-      if (ragged) hipLaunchKernelGGL((adam_transpose_group_kernel<float, true>), grid, dim3(256), 0, stream, g);
-      else hipLaunchKernelGGL((adam_transpose_group_kernel<float, false>), grid, dim3(256), 0, stream, g);
-    }
+    for (int i = 0; i < lean[1].count; ++i) maxtiles = std::max(maxtiles, (int64_t)(lean[1].p[i].rows / 64) * (lean[1].p[i].cols / 64));
+    const dim3 grid((unsigned)(maxtiles > 4096 ? 4096 : maxtiles), (unsigned)lean[1].count);
+    if (n_dtype == DType::BF16) hipLaunchKernelGGL(adam_transpose_group_kernel<__bf16>, grid, dim3(256), 0, stream, lean[1]);
+    else hipLaunchKernelGGL(adam_transpose_group_kernel<float>, grid, dim3(256), 0, stream, lean[1]);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  if (lean[0].count > 0) {
+    int64_t maxcount = 0;
+    for (int i = 0; i < lean[0].count; ++i) maxcount = std::max(maxcount, lean[0].p[i].count);
+    // 4 elements per thread per trip; enough blocks for ~4 trips each, capped to fill the chip a few times over
+    int64_t blocks = (maxcount / 4 + 256 * 4 - 1) / (256 * 4);
+    if (blocks < 1) blocks = 1;
+    if (blocks > 2048) blocks = 2048;
+    const dim3 grid((unsigned)blocks, (unsigned)lean[0].count);
+    if (n_dtype == DType::BF16) hipLaunchKernelGGL(adam_group_kernel<__bf16>, grid, dim3(256), 0, stream, lean[0]);
+    else hipLaunchKernelGGL(adam_group_kernel<float>, grid, dim3(256), 0, stream, lean[0]);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  if (rest.count > 0) {
+    int64_t maxtiles = 0;
+    for (int i = 0; i < rest.count; ++i) maxtiles = std::max(maxtiles, (int64_t)((rest.p[i].rows + 63) / 64) * ((rest.p[i].cols + 63) / 64));
+    const dim3 grid((unsigned)(maxtiles > 4096 ? 4096 : maxtiles), (unsigned)rest.count);
+    if (n_dtype == DType::BF16) hipLaunchKernelGGL(adam_tile_group_kernel<__bf16>, grid, dim3(256), 0, stream, rest);
+    else hipLaunchKernelGGL(adam_tile_group_kernel<float>, grid, dim3(256), 0, stream, rest);
     return hipGetLastError();
   }
-  int64_t maxcount = 0;
-  for (int i = 0; i < g.count; ++i) maxcount = g.p[i].count > maxcount ? g.p[i].count : maxcount;
-  if (maxcount == 0) return hipSuccess;
-  // 4 elements per thread per trip; enough blocks for ~4 trips each, capped to fill the chip a few times over
-  int64_t blocks = (maxcount / 4 + 256 * 4 - 1) / (256 * 4);
-  if (blocks < 1) blocks = 1;
-  if (blocks > 2048) blocks = 2048;
-  dim3 grid((unsigned)blocks, (unsigned)g.count);
-  if (n_dtype == DType::BF16) hipLaunchKernelGGL(adam_group_kernel<__bf16>, grid, dim3(256), 0, stream, g);
-  else hipLaunchKernelGGL(adam_group_kernel<float>, grid, dim3(256), 0, stream, g);
-  return hipGetLastError();
+  return hipSuccess;
 }
 
 // One aligned 16-byte piece of dst per thread and trip; the source piece is read with whatever

@@ -93,7 +93,6 @@ struct galore_ctx {
   // wait until galore_join.  The chunk on stream h uses share h of the workspace (one of `slots`
   // equal parts), so stream order alone protects the workspace.
   bool fused_adam = false;        // Adam in the epilogue of the projection launch (galore_set_fused_adam)
-  bool merged_projection = true;  // LEFT and RIGHT projections of the large-tile kernel in one launch (see gemm_proj_dl.hpp)
   bool overlap_calls = false;
   int slots = 2;
   bool unjoined = false;          // library streams hold work the context's stream has not waited for
@@ -164,17 +163,34 @@ namespace {
 
 
 
+// ---- which kernel projects a tensor ------------------------------------------------------------
+// A launch with enough 256 x 256 tiles runs on the large-tile kernel (kLargeProjectionTiles), otherwise on small tiles,
+// in K pieces where even those leave CUs idle.  Both kernels add the products of an entry in the same order, so the choice
+// does not show in the results; pieces do, hence none for contractions under 512 (galore_set_concurrency promises that).
+
+// Tensors the large-tile kernel may take: tiles of 256 rows mostly used along r.  Where G has to be copied first (rows of
+// no multiple of 8 elements) only at high ranks: a 4096 / 11007 layer at r = 1024 takes 1144 us against 1192 on small
+// tiles, at r = 256 470 against 446, two 2048 / 5461 layers at r = 512 466 against 409.
+bool large_projection_eligible(bool left, int64_t kdim, int64_t ldim, int64_t r, DType dt) {
+  if (dt != DType::BF16 || kdim % 64 != 0 || r < 8 || (!left && r % 8 != 0)) return false;
+  if (10 * r < 7 * ((r + 255) / 256 * 256)) return false;
+  return !left || ldim % 8 == 0 || (r > 512 && ldim >= 8);
+}
+int64_t tiles64(int64_t ldim, int64_t r) { return ((r + 63) / 64) * ((ldim + 63) / 64); }
+
 // The large-tile GEMM moves aligned 16-byte pieces, so G of a LEFT bf16 tensor (contiguous along n, the
 // GEMM's N index) cannot feed it when n is not a multiple of 8: its rows start at odd element offsets.
 // The projection of such a tensor reads a copy of G with the rows padded to a multiple of 8 (zeros) and
 // writes R with the same padded row length; the copy costs one pass over G and buys the 256 x 256 tiles.
-// Returns the row length of R: ldim itself when nothing is padded.
+// Returns the longest row of R: ldim itself when nothing is padded.  (The workspace keeps room for the copy at every
+// rank; whether it is made is large_projection_eligible's choice.)
 int64_t projected_row_length(bool left, int64_t kdim, int64_t ldim, DType dt) {
   const bool pad = left && dt == DType::BF16 && ldim % 8 != 0 && ldim >= 8 && kdim % 64 == 0;
   return pad ? (ldim + 7) / 8 * 8 : ldim;
 }
-size_t step_r_bytes(bool left, int64_t kdim, int64_t ldim, int64_t r, DType dt) {
-  return align_up((size_t)r * projected_row_length(left, kdim, ldim, dt) * 4);
+size_t step_r_bytes(bool left, int64_t kdim, int64_t ldim, int64_t r, DType dt) {  // room for the most pieces any launch group gives the tensor
+  const int64_t pieces = tile_pieces((long)tiles64(ldim, r), kdim, dt);
+  return align_up((size_t)pieces * r * projected_row_length(left, kdim, ldim, dt) * 4);
 }
 size_t step_n_bytes(int64_t ldim, int64_t r, DType dt) { return align_up((size_t)r * ldim * dtype_size(dt)); }
 size_t step_gpad_bytes(bool left, int64_t kdim, int64_t ldim, DType dt) {
@@ -225,11 +241,12 @@ struct StepItem {
   const galore_tensor* G;
   float* R;
   void* N;
-  void* Gpad;    // copy of G with padded rows (see projected_row_length), or nullptr
-  int64_t ldr;   // row length of R
+  void* Gpad;    // room for a copy of G with padded rows (see projected_row_length), or nullptr
+  int64_t ldr;   // row length of R, set by the projection
+  int pieces;    // slabs of R, set by the projection
 };
 
-galore_status run_chain(galore_ctx* ctx, const std::vector<StepItem>& items, float lr, hipStream_t stream,
+galore_status run_chain(galore_ctx* ctx, std::vector<StepItem>& items, float lr, hipStream_t stream,
                         float* slabs = nullptr, size_t slab_bytes = 0) {
   const galore_hparams& hp = ctx->hp;
   const int r = hp.rank;
@@ -253,72 +270,116 @@ galore_status run_chain(galore_ctx* ctx, const std::vector<StepItem>& items, flo
       if (e != hipSuccess) return hip_fail(ctx, e, "projector transpose launch");
     }
     // K1: project.  Both operands are read from layouts in which as much as possible is
-    // contiguous along the contraction index; only G of a LEFT tensor is not.  bf16 tensors that meet the
-    // large-tile kernel's rules go into ONE launch, LEFT and RIGHT together (the layout of B is a field of
-    // each problem there); the rest take the general kernel, one launch per orientation.
+    // contiguous along the contraction index; only G of a LEFT tensor is not.  LEFT and RIGHT tensors share a launch
+    // (the layout of B is a field of each problem).
     std::vector<char> adam_done(items.size(), 0);  // tensors whose Adam ran inside the projection launch
     {
-      ProjGroup pg{}, pgf{};   // pgf: with the update block of Algorithm 2 in the epilogue (galore_set_fused_adam)
+      ProjGroup pg{}, pgf{};        // large-tile kernel; pgf: with the update block of Algorithm 2 in the epilogue (galore_set_fused_adam)
       pgf.beta1 = hp.beta1; pgf.beta2 = hp.beta2; pgf.eps = hp.eps;
-      GemmGroup rest[2] = {};  // [0] RIGHT, [1] LEFT
+      GemmGroup tiles{}, tilesf{};  // small-tile kernel; tilesf: with the update block in the epilogue
+      tilesf.beta1 = hp.beta1; tilesf.beta2 = hp.beta2; tilesf.eps = hp.eps;
+      GemmGroup rest[2] = {};       // [0] RIGHT, [1] LEFT: what neither takes (a side of fewer than 8 elements)
       PadGroup pads{};
+      long t256 = 0, t64 = 0;
+      for (const StepItem& it : items) {
+        const TensorInfo& ti = ctx->tensors[it.tensor];
+        if (ti.dt == dt && large_projection_eligible(ti.left, ti.kdim, ti.ldim, r, dt)) t256 += (long)(((r + 255) / 256) * ((ti.ldim + 255) / 256));
+      }
+      const bool large = t256 >= kLargeProjectionTiles;
+      for (const StepItem& it : items) {
+        const TensorInfo& ti = ctx->tensors[it.tensor];
+        if (ti.dt == dt && !(large && large_projection_eligible(ti.left, ti.kdim, ti.ldim, r, dt))) t64 += (long)tiles64(ti.ldim, r);
+      }
       for (int left = 1; left >= 0; --left) {
         for (size_t ii = 0; ii < items.size(); ++ii) {
-          const StepItem& it = items[ii];
+          StepItem& it = items[ii];
           const TensorInfo& ti = ctx->tensors[it.tensor];
           if (ti.dt != dt || (int)ti.left != left) continue;
+          const bool to_large = large && large_projection_eligible(ti.left, ti.kdim, ti.ldim, r, dt);
+          it.ldr = ti.ldim;
+          it.pieces = 1;
+          const double k = (double)(ti.t + 1);
+          const float ic1 = (float)(1.0 / (1.0 - std::pow((double)hp.beta1, k)));
+          const float ic2 = (float)(1.0 / (1.0 - std::pow((double)hp.beta2, k)));
           GemmProblem p{};
-          if (left && it.Gpad) {  // the same product on the padded copy: the extra columns of G and of R are zero
-            PadProblem& q = pads.p[pads.count++];
-            q.src = it.G->data; q.lds = (int)it.G->ld;
-            q.dst = it.Gpad; q.ldd = (int)it.ldr;
-            q.rows = (int)ti.rows; q.cols = (int)ti.cols;
-            p.A = ti.st.proj_t.data; p.lda = (int)ti.st.proj_t.ld;
-            p.B = it.Gpad; p.ldb = (int)it.ldr;
-            p.M = r; p.N = (int)it.ldr; p.K = (int)ti.rows;
-            p.C = it.R; p.ldc = (int)it.ldr;
-          } else if (left) {  // R (r x n) = P^T G : A = proj_t as [M=r][K=m], B = G as [K=m][N=n]
+          if (left) {  // R (r x n) = P^T G : A = proj_t as [M=r][K=m], B = G as [K=m][N=n]
             p.A = ti.st.proj_t.data; p.lda = (int)ti.st.proj_t.ld;
             p.B = it.G->data; p.ldb = (int)it.G->ld;
             p.M = r; p.N = (int)ti.cols; p.K = (int)ti.rows;
-            p.C = it.R; p.ldc = (int)ti.cols;
           } else {     // R (m x r) = G Q : A = G as [M=m][K=n], B = proj_t as [N=r][K=n]
             p.A = it.G->data; p.lda = (int)it.G->ld;
             p.B = ti.st.proj_t.data; p.ldb = (int)ti.st.proj_t.ld;
             p.M = (int)ti.rows; p.N = r; p.K = (int)ti.cols;
-            p.C = it.R; p.ldc = r;
           }
-          ProjProblem q{};
-          q.A = p.A; q.B = p.B; q.R = static_cast<float*>(p.C);
-          q.M = p.M; q.N = p.N; q.K = p.K; q.lda = p.lda; q.ldb = p.ldb; q.ldr = p.ldc;
-          q.b_kcontig = left ? 0 : 1;
-          if (dt == DType::BF16 && ctx->merged_projection && proj_problem_fits(q)) {
-            if (ctx->fused_adam && !ti.q8) {
-              const double k = (double)(ti.t + 1);
-              q.Mo = static_cast<float*>(ti.st.m.data);
-              q.Vo = static_cast<float*>(ti.st.v.data);
-              q.Nout = it.N;
-              q.ldm = q.cols_valid = left ? (int)ti.cols : r;   // M, V are dense; R may carry padded columns
-              q.ldn = r;                                         // N is always (long side) x r
-              q.n_transposed = left;
-              q.inv_c1 = (float)(1.0 / (1.0 - std::pow((double)hp.beta1, k)));
-              q.inv_c2 = (float)(1.0 / (1.0 - std::pow((double)hp.beta2, k)));
-              pgf.p[pgf.count++] = q;
-              adam_done[ii] = 1;
-            } else {
-              pg.p[pg.count++] = q;
+          p.C = it.R; p.ldc = p.N;
+          if (to_large) {
+            ProjProblem q{};
+            q.A = p.A; q.B = p.B; q.R = it.R;
+            q.M = p.M; q.N = p.N; q.K = p.K; q.lda = p.lda; q.ldb = p.ldb; q.ldr = p.ldc;
+            q.b_kcontig = left ? 0 : 1;
+            const int64_t ldp = projected_row_length(ti.left, ti.kdim, ti.ldim, dt);
+            const bool pad = left && it.Gpad && ldp != ti.ldim;  // the same product on the padded copy: the extra columns of G and of R are zero
+            if (pad) {
+              q.B = it.Gpad;
+              q.N = q.ldb = q.ldr = (int)ldp;
             }
-          } else {
+            if (proj_problem_fits(q)) {
+              if (pad) {
+                PadProblem& c = pads.p[pads.count++];
+                c.src = it.G->data; c.lds = (int)it.G->ld;
+                c.dst = it.Gpad; c.ldd = (int)ldp;
+                c.rows = (int)ti.rows; c.cols = (int)ti.cols;
+                it.ldr = ldp;
+              }
+              if (ctx->fused_adam && !ti.q8) {
+                q.Mo = static_cast<float*>(ti.st.m.data);
+                q.Vo = static_cast<float*>(ti.st.v.data);
+                q.Nout = it.N;
+                q.ldm = q.cols_valid = left ? (int)ti.cols : r;   // M, V are dense; R may carry padded columns
+                q.ldn = r;                                         // N is always (long side) x r
+                q.n_transposed = left;
+                q.inv_c1 = ic1;
+                q.inv_c2 = ic2;
+                pgf.p[pgf.count++] = q;
+                adam_done[ii] = 1;
+              } else {
+                pg.p[pg.count++] = q;
+              }
+              continue;
+            }
+          }
+          if (!tile_problem_fits(p, dt, !left)) {
             rest[left].p[rest[left].count++] = p;
+            continue;
+          }
+          p.b_kcontig = !left;
+          it.pieces = p.splits = std::min(tile_pieces(t64, ti.kdim, dt), tile_pieces((long)tiles64(ti.ldim, r), ti.kdim, dt));
+          p.slab_stride = (int64_t)p.M * p.ldc;
+          // With whole contractions the small-tile kernel can run the update block as well, which saves a launch and the
+          // trip of R through memory: always when asked for, and by itself from 64 Ki entries on, where R is traffic (one
+          // 350M layer 61 against 68 us, a 2768 / 7312 layer at r = 272 297 against 313).
+          if (it.pieces == 1 && !ti.q8 && (ctx->fused_adam || (int64_t)r * ti.ldim >= 65536)) {
+            p.Mo = static_cast<float*>(ti.st.m.data);
+            p.Vo = static_cast<float*>(ti.st.v.data);
+            p.Nout = it.N;
+            p.n_transposed = left;
+            p.inv_c1 = ic1;
+            p.inv_c2 = ic2;
+            tilesf.p[tilesf.count++] = p;
+            adam_done[ii] = 1;
+          } else {
+            tiles.p[tiles.count++] = p;
           }
         }
       }
       {
-        ProfScope prof(ctx, GALORE_STAGE_PROJECT_LEFT, pg.count + pgf.count + rest[1].count > 0, stream);
+        ProfScope prof(ctx, GALORE_STAGE_PROJECT_LEFT, pg.count + pgf.count + tiles.count + tilesf.count + rest[1].count > 0, stream);
         hipError_t e = launch_pad_rows_group(pads, stream);
         if (e != hipSuccess) return hip_fail(ctx, e, "row padding launch");
         e = launch_proj_group(pgf, slabs, slab_bytes, stream, /*fuse_adam=*/true);
         if (e == hipSuccess) e = launch_proj_group(pg, slabs, slab_bytes, stream);
+        if (e == hipSuccess) e = launch_tile_group(tilesf, dt, Epilogue::Adam, stream);
+        if (e == hipSuccess) e = launch_tile_group(tiles, dt, Epilogue::StoreF32, stream);
         if (e == hipSuccess) e = launch_gemm_group(rest[1], dt, /*a_kcontig=*/true, /*b_kcontig=*/false, Epilogue::StoreF32, stream);
         if (e != hipSuccess) return hip_fail(ctx, e, "projection GEMM launch");
       }
@@ -329,27 +390,32 @@ galore_status run_chain(galore_ctx* ctx, const std::vector<StepItem>& items, flo
       }
     }
     // K2: Adam on R.  N always leaves as (long side) x r: transposed for LEFT tensors.
-    for (int left = 1; left >= 0; --left) {
+    {
       AdamGroup g{};
-      AdamQ8Group g8{};
+      AdamQ8Group g8[2] = {};  // by orientation: [1] LEFT
       g.beta1 = hp.beta1; g.beta2 = hp.beta2; g.eps = hp.eps;
-      g8.beta1 = hp.beta1; g8.beta2 = hp.beta2; g8.eps = hp.eps;
-      g8.omb1 = 1.0f - hp.beta1; g8.omb2 = 1.0f - hp.beta2;
+      for (AdamQ8Group& x : g8) {
+        x.beta1 = hp.beta1; x.beta2 = hp.beta2; x.eps = hp.eps;
+        x.omb1 = 1.0f - hp.beta1; x.omb2 = 1.0f - hp.beta2;
+      }
       for (size_t ii = 0; ii < items.size(); ++ii) {
         const StepItem& it = items[ii];
         const TensorInfo& ti = ctx->tensors[it.tensor];
-        if (ti.dt != dt || (int)ti.left != left || adam_done[ii]) continue;
+        if (ti.dt != dt || adam_done[ii]) continue;
+        const bool left = ti.left;
         const double k = (double)(ti.t + 1);
         const float ic1 = (float)(1.0 / (1.0 - std::pow((double)hp.beta1, k)));
         const float ic2 = (float)(1.0 / (1.0 - std::pow((double)hp.beta2, k)));
+        const int64_t slab_stride = (left ? (int64_t)r : ti.rows) * (left ? it.ldr : (int64_t)r);
         if (ti.q8) {
-          AdamQ8Problem& p = g8.p[g8.count++];
+          AdamQ8Problem& p = g8[left].p[g8[left].count++];
           p.R = it.R;
           p.Mc = static_cast<uint8_t*>(ti.st.m.data); p.Vc = static_cast<uint8_t*>(ti.st.v.data);
           p.Ms = static_cast<float*>(ti.st.m_scale.data); p.Vs = static_cast<float*>(ti.st.v_scale.data);
           p.N = it.N;
           p.rows = left ? r : (int)ti.rows;
           p.cols = left ? (int)ti.cols : r;
+          p.slabs = it.pieces; p.slab_stride = slab_stride;
           p.transpose_n = left;
           p.inv_c1 = ic1; p.inv_c2 = ic2;
           continue;
@@ -364,12 +430,13 @@ galore_status run_chain(galore_ctx* ctx, const std::vector<StepItem>& items, flo
         p.ldr = left ? (int)it.ldr : r;
         p.count = (int64_t)r * ti.ldim;
         p.transpose_n = left;
+        p.slabs = it.pieces; p.slab_stride = slab_stride;
         p.inv_c1 = ic1;
         p.inv_c2 = ic2;
       }
-      ProfScope prof(ctx, GALORE_STAGE_ADAM, g.count + g8.count > 0, stream);
+      ProfScope prof(ctx, GALORE_STAGE_ADAM, g.count + g8[0].count + g8[1].count > 0, stream);
       hipError_t e = launch_adam_group(g, dt, stream);
-      if (e == hipSuccess) e = launch_adam_q8_group(g8, dt, stream);
+      for (int left = 1; left >= 0 && e == hipSuccess; --left) e = launch_adam_q8_group(g8[left], dt, stream);
       if (e != hipSuccess) return hip_fail(ctx, e, "Adam launch");
     }
     // K3: project back + apply; with N as (long side) x r both orientations share one layout
@@ -393,7 +460,7 @@ galore_status run_chain(galore_ctx* ctx, const std::vector<StepItem>& items, flo
         p.s1 = lr * hp.scale;
       }
       ProfScope prof(ctx, GALORE_STAGE_BACK, g.count > 0, stream);
-      hipError_t e = launch_gemm_group(g, dt, /*a_kcontig=*/true, /*b_kcontig=*/true, Epilogue::ApplyW, stream);
+      hipError_t e = launch_weight_update(g, dt, stream);
       if (e != hipSuccess) return hip_fail(ctx, e, "back-projection GEMM launch");
     }
   }
@@ -452,7 +519,6 @@ galore_status run_step_chunk(galore_ctx* ctx, std::vector<StepItem>& items, floa
     const size_t gp = step_gpad_bytes(ti.left, ti.kdim, ti.ldim, ti.dt);
     it.Gpad = gp ? ctx->ws + off : nullptr;
     off += gp;
-    it.ldr = projected_row_length(ti.left, ti.kdim, ti.ldim, ti.dt);
   }
   // What is left of this call's part of the workspace holds the partial tiles of the projection GEMM
   // (at most 64 MiB per chain are of use: one 256 x 256 fp32 tile per CU).
@@ -798,7 +864,7 @@ galore_status galore_step(galore_ctx* ctx, const galore_tensor* W, const galore_
       const TensorInfo& ti = ctx->tensors[first + pos];
       const size_t need = step_need(ti.left, ti.kdim, ti.ldim, ctx->hp.rank, ti.dt);
       if (!items.empty() && used + need > limit) break;
-      items.push_back(StepItem{first + pos, &W[pos], &G[pos], nullptr, nullptr, nullptr, ti.ldim});
+      items.push_back(StepItem{first + pos, &W[pos], &G[pos], nullptr, nullptr, nullptr, ti.ldim, 1});
       used += need;
       ++pos;
     }
@@ -844,7 +910,7 @@ galore_status galore_step_static(galore_ctx* ctx, const galore_tensor* W, const 
       const TensorInfo& ti = ctx->tensors[first + pos];
       const size_t need = step_need(ti.left, ti.kdim, ti.ldim, r, ti.dt);
       if (off + need > kStaticScratchBytes) break;
-      StepItem it{first + pos, &W[pos], &G[pos], nullptr, nullptr, nullptr, ti.ldim};
+      StepItem it{first + pos, &W[pos], &G[pos], nullptr, nullptr, nullptr, ti.ldim, 1};
       it.R = reinterpret_cast<float*>(sp + off);
       off += step_r_bytes(ti.left, ti.kdim, ti.ldim, r, ti.dt);
       it.N = sp + off;
@@ -852,8 +918,7 @@ galore_status galore_step_static(galore_ctx* ctx, const galore_tensor* W, const 
       const size_t gp = step_gpad_bytes(ti.left, ti.kdim, ti.ldim, ti.dt);
       it.Gpad = gp ? sp + off : nullptr;
       off += gp;
-      it.ldr = projected_row_length(ti.left, ti.kdim, ti.ldim, ti.dt);
-      items.push_back(it);
+        items.push_back(it);
       ++pos;
     }
     const size_t slab_off = align_up(off);  // what is left of the array holds the projection's partial tiles

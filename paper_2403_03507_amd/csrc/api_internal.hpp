@@ -32,7 +32,7 @@ inline hipError_t single_gemm_store(DType dt, const void* A, int lda, const void
   p.A = A; p.lda = lda; p.B = B; p.ldb = ldb;
   p.M = M; p.N = N; p.K = K;
   p.C = C; p.ldc = N;
-  return launch_gemm_group(g, dt, true, b_kcontig, Epilogue::StoreF32, stream);
+  return launch_product(g, dt, b_kcontig, stream);
 }
 
 inline hipError_t single_transpose(DType dt, const void* src, int rows, int cols, int lds, void* dst, int ldd, hipStream_t stream) {

@@ -50,18 +50,19 @@ galore_status galore_project(const galore_tensor* proj_t, const galore_tensor* G
     p.M = (int)G->rows; p.N = (int)r; p.K = (int)G->cols;
   }
   p.C = R->data; p.ldc = (int)R->ld;
-  // the kernel galore_step uses for this tensor: the grouped projection where its rules are met, else the general GEMM
+  // the kernel galore_step uses for this tensor on its own
   ProjGroup pg{};
   ProjProblem& q = pg.p[0];
   q.A = p.A; q.B = p.B; q.R = static_cast<float*>(p.C);
   q.M = p.M; q.N = p.N; q.K = p.K; q.lda = p.lda; q.ldb = p.ldb; q.ldr = p.ldc;
   q.b_kcontig = left ? 0 : 1;
   hipError_t e;
-  if ((DType)G->dtype == DType::BF16 && proj_problem_fits(q)) {
+  const int64_t t256 = (int64_t)((q.M + 255) / 256) * ((q.N + 255) / 256);
+  if ((DType)G->dtype == DType::BF16 && t256 >= kLargeProjectionTiles && proj_problem_fits(q)) {
     pg.count = 1;
     e = launch_proj_group(pg, nullptr, 0, static_cast<hipStream_t>(hip_stream));
   } else {
-    e = launch_gemm_group(g, (DType)G->dtype, true, !left, Epilogue::StoreF32, static_cast<hipStream_t>(hip_stream));
+    e = launch_product(g, (DType)G->dtype, !left, static_cast<hipStream_t>(hip_stream));
   }
   return e == hipSuccess ? GALORE_OK : hip_fail(nullptr, e, "projection GEMM launch");
 }
@@ -158,7 +159,7 @@ galore_status galore_project_back(const galore_tensor* proj, const galore_tensor
   p.C = W->data; p.ldc = (int)W->ld;
   p.s0 = 1.f - lr * weight_decay;
   p.s1 = lr * scale;
-  hipError_t e = launch_gemm_group(g, (DType)W->dtype, true, true, Epilogue::ApplyW, static_cast<hipStream_t>(hip_stream));
+  hipError_t e = launch_weight_update(g, (DType)W->dtype, static_cast<hipStream_t>(hip_stream));
   return e == hipSuccess ? GALORE_OK : hip_fail(nullptr, e, "back-projection GEMM launch");
 }
 

@@ -148,7 +148,7 @@ galore_status galore_two_sided_step(const galore_hparams* hp, const galore_tenso
     p.C = W->data; p.ldc = (int)W->ld;
     p.s0 = 1.f - lr * hp->weight_decay;
     p.s1 = lr * hp->scale;
-    e = launch_gemm_group(g, dt, true, true, Epilogue::ApplyW, stream);
+    e = launch_weight_update(g, dt, stream);
   }
   return e == hipSuccess ? GALORE_OK : hip_fail(nullptr, e, "two-sided weight update");
 }

@@ -19,33 +19,59 @@ struct GemmProblem {
   const void* A;
   const void* B;
   void* C;        // output / in-place operand of the epilogue
-  void* aux0;     // epilogue extra pointers
-  void* aux1;
-  void* aux2;
+  int64_t slab_stride;  // split contraction (launch_tile_group): elements between the outputs of two pieces
+  int32_t splits;       // pieces of the contraction (0 and 1: whole); piece s writes C + s * slab_stride
+  int32_t b_kcontig;    // layout of B where it is a field of the problem (launch_tile_group)
   int32_t M, N, K;
   int32_t lda, ldb, ldc;
   int32_t tile_begin;  // first block of this problem in the launch
   int32_t tiles_m;     // tiles along M and N; tile ids are decoded by tile_coords()
   int32_t tiles_n;
-  float s0, s1, s2, s3;  // epilogue scalars
+  float s0, s1;  // epilogue scalars
+  // Epilogue::Adam: fp32 moments with the product's shape (dense, row stride N) and the normalised update in the
+  // operands' dtype, n_transposed ? N x M : M x N, dense
+  float* Mo;
+  float* Vo;
+  void* Nout;
+  int32_t n_transposed;
+  float inv_c1, inv_c2;
 };
 
 struct GemmGroup {
   int32_t count;
   int32_t total_tiles;
+  float beta1, beta2, eps;  // Epilogue::Adam
   GemmProblem p[kMaxGroup];
 };
 
 enum class Epilogue : int32_t {
   StoreF32 = 0,   // C (fp32) = acc
   ApplyW = 1,     // C (T) = s0 * C - s1 * acc            (weight update, s0 = 1 - lr*wd, s1 = lr*alpha)
-  StoreSymF32 = 2 // C (fp32) = acc, written to (i,j) and (j,i); tiles with tm > tn skipped (M == N)
+  StoreSymF32 = 2, // C (fp32) = acc, written to (i,j) and (j,i); tiles with tm > tn skipped (M == N)
+  Adam = 3        // the update block of Algorithm 2 on acc: moments in place, N written, the product itself not stored (launch_tile_group)
 };
 
 // Launch one grouped GEMM on `stream`.  All problems share dtype / layouts / epilogue.
 // Host fills everything except tile_begin / tiles_m / total_tiles.
 hipError_t launch_gemm_group(GemmGroup& g, DType dt, bool a_kcontig, bool b_kcontig, Epilogue epi,
                              hipStream_t stream);
+
+// The small-tile GEMM (gemm_tile.hpp): StoreF32 or Adam with A as [M][K] and the layout of B (and, for StoreF32, the
+// number of K pieces) as fields of each problem, or ApplyW with both operands contiguous along K.  Any alignment of
+// operands and output.
+bool tile_problem_fits(const GemmProblem& p, DType dt, bool b_kcontig);
+hipError_t launch_tile_group(GemmGroup& g, DType dt, Epilogue epi, hipStream_t stream);
+constexpr int kMaxTilePieces = 4;
+constexpr long kSplitBelowTiles = 224;  // a launch of as many 64 x 64 tiles keeps its contractions whole
+int tile_pieces(long tiles, int64_t K, DType dt);
+// A projection launch with at least this many 256 x 256 tiles takes the 256 x 256 kernel (a 7B layer at r = 256, 193 tiles:
+// 354 against 390 us per step on the small tiles; one 4096 x 11008 weight at r = 1024, 172 tiles: 256 against 283; one
+// 4096 x 4096 weight, 64 tiles: 149 against 102).
+constexpr long kLargeProjectionTiles = 160;
+// The weight update W = s0 W - s1 A B^T (both operands contiguous along K) and the product C = A B (fp32, optionally in
+// K pieces), on whichever kernel suits each problem.
+hipError_t launch_weight_update(GemmGroup& g, DType dt, hipStream_t stream);
+hipError_t launch_product(GemmGroup& g, DType dt, bool b_kcontig, hipStream_t stream);
 
 // ---- grouped projection GEMM (bf16 operands, fp32 result): R = A * B with A as [M][K] -------------------
 // LEFT tensors:  A = the transposed projector (r x m), B = G as [K = m][N = n]  (b_kcontig = 0)
@@ -96,8 +122,10 @@ struct AdamProblem {
   int64_t count;  // rows * cols
   int32_t rows;   // shape of R, M, V (M, V dense, row-major)
   int32_t cols;
-  int32_t ldr;    // row stride of R, >= cols (only the transposing kernel takes R with padded rows; else ldr == cols)
+  int32_t ldr;    // row stride of R, >= cols (padded rows of R only with transpose_n; else ldr == cols)
   int32_t transpose_n;  // 0: N has R's layout; 1: N is stored transposed (cols x rows)
+  int32_t slabs;        // R is the sum of this many matrices (0 and 1: R itself), added in order
+  int64_t slab_stride;  // elements between them
   float inv_c1;   // 1 / (1 - beta1^k)
   float inv_c2;   // 1 / (1 - beta2^k)
 };
@@ -108,7 +136,7 @@ struct AdamGroup {
   AdamProblem p[kMaxGroup];
 };
 
-// All problems of a group share n_dtype and transpose_n.
+// All problems of a group share n_dtype.
 hipError_t launch_adam_group(const AdamGroup& g, DType n_dtype, hipStream_t stream);
 
 // ---- grouped low-rank Adam with 8-bit block-wise moments ------------------------------------------
@@ -125,6 +153,8 @@ struct AdamQ8Problem {
   int32_t rows;    // shape of R and of the code matrices (dense, row-major)
   int32_t cols;
   int32_t transpose_n;
+  int32_t slabs;   // R is the sum of this many matrices (0 and 1: R itself), added in order
+  int64_t slab_stride;
   float inv_c1, inv_c2;
 };
 

@@ -144,6 +144,9 @@ template <> struct Frag<float> {
   }
 };
 
+// One entry of the weight update, spelled out so that every kernel rounds it the same way.
+__device__ __forceinline__ float apply_entry(float s0, float w, float s1, float acc) { return __builtin_fmaf(s0, w, -(s1 * acc)); }
+
 // Blocks are handed to the 8 XCDs round-robin by block id; give every XCD a contiguous run
 // of logical tiles so neighbouring tiles (which share operand panels) share an L2.
 __device__ __forceinline__ int xcd_contiguous_block_id(int bid, int nblocks) {
@@ -281,7 +284,7 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_group_kernel(const GemmGroup grp
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           const int row = m0 + wm0 + 32 * i + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-          if (row < M && col < N) W[(size_t)row * ldc + col] = (T)(pr.s0 * w_old[v] - pr.s1 * acc[i][j][v]);
+          if (row < M && col < N) W[(size_t)row * ldc + col] = (T)apply_entry(pr.s0, w_old[v], pr.s1, acc[i][j][v]);
         }
       }
     return;
@@ -305,7 +308,7 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_group_kernel(const GemmGroup grp
           } else {
             T* W = static_cast<T*>(pr.C);
             const size_t idx = (size_t)row * ldc + col;
-            W[idx] = (T)(pr.s0 * to_f32(W[idx]) - pr.s1 * a);
+            W[idx] = (T)apply_entry(pr.s0, to_f32(W[idx]), pr.s1, a);
           }
         }
       }

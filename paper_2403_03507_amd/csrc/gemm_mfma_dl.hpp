@@ -399,14 +399,14 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_dl_kernel(const GemmGroup grp) {
             if (W_ANY && col + 8 > N) {  // the piece that straddles the end of the row: its old weights were not prefetched
 #pragma unroll
               for (int e = 0; e < 8; ++e)
-                if (col + e < N) wdst[e] = (__bf16)(pr.s0 * (float)wdst[e] - pr.s1 * (e < 4 ? lo[e & 3] : hi[e & 3]));
+                if (col + e < N) wdst[e] = (__bf16)apply_entry(pr.s0, (float)wdst[e], pr.s1, e < 4 ? lo[e & 3] : hi[e & 3]);
               continue;
             }
             bf16x8 o;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-              o[e] = (__bf16)(pr.s0 * (float)wpre[i][q][ps][e] - pr.s1 * lo[e]);
-              o[e + 4] = (__bf16)(pr.s0 * (float)wpre[i][q][ps][e + 4] - pr.s1 * hi[e]);
+              o[e] = (__bf16)apply_entry(pr.s0, (float)wpre[i][q][ps][e], pr.s1, lo[e]);
+              o[e + 4] = (__bf16)apply_entry(pr.s0, (float)wpre[i][q][ps][e + 4], pr.s1, hi[e]);
             }
             if (W_ANY) __builtin_memcpy(wdst, &o, sizeof(bf16x8));
             else __builtin_nontemporal_store(__builtin_bit_cast(i32x4, o), reinterpret_cast<i32x4*>(wdst));

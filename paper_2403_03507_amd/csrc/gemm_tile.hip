@@ -1,0 +1,130 @@
+// Host side of the small-tile GEMM (gemm_tile.hpp): choice of the tile, launch, and the choice between it and the
+// 256 x 256 kernels.
+#include "gemm_mfma_dl.hpp"
+#include "gemm_tile.hpp"
+
+namespace galore {
+
+bool tile_problem_fits(const GemmProblem& p, DType dt, bool b_kcontig) {
+  const int vec = dt == DType::BF16 ? 8 : 4;  // elements of one piece: clamped pieces have to lie inside a row
+  return p.M >= 1 && p.K >= vec && p.N >= vec && (b_kcontig ? p.K : p.N) >= vec;
+}
+
+namespace {
+
+long tiles_of(const GemmProblem& p, int bm, int bn) { return (long)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn) * (p.splits > 1 ? p.splits : 1); }
+
+template <class T, int BM, int BN> hipError_t launch(GemmGroup& g, Epilogue epi, hipStream_t stream) {
+  long total = 0;
+  for (int i = 0; i < g.count; ++i) {
+    GemmProblem& p = g.p[i];
+    p.tile_begin = (int32_t)total;
+    p.tiles_m = (p.M + BM - 1) / BM;
+    p.tiles_n = (p.N + BN - 1) / BN;
+    total += tiles_of(p, BM, BN);
+  }
+  if (total > INT32_MAX) return hipErrorInvalidValue;
+  g.total_tiles = (int32_t)total;
+  const dim3 grid((unsigned)total);
+  if (epi == Epilogue::StoreF32) hipLaunchKernelGGL((gemm_tile_kernel<T, BM, BN, Epilogue::StoreF32>), grid, dim3(256), 0, stream, g);
+  else if (epi == Epilogue::ApplyW) hipLaunchKernelGGL((gemm_tile_kernel<T, BM, BN, Epilogue::ApplyW>), grid, dim3(256), 0, stream, g);
+  else if (epi == Epilogue::Adam) hipLaunchKernelGGL((gemm_tile_kernel<T, BM, BN, Epilogue::Adam>), grid, dim3(256), 0, stream, g);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
+// A larger tile loads fewer bytes per flop through the L2 -> CU path, a smaller one gives more workgroups to hide latency
+// with: the largest that still makes a workgroup and a half per CU (128 x 128) or two (128 x 64).  Whole steps, us, with
+// the projection on 64 x 64 / 128 x 64 / 128 x 128 tiles: one 350M layer (1028 / 514 / 257 tiles) 54.0 / 49.0 / 57.2, one
+// 1B layer (3088 / 1544 / 772) 266 / 244 / 230, one 4096 x 4096 weight at r = 152 (180 / 120 / 60, two K pieces) 65 / 68 / 83.
+// The weight update has more tiles than that and shorter contractions: 128 x 64 unless the contraction is long (r = 54 on
+// a 1105 / 2688 layer: 104 / 100 / 103; r = 401 on 1904 / 3968: 232 / 208 / 194).
+template <class T> hipError_t launch_typed(GemmGroup& g, Epilogue epi, hipStream_t stream) {
+  long items128 = 0, items96 = 0;
+  int longest = 0;
+  for (int i = 0; i < g.count; ++i) {
+    items128 += tiles_of(g.p[i], 128, 128);
+    items96 += tiles_of(g.p[i], 128, 64);
+    longest = g.p[i].K > longest ? g.p[i].K : longest;
+  }
+  if (items128 == 0) return hipSuccess;
+  const bool update = epi == Epilogue::ApplyW;
+  if (items128 >= 350 && (!update || longest >= 256)) return launch<T, 128, 128>(g, epi, stream);
+  if (items96 >= (update ? 300 : 500)) return launch<T, 128, 64>(g, epi, stream);
+  return launch<T, 64, 64>(g, epi, stream);
+}
+
+bool fits_large(const GemmProblem& p, Epilogue epi, bool b_kcontig, bool w_any) {
+  GemmGroup one{};
+  one.count = 1;
+  one.p[0] = p;
+  return group_fits_dl(one, true, b_kcontig, epi) || (w_any && group_fits_dl(one, true, b_kcontig, epi, 64, true));
+}
+
+}  // namespace
+
+hipError_t launch_tile_group(GemmGroup& g, DType dt, Epilogue epi, hipStream_t stream) {
+  if (g.count <= 0) return hipSuccess;
+  if (g.count > kMaxGroup) return hipErrorInvalidValue;
+  for (int i = 0; i < g.count; ++i) {
+    const GemmProblem& p = g.p[i];
+    if (!tile_problem_fits(p, dt, p.b_kcontig != 0)) return hipErrorInvalidValue;
+    if (epi != Epilogue::StoreF32 && p.splits > 1) return hipErrorInvalidValue;
+    if (epi == Epilogue::ApplyW && !p.b_kcontig) return hipErrorInvalidValue;
+    if (epi == Epilogue::Adam && (!p.Mo || !p.Vo || !p.Nout)) return hipErrorInvalidValue;
+  }
+  return dt == DType::BF16 ? launch_typed<__bf16>(g, epi, stream) : launch_typed<float>(g, epi, stream);
+}
+
+// Pieces of the contraction for a launch of `tiles` 64 x 64 tiles: enough for two workgroups per CU where the tiles alone
+// leave CUs idle, at most 4 (every piece is another fp32 copy of the product to write and to read).  Contractions under
+// 512 stay whole.  Whole steps, us, with 1 / 2 / 4 / 8 pieces: 3805 x 3805 at r = 152 (180 tiles) 71.6 / 65.4 / 61.8 /
+// 66.9; fp32 512 x 512 at r = 128 (16 tiles) 31.0 / 28.5 / 26.6 / 26.6; 2048 x 2048 at r = 512 (256 tiles) 32.3 / 34.8 / 36.1.
+int tile_pieces(long tiles, int64_t K, DType dt) {
+  if (tiles < 1 || tiles >= kSplitBelowTiles || K < 512) return 1;
+  const int64_t by_k = K / (dt == DType::BF16 ? 256 : 128);
+  int64_t pieces = (512 + tiles - 1) / tiles;
+  pieces = pieces < by_k ? pieces : by_k;
+  return (int)(pieces < kMaxTilePieces ? pieces : kMaxTilePieces);
+}
+
+hipError_t launch_weight_update(GemmGroup& g, DType dt, hipStream_t stream) {
+  // The persistent 256 x 256 kernel where its tiles come near filling the CUs (W prefetched across tiles): one 350M
+  // layer (196 tiles) 54.3 against 55.5 us per step on the small tiles, a 7B layer at r = 128 305 against 346, at
+  // r = 1024 995 against 1290; one 2048 x 2048 weight (64 tiles) 58.2 against 53.5.
+  long tiles256 = 0;
+  for (int i = 0; i < g.count; ++i) tiles256 += tiles_of(g.p[i], 256, 256);
+  GemmGroup large{}, tiles{}, rest{};
+  for (int i = 0; i < g.count; ++i) {
+    GemmProblem& p = g.p[i];
+    p.b_kcontig = 1;
+    p.splits = 1;
+    GemmGroup& to = dt == DType::BF16 && tiles256 >= 150 && fits_large(p, Epilogue::ApplyW, true, true) ? large : tile_problem_fits(p, dt, true) ? tiles : rest;
+    to.p[to.count++] = p;
+  }
+  hipError_t e = launch_gemm_group(large, dt, true, true, Epilogue::ApplyW, stream);
+  if (e == hipSuccess) e = launch_tile_group(tiles, dt, Epilogue::ApplyW, stream);
+  if (e == hipSuccess) e = launch_gemm_group(rest, dt, true, true, Epilogue::ApplyW, stream);
+  return e;
+}
+
+hipError_t launch_product(GemmGroup& g, DType dt, bool b_kcontig, hipStream_t stream) {
+  long tiles256 = 0;
+  for (int i = 0; i < g.count; ++i) tiles256 += tiles_of(g.p[i], 256, 256);
+  GemmGroup large{}, tiles{}, rest{};
+  for (int i = 0; i < g.count; ++i) {
+    GemmProblem& p = g.p[i];
+    p.b_kcontig = b_kcontig;
+    GemmGroup& to = dt == DType::BF16 && p.splits <= 1 && tiles256 >= kLargeProjectionTiles && fits_large(p, Epilogue::StoreF32, b_kcontig, false) ? large
+                    : tile_problem_fits(p, dt, b_kcontig) ? tiles : rest;
+    to.p[to.count++] = p;
+  }
+  for (int i = 0; i < rest.count; ++i)
+    if (rest.p[i].splits > 1) return hipErrorInvalidValue;
+  hipError_t e = launch_gemm_group(large, dt, true, b_kcontig, Epilogue::StoreF32, stream);
+  if (e == hipSuccess) e = launch_tile_group(tiles, dt, Epilogue::StoreF32, stream);
+  if (e == hipSuccess) e = launch_gemm_group(rest, dt, true, b_kcontig, Epilogue::StoreF32, stream);
+  return e;
+}
+
+}  // namespace galore

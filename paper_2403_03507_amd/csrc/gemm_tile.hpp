@@ -1,0 +1,360 @@
+// Small-tile grouped MFMA GEMM (gfx950): C = A B with A as [M][K] and B as [K][N] or [N][K], bf16 or fp32 operands at
+// any element alignment, fp32 accumulate, optionally with the contraction cut into pieces.
+//
+// The 256 x 256 kernels (gemm_mfma_dl.hpp, gemm_proj_dl.hpp) need hundreds of tiles to fill the chip; a layer of a
+// small stack, a single weight or a low rank gives them a few dozen, each a serial chain of K steps at one memory
+// latency apiece.  Here a workgroup of 4 wavefronts owns a 64 x 64 (or 128 x 128) tile and several workgroups share a
+// CU, so the latency of one is hidden by the others, and a launch has 4 to 16 times as many of them:
+//   * operands go global -> registers -> LDS in 16-byte pieces.  The pieces of the next K step are requested before the
+//     current one is multiplied.  Pieces are read at element alignment from addresses clamped into the matrix, without a
+//     branch; where a tile reaches past an edge the registers are shifted (zeros move in) before they are stored to
+//     LDS, so rows of any length and any first element run at the speed of aligned ones.
+//   * `splits` pieces of the contraction (StoreF32) go to separate slabs that the consumer adds in slab order: no
+//     atomics, no second launch.
+//   * the weight update reads its W tile before the K loop and writes it back as 16-byte pieces after a trip of the
+//     accumulators through LDS.
+// The order of the additions of one element is that of the 256 x 256 kernels (16 k per bf16 MFMA, ascending), so without
+// `splits` the results are the same bits whichever kernel a tensor takes.
+#pragma once
+#include <cstdlib>
+#include <type_traits>
+
+#include "adam_entry.hpp"
+#include "gemm_mfma.hpp"
+
+namespace galore {
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+template <class T, int BX, int BK> struct TileOperand {
+  using ET = ElemTraits<T>;
+  static constexpr int VEC = ET::VEC;
+  static constexpr int PIECES = BX * BK / VEC;
+  static constexpr int PER = PIECES / 256;
+  static_assert(PIECES % 256 == 0, "pieces divide evenly over the workgroup");
+  static constexpr bool SWZ = sizeof(T) == 2 && BX == 64;  // rows of 128 bytes: unpadded, 64-byte halves swapped every other row pair
+  static constexpr int PK = BK + ET::PADK;
+  static constexpr int PX = SWZ ? BX : BX + ET::PADX;
+  static constexpr int LDS_ELEMS = BX * PK > BK * PX ? BX * PK : BK * PX;
+
+  // Requests this thread's pieces of the tile at (x0, k).  X, K: extents (X >= VEC or K >= VEC along the contiguous index).
+  template <bool KC>
+  static __device__ __forceinline__ void load(u32x4 (&regs)[PER], const T* __restrict__ base, int ld, int x0, int X, int k, int K, int tid) {
+    constexpr int CPR = (KC ? BK : BX) / VEC;
+#pragma unroll
+    for (int it = 0; it < PER; ++it) {
+      const int c = tid + it * 256;
+      int o = (KC ? x0 : k) + c / CPR, i = (KC ? k : x0) + (c % CPR) * VEC;
+      const int olast = (KC ? X : K) - 1, ilast = (KC ? K : X) - VEC;
+      o = o < olast ? o : olast;
+      i = i < ilast ? i : ilast;
+      __builtin_memcpy(&regs[it], base + (size_t)o * ld + i, sizeof(u32x4));
+    }
+  }
+
+  // v shifted towards its first element by n elements, zeros shifted in (n >= VEC: all zero)
+  static __device__ __forceinline__ u32x4 shift_out(u32x4 v, int n) {
+    const int w = sizeof(T) == 2 ? n >> 1 : n;
+    if (sizeof(T) == 2) {
+      const bool half = n & 1;
+      const u32x4 s = {__builtin_amdgcn_alignbit(v.y, v.x, 16), __builtin_amdgcn_alignbit(v.z, v.y, 16),
+                       __builtin_amdgcn_alignbit(v.w, v.z, 16), v.w >> 16};
+      v = half ? s : v;
+    }
+    v = (w & 1) ? u32x4{v.y, v.z, v.w, 0u} : v;
+    v = (w & 2) ? u32x4{v.z, v.w, 0u, 0u} : v;
+    return w >= 4 ? u32x4{0u, 0u, 0u, 0u} : v;
+  }
+
+  // Stores the pieces requested by load() with the same arguments.  `edge` (uniform): the tile reaches past the matrix.
+  template <bool KC>
+  static __device__ __forceinline__ void store(u32x4 (&regs)[PER], T* lds, int x0, int X, int k, int K, bool edge, int tid) {
+    constexpr int CPR = (KC ? BK : BX) / VEC;
+    if (edge) {
+#pragma unroll
+      for (int it = 0; it < PER; ++it) {
+        const int c = tid + it * 256;
+        const int i = (KC ? k : x0) + (c % CPR) * VEC, ilast = (KC ? K : X) - VEC;
+        int n = i > ilast ? i - ilast : 0;
+        if (!KC && k + c / CPR >= K) n = VEC;  // a row past the end of the contraction
+        regs[it] = shift_out(regs[it], n < VEC ? n : VEC);
+      }
+    }
+#pragma unroll
+    for (int it = 0; it < PER; ++it) {
+      const int c = tid + it * 256;
+      const int o = c / CPR, i = (c % CPR) * VEC;
+      T* dst = KC ? lds + o * PK + i : lds + o * PX + (SWZ ? i ^ (32 * ((o >> 1) & 1)) : i);
+      *reinterpret_cast<u32x4*>(dst) = regs[it];
+    }
+  }
+
+  // MFMA operand of the 32 rows (columns) from x on, k = kk .. kk + KSTEP - 1 (see Frag in gemm_mfma.hpp)
+  template <bool KC> static __device__ __forceinline__ void frag(Frag<T>& f, const T* lds, int x, int kk, int lane) {
+    if constexpr (KC) {
+      f.template load_k<PK>(lds, x, kk, lane);
+    } else if constexpr (SWZ) {
+      const int s = lane & 15, g = lane >> 4;
+      const int row = kk + 8 * (g >> 1) + (s >> 2);
+      const T* p = lds + row * PX + ((x + 16 * (g & 1) + 4 * (s & 3)) ^ (32 * ((row >> 1) & 1)));
+      typedef s16x4 __attribute__((address_space(3))) * lds_v4;
+      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(p));
+      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(p + 4 * PX));
+      f.v = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    } else {
+      f.template load_x<PX>(lds, x, kk, lane);
+    }
+  }
+};
+
+template <class T, int BM_, int BN_> struct SmallTile {
+  static constexpr int BM = BM_, BN = BN_;
+  static constexpr int BK = (BM_ * BN_ <= 64 * 64 ? 256 : 128) / (int)sizeof(T);  // 64 x 64: 128 (bf16) or 64 (fp32); larger tiles: 64 or 32
+  using A = TileOperand<T, BM, BK>;
+  using B = TileOperand<T, BN, BK>;
+  static constexpr int SP = BN + 4;                        // floats per row of the epilogue's staging area
+  static constexpr int OPERAND_BYTES = (A::LDS_ELEMS + B::LDS_ELEMS) * (int)sizeof(T);
+  static constexpr int ROWS = 64;                          // rows staged at a time
+  static constexpr int STAGE_BYTES = ROWS * SP * 4;
+  static constexpr int NPITCH = ROWS + 16 / (int)sizeof(T);  // elements per column of the transposed N tile
+  static constexpr int NT_BYTES = BN * NPITCH * (int)sizeof(T);
+  static constexpr int lds_bytes(bool adam) {
+    return OPERAND_BYTES > STAGE_BYTES + (adam ? NT_BYTES : 0) ? OPERAND_BYTES : STAGE_BYTES + (adam ? NT_BYTES : 0);
+  }
+};
+
+template <class T, int BM, int BN_, Epilogue EPI>
+__global__ __launch_bounds__(256, 2) void gemm_tile_kernel(const GemmGroup grp) {
+  using Cfg = SmallTile<T, BM, BN_>;
+  using ET = ElemTraits<T>;
+  constexpr int BN = Cfg::BN, BK = Cfg::BK, SP = Cfg::SP, ROWS = Cfg::ROWS;
+  constexpr int WM = BM / 2, WN = BN / 2, TM = WM / 32, TN = WN / 32;
+  using AOp = typename Cfg::A;
+  using BOp = typename Cfg::B;
+  __shared__ __align__(16) unsigned char smem[Cfg::lds_bytes(EPI == Epilogue::Adam)];
+  T* As = reinterpret_cast<T*>(smem);
+  T* Bs = As + AOp::LDS_ELEMS;
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm0 = (wave & 1) * WM, wn0 = (wave >> 1) * WN;
+
+  const int bid = xcd_contiguous_block_id(blockIdx.x, gridDim.x);
+  int pi = 0;
+  for (int i = 1; i < grp.count; ++i)
+    if (bid >= grp.p[i].tile_begin) pi = i;
+  const GemmProblem& pr = grp.p[pi];
+  const int tiles = pr.tiles_m * pr.tiles_n;
+  const int item = bid - pr.tile_begin;
+  const int piece = item / tiles;
+  int tm, tn;
+  tile_coords(item - piece * tiles, pr.tiles_m, pr.tiles_n, tm, tn);
+  const int m0 = tm * BM, n0 = tn * BN;
+  const int M = pr.M, N = pr.N, K = pr.K;
+  const int KT = (K + BK - 1) / BK, S = pr.splits > 1 ? pr.splits : 1;
+  const int first = (int)((long long)piece * KT / S), last = (int)((long long)(piece + 1) * KT / S);
+  const T* __restrict__ A = static_cast<const T*>(pr.A);
+  const T* __restrict__ B = static_cast<const T*>(pr.B);
+
+  f32x16 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+
+  // W pieces of the weight update: piece q of pass ps is row ps * ROWS + q * RPP + tid / CPW, columns WVEC (tid % CPW) ..
+  constexpr int WVEC = ET::VEC;
+  constexpr int CPW = BN / WVEC, RPP = 256 / CPW, NQ = ROWS / RPP, NPASS = BM / ROWS;
+  u32x4 wold[EPI == Epilogue::ApplyW ? NPASS * NQ : 1];
+  const int wcol = n0 + (tid % CPW) * WVEC;
+
+  auto run = [&](auto kc) {
+    constexpr bool BKC = decltype(kc)::value;
+    const bool edge_n = !BKC && n0 + BN > N;
+    // two register sets: the pieces of the next two K steps are in flight while one is multiplied
+    u32x4 ra0[AOp::PER], rb0[BOp::PER], ra1[AOp::PER], rb1[BOp::PER];
+    auto load = [&](u32x4 (&ra)[AOp::PER], u32x4 (&rb)[BOp::PER], int kt) {
+      AOp::template load<true>(ra, A, pr.lda, m0, M, kt * BK, K, tid);
+      BOp::template load<BKC>(rb, B, pr.ldb, n0, N, kt * BK, K, tid);
+    };
+    auto step = [&](u32x4 (&ra)[AOp::PER], u32x4 (&rb)[BOp::PER], int kt) {
+      const int k = kt * BK;
+      const bool tail = k + BK > K;
+      AOp::template store<true>(ra, As, m0, M, k, K, tail, tid);
+      BOp::template store<BKC>(rb, Bs, n0, N, k, K, tail || edge_n, tid);
+      __syncthreads();
+      if (kt + 2 < last) load(ra, rb, kt + 2);
+#pragma unroll
+      for (int kk = 0; kk < BK; kk += ET::KSTEP) {
+        Frag<T> fa[TM], fb[TN];
+#pragma unroll
+        for (int i = 0; i < TM; ++i) AOp::template frag<true>(fa[i], As, wm0 + 32 * i, kk, lane);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) BOp::template frag<BKC>(fb[j], Bs, wn0 + 32 * j, kk, lane);
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) Frag<T>::mma(acc[i][j], fa[i], fb[j]);
+      }
+      __syncthreads();
+    };
+    load(ra0, rb0, first);
+    if (first + 1 < last) load(ra1, rb1, first + 1);
+    if constexpr (EPI == Epilogue::ApplyW) {
+      const T* W = static_cast<const T*>(pr.C);
+      const int wc = wcol < N - WVEC ? wcol : N - WVEC;
+#pragma unroll
+      for (int q = 0; q < NPASS * NQ; ++q) {
+        const int row = m0 + q * RPP + tid / CPW;
+        __builtin_memcpy(&wold[q], W + (size_t)(row < M ? row : M - 1) * pr.ldc + wc, sizeof(u32x4));
+      }
+    }
+    for (int kt = first; kt < last; kt += 2) {
+      step(ra0, rb0, kt);
+      if (kt + 1 < last) step(ra1, rb1, kt + 1);
+    }
+  };
+  if constexpr (EPI == Epilogue::ApplyW) {
+    run(std::true_type{});
+  } else {
+    if (pr.b_kcontig) run(std::true_type{});
+    else run(std::false_type{});
+  }
+
+  // Epilogue: ROWS rows at a time through LDS, so that global accesses are 16 contiguous bytes per lane.  Accumulator
+  // register v of lane l is element (row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32) of a 32 x 32 block.
+  float* st = reinterpret_cast<float*>(smem);
+  const int ldc = pr.ldc;
+  constexpr int CPC = BN / 4, RPC = 256 / CPC, NC = ROWS / RPC;  // fp32 pieces: columns 4 (tid % CPC) ..
+  const int pc = (tid % CPC) * 4, col = n0 + pc;
+#pragma unroll
+  for (int ps = 0; ps < NPASS; ++ps) {
+    if (ps) __syncthreads();
+    f32x4 mo[EPI == Epilogue::Adam ? NC : 1], vo[EPI == Epilogue::Adam ? NC : 1];
+    if constexpr (EPI == Epilogue::Adam) {  // the moments of the pass, requested before anything waits (N >= 4: see tile_problem_fits)
+      const int cc = col + 4 <= N ? col : 0;
+#pragma unroll
+      for (int q = 0; q < NC; ++q) {
+        const int row = m0 + ps * ROWS + q * RPC + tid / CPC;
+        const size_t at = (size_t)(row < M ? row : M - 1) * N + cc;
+        __builtin_memcpy(&mo[q], pr.Mo + at, 16);
+        __builtin_memcpy(&vo[q], pr.Vo + at, 16);
+      }
+    }
+    if (wm0 / ROWS == ps) {
+      const int wr = wm0 % ROWS;
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int v = 0; v < 16; ++v)
+            st[(wr + 32 * i + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * SP + wn0 + 32 * j + (lane & 31)] = acc[i][j][v];
+    }
+    __syncthreads();
+    if constexpr (EPI == Epilogue::ApplyW) {
+      T* W = static_cast<T*>(pr.C);
+      const float s0 = pr.s0, s1 = pr.s1;
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        const int lr = q * RPP + tid / CPW, row = m0 + ps * ROWS + lr;
+        if (row >= M || wcol >= N) continue;
+        const float* src = st + lr * SP + (tid % CPW) * WVEC;
+        T* dst = W + (size_t)row * ldc + wcol;
+        if (wcol + WVEC <= N) {
+          T o[WVEC], w[WVEC];
+          __builtin_memcpy(w, &wold[ps * NQ + q], sizeof(u32x4));
+#pragma unroll
+          for (int e = 0; e < WVEC; ++e) o[e] = (T)apply_entry(s0, (float)w[e], s1, src[e]);
+          __builtin_memcpy(dst, o, sizeof(u32x4));
+        } else {  // the piece that straddles the end of the row
+#pragma unroll
+          for (int e = 0; e < WVEC; ++e)
+            if (wcol + e < N) dst[e] = (T)apply_entry(s0, (float)dst[e], s1, src[e]);
+        }
+      }
+    } else if constexpr (EPI == Epilogue::Adam) {
+      constexpr int NP = Cfg::NPITCH;
+      T* nt = reinterpret_cast<T*>(smem + Cfg::STAGE_BYTES);  // nt[column][row]
+      T* Nout = static_cast<T*>(pr.Nout);
+      const bool tr = pr.n_transposed != 0;
+#pragma unroll
+      for (int q = 0; q < NC; ++q) {
+        const int lr = q * RPC + tid / CPC, row = m0 + ps * ROWS + lr;
+        if (row >= M || col >= N) continue;
+        const f32x4 g = *reinterpret_cast<const f32x4*>(st + lr * SP + pc);
+        float* Mp = pr.Mo + (size_t)row * N + col;
+        float* Vp = pr.Vo + (size_t)row * N + col;
+        T n[4];
+        if (col + 4 <= N) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            float me = mo[q][e], ve = vo[q][e];
+            n[e] = (T)adam_entry(g[e], me, ve, grp.beta1, grp.beta2, grp.eps, pr.inv_c1, pr.inv_c2);
+            mo[q][e] = me; vo[q][e] = ve;
+          }
+          __builtin_memcpy(Mp, &mo[q], 16);
+          __builtin_memcpy(Vp, &vo[q], 16);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            n[e] = (T)0.f;
+            if (col + e < N) {
+              float me = Mp[e], ve = Vp[e];
+              n[e] = (T)adam_entry(g[e], me, ve, grp.beta1, grp.beta2, grp.eps, pr.inv_c1, pr.inv_c2);
+              Mp[e] = me; Vp[e] = ve;
+            }
+          }
+        }
+        if (tr) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) nt[(pc + e) * NP + lr] = n[e];
+        } else if (col + 4 <= N) {
+          __builtin_memcpy(Nout + (size_t)row * N + col, n, sizeof n);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (col + e < N) Nout[(size_t)row * N + col + e] = n[e];
+        }
+      }
+      if (tr) {  // N^T rows: 16-byte pieces along the tile's rows
+        __syncthreads();
+        constexpr int LPR = ROWS / WVEC, CPP = 256 / LPR;
+#pragma unroll
+        for (int q = 0; q < BN / CPP; ++q) {
+          const int jc = q * CPP + tid / LPR, i = (tid % LPR) * WVEC, row = m0 + ps * ROWS + i;
+          if (n0 + jc >= N || row >= M) continue;
+          const u32x4 o = *reinterpret_cast<const u32x4*>(nt + jc * NP + i);
+          T* dst = Nout + (size_t)(n0 + jc) * M + row;
+          if (row + WVEC <= M) {
+            __builtin_memcpy(dst, &o, sizeof o);
+          } else {
+#pragma unroll
+            for (int e = 0; e < WVEC; ++e)
+              if (row + e < M) dst[e] = nt[jc * NP + i + e];
+          }
+        }
+      }
+    } else {
+      float* C = static_cast<float*>(pr.C) + (size_t)piece * pr.slab_stride;
+#pragma unroll
+      for (int q = 0; q < NC; ++q) {
+        const int lr = q * RPC + tid / CPC, row = m0 + ps * ROWS + lr;
+        if (row >= M || col >= N) continue;
+        const f32x4 x = *reinterpret_cast<const f32x4*>(st + lr * SP + pc);
+        float* dst = C + (size_t)row * ldc + col;
+        if (col + 4 <= N) {
+          __builtin_memcpy(dst, &x, sizeof x);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (col + e < N) dst[e] = x[e];
+        }
+      }
+    }
+  }
+}
+
+}  // namespace galore
