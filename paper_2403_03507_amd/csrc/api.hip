@@ -542,6 +542,15 @@ galore_status run_step_chunk(galore_ctx* ctx, std::vector<StepItem>& items, floa
   int lanes = ctx->lanes;
   if (lanes > 1 && !library_streams_ready(ctx)) lanes = 1;
   if ((int)items.size() < 2) lanes = 1;
+  // Forking and joining streams costs the host some ten calls into the runtime: a step that the chip finishes in less than
+  // that runs as one chain (one 350M layer 61 us, as three chains 93; 7B layers gain from the chains: 558 against 580 us at
+  // r = 512).  The estimate: all traffic at 4 TB/s plus all products at 0.8 PFLOP/s (bf16) or 80 TFLOP/s (fp32).
+  double us = 0;
+  for (const StepItem& it : items) {
+    const TensorInfo& ti = ctx->tensors[it.tensor];
+    us += (3.0 * ti.rows * ti.cols * dtype_size(ti.dt) + 16.0 * r * ti.ldim) / 4e6 + 4.0 * ti.rows * ti.cols * r / (ti.dt == DType::BF16 ? 8e8 : 8e7);
+  }
+  if (us < 150.0) lanes = 1;
   if (lanes <= 1)
     return run_chain(ctx, items, lr, ctx->stream, reinterpret_cast<float*>(ctx->ws + slab_off), slab_avail < kSlabMax ? slab_avail : kSlabMax);
 
