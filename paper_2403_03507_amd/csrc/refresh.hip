@@ -8,6 +8,8 @@
 // decreasing L, each column signed so that its largest-magnitude entry is positive.
 //   * Gram and the tall GEMMs run on the grouped MFMA GEMM; Zt = Qt C runs on the bf16 matrix cores with both
 //     operands split into three bf16 parts (as accurate as an fp32 product; split_rows_kernel below).
+//   * Ranks up to kCholeskyMaxRank: QR (refresh_chol.hip) is Cholesky QR with the r x r part in fp64, and the eigenproblem is
+//     solved on the transposed Cholesky factor of B, whose rotated rows are the eigenvectors already.  Higher ranks:
 //   * QR (refresh_qr.hip) is Householder in panels of 8 reflectors held in registers inside macro panels of 32
 //     columns; the rest of the matrix sees a macro panel once, in compact WY form on the fp32 matrix cores.
 //   * The r x r eigenproblem (refresh_ritz.hip) is solved by one-sided (Hestenes) Jacobi on the rows of B, blocked:
@@ -22,6 +24,8 @@
 // All tensors of a group advance in lock-step (blockIdx.y = tensor), nothing syncs the host,
 // iteration counts are fixed, and no atomics are used, so results are reproducible bit for bit.
 #include "refresh_common.hpp"
+
+#include <utility>
 
 namespace galore {
 namespace rf {
@@ -42,18 +46,28 @@ Layout layout_for(int64_t k, int64_t r) {
   L.Q = take((size_t)k * r * 4);
   L.Z = take((size_t)k * r * 4);
   L.Bw = take((size_t)r * r * 4);
-  L.Jt = take((size_t)r * r * 4);
   L.S = take((size_t)r * r * 4);
   L.tau = take((size_t)r * 4);
-  L.vscale = take((size_t)r * 4);
-  L.vclean = take((size_t)((r + 31) / 32 * 32) * k * 4);
-  L.tmat = take((size_t)((r + 31) / 32) * 1024 * 4);
-  L.tpart = take((size_t)8 * 1024 * 4);
-  L.wpart = take((size_t)((r + 31) / 32 + 1) * 4 * 1024 * 4);
+  if (cholesky_path(r)) {
+    const size_t rp = (size_t)(r + 31) / 32 * 32;
+    L.T = take((size_t)r * r * 4);
+    L.A0 = take(rp * rp * 8);
+    L.A1 = take(rp * rp * 8);
+    L.diag = take((rp + 2) * 8);
+    L.dinv = take((size_t)2 * 1024 * 8);
+    L.flag = take(rp * 4);
+  } else {
+    L.Jt = take((size_t)r * r * 4);
+    L.vscale = take((size_t)r * 4);
+    L.vclean = take((size_t)((r + 31) / 32 * 32) * k * 4);
+    L.tmat = take((size_t)((r + 31) / 32) * 1024 * 4);
+    L.tpart = take((size_t)8 * 1024 * 4);
+    L.wpart = take((size_t)((r + 31) / 32 + 1) * 4 * 1024 * 4);
+  }
   L.lambda = take((size_t)r * 4);
   L.order = take((size_t)r * 4);
   L.sweep_flag = take((size_t)(kJacobiSweeps + 1) * 4);
-  L.group = take(sizeof(RefreshGroup));  // the descriptor table of the group this tensor leads
+  L.group = take(2 * sizeof(RefreshGroup));  // the descriptor tables of the group this tensor leads
   const bool split = split_products(k, r);
   L.Csplit = take(split ? (size_t)k * 6 * k * 2 : 0);
   L.Qsplit = take(split ? (size_t)r * 6 * k * 2 : 0);
@@ -124,14 +138,7 @@ __global__ __launch_bounds__(256) void upload_group_kernel(const RefreshGroup gr
   for (int i = threadIdx.x; i < (int)(sizeof(RefreshGroup) / 4); i += blockDim.x) out[i] = src[i];
 }
 
-// ---- counter-based Gaussian start block ----------------------------------------------------
-__device__ __forceinline__ uint64_t mix64(uint64_t z) {
-  z += 0x9E3779B97F4A7C15ull;
-  z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
-  z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
-  return z ^ (z >> 31);
-}
-
+// ---- Gaussian start block ---------------------------------------------------------------------
 __global__ __launch_bounds__(256) void gaussian_fill_kernel(const RefreshGroup grp) {
   const RefreshTensor& t = grp.t[blockIdx.y];
   const int64_t count = (int64_t)t.k * grp.r;
@@ -200,7 +207,8 @@ hipError_t refresh_group(const std::vector<RefreshItem>& items, int r, int iters
   RefreshGroup grp{};
   grp.count = n;
   grp.r = r;
-  int64_t kmax = 0;
+  int64_t kmax = 0, kmin = INT64_MAX;
+  const bool cholesky = cholesky_path(r);
   for (int i = 0; i < n; ++i) {
     const RefreshItem& it = items[i];
     const int64_t k = it.rows <= it.cols ? it.rows : it.cols;
@@ -210,14 +218,23 @@ hipError_t refresh_group(const std::vector<RefreshItem>& items, int r, int iters
     t.Q = reinterpret_cast<float*>(it.ws + L.Q);
     t.Z = reinterpret_cast<float*>(it.ws + L.Z);
     t.Bw = reinterpret_cast<float*>(it.ws + L.Bw);
-    t.Jt = reinterpret_cast<float*>(it.ws + L.Jt);
     t.S = reinterpret_cast<float*>(it.ws + L.S);
     t.tau = reinterpret_cast<float*>(it.ws + L.tau);
-    t.vscale = reinterpret_cast<float*>(it.ws + L.vscale);
-    t.vclean = reinterpret_cast<float*>(it.ws + L.vclean);
-    t.tmat = reinterpret_cast<float*>(it.ws + L.tmat);
-    t.tpart = reinterpret_cast<float*>(it.ws + L.tpart);
-    t.wpart = reinterpret_cast<float*>(it.ws + L.wpart);
+    if (cholesky) {
+      t.T = reinterpret_cast<float*>(it.ws + L.T);
+      t.A0 = reinterpret_cast<double*>(it.ws + L.A0);
+      t.A1 = reinterpret_cast<double*>(it.ws + L.A1);
+      t.diag = reinterpret_cast<double*>(it.ws + L.diag);
+      t.dinv = reinterpret_cast<double*>(it.ws + L.dinv);
+      t.flag = reinterpret_cast<int32_t*>(it.ws + L.flag);
+    } else {
+      t.Jt = reinterpret_cast<float*>(it.ws + L.Jt);
+      t.vscale = reinterpret_cast<float*>(it.ws + L.vscale);
+      t.vclean = reinterpret_cast<float*>(it.ws + L.vclean);
+      t.tmat = reinterpret_cast<float*>(it.ws + L.tmat);
+      t.tpart = reinterpret_cast<float*>(it.ws + L.tpart);
+      t.wpart = reinterpret_cast<float*>(it.ws + L.wpart);
+    }
     t.lambda = reinterpret_cast<float*>(it.ws + L.lambda);
     t.order = reinterpret_cast<int32_t*>(it.ws + L.order);
     t.sweep_flag = reinterpret_cast<int32_t*>(it.ws + L.sweep_flag);
@@ -230,14 +247,31 @@ hipError_t refresh_group(const std::vector<RefreshItem>& items, int r, int iters
     t.Csplit = reinterpret_cast<__bf16*>(it.ws + L.Csplit);
     t.Qsplit = reinterpret_cast<__bf16*>(it.ws + L.Qsplit);
     kmax = k > kmax ? k : kmax;
+    kmin = k < kmin ? k : kmin;
   }
 
+  // Cholesky path: two tables in device memory, with the roles of Q and Z as they are and exchanged; flip() makes the
+  // orthonormal block the input of the next pass.
   RefreshGroup* dgrp;
+  RefreshGroup* dgrp_flipped;
+  auto flip = [&] {
+    for (int i = 0; i < n; ++i) std::swap(grp.t[i].Q, grp.t[i].Z);
+    std::swap(dgrp, dgrp_flipped);
+  };
+  auto upload = [&]() -> hipError_t {
+    hipLaunchKernelGGL(upload_group_kernel, dim3(1), dim3(256), 0, stream, grp, dgrp);
+    return hipGetLastError();
+  };
   {
     const RefreshItem& lead = items[0];
     dgrp = reinterpret_cast<RefreshGroup*>(lead.ws + layout_for(lead.rows <= lead.cols ? lead.rows : lead.cols, r).group);
-    hipLaunchKernelGGL(upload_group_kernel, dim3(1), dim3(256), 0, stream, grp, dgrp);
-    GALORE_RETURN_IF(hipGetLastError());
+    dgrp_flipped = dgrp + 1;
+    GALORE_RETURN_IF(upload());
+    if (cholesky) {
+      flip();
+      GALORE_RETURN_IF(upload());
+      flip();
+    }
   }
 
   // Gram matrix of the short side, split by (dtype, orientation).
@@ -270,6 +304,10 @@ hipError_t refresh_group(const std::vector<RefreshItem>& items, int r, int iters
     GALORE_RETURN_IF(hipGetLastError());
   }
 
+  auto gemm = [&](GemmGroup& g, bool b_kcontig) -> hipError_t {
+    if (cholesky) return launch_product(g, DType::F32, b_kcontig, stream);  // small tiles: a low rank leaves the general kernel short of them
+    return launch_gemm_group(g, DType::F32, true, b_kcontig, Epilogue::StoreF32, stream);
+  };
   auto gemm_f32 = [&](int which) -> hipError_t {
     GemmGroup g{};
     if (which == 0 && any_split) {
@@ -288,7 +326,7 @@ hipError_t refresh_group(const std::vector<RefreshItem>& items, int r, int iters
       }
       GALORE_RETURN_IF(launch_gemm_group(gs, DType::BF16, true, true, Epilogue::StoreF32, stream));
       if (g.count == 0) return hipSuccess;
-      return launch_gemm_group(g, DType::F32, true, false, Epilogue::StoreF32, stream);
+      return gemm(g, false);
     }
     g.count = n;
     for (int i = 0; i < n; ++i) {
@@ -299,20 +337,31 @@ hipError_t refresh_group(const std::vector<RefreshItem>& items, int r, int iters
       } else if (which == 1) {  // Bw (r x r) = Qt Zt^T = Q^T C Q
         p.A = t.Q; p.lda = t.k; p.B = t.Z; p.ldb = t.k; p.M = r; p.N = r; p.K = t.k; p.C = t.Bw; p.ldc = r;
       } else {                  // Zt (r x k) = St Qt = (Q S)^T
-        p.A = t.S; p.lda = r; p.B = t.Q; p.ldb = t.k; p.M = r; p.N = t.k; p.K = r; p.C = t.Z; p.ldc = t.k;
+        p.A = cholesky ? t.Bw : t.S; p.lda = r; p.B = t.Q; p.ldb = t.k; p.M = r; p.N = t.k; p.K = r; p.C = t.Z; p.ldc = t.k;
       }
     }
-    return launch_gemm_group(g, DType::F32, true, which == 1, Epilogue::StoreF32, stream);
+    return gemm(g, which == 1);
   };
 
   for (int it = 0; it < iters; ++it) {
     GALORE_RETURN_IF(gemm_f32(0));
-    GALORE_RETURN_IF(launch_householder_qr(grp, dgrp, kmax, stream));
+    if (!cholesky) {
+      GALORE_RETURN_IF(launch_householder_qr(grp, dgrp, kmax, stream));
+      continue;
+    }
+    // The last round's block is the basis of the Rayleigh-Ritz step and has to be orthonormal: a second pass on the result
+    // of the first, whose condition number is small; a third where replaced columns leave little room to be independent.
+    const int passes = it + 1 < iters ? 1 : 2 * r > kmin ? 3 : 2;
+    for (int pass = 0; pass < passes; ++pass) {
+      if (pass) flip();
+      GALORE_RETURN_IF(launch_orthonormalise(grp, dgrp, 4 * it + pass, /*followed_by_pass=*/passes > 1, stream));
+    }
   }
 
   // Rayleigh-Ritz
   GALORE_RETURN_IF(gemm_f32(0));
-  GALORE_RETURN_IF(gemm_f32(1));
+  if (cholesky) GALORE_RETURN_IF(launch_ritz_factor(grp, dgrp, stream));
+  else GALORE_RETURN_IF(gemm_f32(1));
   GALORE_RETURN_IF(launch_ritz_solve(grp, dgrp, crowded, stream));
   GALORE_RETURN_IF(gemm_f32(2));
 

@@ -1,7 +1,7 @@
 // Shared pieces of the subspace refresh (Algorithm 2, refresh branch; Sec. 3.3 SVD equation): the per-tensor
 // descriptor table the kernels read, workspace layout, tuning constants, block reductions, and the entry points
-// of the two long launch sequences (Householder QR in refresh_qr.hip, Rayleigh-Ritz eigen-solve in
-// refresh_ritz.hip) that the driver in refresh.hip strings together.
+// of the long launch sequences (Householder QR in refresh_qr.hip, Cholesky QR in refresh_chol.hip, Rayleigh-Ritz eigen-solve
+// in refresh_ritz.hip) that the driver in refresh.hip strings together.
 #pragma once
 #include <cstdlib>
 #include <type_traits>
@@ -20,17 +20,38 @@ constexpr float kJacobiTol = 1e-5f;  // |b_p.b_q| <= tol |b_p||b_q|: a few times
 // products of long fp32 rows keep crossing kJacobiTol by rounding alone, so "no rotation at all" is
 // rarely reached although the result has stopped changing.
 constexpr float kJacobiStopTol = 4e-5f;
+// The Cholesky path (below) rotates the rows of a factor L^T of the Rayleigh-Ritz matrix, whose lengths are the square roots of
+// the Ritz values, so the same inner product is twice the angle; and no rotation is accumulated, so tighter levels cost little:
+// 7B layer, neighbouring Ritz values 0.4% apart, median error of a bf16 column (1.62e-3 by its rounding alone) 1.76e-3 at a level of
+// 5e-6, 1.65e-3 at 2e-6, 1.63e-3 at 1e-6, in 14.4, 14.8 and 15.9 ms.
+constexpr float kFactorTol = 2e-6f;
+constexpr float kFactorStopTol = 1e-5f;
+// Largest rank of the Cholesky path (refresh_chol.hip); higher ranks take Householder QR and Jacobi on the Rayleigh-Ritz matrix itself.
+// The Cholesky path is faster at every rank (7B layer set, r = 1024: 34 ms against 62) and closer to the exact vectors.  But a
+// projector's columns are signed by their largest entry, and with a thousand directions inside a factor of 8 some columns
+// have two entries that tie to 1e-3 or less: there the two paths, each right to its rounding, differ by the signs of about
+// one column in 10^4, which a run that is resumed or compared across versions would see.  At r = 256 (350M) they agree
+// to 8e-4 in norm.
+constexpr int kCholeskyMaxRank = 256;
+inline bool cholesky_path(int64_t r) { return r <= kCholeskyMaxRank; }
 constexpr int kNB = 8;               // reflectors per Householder panel (block_sum_vec sums 8 values)
 constexpr int kRPT = 4;              // rows per thread in the panel kernels (1024 threads): k - j0 <= 4096
 constexpr int kSW = 8;               // columns per block in the blocked reflector application
 
 struct RefreshTensor {
+  // Jt, tau .. wpart belong to the Householder path, T .. flag to the Cholesky path; null in the other.
   float* C;      // k x k Gram matrix
   float* Q;      // Qt: r x k, the iteration block transposed
   float* Z;      // Zt: r x k, product block / factored reflectors / fp32 projector, transposed
-  float* Bw;     // r x r Rayleigh-Ritz matrix, rotated in place
+  float* Bw;     // r x r Rayleigh-Ritz matrix (Cholesky path: its transposed Cholesky factor), rotated in place
   float* Jt;     // r x r accumulated rotations (rows = eigenvectors)
-  float* S;      // St: r x r, rows = eigenvectors, ordered by decreasing Ritz value, unit length
+  float* S;      // St: r x r, rows = eigenvectors, ordered by decreasing Ritz value, unit length (Cholesky path: before, the inverse factor of a QR)
+  float* T;      // r x r: factor that makes St orthonormal
+  double* A0;    // round_up(r, 32) squared, twice: the matrix being factored (see chol_step_kernel)
+  double* A1;
+  double* diag;  // round_up(r, 32) + 2: diagonal of the matrix being factored; its shift and scale
+  double* dinv;  // 2 x 32 x 32: inverse of the diagonal block of the step
+  int32_t* flag; // round_up(r, 32): dependent columns
   float* tau;    // r
   float* vscale; // r
   float* vclean; // round_up(r, 32) x k: reflectors as plain vectors (unit diagonal, zeros above, scaled), transposed
@@ -62,7 +83,7 @@ struct RefreshGroup {
 };
 
 struct Layout {
-  size_t C, Q, Z, Bw, Jt, S, tau, vscale, vclean, tmat, tpart, wpart, lambda, order, sweep_flag, group, Csplit, Qsplit, total;
+  size_t C, Q, Z, Bw, Jt, S, T, A0, A1, diag, dinv, flag, tau, vscale, vclean, tmat, tpart, wpart, lambda, order, sweep_flag, group, Csplit, Qsplit, total;
 };
 
 bool split_products(int64_t k, int64_t r);
@@ -84,8 +105,13 @@ inline unsigned blocks_for(int64_t count, int per_block, unsigned cap) {
 // Householder QR of Zt (r x k per tensor, transposed layout) of every tensor of the group, reflectors left in Zt,
 // then Qt <- the orthonormal factor (refresh_qr.hip).  dgrp: the group's table in device memory; kmax: largest short side.
 hipError_t launch_householder_qr(const RefreshGroup& grp, const RefreshGroup* dgrp, int64_t kmax, hipStream_t stream);
-// Eigen-decomposition of the symmetric r x r matrix in Bw by blocked one-sided Jacobi, eigenvectors ordered by
-// decreasing Ritz value and normalised into S (refresh_ritz.hip).
+// Cholesky path: Qt <- orthonormal rows spanning those of Zt (refresh_chol.hip).  pass: number of this pass within the
+// refresh; followed_by_pass: another pass works on the result.
+hipError_t launch_orthonormalise(const RefreshGroup& grp, const RefreshGroup* dgrp, int pass, bool followed_by_pass, hipStream_t stream);
+// Cholesky path: Bw <- L^T with L L^T = Qt Zt^T, the Rayleigh-Ritz matrix, shifted by a little of its norm (refresh_chol.hip).
+hipError_t launch_ritz_factor(const RefreshGroup& grp, const RefreshGroup* dgrp, hipStream_t stream);
+// Eigen-decomposition of the symmetric r x r matrix in Bw (Cholesky path: given by its transposed factor) by blocked
+// one-sided Jacobi, eigenvectors ordered by decreasing Ritz value and normalised into S (Cholesky path: Bw) (refresh_ritz.hip).
 hipError_t launch_ritz_solve(const RefreshGroup& grp, const RefreshGroup* dgrp, bool crowded, hipStream_t stream);
 
 namespace {
@@ -122,12 +148,21 @@ __device__ __forceinline__ float block_sum(float v, float* red) {
   return s;
 }
 
+// ---- counter-based pseudo-random bits --------------------------------------------------------
+__device__ __forceinline__ uint64_t mix64(uint64_t z) {
+  z += 0x9E3779B97F4A7C15ull;
+  z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+  z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+  return z ^ (z >> 31);
+}
+
 // which 0: Qt <- [I_r 0] (r x k);  which 1: Jt <- I_r and the sweep flags <- 0
 __global__ __launch_bounds__(256) void identity_fill_kernel(const RefreshGroup* __restrict__ gp, int which) {
   const RefreshGroup& grp = *gp;
   const RefreshTensor& t = grp.t[blockIdx.y];
   const int r = grp.r;
   if (which == 1 && blockIdx.x == 0 && threadIdx.x <= kJacobiSweeps) t.sweep_flag[threadIdx.x] = 0;
+  if (which == 1 && !t.Jt) return;
   float* X = which == 0 ? t.Q : t.Jt;
   const int64_t width = which == 0 ? t.k : r;
   const int64_t count = width * r;

@@ -40,22 +40,21 @@ __global__ __launch_bounds__(256) void jacobi_round_kernel(const RefreshGroup* _
   b = red[1][0] + red[1][1] + red[1][2] + red[1][3];
   c = red[2][0] + red[2][1] + red[2][2] + red[2][3];
   if (a == 0.f || b == 0.f) return;
-  if (fabsf(c) <= kJacobiTol * sqrtf(a) * sqrtf(b)) return;
+  if (fabsf(c) <= (t.Jt ? kJacobiTol : kFactorTol) * sqrtf(a) * sqrtf(b)) return;
   const float zeta = (b - a) / (2.f * c);
   const float tt = copysignf(1.f, zeta) / (fabsf(zeta) + sqrtf(1.f + zeta * zeta));
   const float cs = 1.f / sqrtf(1.f + tt * tt);
   const float sn = cs * tt;
   if (threadIdx.x == 0) t.sweep_flag[sweep] = 1;  // idempotent plain store, no atomics
-  float* jp = t.Jt + (size_t)p * r;
-  float* jq = t.Jt + (size_t)q * r;
-  for (int i = threadIdx.x; i < r; i += 256) {
-    const float x = bp[i], y = bq[i];
-    bp[i] = cs * x - sn * y;
-    bq[i] = sn * x + cs * y;
-    const float u = jp[i], v = jq[i];
-    jp[i] = cs * u - sn * v;
-    jq[i] = sn * u + cs * v;
-  }
+  auto rotate = [&](float* yp, float* yq) {
+    for (int i = threadIdx.x; i < r; i += 256) {
+      const float x = yp[i], y = yq[i];
+      yp[i] = cs * x - sn * y;
+      yq[i] = sn * x + cs * y;
+    }
+  };
+  rotate(bp, bq);
+  if (t.Jt) rotate(t.Jt + (size_t)p * r, t.Jt + (size_t)q * r);
 }
 
 // ---- block one-sided Jacobi ------------------------------------------------------------------
@@ -120,6 +119,7 @@ __global__ __launch_bounds__(1024) void jacobi_block_round_kernel(const RefreshG
 
   constexpr int NV = kJacobiMaxR / 256;      // float4 per lane per row, upper bound
   const bool row_ok = wave < B;
+  const float tol2 = t.Jt ? kJacobiTol * kJacobiTol : kFactorTol * kFactorTol;
   for (int isw = 0; isw < kInnerSweeps; ++isw)
     for (int ir = 0; ir < R2 - 1; ++ir) {
       if (row_ok) {
@@ -141,7 +141,7 @@ __global__ __launch_bounds__(1024) void jacobi_block_round_kernel(const RefreshG
             for (int k = 0; k < 4; ++k) { a += u[i][k] * u[i][k]; bb += v[i][k] * v[i][k]; c += u[i][k] * v[i][k]; }
           }
           a = wave_sum(a); bb = wave_sum(bb); c = wave_sum(c);
-          if (a != 0.f && bb != 0.f && c * c > (kJacobiTol * kJacobiTol) * a * bb) {
+          if (a != 0.f && bb != 0.f && c * c > tol2 * a * bb) {
             const float zeta = (bb - a) / (2.f * c);
             const float tt = copysignf(1.f, zeta) / (fabsf(zeta) + sqrtf(1.f + zeta * zeta));
             const float cs = 1.f / sqrtf(1.f + tt * tt);
@@ -179,6 +179,7 @@ __global__ __launch_bounds__(1024) void jacobi_block_round_kernel(const RefreshG
       for (int e = lane; e < r; e += 64) t.Bw[(size_t)g * r + e] = X[(size_t)ls * rp + e];
     }
   }
+  if (!t.Jt) return;
   // Jt rows <- Rot * Jt rows, one column per thread; RotT[j][:] is read as broadcast float4
   int gr[R2];
 #pragma unroll
@@ -367,6 +368,8 @@ __global__ __launch_bounds__(64 * NW, 16 / NW) void jacobi_gram_round_kernel(con
   // wavefront updates per share take theirs from the lanes whose column has that number, and G and the
   // accumulated rotation are both updated entry by entry from one buffer into the other.
   int cur = 0;
+  const float tol2 = t.Jt ? kJacobiTol * kJacobiTol : kFactorTol * kFactorTol;
+  const float stop2 = t.Jt ? kJacobiStopTol * kJacobiStopTol : kFactorStopTol * kFactorStopTol;
   // Round 0 of a sweep pairs every block exactly once: there the inner sweep covers all pairs of the
   // 32 rows (31 rounds), which also rotates the pairs INSIDE each block once per sweep.  The other
   // rounds only need the 16 x 16 pairs between the two blocks: 16 rounds of (i, 16 + (i + ir) % 16).
@@ -409,7 +412,7 @@ __global__ __launch_bounds__(64 * NW, 16 / NW) void jacobi_gram_round_kernel(con
         rij[sh] = Rc[i * GP + j]; rpij[sh] = Rc[pi * GP + j];
       }
       __builtin_amdgcn_sched_barrier(0);
-      const bool rot = ((exist >> p) & (exist >> q) & 1u) != 0 && a > 0.f && bb > 0.f && c * c > (kJacobiTol * kJacobiTol) * a * bb;
+      const bool rot = ((exist >> p) & (exist >> q) & 1u) != 0 && a > 0.f && bb > 0.f && c * c > tol2 * a * bb;
       // hardware reciprocal / square-root approximations (1 ulp): a rotation with c^2 + s^2 = 1 to
       // within a few ulps is all that is needed, and this chain is the latency of every inner round.
       // Computed by every lane and selected afterwards (a pair that is not rotated may divide by zero).
@@ -421,7 +424,7 @@ __global__ __launch_bounds__(64 * NW, 16 / NW) void jacobi_gram_round_kernel(con
       const float aj = cs, bj2 = j == p ? -sn : sn;
       if (wave == 0 && rot) {  // same value from every lane that writes
         rotated = 1;
-        if (c * c > (kJacobiStopTol * kJacobiStopTol) * a * bb) significant = 1;
+        if (c * c > stop2 * a * bb) significant = 1;
       }
 #pragma unroll
       for (int sh = 0; sh < VW; ++sh) {
@@ -462,21 +465,23 @@ __global__ __launch_bounds__(64 * NW, 16 / NW) void jacobi_gram_round_kernel(con
 #pragma unroll
       for (int v = 0; v < 4; ++v) out_rows[h][v] = grow(16 * h + 4 * g + v);
     gram_apply_rotation(t.Bw, r, rows, out_rows, rot, wave, lane, NW);
-    gram_apply_rotation(t.Jt, r, rows, out_rows, rot, wave, lane, NW);
+    if (t.Jt) gram_apply_rotation(t.Jt, r, rows, out_rows, rot, wave, lane, NW);
   }
 }
 
 // lambda_i = |row i of Bw| ; order[i] = number of rows that come before row i when sorted by
 // decreasing lambda (ties: lower index first).  The thousands of fp32 rotations let the length
 // of each accumulated eigenvector drift by a few 1e-6; tau[i] (free by now) gets 1 / |row i of Jt|
-// so the vectors are rescaled to unit length when they are copied out.
+// so the vectors are rescaled to unit length when they are copied out.  On the Cholesky path row i of Bw is
+// the square root of the Ritz value times the eigenvector: the same order, and the vectors are the rows themselves.
 __global__ __launch_bounds__(256) void ritz_values_kernel(const RefreshGroup grp) {
   __shared__ float red[2][4];
   const RefreshTensor& t = grp.t[blockIdx.y];
   const int r = grp.r, i = blockIdx.x;
+  const float* V = t.Jt ? t.Jt : t.Bw;
   float a = 0.f, b = 0.f;
   for (int c = threadIdx.x; c < r; c += 256) {
-    const float x = t.Bw[(size_t)i * r + c], y = t.Jt[(size_t)i * r + c];
+    const float x = t.Bw[(size_t)i * r + c], y = V[(size_t)i * r + c];
     a += x * x; b += y * y;
   }
   a = wave_sum(a); b = wave_sum(b);
@@ -502,16 +507,27 @@ __global__ __launch_bounds__(256) void ritz_order_kernel(const RefreshGroup grp)
   }
 }
 
-// St[order[i]][:] = Jt[i][:] / |Jt[i]|
+// St[order[i]][:] = Jt[i][:] / |Jt[i]| (Cholesky path: of Bw)
 __global__ __launch_bounds__(256) void ritz_vectors_kernel(const RefreshGroup grp) {
   const RefreshTensor& t = grp.t[blockIdx.y];
   const int r = grp.r;
+  const float* V = t.Jt ? t.Jt : t.Bw;
   const int64_t count = (int64_t)r * r;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < count; e += stride) {
     const int i = (int)(e / r), kk = (int)(e % r);
-    t.S[(size_t)t.order[i] * r + kk] = t.Jt[e] * t.tau[i];
+    t.S[(size_t)t.order[i] * r + kk] = V[e] * t.tau[i];
   }
+}
+
+// T <- (3 I - T) / 2
+__global__ __launch_bounds__(256) void polish_factor_kernel(const RefreshGroup grp) {
+  const RefreshTensor& t = grp.t[blockIdx.y];
+  const int r = grp.r;
+  const int64_t count = (int64_t)r * r;
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < count; e += stride)
+    t.T[e] = (e / r == e % r ? 1.5f : 0.f) - 0.5f * t.T[e];
 }
 
 }  // namespace
@@ -558,7 +574,22 @@ hipError_t launch_ritz_solve(const RefreshGroup& grp, const RefreshGroup* dgrp, 
   hipLaunchKernelGGL(ritz_order_kernel, dim3((r + 255) / 256, n), dim3(256), 0, stream, grp);
   hipLaunchKernelGGL(ritz_vectors_kernel, dim3(blocks_for((int64_t)r * r, 256 * 8, 1024), n), dim3(256), 0, stream, grp);
   GALORE_RETURN_IF(hipGetLastError());
-  return hipGetLastError();
+  if (!cholesky_path(r)) return hipSuccess;
+  // The normalised rows are as orthogonal as Jacobi left them: one step of S <- (3 I - S S^T) S / 2 squares what is missing.
+  for (int which = 0; which < 2; ++which) {
+    GemmGroup g{};
+    g.count = n;
+    for (int i = 0; i < n; ++i) {
+      const RefreshTensor& t = grp.t[i];
+      GemmProblem& p = g.p[i];
+      p.A = which ? t.T : t.S; p.B = t.S; p.C = which ? t.Bw : t.T;
+      p.lda = p.ldb = p.ldc = p.M = p.N = p.K = r;
+    }
+    GALORE_RETURN_IF(launch_product(g, DType::F32, which == 0, stream));
+    if (which == 0) hipLaunchKernelGGL(polish_factor_kernel, dim3(blocks_for((int64_t)r * r, 256 * 8, 1024), n), dim3(256), 0, stream, grp);
+    GALORE_RETURN_IF(hipGetLastError());
+  }
+  return hipSuccess;
 }
 
 }  // namespace rf

@@ -1,0 +1,86 @@
+"""Cholesky QR and the Cholesky-factored Ritz step of the subspace refresh against the fp64 oracle, at the sizes where they
+can go wrong: one column to either side of a 32-column block, contractions of no multiple of a 16-position group, ranks up to
+the short side, and blocks whose columns become dependent (gradients of rank below r) inside and across column blocks."""
+import numpy as np
+import pytest
+import torch
+
+from helpers import to64
+from oracle import galore_oracle as orc
+from paper_2403_03507_amd import binding as gb
+from paper_2403_03507_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def _projector(G, r, iters=6):
+    W = [torch.zeros_like(G).cuda()]
+    opt = gb.GaLore(W, r, refresh_iters=iters, auto_refresh=False)
+    opt.refresh([G.cuda()])
+    torch.cuda.synchronize()
+    P = to64(opt.proj[0])
+    opt.close()
+    return P
+
+
+def _check_orthonormal(P):
+    # fp32 columns, each entry a sum of up to k products: 1e-5 as in every refresh test
+    assert np.isfinite(P).all()
+    assert np.abs(P.T @ P - np.eye(P.shape[1])).max() <= 1e-5
+
+
+@pytest.mark.parametrize("k", [130, 133, 200, 256])
+@pytest.mark.parametrize("r", [1, 31, 32, 33, 64, 95])
+def test_block_edges(k, r):
+    # gapped spectrum: the subspace and its vectors are determined; 1e-3 as in the other fp32 refresh tests
+    G = wl.GradientSource(k, 300, 501 + r, "gapped", gap_rank=r).grad(0)
+    P = _projector(G, r)
+    _check_orthonormal(P)
+    P0, _ = orc.projector(to64(G), r)
+    assert np.linalg.norm(P @ P.T - P0 @ P0.T) <= 1e-3
+
+
+@pytest.mark.parametrize("r", [255, 256, 257])
+def test_largest_rank_of_the_path(r):
+    # 257 takes the Householder path
+    G = wl.GradientSource(520, 530, 520 + r, "gapped", gap_rank=r).grad(0)
+    P = _projector(G, r)
+    _check_orthonormal(P)
+    s = np.linalg.svd(to64(G), compute_uv=False)
+    assert np.linalg.norm(P.T @ to64(G)) ** 2 >= (1 - 1e-5) * np.sum(s[:r] ** 2)
+
+
+@pytest.mark.parametrize("k,r", [(48, 48), (65, 65), (100, 97)])
+def test_rank_up_to_the_short_side(k, r):
+    G = wl.GradientSource(k, 190, 540 + r, "gapped", gap_rank=min(r, k - 1)).grad(0)
+    P = _projector(G, r)
+    _check_orthonormal(P)
+    assert np.linalg.norm(P.T @ to64(G)) ** 2 >= (1 - 1e-5) * np.sum(np.linalg.svd(to64(G), compute_uv=False)[:r] ** 2)
+
+
+@pytest.mark.parametrize("rank", [0, 1, 5, 31, 33, 40])
+@pytest.mark.parametrize("rows", ["dense", "few"])
+@pytest.mark.parametrize("k,r", [(128, 48), (129, 70), (96, 96)])
+def test_dependent_columns(rank, rows, k, r):
+    # rank(G) < r: whatever completes the basis, it is orthonormal and captures all of G
+    g = torch.Generator().manual_seed(560 + rank)
+    a = torch.randn(k, rank, generator=g)
+    if rows == "few":
+        a[rank:] = 0
+    G = a @ torch.randn(rank, 200, generator=g) if rank else torch.zeros(k, 200)
+    P = _projector(G, r, iters=4)
+    _check_orthonormal(P)
+    total = np.linalg.norm(to64(G)) ** 2
+    assert abs(np.linalg.norm(P.T @ to64(G)) ** 2 - total) <= 1e-5 * total
+
+
+@pytest.mark.parametrize("scale", [1e-18, 1e-12, 1e-6, 1e6, 1e12])
+def test_scale_of_the_gradient(scale):
+    # Gram entries from below the smallest fp32 number to 1e26: orthonormal, and the same subspace wherever C does not underflow
+    r = 40
+    G = wl.GradientSource(144, 300, 580, "gapped", gap_rank=r).grad(0)
+    P = _projector(G * scale, r)
+    _check_orthonormal(P)
+    if scale >= 1e-12:
+        P0, _ = orc.projector(to64(G), r)
+        assert np.linalg.norm(P @ P.T - P0 @ P0.T) <= 1e-3
