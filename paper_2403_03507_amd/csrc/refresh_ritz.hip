@@ -66,10 +66,6 @@ __global__ __launch_bounds__(256) void jacobi_round_kernel(const RefreshGroup* _
 // blocks), so a sweep over all pairs of rows costs (blocks - 1) launches that each read and write
 // Bw and Jt once, instead of (r - 1) launches.
 constexpr int kInnerSweeps = 1;
-#ifndef GALORE_GRAM_INNER
-#define GALORE_GRAM_INNER 1
-#endif
-constexpr int kGramInnerSweeps = GALORE_GRAM_INNER;  // inner sweeps of the Gram-maintained block round
 constexpr int kJacobiMaxR = 1280;  // longest row the register-resident inner loop is unrolled for (5 float4 per lane and row)
 
 typedef float jf4 __attribute__((ext_vector_type(4)));
@@ -254,6 +250,11 @@ __device__ __forceinline__ void gram_apply_rotation(float* __restrict__ Y, int r
   }
 }
 
+// Value of the first lane of each row of 16 lanes, in all lanes of the row.
+__device__ __forceinline__ float row_first(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x150, 0xF, 0xF, false));  // row_newbcast:0
+}
+
 // NW = wavefronts per workgroup.  The work is laid out in 16 shares (two Gram rows per share and inner
 // round, one entry per lane); a wavefront takes 16 / NW of them and 16 / NW workgroups fit a CU (<= 128
 // registers per lane).  An inner round is bound by latency (one LDS round trip, the reciprocal / square
@@ -289,6 +290,12 @@ __global__ __launch_bounds__(64 * NW, 16 / NW) void jacobi_gram_round_kernel(con
     const int g = ls < B ? bi * B + ls : bj * B + (ls - B);
     return ((ls < B || bj < nblocks) && g < r) ? g : -1;
   };
+
+  // Round 0 of a sweep pairs every block exactly once: there the inner sweep covers all pairs of the
+  // 32 rows (31 rounds), which also rotates the pairs INSIDE each block once per sweep.  The other
+  // rounds only need the 16 x 16 pairs between the two blocks: 16 rounds of (i, 16 + (i + ir) % 16).
+  const bool all_pairs = round == 0;
+  auto slot = [&](int x) { return !all_pairs ? x : x < B ? B + x : R2 - 1 - x; };  // where a row starts (see 2. below)
 
   // 1. Gram matrix.  The columns are dealt in groups of 16 to kGramSlices slices (group S belongs to
   // slice S mod kGramSlices; the number of slices is fixed so that the result does not depend on NW).  A
@@ -356,94 +363,87 @@ __global__ __launch_bounds__(64 * NW, 16 / NW) void jacobi_gram_round_kernel(con
     float sum = 0.f;
 #pragma unroll
     for (int sl = 0; sl < kGramSlices; ++sl) sum += stage[(sl * 3 + b3) * 256 + rr * 16 + cc];
-    Gm[0][i * GP + j] = sum;
-    Rot[i * GP + j] = i == j ? 1.f : 0.f;
+    Gm[0][slot(i) * GP + slot(j)] = sum;
+    Rot[slot(i) * GP + j] = i == j ? 1.f : 0.f;
   }
   __syncthreads();
 
-  // 2. inner sweeps on the Gram matrix.  One barrier and one LDS round trip per inner round: the pairing
-  // of a round is arithmetic (mate()), so every lane derives the rotation of the pair that holds its
-  // column j from three Gram entries by itself (the 32 columns of a wavefront cover all 16 pairs; the
-  // lanes of a pair read the same entries in the same order, so they agree to the bit), the two rows a
-  // wavefront updates per share take theirs from the lanes whose column has that number, and G and the
-  // accumulated rotation are both updated entry by entry from one buffer into the other.
+  // 2. inner sweep on the Gram matrix.  Rows sit in 32 slots and slot x < 16 always meets slot x + 16: what changes from
+  // inner round to inner round is which row a slot holds, because every round writes its results to where the next one
+  // expects them.  All LDS addresses are therefore constants of a thread.  Thread (x, y) of the first four wavefronts owns
+  // the 2 x 2 entries of G where pairs x and y cross, and two columns of the rows of pair x in the accumulated rotation.
+  // It derives the rotation of pair y from three Gram entries by itself; as y = x + tid % 16 (mod 16), the rotation of pair
+  // x is what the first lane of its row of 16 lanes has.  One barrier and one LDS round trip per inner round.  (With rows that
+  // stay and one entry per lane, over all wavefronts, the index arithmetic of the pairing was most of an inner round.)
   int cur = 0;
   const float tol2 = t.Jt ? kJacobiTol * kJacobiTol : kFactorTol * kFactorTol;
   const float stop2 = t.Jt ? kJacobiStopTol * kJacobiStopTol : kFactorStopTol * kFactorStopTol;
-  // Round 0 of a sweep pairs every block exactly once: there the inner sweep covers all pairs of the
-  // 32 rows (31 rounds), which also rotates the pairs INSIDE each block once per sweep.  The other
-  // rounds only need the 16 x 16 pairs between the two blocks: 16 rounds of (i, 16 + (i + ir) % 16).
-  const int j = lane & 31;
-  const unsigned exist = (unsigned)__ballot(grow(lane & 31) >= 0);  // bit x: local row x exists
-  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-  const bool upper = lane >= 32;
+  const bool worker = __builtin_amdgcn_readfirstlane(wave) < 4;   // uniform; the other wavefronts only keep the barriers
+  const int px = (tid >> 4) & 15, py = (px + tid) & 15, c0 = tid & 15;
+  bool any = false, sig = false;
   // the two pairings are compiled apart (the choice is uniform), so each inner loop carries only its own index arithmetic
-  auto inner_sweeps = [&](auto all_pairs_t) {
-  constexpr bool all_pairs = decltype(all_pairs_t)::value;
-  constexpr int inner_rounds = all_pairs ? R2 - 1 : B;
-  for (int isw = 0; isw < kGramInnerSweeps; ++isw)
+  auto inner_sweep = [&](auto all_pairs_t) {
+    constexpr bool all_pairs = decltype(all_pairs_t)::value;
+    constexpr int inner_rounds = all_pairs ? R2 - 1 : B;
+    // slot of the next round for what is in slot z now; after all inner rounds every row is back in its first slot.
+    // All pairs: round robin of 32 players, slot 0 stays, 1 .. 15 move up, 15 -> 31, 31 .. 17 move down, 16 -> 1.
+    auto next = [&](int z) {
+      if constexpr (all_pairs) return z == 0 ? 0 : z < B - 1 ? z + 1 : z == B - 1 ? R2 - 1 : z == B ? 1 : z - 1;
+      else return z < B ? z : B + ((z - 1) & (B - 1));
+    };
+    const int nx0 = next(px) * GP, nx1 = next(px + B) * GP, ny0 = next(py), ny1 = next(py + B);
+    const int x0 = px * GP, x1 = (px + B) * GP, y0 = py * GP, y1 = (py + B) * GP;
     for (int ir = 0; ir < inner_rounds; ++ir) {
-      const float* G = Gm[cur];
-      float* Gn = Gm[cur ^ 1];
-      const float* Rc = cur ? stage : Rot;   // the staging area of the Gram phase is free by now
-      float* Rn = cur ? Rot : stage;
-      // the row that row x is paired with in this inner round (selects only: no divergent branches)
-      auto mate = [&](int x) {
-        // round robin of 32 players: row 31 stays, rows with p + q = 2 ir (mod 31) meet
-        int y = 2 * ir - x;
-        y += y < 0 ? R2 - 1 : 0;
-        y -= y >= R2 - 1 ? R2 - 1 : 0;
-        y = x == ir ? R2 - 1 : y;
-        y = x == R2 - 1 ? ir : y;
-        const int z = x < B ? B + ((x + ir) & (B - 1)) : ((x - B - ir) & (B - 1));
-        if constexpr (all_pairs) return y;
-        else return z;
-      };
-      const int pj = mate(j);
-      const int p = j < pj ? j : pj, q = j < pj ? pj : j;
-      // every LDS read of the round is issued here, ahead of the arithmetic: one round trip
-      const float a = G[p * GP + p], bb = G[q * GP + q], c = G[p * GP + q];
-      float gij[VW], gipj[VW], gpij[VW], gpipj[VW], rij[VW], rpij[VW];
-#pragma unroll
-      for (int sh = 0; sh < VW; ++sh) {
-        const int i = 2 * (wave_u + NW * sh) + (upper ? 1 : 0);  // lanes 0 .. 31 update row i0, lanes 32 .. 63 row i0 + 1
-        const int pi = mate(i);
-        gij[sh] = G[i * GP + j]; gipj[sh] = G[i * GP + pj]; gpij[sh] = G[pi * GP + j]; gpipj[sh] = G[pi * GP + pj];
-        rij[sh] = Rc[i * GP + j]; rpij[sh] = Rc[pi * GP + j];
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      const bool rot = ((exist >> p) & (exist >> q) & 1u) != 0 && a > 0.f && bb > 0.f && c * c > tol2 * a * bb;
-      // hardware reciprocal / square-root approximations (1 ulp): a rotation with c^2 + s^2 = 1 to
-      // within a few ulps is all that is needed, and this chain is the latency of every inner round.
-      // Computed by every lane and selected afterwards (a pair that is not rotated may divide by zero).
-      const float zeta = (bb - a) * __builtin_amdgcn_rcpf(2.f * c);
-      const float tt = copysignf(1.f, zeta) * __builtin_amdgcn_rcpf(fabsf(zeta) + __builtin_amdgcn_sqrtf(1.f + zeta * zeta));
-      const float cs0 = __builtin_amdgcn_rsqf(1.f + tt * tt);
-      const float cs = rot ? cs0 : 1.f, sn = rot ? cs0 * tt : 0.f;
-      // new row x = alpha_x * row x + beta_x * row mate(x): (cs, -sn) for the lower row of a pair, (cs, sn) for the upper
-      const float aj = cs, bj2 = j == p ? -sn : sn;
-      if (wave == 0 && rot) {  // same value from every lane that writes
-        rotated = 1;
-        if (c * c > stop2 * a * bb) significant = 1;
-      }
-#pragma unroll
-      for (int sh = 0; sh < VW; ++sh) {
-        const int i0 = 2 * (wave_u + NW * sh);
-        const float al0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(aj), i0));
-        const float al1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(aj), i0 + 1));
-        const float be0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(bj2), i0));
-        const float be1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(bj2), i0 + 1));
-        const int i = i0 + (upper ? 1 : 0);
-        const float ai = upper ? al1 : al0, bi2 = upper ? be1 : be0;
-        Gn[i * GP + j] = ai * (aj * gij[sh] + bj2 * gipj[sh]) + bi2 * (aj * gpij[sh] + bj2 * gpipj[sh]);
-        Rn[i * GP + j] = ai * rij[sh] + bi2 * rpij[sh];
+      if (worker) {
+        const float* G = Gm[cur];
+        float* Gn = Gm[cur ^ 1];
+        const float* Rc = cur ? stage : Rot;   // the staging area of the Gram phase is free by now
+        float* Rn = cur ? Rot : stage;
+        // in inner round ir slots x and 16 + x hold rows ir - x and ir + x (mod 31); row 31 stays in slot 0
+        const bool swapped = all_pairs && (py == 0 || ir < py || ir + py >= R2 - 1);   // the lower slot holds the row of the higher number
+        // every LDS read of the round is issued here, ahead of the arithmetic: one round trip
+        const float gl = G[y0 + py], gu = G[y1 + py + B];
+        const float c = G[swapped ? y1 + py : y0 + py + B];
+        const float g00 = G[x0 + py], g01 = G[x0 + py + B], g10 = G[x1 + py], g11 = G[x1 + py + B];
+        const float r00 = Rc[x0 + c0], r01 = Rc[x0 + c0 + B], r10 = Rc[x1 + c0], r11 = Rc[x1 + c0 + B];
+        __builtin_amdgcn_sched_barrier(0);
+        const float a = swapped ? gu : gl, bb = swapped ? gl : gu;
+        const bool rot = a > 0.f && bb > 0.f && c * c > tol2 * a * bb;  // rows that do not exist: a or bb is 0
+        // hardware reciprocal / square-root approximations (1 ulp): a rotation with c^2 + s^2 = 1 to
+        // within a few ulps is all that is needed, and this chain is the latency of every inner round.
+        // Computed by every lane and selected afterwards (a pair that is not rotated may divide by zero).
+        const float zeta = (bb - a) * __builtin_amdgcn_rcpf(2.f * c);
+        const float tt = copysignf(1.f, zeta) * __builtin_amdgcn_rcpf(fabsf(zeta) + __builtin_amdgcn_sqrtf(1.f + zeta * zeta));
+        const float cs0 = __builtin_amdgcn_rsqf(1.f + tt * tt);
+        const float cy = rot ? cs0 : 1.f, sn = rot ? cs0 * tt : 0.f;
+        // new row = c * row + s * row of the other slot, s = -sn for the row of the lower number, sn for the other
+        const float sy = swapped ? sn : -sn;
+        const float cx = row_first(cy), sx = row_first(sy);
+        any |= rot;
+        sig |= rot && c * c > stop2 * a * bb;
+        // written as fused operations so that the results do not hang on the compiler's choice of which product to fuse
+        const float h00 = __builtin_fmaf(cy, g00, sy * g01), h01 = __builtin_fmaf(cy, g01, -sy * g00);  // columns
+        const float h10 = __builtin_fmaf(cy, g10, sy * g11), h11 = __builtin_fmaf(cy, g11, -sy * g10);
+        Gn[nx0 + ny0] = __builtin_fmaf(cx, h00, sx * h10);  // rows
+        Gn[nx0 + ny1] = __builtin_fmaf(cx, h01, sx * h11);
+        Gn[nx1 + ny0] = __builtin_fmaf(cx, h10, -sx * h00);
+        Gn[nx1 + ny1] = __builtin_fmaf(cx, h11, -sx * h01);
+        Rn[nx0 + c0] = __builtin_fmaf(cx, r00, sx * r10);
+        Rn[nx0 + c0 + B] = __builtin_fmaf(cx, r01, sx * r11);
+        Rn[nx1 + c0] = __builtin_fmaf(cx, r10, -sx * r00);
+        Rn[nx1 + c0 + B] = __builtin_fmaf(cx, r11, -sx * r01);
       }
       __syncthreads();
       cur ^= 1;
     }
   };
-  if (round == 0) inner_sweeps(std::true_type{});
-  else inner_sweeps(std::false_type{});
+  if (all_pairs) inner_sweep(std::true_type{});
+  else inner_sweep(std::false_type{});
+  if (wave == 0) {  // same value from every lane that writes
+    if (any) rotated = 1;
+    if (sig) significant = 1;
+  }
+  __syncthreads();
 
   if (rotated == 0) return;  // nothing changed: leave Bw, Jt and the sweep flag alone (uniform)
   if (tid == 0 && significant) t.sweep_flag[sweep] = 1;  // idempotent plain store, no atomics
@@ -457,7 +457,7 @@ __global__ __launch_bounds__(64 * NW, 16 / NW) void jacobi_gram_round_kernel(con
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int sidx = 0; sidx < 8; ++sidx) rot[h][sidx] = Rf[(16 * h + i) * GP + 4 * sidx + g];
+      for (int sidx = 0; sidx < 8; ++sidx) rot[h][sidx] = Rf[slot(16 * h + i) * GP + 4 * sidx + g];
 #pragma unroll
     for (int sidx = 0; sidx < 8; ++sidx) rows[sidx] = grow(4 * sidx + g);
 #pragma unroll
