@@ -72,6 +72,8 @@ constexpr long kLargeProjectionTiles = 160;
 // K pieces), on whichever kernel suits each problem.
 hipError_t launch_weight_update(GemmGroup& g, DType dt, hipStream_t stream);
 hipError_t launch_product(GemmGroup& g, DType dt, bool b_kcontig, hipStream_t stream);
+// The symmetric product C = A A^T (fp32; M == N, B == A) of A as [M][K] (kcontig) or [K][M], likewise.
+hipError_t launch_gram(GemmGroup& g, DType dt, bool kcontig, hipStream_t stream);
 
 // ---- grouped projection GEMM (bf16 operands, fp32 result): R = A * B with A as [M][K] -------------------
 // LEFT tensors:  A = the transposed projector (r x m), B = G as [K = m][N = n]  (b_kcontig = 0)

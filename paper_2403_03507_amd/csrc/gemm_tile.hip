@@ -14,7 +14,7 @@ namespace {
 
 long tiles_of(const GemmProblem& p, int bm, int bn) { return (long)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn) * (p.splits > 1 ? p.splits : 1); }
 
-template <class T, int BM, int BN> hipError_t launch(GemmGroup& g, Epilogue epi, hipStream_t stream) {
+template <class T, int BM, int BN> hipError_t launch(GemmGroup& g, Epilogue epi, hipStream_t stream, bool a_kcontig = true) {
   long total = 0;
   for (int i = 0; i < g.count; ++i) {
     GemmProblem& p = g.p[i];
@@ -26,6 +26,11 @@ template <class T, int BM, int BN> hipError_t launch(GemmGroup& g, Epilogue epi,
   if (total > INT32_MAX) return hipErrorInvalidValue;
   g.total_tiles = (int32_t)total;
   const dim3 grid((unsigned)total);
+  if (!a_kcontig) {
+    if (epi != Epilogue::StoreF32) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((gemm_tile_kernel<T, BM, BN, Epilogue::StoreF32, false>), grid, dim3(256), 0, stream, g);
+    return hipGetLastError();
+  }
   if (epi == Epilogue::StoreF32) hipLaunchKernelGGL((gemm_tile_kernel<T, BM, BN, Epilogue::StoreF32>), grid, dim3(256), 0, stream, g);
   else if (epi == Epilogue::ApplyW) hipLaunchKernelGGL((gemm_tile_kernel<T, BM, BN, Epilogue::ApplyW>), grid, dim3(256), 0, stream, g);
   else if (epi == Epilogue::Adam) hipLaunchKernelGGL((gemm_tile_kernel<T, BM, BN, Epilogue::Adam>), grid, dim3(256), 0, stream, g);
@@ -53,6 +58,8 @@ template <class T> hipError_t launch_typed(GemmGroup& g, Epilogue epi, hipStream
   if (items96 >= (update ? 300 : 500)) return launch<T, 128, 64>(g, epi, stream);
   return launch<T, 64, 64>(g, epi, stream);
 }
+
+constexpr long kGramTiles = 4096;  // 16 per CU: beyond, the general kernel has tiles enough and does half the products
 
 bool fits_large(const GemmProblem& p, Epilogue epi, bool b_kcontig, bool w_any) {
   GemmGroup one{};
@@ -125,6 +132,29 @@ hipError_t launch_product(GemmGroup& g, DType dt, bool b_kcontig, hipStream_t st
   if (e == hipSuccess) e = launch_tile_group(tiles, dt, Epilogue::StoreF32, stream);
   if (e == hipSuccess) e = launch_gemm_group(rest, dt, true, b_kcontig, Epilogue::StoreF32, stream);
   return e;
+}
+
+// Every tile is computed, also those below the diagonal: C_ij and C_ji are the same sum of the same products, and twice the
+// work on 64 x 64 tiles is still less than a handful of 128 x 128 ones.  Whole products of a layer set, us, on the general kernel
+// (LEFT and RIGHT tensors) and here: 60M fp32 (k = 512) 136 + 147 -> 58 + 58, 350M bf16 (k = 1024) 101 + 84 -> 73 + 20.
+hipError_t launch_gram(GemmGroup& g, DType dt, bool kcontig, hipStream_t stream) {
+  long tiles64 = 0;
+  for (int i = 0; i < g.count; ++i) tiles64 += tiles_of(g.p[i], 64, 64);
+  GemmGroup tiles{}, rest{};
+  for (int i = 0; i < g.count; ++i) {
+    GemmProblem& p = g.p[i];
+    p.b_kcontig = kcontig;
+    p.splits = 1;
+    const bool fits = tile_problem_fits(p, dt, kcontig) && tile_problem_fits(p, dt, false) && tiles64 <= kGramTiles;
+    GemmGroup& to = fits ? tiles : rest;
+    to.p[to.count++] = p;
+  }
+  if (tiles.count > 0) {
+    const hipError_t e = dt == DType::BF16 ? launch<__bf16, 64, 64>(tiles, Epilogue::StoreF32, stream, kcontig)
+                                           : launch<float, 64, 64>(tiles, Epilogue::StoreF32, stream, kcontig);
+    if (e != hipSuccess) return e;
+  }
+  return launch_gemm_group(rest, dt, kcontig, kcontig, Epilogue::StoreSymF32, stream);
 }
 
 }  // namespace galore

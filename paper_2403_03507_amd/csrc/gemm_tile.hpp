@@ -1,4 +1,4 @@
-// Small-tile grouped MFMA GEMM (gfx950): C = A B with A as [M][K] and B as [K][N] or [N][K], bf16 or fp32 operands at
+// Small-tile grouped MFMA GEMM (gfx950): C = A B with A as [M][K] (or, for Gram matrices, [K][M]) and B as [K][N] or [N][K], bf16 or fp32 operands at
 // any element alignment, fp32 accumulate, optionally with the contraction cut into pieces.
 //
 // The 256 x 256 kernels (gemm_mfma_dl.hpp, gemm_proj_dl.hpp) need hundreds of tiles to fill the chip; a layer of a
@@ -123,7 +123,8 @@ template <class T, int BM_, int BN_> struct SmallTile {
   }
 };
 
-template <class T, int BM, int BN_, Epilogue EPI>
+// AKC: A as [M][K]; else (StoreF32 only) as [K][M]
+template <class T, int BM, int BN_, Epilogue EPI, bool AKC = true>
 __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(const GemmGroup grp) {
   using Cfg = SmallTile<T, BM, BN_>;
   using ET = ElemTraits<T>;
@@ -173,16 +174,17 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(const GemmGroup grp) 
   auto run = [&](auto kc) {
     constexpr bool BKC = decltype(kc)::value;
     const bool edge_n = !BKC && n0 + BN > N;
+    const bool edge_m = !AKC && m0 + BM > M;
     // two register sets: the pieces of the next two K steps are in flight while one is multiplied
     u32x4 ra0[AOp::PER], rb0[BOp::PER], ra1[AOp::PER], rb1[BOp::PER];
     auto load = [&](u32x4 (&ra)[AOp::PER], u32x4 (&rb)[BOp::PER], int kt) {
-      AOp::template load<true>(ra, A, pr.lda, m0, M, kt * BK, K, tid);
+      AOp::template load<AKC>(ra, A, pr.lda, m0, M, kt * BK, K, tid);
       BOp::template load<BKC>(rb, B, pr.ldb, n0, N, kt * BK, K, tid);
     };
     auto step = [&](u32x4 (&ra)[AOp::PER], u32x4 (&rb)[BOp::PER], int kt) {
       const int k = kt * BK;
       const bool tail = k + BK > K;
-      AOp::template store<true>(ra, As, m0, M, k, K, tail, tid);
+      AOp::template store<AKC>(ra, As, m0, M, k, K, tail || edge_m, tid);
       BOp::template store<BKC>(rb, Bs, n0, N, k, K, tail || edge_n, tid);
       __syncthreads();
       if (kt + 2 < last) load(ra, rb, kt + 2);
@@ -190,7 +192,7 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(const GemmGroup grp) 
       for (int kk = 0; kk < BK; kk += ET::KSTEP) {
         Frag<T> fa[TM], fb[TN];
 #pragma unroll
-        for (int i = 0; i < TM; ++i) AOp::template frag<true>(fa[i], As, wm0 + 32 * i, kk, lane);
+        for (int i = 0; i < TM; ++i) AOp::template frag<AKC>(fa[i], As, wm0 + 32 * i, kk, lane);
 #pragma unroll
         for (int j = 0; j < TN; ++j) BOp::template frag<BKC>(fb[j], Bs, wn0 + 32 * j, kk, lane);
 #pragma unroll
@@ -218,6 +220,8 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(const GemmGroup grp) 
   };
   if constexpr (EPI == Epilogue::ApplyW) {
     run(std::true_type{});
+  } else if constexpr (!AKC) {
+    run(std::false_type{});
   } else {
     if (pr.b_kcontig) run(std::true_type{});
     else run(std::false_type{});

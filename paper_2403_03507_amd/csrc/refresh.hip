@@ -289,7 +289,8 @@ hipError_t refresh_group(const std::vector<RefreshItem>& items, int r, int iters
         p.C = grp.t[i].C; p.ldc = grp.t[i].k;
       }
       // LEFT: C = G G^T, both operands [row][K] ; RIGHT: C = G^T G, both operands [K][col]
-      GALORE_RETURN_IF(launch_gemm_group(g, dt, left != 0, left != 0, Epilogue::StoreSymF32, stream));
+      if (cholesky) GALORE_RETURN_IF(launch_gram(g, dt, left != 0, stream));
+      else GALORE_RETURN_IF(launch_gemm_group(g, dt, left != 0, left != 0, Epilogue::StoreSymF32, stream));
     }
 
   const dim3 fill_grid(blocks_for(kmax * r, 256 * 8, 1024), n);
@@ -304,9 +305,11 @@ hipError_t refresh_group(const std::vector<RefreshItem>& items, int r, int iters
     GALORE_RETURN_IF(hipGetLastError());
   }
 
-  auto gemm = [&](GemmGroup& g, bool b_kcontig) -> hipError_t {
-    if (cholesky) return launch_product(g, DType::F32, b_kcontig, stream);  // small tiles: a low rank leaves the general kernel short of them
-    return launch_gemm_group(g, DType::F32, true, b_kcontig, Epilogue::StoreF32, stream);
+  // At the ranks of the Cholesky path the 256 x 256 and 128 x 128 kernels are short of tiles (350M: 28 of 256 x 256 for 256 CUs,
+  // each a chain of 96 K steps): launch_product chooses.  us per product, before and after: split bf16 350M 100 -> 54, 60M 58 -> 21.
+  auto gemm = [&](GemmGroup& g, DType dt, bool b_kcontig) -> hipError_t {
+    if (cholesky) return launch_product(g, dt, b_kcontig, stream);
+    return launch_gemm_group(g, dt, true, b_kcontig, Epilogue::StoreF32, stream);
   };
   auto gemm_f32 = [&](int which) -> hipError_t {
     GemmGroup g{};
@@ -324,9 +327,9 @@ hipError_t refresh_group(const std::vector<RefreshItem>& items, int r, int iters
           p.A = t.Q; p.lda = t.k; p.B = t.C; p.ldb = t.k; p.M = r; p.N = t.k; p.K = t.k; p.C = t.Z; p.ldc = t.k;
         }
       }
-      GALORE_RETURN_IF(launch_gemm_group(gs, DType::BF16, true, true, Epilogue::StoreF32, stream));
+      GALORE_RETURN_IF(gemm(gs, DType::BF16, true));
       if (g.count == 0) return hipSuccess;
-      return gemm(g, false);
+      return gemm(g, DType::F32, false);
     }
     g.count = n;
     for (int i = 0; i < n; ++i) {
@@ -340,7 +343,7 @@ hipError_t refresh_group(const std::vector<RefreshItem>& items, int r, int iters
         p.A = cholesky ? t.Bw : t.S; p.lda = r; p.B = t.Q; p.ldb = t.k; p.M = r; p.N = t.k; p.K = r; p.C = t.Z; p.ldc = t.k;
       }
     }
-    return gemm(g, which == 1);
+    return gemm(g, DType::F32, which == 1);
   };
 
   for (int it = 0; it < iters; ++it) {
