@@ -35,6 +35,24 @@ inline hipError_t single_gemm_store(DType dt, const void* A, int lda, const void
   return launch_product(g, dt, b_kcontig, stream);
 }
 
+// The same with the result in dt for the next product to read: `rounded` (`C` itself for fp32), with C as scratch.
+inline hipError_t single_gemm_store_rounded(DType dt, const void* A, int lda, const void* B, int ldb, bool b_kcontig, float* C, void* rounded,
+                                            int M, int N, int K, hipStream_t stream) {
+  if (dt == DType::BF16) {
+    GemmGroup g{};
+    g.count = 1;
+    GemmProblem& p = g.p[0];
+    p.A = A; p.lda = lda; p.B = B; p.ldb = ldb;
+    p.M = M; p.N = N; p.K = K;
+    p.C = rounded; p.ldc = N;
+    const hipError_t e = launch_product_bf16(g, b_kcontig, stream);
+    if (e != hipErrorNotSupported) return e;
+  }
+  hipError_t e = single_gemm_store(dt, A, lda, B, ldb, b_kcontig, C, M, N, K, stream);
+  if (e == hipSuccess && dt != DType::F32) e = launch_cast_rows(C, rounded, M, N, N, dt, stream);
+  return e;
+}
+
 inline hipError_t single_transpose(DType dt, const void* src, int rows, int cols, int lds, void* dst, int ldd, hipStream_t stream) {
   TransposeGroup g{};
   g.count = 1;

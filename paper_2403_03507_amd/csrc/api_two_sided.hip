@@ -113,8 +113,7 @@ galore_status galore_two_sided_step(const galore_hparams* hp, const galore_tenso
   hipError_t e;
   // T1 (r x n) = P^T G, then R (r x r) = T1 Q: every product reads its operands in the storage dtype
   e = single_transpose(dt, S->p.data, m, r, (int)S->p.ld, ws + L.pt, m, stream);
-  if (e == hipSuccess) e = single_gemm_store(dt, ws + L.pt, m, G->data, (int)G->ld, false, T1, r, n, m, stream);
-  if (e == hipSuccess && dt != DType::F32) e = launch_cast_rows(T1, ws + L.t1c, r, n, n, dt, stream);
+  if (e == hipSuccess) e = single_gemm_store_rounded(dt, ws + L.pt, m, G->data, (int)G->ld, false, T1, ws + L.t1c, r, n, m, stream);
   if (e == hipSuccess) e = single_gemm_store(dt, ws + L.t1c, n, S->q.data, (int)S->q.ld, false, R, r, r, n, stream);
   if (e != hipSuccess) return hip_fail(nullptr, e, "two-sided projection");
   // Adam on R (Algorithm 2, update block), k = t + 1
@@ -136,8 +135,7 @@ galore_status galore_two_sided_step(const galore_hparams* hp, const galore_tenso
     if (e != hipSuccess) return hip_fail(nullptr, e, "two-sided Adam");
   }
   // T2 (n x r) = Q N^T, then W <- (1 - lr wd) W - lr alpha P T2^T in the epilogue of the last product
-  e = single_gemm_store(dt, S->q.data, (int)S->q.ld, ws + L.nn, r, true, T2, n, r, r, stream);
-  if (e == hipSuccess && dt != DType::F32) e = launch_cast_rows(T2, ws + L.t2c, n, r, r, dt, stream);
+  e = single_gemm_store_rounded(dt, S->q.data, (int)S->q.ld, ws + L.nn, r, true, T2, ws + L.t2c, n, r, r, stream);
   if (e == hipSuccess) {
     GemmGroup g{};
     g.count = 1;

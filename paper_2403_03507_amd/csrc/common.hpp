@@ -48,6 +48,7 @@ enum class Epilogue : int32_t {
   StoreF32 = 0,   // C (fp32) = acc
   ApplyW = 1,     // C (T) = s0 * C - s1 * acc            (weight update, s0 = 1 - lr*wd, s1 = lr*alpha)
   StoreSymF32 = 2, // C (fp32) = acc, written to (i,j) and (j,i); tiles with tm > tn skipped (M == N)
+  StoreBF16 = 4,  // C (bf16) = acc rounded to nearest even (launch_product_bf16)
   Adam = 3        // the update block of Algorithm 2 on acc: moments in place, N written, the product itself not stored (launch_tile_group)
 };
 
@@ -72,6 +73,9 @@ constexpr long kLargeProjectionTiles = 160;
 // K pieces), on whichever kernel suits each problem.
 hipError_t launch_weight_update(GemmGroup& g, DType dt, hipStream_t stream);
 hipError_t launch_product(GemmGroup& g, DType dt, bool b_kcontig, hipStream_t stream);
+// The product rounded to bf16 for the next one to read (bf16 operands): C (bf16) = A B with C's row stride N, on the small-tile
+// kernel.  hipErrorNotSupported, with nothing launched, where launch_product would choose another kernel.
+hipError_t launch_product_bf16(GemmGroup& g, bool b_kcontig, hipStream_t stream);
 // The symmetric product C = A A^T (fp32; M == N, B == A) of A as [M][K] (kcontig) or [K][M], likewise.
 hipError_t launch_gram(GemmGroup& g, DType dt, bool kcontig, hipStream_t stream);
 

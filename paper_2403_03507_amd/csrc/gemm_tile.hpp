@@ -279,6 +279,24 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(const GemmGroup grp) 
             if (wcol + e < N) dst[e] = (T)apply_entry(s0, (float)dst[e], s1, src[e]);
         }
       }
+    } else if constexpr (EPI == Epilogue::StoreBF16) {
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        const int lr = q * RPP + tid / CPW, row = m0 + ps * ROWS + lr;
+        if (row >= M || wcol >= N) continue;
+        const float* src = st + lr * SP + (tid % CPW) * WVEC;
+        T* dst = static_cast<T*>(pr.C) + (size_t)row * ldc + wcol;
+        T o[WVEC];
+#pragma unroll
+        for (int e = 0; e < WVEC; ++e) o[e] = (T)src[e];
+        if (wcol + WVEC <= N) {
+          __builtin_memcpy(dst, o, sizeof(u32x4));
+        } else {
+#pragma unroll
+          for (int e = 0; e < WVEC; ++e)
+            if (wcol + e < N) dst[e] = o[e];
+        }
+      }
     } else if constexpr (EPI == Epilogue::Adam) {
       constexpr int NP = Cfg::NPITCH;
       T* nt = reinterpret_cast<T*>(smem + Cfg::STAGE_BYTES);  // nt[column][row]
