@@ -4,10 +4,12 @@
 //   rowv_i <- b2 rowv_i + (1 - b2) sum_j (R_ij^2 + eps1),  colv_j <- b2 colv_j + (1 - b2) sum_i (R_ij^2 + eps1),  b2 = 1 - k^-0.8
 //   Vhat_ij = rowv_i colv_j / sum_i rowv_i,  U = R / sqrt(Vhat),  Uhat = U / max(1, RMS(U) / d)
 //   M <- b1 M + (1 - b1) Uhat,  N = M
-// Six launches, three passes over R: partial sums of the squares by rows and by columns; the statistics; their total;
-// partial sums of U^2; the clipping factor; the update.  Every sum has a fixed order (partials per workgroup, added in index order by one
-// workgroup): no atomics, bit-identical from run to run.  Bound by memory traffic: 3 reads of R, one read and write of M,
-// one write of N.
+// Four launches, three passes over R: partial sums of the squares by rows and by columns; the statistics and partial sums of
+// the row statistics; partial sums of U^2; the update.  The total of the row statistics and the clipping factor are sums of
+// some dozens to some thousand partials: every workgroup that needs them adds them itself, in the same fixed order, which
+// takes less than the launch of a workgroup that would (4.7 us each).  No atomics, bit-identical from run to run.  Bound by memory
+// traffic: 3 reads of R, one read and write of M, one write of N, transposed where the product that reads it wants it so
+// (a transpose of its own took 19 us for 1024 x 11008, the transposed store takes 7).
 #include "adafactor.hpp"
 
 namespace galore {
@@ -22,13 +24,13 @@ __device__ __forceinline__ float af_wave_sum(float v) {
   return v;
 }
 
-// scratch layout (floats): rowpart [cb][rows] | colpart [rb][cols] | blockpart [rb * cb] | scal [4]: total of rowv, clip factor
+// scratch layout (floats): rowpart [cb][rows] | colpart [rb][cols] | blockpart [rb * cb] | statpart [sb]: sums of rowv over 256 rows
 struct AfScratch {
   float* rowpart;
   float* colpart;
   float* blockpart;
-  float* scal;
-  int cb, rb;
+  float* statpart;
+  int cb, rb, sb;
 };
 __host__ __device__ inline AfScratch af_scratch(float* base, int rows, int cols) {
   AfScratch s;
@@ -37,7 +39,8 @@ __host__ __device__ inline AfScratch af_scratch(float* base, int rows, int cols)
   s.rowpart = base;
   s.colpart = s.rowpart + (size_t)s.cb * rows;
   s.blockpart = s.colpart + (size_t)s.rb * cols;
-  s.scal = s.blockpart + (size_t)s.rb * s.cb;
+  s.statpart = s.blockpart + (size_t)s.rb * s.cb;
+  s.sb = (rows + 255) / 256;
   return s;
 }
 
@@ -78,27 +81,30 @@ __global__ __launch_bounds__(kAfCols) void adafactor_sums_kernel(const Adafactor
   if (part == 0 && row0 + rl < p.rows) s.rowpart[(size_t)blockIdx.x * p.rows + row0 + rl] = a;
 }
 
-// sum of `count` values f(i), i = 0 .. count - 1, over one workgroup of 1024 threads, in a fixed order; every thread gets it
-template <class F> __device__ __forceinline__ float af_block_total(int count, F f, float* red) {
-  float a = 0.f;
-  for (int i = threadIdx.x; i < count; i += 1024) a += f(i);
+// sum over a workgroup of 256 threads, in a fixed order; every thread gets it.  `red`: 4 floats.
+__device__ __forceinline__ float af_block_sum(float a, float* red) {
   a = af_wave_sum(a);
-  __syncthreads();
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = a;
   __syncthreads();
-  float t = 0.f;
-  for (int w = 0; w < 16; ++w) t += red[w];
-  return t;
+  return ((red[0] + red[1]) + red[2]) + red[3];
+}
+
+// the total of the row statistics, by every wavefront
+__device__ __forceinline__ float af_total(const AfScratch& s) {
+  float a = 0.f;
+  for (int i = threadIdx.x & 63; i < s.sb; i += 64) a += s.statpart[i];
+  return af_wave_sum(a);
 }
 
 // the statistics: partial sums added in index order (loads in batches of eight), then the decayed averages; one thread per
-// row statistic (idx < rows) or column statistic
+// row statistic (the first sb workgroups, which also add up theirs) or column statistic
 __global__ __launch_bounds__(256) void adafactor_stats_kernel(const AdafactorProblem p) {
   const AfScratch s = af_scratch(p.scratch, p.rows, p.cols);
-  const int idx = blockIdx.x * 256 + threadIdx.x;
-  if (idx >= p.rows + p.cols) return;
-  const bool is_row = idx < p.rows;
-  const int i = is_row ? idx : idx - p.rows;
+  __shared__ float red[4];
+  const bool is_row = (int)blockIdx.x < s.sb;
+  const int i0 = (is_row ? blockIdx.x : blockIdx.x - s.sb) * 256 + threadIdx.x, n = is_row ? p.rows : p.cols;
+  const bool ok = i0 < n;
+  const int i = ok ? i0 : n - 1;
   const float* part = is_row ? s.rowpart + i : s.colpart + i;
   const size_t stride = is_row ? p.rows : p.cols;
   const int count = is_row ? s.cb : s.rb;
@@ -106,15 +112,12 @@ __global__ __launch_bounds__(256) void adafactor_stats_kernel(const AdafactorPro
 #pragma unroll 8
   for (int b = 0; b < count; ++b) a += part[(size_t)b * stride];
   float* stat = is_row ? p.rowv + i : p.colv + i;
-  *stat = p.beta2t * *stat + (1.f - p.beta2t) * a;
-}
-
-// the total of the row statistics
-__global__ __launch_bounds__(1024) void adafactor_total_kernel(const AdafactorProblem p) {
-  __shared__ float red[16];
-  const AfScratch s = af_scratch(p.scratch, p.rows, p.cols);
-  const float total = af_block_total(p.rows, [&](int i) { return p.rowv[i]; }, red);
-  if (threadIdx.x == 0) s.scal[0] = total;
+  const float v = p.beta2t * *stat + (1.f - p.beta2t) * a;
+  if (is_row) {  // uniform
+    const float sum = af_block_sum(ok ? v : 0.f, red);
+    if (threadIdx.x == 0) s.statpart[blockIdx.x] = sum;
+  }
+  if (ok) *stat = v;
 }
 
 // U_ij = R_ij / sqrt(rowv_i colv_j / total); the association keeps the quotient colv_j / total (of order 1 / rows) away
@@ -125,15 +128,13 @@ __device__ __forceinline__ float af_u(float x, float rv, float cv_over_total) { 
 __global__ __launch_bounds__(kAfCols) void adafactor_rms_kernel(const AdafactorProblem p) {
   __shared__ float sm[4];
   const AfScratch s = af_scratch(p.scratch, p.rows, p.cols);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x;
   const int c = blockIdx.x * kAfCols + tid;
   const int row0 = blockIdx.y * kAfRows;
-  const float total = s.scal[0];
   float acc = 0.f;
   {
     const bool cok = c < p.cols;
     const int cc = cok ? c : p.cols - 1;
-    const float cvt = p.colv[cc] / total;
     float x[kAfRows], rv[kAfRows];
 #pragma unroll
     for (int rl = 0; rl < kAfRows; ++rl) {        // independent loads from clamped addresses, masked below
@@ -141,57 +142,68 @@ __global__ __launch_bounds__(kAfCols) void adafactor_rms_kernel(const AdafactorP
       x[rl] = p.R[(size_t)row * p.ldr + cc];
       rv[rl] = p.rowv[row];
     }
+    const float cvt = p.colv[cc] / af_total(s);
 #pragma unroll
     for (int rl = 0; rl < kAfRows; ++rl) {
       const float u = af_u(x[rl], rv[rl], cvt);
       acc += (cok && row0 + rl < p.rows) ? u * u : 0.f;
     }
   }
-  acc = af_wave_sum(acc);
-  if (lane == 0) sm[wave] = acc;
-  __syncthreads();
-  if (tid == 0) s.blockpart[blockIdx.y * s.cb + blockIdx.x] = ((sm[0] + sm[1]) + sm[2]) + sm[3];
+  acc = af_block_sum(acc, sm);
+  if (tid == 0) s.blockpart[blockIdx.y * s.cb + blockIdx.x] = acc;
 }
 
-// the clipping factor 1 / max(1, RMS(U) / d)
-__global__ __launch_bounds__(1024) void adafactor_clip_kernel(const AdafactorProblem p) {
-  __shared__ float red[16];
-  const AfScratch s = af_scratch(p.scratch, p.rows, p.cols);
-  const float sumsq = af_block_total(s.rb * s.cb, [&](int i) { return s.blockpart[i]; }, red);
-  if (threadIdx.x == 0) {
-    const float rms = sqrtf(sumsq / ((float)p.rows * (float)p.cols));
-    const float over = rms / p.clip_d;
-    s.scal[1] = 1.f / (over > 1.f ? over : 1.f);
-  }
-}
-
-// pass 3: Uhat, the momentum, N
+// pass 3: the clipping factor 1 / max(1, RMS(U) / d), Uhat, the momentum, N
 template <class TN>
 __global__ __launch_bounds__(kAfCols) void adafactor_update_kernel(const AdafactorProblem p) {
+  constexpr int VEC = 16 / (int)sizeof(TN), PIECES = kAfRows / VEC;
+  __shared__ float red[4];
+  __shared__ __align__(16) TN turned[kAfCols][kAfRows + VEC];
   const AfScratch s = af_scratch(p.scratch, p.rows, p.cols);
-  const int c = blockIdx.x * kAfCols + threadIdx.x;
+  const int tid = threadIdx.x;
+  const int c = blockIdx.x * kAfCols + tid;
   const int row0 = blockIdx.y * kAfRows;
-  if (c >= p.cols) return;
-  const float total = s.scal[0], factor = s.scal[1];
-  const float cvt = p.colv[c] / total;
-  TN* N = static_cast<TN*>(p.N);
+  const bool cok = c < p.cols;
+  const int cc = cok ? c : p.cols - 1;
   float x[kAfRows], rv[kAfRows], mo[kAfRows];
 #pragma unroll
   for (int rl = 0; rl < kAfRows; ++rl) {          // independent loads from clamped addresses
     const int row = row0 + rl < p.rows ? row0 + rl : p.rows - 1;
-    x[rl] = p.R[(size_t)row * p.ldr + c];
+    x[rl] = p.R[(size_t)row * p.ldr + cc];
     rv[rl] = p.rowv[row];
-    mo[rl] = p.M[(size_t)row * p.cols + c];
+    mo[rl] = p.M[(size_t)row * p.cols + cc];
   }
+  const float cvt = p.colv[cc] / af_total(s);
+  float sumsq = 0.f;
+  for (int i = threadIdx.x; i < s.rb * s.cb; i += 256) sumsq += s.blockpart[i];
+  const float over = sqrtf(af_block_sum(sumsq, red) / ((float)p.rows * (float)p.cols)) / p.clip_d;
+  const float factor = 1.f / (over > 1.f ? over : 1.f);
+  TN* N = static_cast<TN*>(p.N);
 #pragma unroll
   for (int rl = 0; rl < kAfRows; ++rl) {
     const int row = row0 + rl;
-    if (row < p.rows) {
-      const float uhat = af_u(x[rl], rv[rl], cvt) * factor;
-      const size_t e = (size_t)row * p.cols + c;
-      const float m = p.beta1 * mo[rl] + (1.f - p.beta1) * uhat;
-      p.M[e] = m;
-      N[e] = (TN)m;
+    const float uhat = af_u(x[rl], rv[rl], cvt) * factor;
+    const float m = p.beta1 * mo[rl] + (1.f - p.beta1) * uhat;
+    turned[tid][rl] = (TN)m;
+    if (cok && row < p.rows) {
+      p.M[(size_t)row * p.cols + c] = m;
+      if (!p.n_transposed) N[(size_t)row * p.cols + c] = (TN)m;
+    }
+  }
+  if (!p.n_transposed) return;
+  // N^T: the 32 entries of a column of the tile leave as 16-byte pieces of neighbouring lanes, at any alignment
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < PIECES; ++q) {
+    const int col = (tid + 256 * q) / PIECES, i = (tid + 256 * q) % PIECES * VEC;
+    if ((int)blockIdx.x * kAfCols + col >= p.cols) continue;
+    TN* dst = N + (size_t)(blockIdx.x * kAfCols + col) * p.rows + row0 + i;
+    if (row0 + i + VEC <= p.rows) {
+      __builtin_memcpy(dst, &turned[col][i], 16);
+    } else {
+#pragma unroll
+      for (int e = 0; e < VEC; ++e)
+        if (row0 + i + e < p.rows) dst[e] = turned[col][i + e];
     }
   }
 }
@@ -200,7 +212,7 @@ __global__ __launch_bounds__(kAfCols) void adafactor_update_kernel(const Adafact
 
 size_t adafactor_scratch_floats(int rows, int cols) {
   const AfScratch s = af_scratch(nullptr, rows, cols);
-  return (size_t)(s.scal - s.rowpart) + 4;
+  return (size_t)(s.statpart - s.rowpart) + s.sb;
 }
 
 hipError_t launch_adafactor(const AdafactorProblem& p, DType n_dtype, hipStream_t stream) {
@@ -209,10 +221,8 @@ hipError_t launch_adafactor(const AdafactorProblem& p, DType n_dtype, hipStream_
   if (s.rb > 65535) return hipErrorInvalidValue;   // grid.y
   const dim3 grid(s.cb, s.rb);
   hipLaunchKernelGGL(adafactor_sums_kernel, grid, dim3(kAfCols), 0, stream, p);
-  hipLaunchKernelGGL(adafactor_stats_kernel, dim3((p.rows + p.cols + 255) / 256), dim3(256), 0, stream, p);
-  hipLaunchKernelGGL(adafactor_total_kernel, dim3(1), dim3(1024), 0, stream, p);
+  hipLaunchKernelGGL(adafactor_stats_kernel, dim3(s.sb + s.cb), dim3(256), 0, stream, p);
   hipLaunchKernelGGL(adafactor_rms_kernel, grid, dim3(kAfCols), 0, stream, p);
-  hipLaunchKernelGGL(adafactor_clip_kernel, dim3(1), dim3(1024), 0, stream, p);
   if (n_dtype == DType::BF16) hipLaunchKernelGGL(adafactor_update_kernel<__bf16>, grid, dim3(kAfCols), 0, stream, p);
   else hipLaunchKernelGGL(adafactor_update_kernel<float>, grid, dim3(kAfCols), 0, stream, p);
   return hipGetLastError();

@@ -4,8 +4,8 @@
 
 namespace galore {
 
-// R rows x cols fp32 (row stride ldr); M rows x cols fp32 dense; rowv (rows), colv (cols) fp32; N rows x cols in n_dtype,
-// dense.  `scratch` holds adafactor_scratch_floats(rows, cols) floats of partial sums (fixed reduction order, no atomics).
+// R rows x cols fp32 (row stride ldr); M rows x cols fp32 dense; rowv (rows), colv (cols) fp32; N in n_dtype, dense,
+// rows x cols or (n_transposed) cols x rows.  `scratch` holds adafactor_scratch_floats(rows, cols) floats of partial sums (fixed reduction order, no atomics).
 struct AdafactorProblem {
   const float* R;
   float* M;
@@ -14,6 +14,7 @@ struct AdafactorProblem {
   void* N;
   float* scratch;
   int rows, cols, ldr;
+  int n_transposed;
   float beta1, beta2t;   // momentum; decay rate 1 - k^decay_pow of this step
   float eps1, clip_d;
 };

@@ -18,7 +18,7 @@ constexpr float kEps1 = 1e-30f;      // added to every squared gradient entry
 constexpr float kClip = 1.0f;        // clipping threshold d on RMS(U)
 
 struct AdafactorLayout {
-  size_t pt, R, nn, nt, scratch, step_total;   // step
+  size_t pt, R, nl, scratch, step_total;   // step
   size_t rws, r_pt, refresh_total;             // refresh (overlays the step's region)
   size_t total;
 };
@@ -32,8 +32,7 @@ AdafactorLayout adafactor_layout(int64_t m, int64_t n, int64_t r, DType dt) {
   auto take = [&](size_t bytes) { const size_t o = off; off += align_up(bytes); return o; };
   L.pt = take((size_t)r * k * s);
   L.R = take((size_t)mrows * mcols * 4);
-  L.nn = take((size_t)mrows * mcols * s);
-  L.nt = take((size_t)l * r * s);
+  L.nl = take((size_t)l * r * s);
   L.scratch = take(adafactor_scratch_floats((int)mrows, (int)mcols) * 4);
   L.step_total = off;
   off = 0;
@@ -182,7 +181,8 @@ galore_status galore_adafactor_step(const galore_hparams* hp, const galore_tenso
     p.M = static_cast<float*>(S->m.data);
     p.rowv = static_cast<float*>(S->row.data);
     p.colv = static_cast<float*>(S->col.data);
-    p.N = ws + L.nn;
+    p.N = ws + L.nl;
+    p.n_transposed = left;  // the weight update reads N as (long side) x r
     p.scratch = reinterpret_cast<float*>(ws + L.scratch);
     p.rows = mrows; p.cols = mcols; p.ldr = mcols;
     p.beta1 = hp->beta1;
@@ -192,13 +192,8 @@ galore_status galore_adafactor_step(const galore_hparams* hp, const galore_tenso
     if (e != hipSuccess) return hip_fail(nullptr, e, "Adafactor launch");
   }
   // W <- (1 - lr wd) W - lr alpha (P N | N Q^T) in the epilogue of the product (Algorithm 2, last lines); the kernel
-  // reads N as (long side) x r, i.e. transposed for a LEFT tensor
-  const void* Nl = ws + L.nn;
-  if (left) {
-    e = single_transpose(dt, ws + L.nn, r, n, n, ws + L.nt, r, stream);
-    if (e != hipSuccess) return hip_fail(nullptr, e, "transpose of N");
-    Nl = ws + L.nt;
-  }
+  // reads N as (long side) x r
+  const void* Nl = ws + L.nl;
   GemmGroup g{};
   g.count = 1;
   GemmProblem& p = g.p[0];
