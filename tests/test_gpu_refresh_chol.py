@@ -50,6 +50,17 @@ def test_largest_rank_of_the_path(r):
     assert np.linalg.norm(P.T @ to64(G)) ** 2 >= (1 - 1e-5) * np.sum(s[:r] ** 2)
 
 
+@pytest.mark.parametrize("k,n,r", [(263, 300, 258), (300, 263, 260), (4100, 4110, 257)])
+def test_forms_of_the_householder_path(k, n, r):
+    # ranks beyond the Cholesky path at short sides of no multiple of 4 (no compact-WY panels) and beyond 4096 (reflector by reflector)
+    src = wl.GradientSource(k, n, 530 + r, "gapped", gap_rank=r)
+    G = src.grad(0)
+    P = _projector(G, r, iters=3)
+    _check_orthonormal(P)
+    R = P.T @ to64(G) if k <= n else to64(G) @ P
+    assert np.linalg.norm(R) ** 2 >= 0.99 * np.sum(to64(src.sigma) ** 2)
+
+
 @pytest.mark.parametrize("k,r", [(48, 48), (65, 65), (100, 97)])
 def test_rank_up_to_the_short_side(k, r):
     G = wl.GradientSource(k, 190, 540 + r, "gapped", gap_rank=min(r, k - 1)).grad(0)
