@@ -14,7 +14,8 @@
 // the next pass.  One pass gives a basis of span(Z) that is orthonormal to fp32 rounding times the condition number, which
 // is all that the next product with C needs; the last round takes a second pass (see refresh.hip).
 // Householder reflectors (refresh_qr.hip) are a serial chain of r reflections; whole refreshes, ms, before and after: 350M layer
-// set (k = 1024, r = 256, 4 rounds) 8.48 -> 3.7, 60M (k = 512, r = 128, 6 rounds, with five steps of the optimizer) 6.8 -> 2.4.
+// set (k = 1024, r = 256, 4 rounds) 8.48 -> 3.80, 60M (k = 512, r = 128, 6 rounds, with five steps of the optimizer) 6.83 -> 2.46 (3.25 and
+// 1.95 since, with the products on small tiles).
 // No atomics and fixed summation orders: results are reproducible bit for bit.
 #include "refresh_common.hpp"
 

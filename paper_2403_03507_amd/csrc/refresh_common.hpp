@@ -27,7 +27,7 @@ constexpr float kJacobiStopTol = 4e-5f;
 constexpr float kFactorTol = 2e-6f;
 constexpr float kFactorStopTol = 1e-5f;
 // Largest rank of the Cholesky path (refresh_chol.hip); higher ranks take Householder QR and Jacobi on the Rayleigh-Ritz matrix itself.
-// The Cholesky path is faster at every rank (7B layer set, r = 1024: 34 ms against 62) and closer to the exact vectors.  But a
+// The Cholesky path is faster at every rank (7B layer set, r = 1024: 34 ms against 61) and closer to the exact vectors.  But a
 // projector's columns are signed by their largest entry, and with a thousand directions inside a factor of 8 some columns
 // have two entries that tie to 1e-3 or less: there the two paths, each right to its rounding, differ by the signs of about
 // one column in 10^4, which a run that is resumed or compared across versions would see.  At r = 256 (350M) they agree
