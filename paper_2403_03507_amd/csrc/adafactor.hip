@@ -24,12 +24,12 @@ __device__ __forceinline__ float af_wave_sum(float v) {
   return v;
 }
 
-// scratch layout (floats): rowpart [cb][rows] | colpart [rb][cols] | blockpart [rb * cb] | statpart [sb]: sums of rowv over 256 rows
+// scratch layout (floats): rowpart [cb][rows] | colpart [rb][cols] | blockpart [rb * cb].  The sums of rowv over 256 rows take the
+// place of the first row partial of those rows, which only the workgroup that forms the sum reads.
 struct AfScratch {
   float* rowpart;
   float* colpart;
   float* blockpart;
-  float* statpart;
   int cb, rb, sb;
 };
 __host__ __device__ inline AfScratch af_scratch(float* base, int rows, int cols) {
@@ -39,7 +39,6 @@ __host__ __device__ inline AfScratch af_scratch(float* base, int rows, int cols)
   s.rowpart = base;
   s.colpart = s.rowpart + (size_t)s.cb * rows;
   s.blockpart = s.colpart + (size_t)s.rb * cols;
-  s.statpart = s.blockpart + (size_t)s.rb * s.cb;
   s.sb = (rows + 255) / 256;
   return s;
 }
@@ -89,11 +88,11 @@ __device__ __forceinline__ float af_block_sum(float a, float* red) {
   return ((red[0] + red[1]) + red[2]) + red[3];
 }
 
-// the total of the row statistics, by every wavefront
-__device__ __forceinline__ float af_total(const AfScratch& s) {
+// the total of the row statistics; `red`: 4 floats
+__device__ __forceinline__ float af_total(const AfScratch& s, float* red) {
   float a = 0.f;
-  for (int i = threadIdx.x & 63; i < s.sb; i += 64) a += s.statpart[i];
-  return af_wave_sum(a);
+  for (int i = threadIdx.x; i < s.sb; i += 256) a += s.rowpart[(size_t)i * 256];
+  return af_block_sum(a, red);
 }
 
 // the statistics: partial sums added in index order (loads in batches of eight), then the decayed averages; one thread per
@@ -114,8 +113,8 @@ __global__ __launch_bounds__(256) void adafactor_stats_kernel(const AdafactorPro
   float* stat = is_row ? p.rowv + i : p.colv + i;
   const float v = p.beta2t * *stat + (1.f - p.beta2t) * a;
   if (is_row) {  // uniform
-    const float sum = af_block_sum(ok ? v : 0.f, red);
-    if (threadIdx.x == 0) s.statpart[blockIdx.x] = sum;
+    const float sum = af_block_sum(ok ? v : 0.f, red);  // every thread has read its partials before the barrier in here
+    if (threadIdx.x == 0) s.rowpart[(size_t)blockIdx.x * 256] = sum;
   }
   if (ok) *stat = v;
 }
@@ -126,7 +125,7 @@ __device__ __forceinline__ float af_u(float x, float rv, float cv_over_total) { 
 
 // pass 2: sum of U^2 over this workgroup's tile
 __global__ __launch_bounds__(kAfCols) void adafactor_rms_kernel(const AdafactorProblem p) {
-  __shared__ float sm[4];
+  __shared__ float sm[4], red[4];
   const AfScratch s = af_scratch(p.scratch, p.rows, p.cols);
   const int tid = threadIdx.x;
   const int c = blockIdx.x * kAfCols + tid;
@@ -142,7 +141,7 @@ __global__ __launch_bounds__(kAfCols) void adafactor_rms_kernel(const AdafactorP
       x[rl] = p.R[(size_t)row * p.ldr + cc];
       rv[rl] = p.rowv[row];
     }
-    const float cvt = p.colv[cc] / af_total(s);
+    const float cvt = p.colv[cc] / af_total(s, red);
 #pragma unroll
     for (int rl = 0; rl < kAfRows; ++rl) {
       const float u = af_u(x[rl], rv[rl], cvt);
@@ -157,7 +156,7 @@ __global__ __launch_bounds__(kAfCols) void adafactor_rms_kernel(const AdafactorP
 template <class TN>
 __global__ __launch_bounds__(kAfCols) void adafactor_update_kernel(const AdafactorProblem p) {
   constexpr int VEC = 16 / (int)sizeof(TN), PIECES = kAfRows / VEC;
-  __shared__ float red[4];
+  __shared__ float red[4], red_total[4];
   __shared__ __align__(16) TN turned[kAfCols][kAfRows + VEC];
   const AfScratch s = af_scratch(p.scratch, p.rows, p.cols);
   const int tid = threadIdx.x;
@@ -173,7 +172,7 @@ __global__ __launch_bounds__(kAfCols) void adafactor_update_kernel(const Adafact
     rv[rl] = p.rowv[row];
     mo[rl] = p.M[(size_t)row * p.cols + cc];
   }
-  const float cvt = p.colv[cc] / af_total(s);
+  const float cvt = p.colv[cc] / af_total(s, red_total);
   float sumsq = 0.f;
   for (int i = threadIdx.x; i < s.rb * s.cb; i += 256) sumsq += s.blockpart[i];
   const float over = sqrtf(af_block_sum(sumsq, red) / ((float)p.rows * (float)p.cols)) / p.clip_d;
@@ -212,7 +211,7 @@ __global__ __launch_bounds__(kAfCols) void adafactor_update_kernel(const Adafact
 
 size_t adafactor_scratch_floats(int rows, int cols) {
   const AfScratch s = af_scratch(nullptr, rows, cols);
-  return (size_t)(s.statpart - s.rowpart) + s.sb;
+  return (size_t)(s.blockpart - s.rowpart) + (size_t)s.rb * s.cb + 4;  // the size that galore.h states for galore_adafactor
 }
 
 hipError_t launch_adafactor(const AdafactorProblem& p, DType n_dtype, hipStream_t stream) {
