@@ -4,10 +4,10 @@
 //   rowv_i <- b2 rowv_i + (1 - b2) sum_j (R_ij^2 + eps1),  colv_j <- b2 colv_j + (1 - b2) sum_i (R_ij^2 + eps1),  b2 = 1 - k^-0.8
 //   Vhat_ij = rowv_i colv_j / sum_i rowv_i,  U = R / sqrt(Vhat),  Uhat = U / max(1, RMS(U) / d)
 //   M <- b1 M + (1 - b1) Uhat,  N = M
-// Four launches, three passes over R: partial sums of the squares by rows and by columns; the statistics and partial sums of
-// the row statistics; partial sums of U^2; the update.  The total of the row statistics and the clipping factor are sums of
-// some dozens to some thousand partials: every workgroup that needs them adds them itself, in the same fixed order, which
-// takes less than the launch of a workgroup that would (4.7 us each).  No atomics, bit-identical from run to run.  Bound by memory
+// Four or five launches, three passes over R: partial sums of the squares by rows and by columns; the statistics and partial sums of
+// the row statistics; partial sums of U^2; for a large matrix their sum; the update.  The total of the row statistics, and for a
+// small matrix the sum of U^2, is added by every workgroup that needs it, in the same fixed order, which takes less than the
+// launch of a workgroup that would (kAfClipPartials).  No atomics, bit-identical from run to run.  Bound by memory
 // traffic: 3 reads of R, one read and write of M, one write of N, transposed where the product that reads it wants it so
 // (a transpose of its own took 19 us for 1024 x 11008, the transposed store takes 7).
 #include "adafactor.hpp"
@@ -17,6 +17,11 @@ namespace {
 
 constexpr int kAfCols = 256;  // columns per workgroup (one per thread)
 constexpr int kAfRows = 32;   // rows per workgroup
+// Partial sums of U^2 (one per 32 x 256 tile) up to which every workgroup of the update adds them all itself: that work grows with
+// the square of the tiles, a launch of one workgroup that adds them once costs about 3 us.  Update block, us, every workgroup / once:
+// 512 tiles (512 x 8192) 27.5 / 29.9, 1024 (1024 x 8192) 42.8 / 43.7, 1376 (1024 x 11008) 58.7 / 57.3, 16000 (4096 x 32000) 602 / 581,
+// 65536 (8192 x 65536) 2581 / 2152.
+constexpr int64_t kAfClipPartials = 1200;
 
 __device__ __forceinline__ float af_wave_sum(float v) {
 #pragma unroll
@@ -152,9 +157,26 @@ __global__ __launch_bounds__(kAfCols) void adafactor_rms_kernel(const AdafactorP
   if (tid == 0) s.blockpart[blockIdx.y * s.cb + blockIdx.x] = acc;
 }
 
+// the sum of U^2 from `count` partial sums; `red`: 4 floats
+__device__ __forceinline__ float af_sum_of_squares(const float* part, int count, float* red) {
+  float a = 0.f;
+#pragma unroll 8
+  for (int i = threadIdx.x; i < count; i += 256) a += part[i];
+  return af_block_sum(a, red);
+}
+
+// The same for a large matrix, once: the column partials are used up by now, so the first of them takes the sum.
+__global__ __launch_bounds__(256) void adafactor_clip_kernel(const AdafactorProblem p) {
+  __shared__ float red[4];
+  const AfScratch s = af_scratch(p.scratch, p.rows, p.cols);
+  const float sum = af_sum_of_squares(s.blockpart, s.rb * s.cb, red);
+  if (threadIdx.x == 0) s.colpart[0] = sum;
+}
+
 // pass 3: the clipping factor 1 / max(1, RMS(U) / d), Uhat, the momentum, N
+// summed: the sum of U^2 is in colpart[0], else every workgroup adds the partial sums
 template <class TN>
-__global__ __launch_bounds__(kAfCols) void adafactor_update_kernel(const AdafactorProblem p) {
+__global__ __launch_bounds__(kAfCols) void adafactor_update_kernel(const AdafactorProblem p, int summed) {
   constexpr int VEC = 16 / (int)sizeof(TN), PIECES = kAfRows / VEC;
   __shared__ float red[4], red_total[4];
   __shared__ __align__(16) TN turned[kAfCols][kAfRows + VEC];
@@ -173,9 +195,8 @@ __global__ __launch_bounds__(kAfCols) void adafactor_update_kernel(const Adafact
     mo[rl] = p.M[(size_t)row * p.cols + cc];
   }
   const float cvt = p.colv[cc] / af_total(s, red_total);
-  float sumsq = 0.f;
-  for (int i = threadIdx.x; i < s.rb * s.cb; i += 256) sumsq += s.blockpart[i];
-  const float over = sqrtf(af_block_sum(sumsq, red) / ((float)p.rows * (float)p.cols)) / p.clip_d;
+  const float sumsq = summed ? s.colpart[0] : af_sum_of_squares(s.blockpart, s.rb * s.cb, red);
+  const float over = sqrtf(sumsq / ((float)p.rows * (float)p.cols)) / p.clip_d;
   const float factor = 1.f / (over > 1.f ? over : 1.f);
   TN* N = static_cast<TN*>(p.N);
 #pragma unroll
@@ -222,8 +243,10 @@ hipError_t launch_adafactor(const AdafactorProblem& p, DType n_dtype, hipStream_
   hipLaunchKernelGGL(adafactor_sums_kernel, grid, dim3(kAfCols), 0, stream, p);
   hipLaunchKernelGGL(adafactor_stats_kernel, dim3(s.sb + s.cb), dim3(256), 0, stream, p);
   hipLaunchKernelGGL(adafactor_rms_kernel, grid, dim3(kAfCols), 0, stream, p);
-  if (n_dtype == DType::BF16) hipLaunchKernelGGL(adafactor_update_kernel<__bf16>, grid, dim3(kAfCols), 0, stream, p);
-  else hipLaunchKernelGGL(adafactor_update_kernel<float>, grid, dim3(kAfCols), 0, stream, p);
+  const int summed = (int64_t)s.rb * s.cb > kAfClipPartials;
+  if (summed) hipLaunchKernelGGL(adafactor_clip_kernel, dim3(1), dim3(256), 0, stream, p);
+  if (n_dtype == DType::BF16) hipLaunchKernelGGL(adafactor_update_kernel<__bf16>, grid, dim3(kAfCols), 0, stream, p, summed);
+  else hipLaunchKernelGGL(adafactor_update_kernel<float>, grid, dim3(kAfCols), 0, stream, p, summed);
   return hipGetLastError();
 }
 
