@@ -49,10 +49,11 @@ Layout layout_for(int64_t k, int64_t r) {
   L.S = take((size_t)r * r * 4);
   L.tau = take((size_t)r * 4);
   if (cholesky_path(r)) {
-    const size_t rp = (size_t)(r + 31) / 32 * 32;
-    L.T = take((size_t)r * r * 4);
-    L.A0 = take(rp * rp * 8);
-    L.A1 = take(rp * rp * 8);
+    // blocks of the lower triangle only, and A0 doubles as the r x r factor T (RefreshTensor::T): together no more than the
+    // Householder path takes at any k >= r
+    const size_t nb = (size_t)(r + 31) / 32, rp = nb * 32, triangle = nb * (nb + 1) / 2 * 1024 * 8;
+    L.A0 = take(triangle);
+    L.A1 = take(triangle);
     L.diag = take((rp + 2) * 8);
     L.dinv = take((size_t)2 * 1024 * 8);
     L.flag = take(rp * 4);
@@ -67,7 +68,7 @@ Layout layout_for(int64_t k, int64_t r) {
   L.lambda = take((size_t)r * 4);
   L.order = take((size_t)r * 4);
   L.sweep_flag = take((size_t)(kJacobiSweeps + 1) * 4);
-  L.group = take(2 * sizeof(RefreshGroup));  // the descriptor tables of the group this tensor leads
+  L.group = take((cholesky_path(r) ? 2 : 1) * sizeof(RefreshGroup));  // the descriptor tables of the group this tensor leads
   const bool split = split_products(k, r);
   L.Csplit = take(split ? (size_t)k * 6 * k * 2 : 0);
   L.Qsplit = take(split ? (size_t)r * 6 * k * 2 : 0);
@@ -221,7 +222,6 @@ hipError_t refresh_group(const std::vector<RefreshItem>& items, int r, int iters
     t.S = reinterpret_cast<float*>(it.ws + L.S);
     t.tau = reinterpret_cast<float*>(it.ws + L.tau);
     if (cholesky) {
-      t.T = reinterpret_cast<float*>(it.ws + L.T);
       t.A0 = reinterpret_cast<double*>(it.ws + L.A0);
       t.A1 = reinterpret_cast<double*>(it.ws + L.A1);
       t.diag = reinterpret_cast<double*>(it.ws + L.diag);

@@ -40,6 +40,10 @@ __device__ __forceinline__ void tri_decode(int x, int& i, int& j) {  // x = i (i
   j = x - i * (i + 1) / 2;
 }
 
+// The matrices being factored are kept as the 32 x 32 blocks of their lower triangle, each contiguous: block (i, j), j <= i
+__host__ __device__ __forceinline__ int tri(int i) { return i * (i + 1) / 2; }
+template <class D> __device__ __forceinline__ D* block_at(D* a, int i, int j) { return a + (size_t)(tri(i) + j) * (kCB * kCB); }
+
 // Lower triangle of X Y^T (r x r, contraction k) in fp64 into A0 and its diagonal into diag: X = Y = Zt, or (ritz) X = Qt.
 // A workgroup of 4 wavefronts owns 32 x 32 entries, a wavefront 16 x 16: at these ranks there are too few tiles for larger ones.
 // The products of one MFMA step take 16 positions of every row as one 16-byte piece per lane, in an order that is the same
@@ -48,7 +52,7 @@ __global__ __launch_bounds__(256) void gram_f64_kernel(const RefreshGroup* __res
   const RefreshGroup& grp = *gp;
   constexpr int U = 8;
   const RefreshTensor& t = grp.t[blockIdx.y];
-  const int k = t.k, r = grp.r, rp = (r + kCB - 1) / kCB * kCB;
+  const int k = t.k, r = grp.r;
   int ti, tj;
   tri_decode(blockIdx.x, ti, tj);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -89,7 +93,7 @@ __global__ __launch_bounds__(256) void gram_f64_kernel(const RefreshGroup* __res
   for (int v = 0; v < 4; ++v) {
     const int row = i0 + out_row(v, lane), col = j0 + i;
     const double e = row < r && col < r ? acc[v] : 0.;
-    t.A0[(size_t)row * rp + col] = e;
+    block_at(t.A0, ti, tj)[(row - ti * kCB) * kCB + col - tj * kCB] = e;
     if (row == col) t.diag[row] = e;
   }
 }
@@ -143,17 +147,17 @@ __global__ __launch_bounds__(256) void chol_step_kernel(const RefreshGroup* __re
     i = s;
     j = x - 1;
   } else {
-    tri_decode(x - 1 - nb + (s + 1) * (s + 2) / 2, i, j);
+    tri_decode(x - 1 - nb + tri(s + 1), i, j);
     if (i == s + 1 && j == s + 1) return;
   }
   // 8 entries of a block per thread pair of rows: thread tid moves columns 4 (tid % 8) .. of row tid / 8
   const int mr = tid >> 3, mc = (tid & 7) * 4;
-  auto load = [&](double* lds, const double* from, int pitch) {
-    const d4 v = *reinterpret_cast<const d4*>(from + (size_t)mr * pitch + mc);
+  auto load = [&](double* lds, const double* from) {
+    const d4 v = *reinterpret_cast<const d4*>(from + mr * kCB + mc);
 #pragma unroll
     for (int e = 0; e < 4; ++e) lds[mr * kLP + mc + e] = v[e];
   };
-  auto block = [&](int bi, int bj) { return src + (size_t)bi * kCB * rp + bj * kCB; };
+  auto block = [&](int bi, int bj) { return block_at(src, bi, bj); };
   const int i0 = (wave & 1) * 16, j0 = (wave >> 1) * 16, oc = lane & 15;
   auto put = [&](double* lds, const d4& v) {
 #pragma unroll
@@ -166,9 +170,9 @@ __global__ __launch_bounds__(256) void chol_step_kernel(const RefreshGroup* __re
     float* out = ritz ? t.Bw : t.S;
     d4 v = zero;
     if (j <= s && !ritz) {
-      load(D, dinv, kCB);
+      load(D, dinv);
       if (j < s) {
-        load(P, block(s, j), rp);
+        load(P, block(s, j));
         __syncthreads();
         block_product<false>(v, D, P, i0, j0, lane);
       } else {
@@ -188,11 +192,11 @@ __global__ __launch_bounds__(256) void chol_step_kernel(const RefreshGroup* __re
   if (ritz && j < s) return;
 
   // what is updated, and what the factorisation asks for, requested before anything waits
-  const size_t at0 = (size_t)(i0 + (lane >> 4)) * rp + j0 + oc;
+  const int at0 = (i0 + (lane >> 4)) * kCB + j0 + oc;
   d4 v = zero;
   if (j != s)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = block(i, j)[at0 + (size_t)4 * e * rp];
+    for (int e = 0; e < 4; ++e) v[e] = block(i, j)[at0 + 4 * e * kCB];
   double shift = 0., scale = 0., low = 0.;
   if (x == 0) {
     if (ritz && s >= 0) { shift = t.diag[rp]; scale = t.diag[rp + 1]; }
@@ -200,9 +204,9 @@ __global__ __launch_bounds__(256) void chol_step_kernel(const RefreshGroup* __re
   }
   d4 upd = zero;
   if (s >= 0) {
-    load(D, dinv, kCB);
-    load(P, block(i, s), rp);
-    if (j != s && j != i) load(Q, block(j < s ? s : j, j < s ? j : s), rp);
+    load(D, dinv);
+    load(P, block(i, s));
+    if (j != s && j != i) load(Q, block(j < s ? s : j, j < s ? j : s));
     __syncthreads();
     d4 l = zero, q = zero;
     block_product<true>(l, P, D, i0, j0, lane);                             // L_is = A_is D^T
@@ -229,9 +233,9 @@ __global__ __launch_bounds__(256) void chol_step_kernel(const RefreshGroup* __re
   }
   v -= upd;
   if (x != 0) {
-    double* to = dst + (size_t)i * kCB * rp + j * kCB;
+    double* to = block_at(dst, i, j);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) to[at0 + (size_t)4 * e * rp] = v[e];
+    for (int e = 0; e < 4; ++e) to[at0 + 4 * e * kCB] = v[e];
     return;
   }
   put(Q, v);  // Q has not been read since the last barrier (j == i)
@@ -297,7 +301,6 @@ __global__ __launch_bounds__(256) void refill_kernel(const RefreshGroup* __restr
 
 hipError_t launch_factor(const RefreshGroup& grp, const RefreshGroup* dgrp, int ritz, double dependent, hipStream_t stream) {
   const int n = grp.count, r = grp.r;
-  auto tri = [](int x) { return x * (x + 1) / 2; };
   hipLaunchKernelGGL(gram_f64_kernel, dim3(tri((r + kCB - 1) / kCB), n), dim3(256), 0, stream, dgrp, ritz);
   const int nb = (r + kCB - 1) / kCB;
   for (int s = -1; s < nb; ++s)

@@ -39,25 +39,29 @@ constexpr int kRPT = 4;              // rows per thread in the panel kernels (10
 constexpr int kSW = 8;               // columns per block in the blocked reflector application
 
 struct RefreshTensor {
-  // Jt, tau .. wpart belong to the Householder path, T .. flag to the Cholesky path; null in the other.
   float* C;      // k x k Gram matrix
   float* Q;      // Qt: r x k, the iteration block transposed
   float* Z;      // Zt: r x k, product block / factored reflectors / fp32 projector, transposed
   float* Bw;     // r x r Rayleigh-Ritz matrix (Cholesky path: its transposed Cholesky factor), rotated in place
-  float* Jt;     // r x r accumulated rotations (rows = eigenvectors)
+  float* Jt;     // r x r accumulated rotations (rows = eigenvectors); Householder path only, null on the Cholesky path
   float* S;      // St: r x r, rows = eigenvectors, ordered by decreasing Ritz value, unit length (Cholesky path: before, the inverse factor of a QR)
-  float* T;      // r x r: factor that makes St orthonormal
-  double* A0;    // round_up(r, 32) squared, twice: the matrix being factored (see chol_step_kernel)
-  double* A1;
-  double* diag;  // round_up(r, 32) + 2: diagonal of the matrix being factored; its shift and scale
-  double* dinv;  // 2 x 32 x 32: inverse of the diagonal block of the step
-  int32_t* flag; // round_up(r, 32): dependent columns
-  float* tau;    // r
-  float* vscale; // r
-  float* vclean; // round_up(r, 32) x k: reflectors as plain vectors (unit diagonal, zeros above, scaled), transposed
-  float* tmat;   // (r / 32 macro panels) x 32 x 32: triangular factors T of the compact WY form
-  float* tpart;  // 8 x 32 x 32: shares of V^T V of the macro panel being prepared
-  float* wpart;  // (r / 32 + 1) x 4 x 32 x 32: shares of w = x V^T, per block of 32 target rows and slice of positions
+  float* tau;    // r: factors of the reflectors; later the reciprocal lengths of the eigenvectors (both paths)
+  union {
+    struct {         // Householder path
+      float* vscale; // r
+      float* vclean; // round_up(r, 32) x k: reflectors as plain vectors (unit diagonal, zeros above, scaled), transposed
+      float* tmat;   // (r / 32 macro panels) x 32 x 32: triangular factors T of the compact WY form
+      float* tpart;  // 8 x 32 x 32: shares of V^T V of the macro panel being prepared
+      float* wpart;  // (r / 32 + 1) x 4 x 32 x 32: shares of w = x V^T, per block of 32 target rows and slice of positions
+    };
+    struct {         // Cholesky path
+      double* A0;    // lower triangle of 32 x 32 blocks, twice: the matrix being factored (see chol_step_kernel)
+      double* A1;
+      double* diag;  // round_up(r, 32) + 2: diagonal of the matrix being factored; its shift and scale
+      double* dinv;  // 2 x 32 x 32: inverse of the diagonal block of the step
+      int32_t* flag; // round_up(r, 32): dependent columns
+    };
+  };
   float* lambda; // r
   int32_t* order;// r : order[i] = output column of eigenvector i
   int32_t* sweep_flag;  // kJacobiSweeps + 1 : sweep s rotated something
@@ -69,11 +73,14 @@ struct RefreshTensor {
   int32_t split;         // Zt = Qt C runs as a bf16 product of three-way split operands (see split3)
   __bf16* Csplit;        // k x 6k: row n = [hi | mid | hi | mid | lo | hi] parts of row n of C
   __bf16* Qsplit;        // r x 6k: row i = [hi | hi | mid | mid | hi | lo] parts of row i of Qt
+
+  // Cholesky path, r x r: the factor that makes St orthonormal, formed when the last factorisation is done with A0
+  __host__ __device__ float* T() const { return reinterpret_cast<float*>(A0); }
 };
 
 // The kernels of the long launch sequences (QR panels, Jacobi rounds: about two thousand launches per
 // refresh) read this table from device memory through a pointer; the few one-off kernels take it by
-// value.  By value every launch would put 2.3 KB into the runtime's kernel-argument ring, whose few MB
+// value.  By value every launch would put 2.7 KB into the runtime's kernel-argument ring, whose few MB
 // then hold only some hundred launches: the host thread ends up waiting for the GPU launch by launch
 // for the whole refresh instead of running ahead of it.
 struct RefreshGroup {
@@ -81,9 +88,10 @@ struct RefreshGroup {
   int32_t r;
   RefreshTensor t[kMaxGroup];
 };
+static_assert(sizeof(RefreshGroup) <= 4096 - 256, "some kernels take the table, and a little more, by value: 4 KB of kernel arguments");
 
 struct Layout {
-  size_t C, Q, Z, Bw, Jt, S, T, A0, A1, diag, dinv, flag, tau, vscale, vclean, tmat, tpart, wpart, lambda, order, sweep_flag, group, Csplit, Qsplit, total;
+  size_t C, Q, Z, Bw, Jt, S, A0, A1, diag, dinv, flag, tau, vscale, vclean, tmat, tpart, wpart, lambda, order, sweep_flag, group, Csplit, Qsplit, total;
 };
 
 bool split_products(int64_t k, int64_t r);

@@ -527,7 +527,7 @@ __global__ __launch_bounds__(256) void polish_factor_kernel(const RefreshGroup g
   const int64_t count = (int64_t)r * r;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < count; e += stride)
-    t.T[e] = (e / r == e % r ? 1.5f : 0.f) - 0.5f * t.T[e];
+    t.T()[e] = (e / r == e % r ? 1.5f : 0.f) - 0.5f * t.T()[e];
 }
 
 }  // namespace
@@ -582,7 +582,7 @@ hipError_t launch_ritz_solve(const RefreshGroup& grp, const RefreshGroup* dgrp, 
     for (int i = 0; i < n; ++i) {
       const RefreshTensor& t = grp.t[i];
       GemmProblem& p = g.p[i];
-      p.A = which ? t.T : t.S; p.B = t.S; p.C = which ? t.Bw : t.T;
+      p.A = which ? t.T() : t.S; p.B = t.S; p.C = which ? t.Bw : t.T();
       p.lda = p.ldb = p.ldc = p.M = p.N = p.K = r;
     }
     GALORE_RETURN_IF(launch_product(g, DType::F32, which == 0, stream));
