@@ -128,13 +128,13 @@ typedef struct galore_ctx galore_ctx; /* opaque; OWNED by the library; host memo
 const char* galore_status_string(galore_status s);
 
 /* Workspace, in bytes, that lets one call process up to 8 consecutive tensors of the
- * list per kernel launch (transients R and N of the step; R up to four times, where a projection of few
- * tiles may cut its contraction into pieces; for a bf16 tensor with
+ * list per kernel launch (transients R and N of the step; R up to four times, where a projection of fewer
+ * than 224 tiles of 64 x 64 may cut its contraction into pieces; for a bf16 tensor with
  * rows <= cols, rows a multiple of 64 and cols not a multiple of 8, a copy of G with its rows
  * padded to a multiple of 8 elements, which the projection may then read instead of G; Gram
  * matrix, iteration blocks and reflector storage of the refresh).  Any 256-byte-aligned workspace at least as
- * large as the largest single-tensor need is accepted by galore_init; a smaller one
- * only means more, smaller launches.  What a call's transients leave free of its share of the
+ * large as the largest single-tensor need, with R counted once, is accepted by galore_init; a smaller one
+ * only means more, smaller launches, and fewer pieces where there is no room for them.  What a call's transients leave free of its share of the
  * workspace also serves, up to 64 MiB, as the area for the partial tiles of projection tiles that are cut
  * along K (see galore_set_concurrency); without room for them nothing is cut.  No device access. */
 galore_status galore_workspace_bytes(const galore_hparams* hp, const galore_tensor* W,
@@ -169,7 +169,7 @@ galore_status galore_step(galore_ctx* ctx, const galore_tensor* W, const galore_
  * the array (galore_set_concurrency and galore_set_call_overlap do not apply; pending overlapped
  * calls are joined first).
  * Limits: GALORE_ERR_WORKSPACE if one tensor's transients exceed the array (4 r max(rows, cols) bytes
- * of R, up to four times where the projection may be cut into pieces (fewer than 224 tiles of 64 x 64), plus s r max(rows, cols) of N, s = element size of W; every tensor of the LLaMA 60M ... 7B
+ * of R plus s r max(rows, cols) of N, s = element size of W, plus the padded copy; every tensor of the LLaMA 60M ... 7B
  * stacks at the paper's ranks fits); GALORE_ERR_UNIMPLEMENTED if auto_refresh is on and a tensor of
  * the call is due for a subspace refresh (t mod T == 0: the refresh needs hundreds of MB; take that
  * step with galore_step); GALORE_ERR_INVALID_ARG between galore_profile_start and _stop.  On any

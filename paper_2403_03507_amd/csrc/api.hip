@@ -188,21 +188,23 @@ int64_t projected_row_length(bool left, int64_t kdim, int64_t ldim, DType dt) {
   const bool pad = left && dt == DType::BF16 && ldim % 8 != 0 && ldim >= 8 && kdim % 64 == 0;
   return pad ? (ldim + 7) / 8 * 8 : ldim;
 }
-size_t step_r_bytes(bool left, int64_t kdim, int64_t ldim, int64_t r, DType dt) {  // room for the most pieces any launch group gives the tensor
-  const int64_t pieces = tile_pieces((long)tiles64(ldim, r), kdim, dt);
+size_t step_r_bytes(bool left, int64_t kdim, int64_t ldim, int64_t r, DType dt, int pieces) {
   return align_up((size_t)pieces * r * projected_row_length(left, kdim, ldim, dt) * 4);
 }
+// The most K pieces that any launch group gives the tensor
+int most_pieces(int64_t kdim, int64_t ldim, int64_t r, DType dt) { return tile_pieces((long)tiles64(ldim, r), kdim, dt); }
 size_t step_n_bytes(int64_t ldim, int64_t r, DType dt) { return align_up((size_t)r * ldim * dtype_size(dt)); }
 size_t step_gpad_bytes(bool left, int64_t kdim, int64_t ldim, DType dt) {
   const int64_t ldp = projected_row_length(left, kdim, ldim, dt);
   return ldp == ldim ? 0 : align_up((size_t)kdim * ldp * dtype_size(dt));
 }
-size_t step_need(bool left, int64_t kdim, int64_t ldim, int64_t r, DType dt) {
-  return step_r_bytes(left, kdim, ldim, r, dt) + step_n_bytes(ldim, r, dt) + step_gpad_bytes(left, kdim, ldim, dt);
+// What a step cannot do without: R is one matrix.  Its further K pieces go where the workspace has room (place_transients).
+size_t step_need(bool left, int64_t kdim, int64_t ldim, int64_t r, DType dt, int pieces = 1) {
+  return step_r_bytes(left, kdim, ldim, r, dt, pieces) + step_n_bytes(ldim, r, dt) + step_gpad_bytes(left, kdim, ldim, dt);
 }
 
-size_t tensor_need(const galore_hparams& hp, bool left, int64_t kdim, int64_t ldim, DType dt) {
-  const size_t a = step_need(left, kdim, ldim, hp.rank, dt);
+size_t tensor_need(const galore_hparams& hp, bool left, int64_t kdim, int64_t ldim, DType dt, int pieces = 1) {
+  const size_t a = step_need(left, kdim, ldim, hp.rank, dt, pieces);
   const size_t b = refresh_workspace_bytes(kdim, hp.rank);
   return a > b ? a : b;
 }
@@ -243,8 +245,35 @@ struct StepItem {
   void* N;
   void* Gpad;    // room for a copy of G with padded rows (see projected_row_length), or nullptr
   int64_t ldr;   // row length of R, set by the projection
-  int pieces;    // slabs of R, set by the projection
+  int pieces;    // slabs of R: as many as there is room for, then as many as the projection makes
 };
+
+// Places R, N and the padded copy of the items, in [off, end) of `base`; returns the end of what is taken.  end - off is at
+// least the sum of their step_need; what is beyond that goes to the K pieces of R, in list order, as far as it lasts.
+size_t place_transients(const galore_ctx* ctx, std::vector<StepItem>& items, unsigned char* base, size_t off, size_t end) {
+  const int r = ctx->hp.rank;
+  size_t spare = end - off;
+  for (const StepItem& it : items) {
+    const TensorInfo& ti = ctx->tensors[it.tensor];
+    spare -= step_need(ti.left, ti.kdim, ti.ldim, r, ti.dt);
+  }
+  for (StepItem& it : items) {
+    const TensorInfo& ti = ctx->tensors[it.tensor];
+    const size_t one = step_r_bytes(ti.left, ti.kdim, ti.ldim, r, ti.dt, 1);
+    it.pieces = most_pieces(ti.kdim, ti.ldim, r, ti.dt);
+    while (it.pieces > 1 && step_r_bytes(ti.left, ti.kdim, ti.ldim, r, ti.dt, it.pieces) - one > spare) --it.pieces;
+    const size_t rb = step_r_bytes(ti.left, ti.kdim, ti.ldim, r, ti.dt, it.pieces);
+    spare -= rb - one;
+    it.R = reinterpret_cast<float*>(base + off);
+    off += rb;
+    it.N = base + off;
+    off += step_n_bytes(ti.ldim, r, ti.dt);
+    const size_t gp = step_gpad_bytes(ti.left, ti.kdim, ti.ldim, ti.dt);
+    it.Gpad = gp ? base + off : nullptr;
+    off += gp;
+  }
+  return off;
+}
 
 galore_status run_chain(galore_ctx* ctx, std::vector<StepItem>& items, float lr, hipStream_t stream,
                         float* slabs = nullptr, size_t slab_bytes = 0) {
@@ -296,6 +325,7 @@ galore_status run_chain(galore_ctx* ctx, std::vector<StepItem>& items, float lr,
           const TensorInfo& ti = ctx->tensors[it.tensor];
           if (ti.dt != dt || (int)ti.left != left) continue;
           const bool to_large = large && large_projection_eligible(ti.left, ti.kdim, ti.ldim, r, dt);
+          const int room = it.pieces;
           it.ldr = ti.ldim;
           it.pieces = 1;
           const double k = (double)(ti.t + 1);
@@ -353,7 +383,7 @@ galore_status run_chain(galore_ctx* ctx, std::vector<StepItem>& items, float lr,
             continue;
           }
           p.b_kcontig = !left;
-          it.pieces = p.splits = std::min(tile_pieces(t64, ti.kdim, dt), tile_pieces((long)tiles64(ti.ldim, r), ti.kdim, dt));
+          it.pieces = p.splits = std::min(tile_pieces(t64, ti.kdim, dt), room);
           p.slab_stride = (int64_t)p.M * p.ldc;
           // With whole contractions the small-tile kernel can run the update block as well, which saves a launch and the
           // trip of R through memory: always when asked for, and by itself from 64 Ki entries on, where R is traffic (one
@@ -509,20 +539,10 @@ galore_status run_step_chunk(galore_ctx* ctx, std::vector<StepItem>& items, floa
       if (s) return s;
     }
   }
-  size_t off = overlap ? (size_t)ctx->parity * workspace_share(ctx) : 0;
-  for (StepItem& it : items) {
-    const TensorInfo& ti = ctx->tensors[it.tensor];
-    it.R = reinterpret_cast<float*>(ctx->ws + off);
-    off += step_r_bytes(ti.left, ti.kdim, ti.ldim, r, ti.dt);
-    it.N = ctx->ws + off;
-    off += step_n_bytes(ti.ldim, r, ti.dt);
-    const size_t gp = step_gpad_bytes(ti.left, ti.kdim, ti.ldim, ti.dt);
-    it.Gpad = gp ? ctx->ws + off : nullptr;
-    off += gp;
-  }
+  const size_t region_end = overlap ? (size_t)(ctx->parity + 1) * workspace_share(ctx) : ctx->ws_bytes;
+  const size_t off = place_transients(ctx, items, ctx->ws, overlap ? (size_t)ctx->parity * workspace_share(ctx) : 0, region_end);
   // What is left of this call's part of the workspace holds the partial tiles of the projection GEMM
   // (at most 64 MiB per chain are of use: one 256 x 256 fp32 tile per CU).
-  const size_t region_end = overlap ? (size_t)(ctx->parity + 1) * workspace_share(ctx) : ctx->ws_bytes;
   const size_t slab_off = align_up(off);
   size_t slab_avail = region_end > slab_off ? region_end - slab_off : 0;
   constexpr size_t kSlabMax = (size_t)64 << 20;
@@ -696,7 +716,8 @@ galore_status galore_workspace_bytes(const galore_hparams* hp, const galore_tens
     s = check_weight_shape(nullptr, *hp, W[i], i);
     if (s) return s;
     const bool left = W[i].rows <= W[i].cols;
-    need[i] = tensor_need(*hp, left, left ? W[i].rows : W[i].cols, left ? W[i].cols : W[i].rows, (DType)W[i].dtype);
+    const int64_t k = left ? W[i].rows : W[i].cols, l = left ? W[i].cols : W[i].rows;
+    need[i] = tensor_need(*hp, left, k, l, (DType)W[i].dtype, most_pieces(k, l, hp->rank, (DType)W[i].dtype));
   }
   size_t best = 0;
   for (int i = 0; i < n_tensors; ++i) {
@@ -914,23 +935,16 @@ galore_status galore_step_static(galore_ctx* ctx, const galore_tensor* W, const 
   int pos = 0;
   while (pos < count) {
     std::vector<StepItem> items;
-    size_t off = 0;
+    size_t used = 0;
     while (pos < count && (int)items.size() < kMaxGroup) {
       const TensorInfo& ti = ctx->tensors[first + pos];
       const size_t need = step_need(ti.left, ti.kdim, ti.ldim, r, ti.dt);
-      if (off + need > kStaticScratchBytes) break;
-      StepItem it{first + pos, &W[pos], &G[pos], nullptr, nullptr, nullptr, ti.ldim, 1};
-      it.R = reinterpret_cast<float*>(sp + off);
-      off += step_r_bytes(ti.left, ti.kdim, ti.ldim, r, ti.dt);
-      it.N = sp + off;
-      off += step_n_bytes(ti.ldim, r, ti.dt);
-      const size_t gp = step_gpad_bytes(ti.left, ti.kdim, ti.ldim, ti.dt);
-      it.Gpad = gp ? sp + off : nullptr;
-      off += gp;
-        items.push_back(it);
+      if (used + need > kStaticScratchBytes) break;
+      items.push_back(StepItem{first + pos, &W[pos], &G[pos], nullptr, nullptr, nullptr, ti.ldim, 1});
+      used += need;
       ++pos;
     }
-    const size_t slab_off = align_up(off);  // what is left of the array holds the projection's partial tiles
+    const size_t slab_off = align_up(place_transients(ctx, items, sp, 0, kStaticScratchBytes));  // what is left of the array holds the projection's partial tiles
     s = run_chain(ctx, items, lr, ctx->stream, reinterpret_cast<float*>(sp + slab_off),
                   kStaticScratchBytes > slab_off ? kStaticScratchBytes - slab_off : 0);
     if (s) return s;
