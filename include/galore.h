@@ -161,7 +161,7 @@ galore_status galore_step(galore_ctx* ctx, const galore_tensor* W, const galore_
 
 /* galore_step for callers that cannot allocate device memory or size a workspace at call time: code
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments,
- * same kernels and bit-identical results, but the transients of the step (R, N and, for a bf16 tensor
+ * same kernels and results, bit for bit under the condition that galore_set_concurrency states, but the transients of the step (R, N and, for a bf16 tensor
  * with an odd row length, the padded copy of G) live in a file-scope device array of the library,
  * 80 MiB on every GPU the library runs on, held until the process ends, instead of the caller's
  * workspace; the call allocates nothing (no hipMalloc / hipFree, no events, no streams).  The tensors
@@ -206,8 +206,10 @@ galore_status galore_refresh_subspace(galore_ctx* ctx, const galore_tensor* G, i
  * the forking takes the host runs as one chain).  1 = strictly serial on the
  * context's stream.  W, M, V agree between settings to the fp32 rounding of R, and bit for bit whenever
  * the projection launches cut no tile into K pieces (short sides under 512) or cut the same tiles
- * the same way: the projection sums the K range of a tile that does not fill a round of the chip
- * in pieces, and which tiles those are depends on what shares the launch.  For one setting and one
+ * the same way: a large projection (160 and more tiles of 256 x 256) sums the K range of a tile that does not fill a round
+ * of the chip in pieces, and which tiles those are depends on what shares the launch.  (A projection of few
+ * tiles is cut into pieces as well; how many depends on the tensors of the call and on galore_workspace_bytes' room
+ * for them, not on the setting.)  For one setting and one
  * sequence of calls results are bit-identical from run to run. */
 galore_status galore_set_concurrency(galore_ctx* ctx, int32_t lanes);
 

@@ -245,8 +245,27 @@ struct StepItem {
   void* N;
   void* Gpad;    // room for a copy of G with padded rows (see projected_row_length), or nullptr
   int64_t ldr;   // row length of R, set by the projection
-  int pieces;    // slabs of R: as many as there is room for, then as many as the projection makes
+  int pieces;    // slabs of R: as planned (pieces_of_call), as many as there is room for, then as many as the projection makes
 };
+
+// The K pieces of every tensor of a call.  The tiles counted are those of the tensor's block of kMaxGroup consecutive
+// tensors of the call, whichever of them share a launch in the end: the chains of a call run at the same time, so their tiles
+// fill the chip together, and the rounding of R is the same for every number of chains, every workspace with room for the
+// pieces, and in galore_step_static.
+std::vector<int> pieces_of_call(const galore_ctx* ctx, int32_t first, int32_t count) {
+  std::vector<int> pieces(count);
+  const int r = ctx->hp.rank;
+  for (int a = 0; a < count; a += kMaxGroup) {
+    const int b = std::min(a + kMaxGroup, count);
+    long tiles[2] = {0, 0};  // by dtype: no launch mixes them
+    for (int i = a; i < b; ++i) tiles[ctx->tensors[first + i].dt == DType::BF16] += (long)tiles64(ctx->tensors[first + i].ldim, r);
+    for (int i = a; i < b; ++i) {
+      const TensorInfo& ti = ctx->tensors[first + i];
+      pieces[i] = tile_pieces(tiles[ti.dt == DType::BF16], ti.kdim, ti.dt);
+    }
+  }
+  return pieces;
+}
 
 // Places R, N and the padded copy of the items, in [off, end) of `base`; returns the end of what is taken.  end - off is at
 // least the sum of their step_need; what is beyond that goes to the K pieces of R, in list order, as far as it lasts.
@@ -260,7 +279,6 @@ size_t place_transients(const galore_ctx* ctx, std::vector<StepItem>& items, uns
   for (StepItem& it : items) {
     const TensorInfo& ti = ctx->tensors[it.tensor];
     const size_t one = step_r_bytes(ti.left, ti.kdim, ti.ldim, r, ti.dt, 1);
-    it.pieces = most_pieces(ti.kdim, ti.ldim, r, ti.dt);
     while (it.pieces > 1 && step_r_bytes(ti.left, ti.kdim, ti.ldim, r, ti.dt, it.pieces) - one > spare) --it.pieces;
     const size_t rb = step_r_bytes(ti.left, ti.kdim, ti.ldim, r, ti.dt, it.pieces);
     spare -= rb - one;
@@ -309,23 +327,19 @@ galore_status run_chain(galore_ctx* ctx, std::vector<StepItem>& items, float lr,
       tilesf.beta1 = hp.beta1; tilesf.beta2 = hp.beta2; tilesf.eps = hp.eps;
       GemmGroup rest[2] = {};       // [0] RIGHT, [1] LEFT: what neither takes (a side of fewer than 8 elements)
       PadGroup pads{};
-      long t256 = 0, t64 = 0;
+      long t256 = 0;
       for (const StepItem& it : items) {
         const TensorInfo& ti = ctx->tensors[it.tensor];
         if (ti.dt == dt && large_projection_eligible(ti.left, ti.kdim, ti.ldim, r, dt)) t256 += (long)(((r + 255) / 256) * ((ti.ldim + 255) / 256));
       }
       const bool large = t256 >= kLargeProjectionTiles;
-      for (const StepItem& it : items) {
-        const TensorInfo& ti = ctx->tensors[it.tensor];
-        if (ti.dt == dt && !(large && large_projection_eligible(ti.left, ti.kdim, ti.ldim, r, dt))) t64 += (long)tiles64(ti.ldim, r);
-      }
       for (int left = 1; left >= 0; --left) {
         for (size_t ii = 0; ii < items.size(); ++ii) {
           StepItem& it = items[ii];
           const TensorInfo& ti = ctx->tensors[it.tensor];
           if (ti.dt != dt || (int)ti.left != left) continue;
           const bool to_large = large && large_projection_eligible(ti.left, ti.kdim, ti.ldim, r, dt);
-          const int room = it.pieces;
+          const int pieces = it.pieces;
           it.ldr = ti.ldim;
           it.pieces = 1;
           const double k = (double)(ti.t + 1);
@@ -383,7 +397,7 @@ galore_status run_chain(galore_ctx* ctx, std::vector<StepItem>& items, float lr,
             continue;
           }
           p.b_kcontig = !left;
-          it.pieces = p.splits = std::min(tile_pieces(t64, ti.kdim, dt), room);
+          it.pieces = p.splits = pieces;
           p.slab_stride = (int64_t)p.M * p.ldc;
           // With whole contractions the small-tile kernel can run the update block as well, which saves a launch and the
           // trip of R through memory: always when asked for, and by itself from 64 Ki entries on, where R is traffic (one
@@ -886,6 +900,7 @@ galore_status galore_step(galore_ctx* ctx, const galore_tensor* W, const galore_
   }
   // with overlapping calls a chunk has to fit one call's share of the workspace
   const size_t limit = ctx->overlap_calls ? workspace_share(ctx) : ctx->ws_bytes;
+  const std::vector<int> pieces = pieces_of_call(ctx, first, count);
   int pos = 0;
   while (pos < count) {
     std::vector<StepItem> items;
@@ -894,7 +909,7 @@ galore_status galore_step(galore_ctx* ctx, const galore_tensor* W, const galore_
       const TensorInfo& ti = ctx->tensors[first + pos];
       const size_t need = step_need(ti.left, ti.kdim, ti.ldim, ctx->hp.rank, ti.dt);
       if (!items.empty() && used + need > limit) break;
-      items.push_back(StepItem{first + pos, &W[pos], &G[pos], nullptr, nullptr, nullptr, ti.ldim, 1});
+      items.push_back(StepItem{first + pos, &W[pos], &G[pos], nullptr, nullptr, nullptr, ti.ldim, pieces[pos]});
       used += need;
       ++pos;
     }
@@ -932,6 +947,7 @@ galore_status galore_step_static(galore_ctx* ctx, const galore_tensor* W, const 
   }
   // Launch groups of as many consecutive tensors as fit the array, one chain on the context's stream.
   // Stream order protects the array between groups and between calls on this stream.
+  const std::vector<int> pieces = pieces_of_call(ctx, first, count);
   int pos = 0;
   while (pos < count) {
     std::vector<StepItem> items;
@@ -940,7 +956,7 @@ galore_status galore_step_static(galore_ctx* ctx, const galore_tensor* W, const 
       const TensorInfo& ti = ctx->tensors[first + pos];
       const size_t need = step_need(ti.left, ti.kdim, ti.ldim, r, ti.dt);
       if (used + need > kStaticScratchBytes) break;
-      items.push_back(StepItem{first + pos, &W[pos], &G[pos], nullptr, nullptr, nullptr, ti.ldim, 1});
+      items.push_back(StepItem{first + pos, &W[pos], &G[pos], nullptr, nullptr, nullptr, ti.ldim, pieces[pos]});
       used += need;
       ++pos;
     }

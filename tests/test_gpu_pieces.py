@@ -1,0 +1,48 @@
+"""K pieces of small projections: how a call is divided into chains and launches does not show in the results."""
+import pytest
+import torch
+
+from paper_2403_03507_amd import binding as gb
+
+pytestmark = pytest.mark.gpu
+
+# rank and tensors (rows, cols, dtype) of one call; short sides of 512 and more, so that contractions may be cut
+CALLS = {
+    # one launch of 512 tiles of 64 x 64, or three of 192, 192 and 128: a call long enough to be divided into chains
+    "eight 4096": (8, [(4096, 4096, torch.bfloat16)] * 8),
+    # 120 tiles, cut into 4 pieces, in one chain
+    "mixed": (40, [(512, 640, torch.float32), (1300, 520, torch.float32), (768, 777, torch.bfloat16), (640, 512, torch.bfloat16), (2050, 600, torch.float32)]),
+    # more tensors than a launch takes, both dtypes
+    "twenty": (32, [(512, 2048, torch.float32), (2048, 512, torch.bfloat16)] * 10),
+}
+
+
+@pytest.mark.parametrize("name", list(CALLS))
+def test_chains_workspaces_and_the_static_array_give_the_same_bits(name):
+    rank, tensors = CALLS[name]
+    g = torch.Generator(device="cuda").manual_seed(17)
+    rand = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    W0 = [(0.02 * rand(m, n)).to(dt) for m, n, dt in tensors]
+    G = [rand(m, n).to(dt) for m, n, dt in tensors]
+    P = [torch.linalg.qr(rand(min(m, n), rank))[0] for m, n, _ in tensors]
+    results = {}
+    for variant in ("3 chains", "2 chains", "1 chain", "fused", "static", "overlap", "workspace x 4"):
+        W = [w.clone() for w in W0]
+        opt = gb.GaLore(W, rank, update_gap=1 << 30, workspace_factor=4 if variant in ("overlap", "workspace x 4") else 1)
+        for i, p in enumerate(P):
+            opt.proj[i].copy_(p)
+            opt.set_step(i, 7)
+        if variant.endswith("chains") or variant == "1 chain":
+            gb.galore_set_concurrency(opt.ctx, int(variant[0]))
+        opt.set_fused_adam(variant == "fused")
+        opt.set_call_overlap(2 if variant == "overlap" else 0)
+        for _ in range(2):
+            (opt.step_static if variant == "static" else opt.step)(W, G, 1e-3)
+        opt.join()
+        torch.cuda.synchronize()
+        results[variant] = W + [x.clone() for x in opt.M + opt.V]
+        opt.close()
+    for variant, out in results.items():
+        for i, (a, b) in enumerate(zip(out, results["3 chains"])):
+            assert torch.equal(a, b), (variant, i)
+    assert not torch.equal(results["1 chain"][0], W0[0])
