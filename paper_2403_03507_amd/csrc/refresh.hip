@@ -208,7 +208,7 @@ hipError_t refresh_group(const std::vector<RefreshItem>& items, int r, int iters
   RefreshGroup grp{};
   grp.count = n;
   grp.r = r;
-  int64_t kmax = 0, kmin = INT64_MAX;
+  int64_t kmax = 0;
   const bool cholesky = cholesky_path(r);
   for (int i = 0; i < n; ++i) {
     const RefreshItem& it = items[i];
@@ -247,7 +247,6 @@ hipError_t refresh_group(const std::vector<RefreshItem>& items, int r, int iters
     t.Csplit = reinterpret_cast<__bf16*>(it.ws + L.Csplit);
     t.Qsplit = reinterpret_cast<__bf16*>(it.ws + L.Qsplit);
     kmax = k > kmax ? k : kmax;
-    kmin = k < kmin ? k : kmin;
   }
 
   // Cholesky path: two tables in device memory, with the roles of Q and Z as they are and exchanged; flip() makes the
@@ -258,18 +257,18 @@ hipError_t refresh_group(const std::vector<RefreshItem>& items, int r, int iters
     for (int i = 0; i < n; ++i) std::swap(grp.t[i].Q, grp.t[i].Z);
     std::swap(dgrp, dgrp_flipped);
   };
-  auto upload = [&]() -> hipError_t {
-    hipLaunchKernelGGL(upload_group_kernel, dim3(1), dim3(256), 0, stream, grp, dgrp);
+  auto upload = [&](const RefreshGroup& table, RefreshGroup* to) -> hipError_t {
+    hipLaunchKernelGGL(upload_group_kernel, dim3(1), dim3(256), 0, stream, table, to);
     return hipGetLastError();
   };
   {
     const RefreshItem& lead = items[0];
     dgrp = reinterpret_cast<RefreshGroup*>(lead.ws + layout_for(lead.rows <= lead.cols ? lead.rows : lead.cols, r).group);
     dgrp_flipped = dgrp + 1;
-    GALORE_RETURN_IF(upload());
+    GALORE_RETURN_IF(upload(grp, dgrp));
     if (cholesky) {
       flip();
-      GALORE_RETURN_IF(upload());
+      GALORE_RETURN_IF(upload(grp, dgrp));
       flip();
     }
   }
@@ -354,11 +353,25 @@ hipError_t refresh_group(const std::vector<RefreshItem>& items, int r, int iters
     }
     // The last round's block is the basis of the Rayleigh-Ritz step and has to be orthonormal: a second pass on the result
     // of the first, whose condition number is small; a third where replaced columns leave little room to be independent.
-    const int passes = it + 1 < iters ? 1 : 2 * r > kmin ? 3 : 2;
-    for (int pass = 0; pass < passes; ++pass) {
-      if (pass) flip();
-      GALORE_RETURN_IF(launch_orthonormalise(grp, dgrp, 4 * it + pass, /*followed_by_pass=*/passes > 1, stream));
+    const bool last = it + 1 == iters;
+    GALORE_RETURN_IF(launch_orthonormalise(grp, dgrp, 4 * it, last, stream));
+    if (!last) continue;
+    flip();
+    GALORE_RETURN_IF(launch_orthonormalise(grp, dgrp, 4 * it + 1, last, stream));
+    // The third pass is each tensor's own: whatever shares its group, a tensor is refreshed as it is alone.
+    RefreshGroup third{};
+    third.r = r;
+    for (int i = 0; i < n; ++i) {
+      RefreshTensor& t = grp.t[i];
+      if (2 * r <= t.k) continue;
+      std::swap(t.Q, t.Z);
+      third.t[third.count++] = t;
     }
+    if (third.count == 0) continue;
+    std::swap(dgrp, dgrp_flipped);  // the same as the table of all tensors with the roles exchanged, if that is what `third` holds
+    if (third.count < n) GALORE_RETURN_IF(upload(third, dgrp));
+    GALORE_RETURN_IF(launch_orthonormalise(third, dgrp, 4 * it + 2, last, stream));
+    if (third.count < n) GALORE_RETURN_IF(upload(grp, dgrp));
   }
 
   // Rayleigh-Ritz

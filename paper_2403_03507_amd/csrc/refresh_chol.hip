@@ -116,7 +116,7 @@ template <bool BT> __device__ __forceinline__ void block_product(d4& acc, const 
   }
 }
 
-constexpr double kDependent = 1e-12;   // sin^2 to the span of the columns before, in a pass that another pass follows
+constexpr double kDependent = 1e-12;   // sin^2 to the span of the columns before, in the passes of the last round
 constexpr double kDependentRaw = 1e-14;  // in a pass that is followed by a product with C: little above fp64 rounding
 constexpr double kZeroColumn = 1e-56;    // squared length below which a column counts as zero: its reciprocal has to fit fp32
 constexpr double kRitzShift = 2.4e-7;    // 2^-22
@@ -310,8 +310,8 @@ hipError_t launch_factor(const RefreshGroup& grp, const RefreshGroup* dgrp, int 
 
 }  // namespace
 
-hipError_t launch_orthonormalise(const RefreshGroup& grp, const RefreshGroup* dgrp, int pass, bool followed_by_pass, hipStream_t stream) {
-  GALORE_RETURN_IF(launch_factor(grp, dgrp, 0, followed_by_pass ? kDependent : kDependentRaw, stream));
+hipError_t launch_orthonormalise(const RefreshGroup& grp, const RefreshGroup* dgrp, int pass, bool final_round, hipStream_t stream) {
+  GALORE_RETURN_IF(launch_factor(grp, dgrp, 0, final_round ? kDependent : kDependentRaw, stream));
   GemmGroup g{};
   g.count = grp.count;
   for (int i = 0; i < grp.count; ++i) {

@@ -114,8 +114,8 @@ inline unsigned blocks_for(int64_t count, int per_block, unsigned cap) {
 // then Qt <- the orthonormal factor (refresh_qr.hip).  dgrp: the group's table in device memory; kmax: largest short side.
 hipError_t launch_householder_qr(const RefreshGroup& grp, const RefreshGroup* dgrp, int64_t kmax, hipStream_t stream);
 // Cholesky path: Qt <- orthonormal rows spanning those of Zt (refresh_chol.hip).  pass: number of this pass within the
-// refresh; followed_by_pass: another pass works on the result.
-hipError_t launch_orthonormalise(const RefreshGroup& grp, const RefreshGroup* dgrp, int pass, bool followed_by_pass, hipStream_t stream);
+// refresh; final_round: of the last round, whose passes work on the result of the one before and have to end orthonormal.
+hipError_t launch_orthonormalise(const RefreshGroup& grp, const RefreshGroup* dgrp, int pass, bool final_round, hipStream_t stream);
 // Cholesky path: Bw <- L^T with L L^T = Qt Zt^T, the Rayleigh-Ritz matrix, shifted by a little of its norm (refresh_chol.hip).
 hipError_t launch_ritz_factor(const RefreshGroup& grp, const RefreshGroup* dgrp, hipStream_t stream);
 // Eigen-decomposition of the symmetric r x r matrix in Bw (Cholesky path: given by its transposed factor) by blocked
