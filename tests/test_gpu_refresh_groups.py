@@ -16,6 +16,10 @@ GROUPS = {
     "gram bf16": (16, [(2048, 2100, torch.bfloat16)] * 3 + [(2100, 2048, torch.bfloat16)] * 2),
     # 16 x 10 tiles of 256 x 256: the large-tile kernel for the split products, small tiles alone
     "large products": (256, [(2560, 2600, torch.bfloat16)] * 16),
+    # products of 352 tiles of 128 x 128 and of 528 of 128 x 64, on 64 x 64 tiles alone, in fp32 and (short sides of a multiple of 32) split
+    "tiles 128 x 128": (129, [(1301, 1310, torch.float32)] * 16),
+    "tiles 128 x 128 split": (129, [(1312, 1320, torch.bfloat16)] * 16),
+    "tiles 128 x 64": (70, [(2051, 2060, torch.float32)] * 16),
     # the Householder path
     "rank 300": (300, [(512, 600, torch.bfloat16), (1024, 700, torch.bfloat16), (320, 400, torch.float32)]),
 }

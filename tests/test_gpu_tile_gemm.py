@@ -1,6 +1,9 @@
 """The small-tile GEMM (projection with K pieces or with Adam in its epilogue, weight update) against the fp64 oracle,
 at the sizes where it can go wrong: one element to either side of a tile, contractions and rows of no multiple of
 anything, the smallest sides it takes, the group sizes at which each tile shape and the K pieces are chosen."""
+import os
+import re
+
 import pytest
 import torch
 
@@ -10,6 +13,27 @@ from paper_2403_03507_amd import binding as gb
 from paper_2403_03507_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
+
+
+def _tile(problems, update=False):
+    """The tile of a launch of the small-tile GEMM over problems (M, N, K), as csrc/gemm_tile.hip chooses it (the constants are read
+    from there: where the rule takes another form, this has to follow)."""
+    src = open(os.path.join(os.path.dirname(gb.__file__), "csrc", "gemm_tile.hip")).read()
+    rule = re.search(r"if \(items128 >= (\d+) && \(!update \|\| longest >= (\d+)\)\) return launch<T, 128, 128>\(g, epi, stream\);\s*"
+                     r"if \(items96 >= \(update \? (\d+) : (\d+)\)\) return launch<T, 128, 64>", src)
+    many128, long_k, many96_update, many96 = (int(x) for x in rule.groups())
+    count = lambda bm, bn: sum(-(-m // bm) * -(-n // bn) for m, n, _ in problems)
+    if count(128, 128) >= many128 and (not update or max(k for _, _, k in problems) >= long_k):
+        return 128, 128
+    return (128, 64) if count(128, 64) >= (many96_update if update else many96) else (64, 64)
+
+
+def _projection(shapes, rank):
+    return [(rank, n, m) if m <= n else (m, rank, n) for m, n in shapes]
+
+
+def _update(shapes, rank):
+    return [(m, n, rank) for m, n in shapes]
 
 
 def _steps(shapes, rank, dtype, steps=2, fused=False, pad=0, static=False):
@@ -22,7 +46,7 @@ def _steps(shapes, rank, dtype, steps=2, fused=False, pad=0, static=False):
     srcs = [wl.GradientSource(m, n, 1300 + i, "lowrank", dtype=dtype, signal_rank=min(16, m, n), noise=0.01) for i, (m, n) in enumerate(shapes)]
     W0 = [wl.make_weight(m, n, 1320 + i, dtype) for i, (m, n) in enumerate(shapes)]
     Wd = [lay(w.cuda()) for w in W0]
-    opt = gb.GaLore(Wd, rank, auto_refresh=False, weight_decay=0.01)
+    opt = gb.GaLore(Wd, rank, auto_refresh=False, weight_decay=0.01, workspace_factor=2)  # room for 16 tensors in a launch
     opt.set_fused_adam(fused)
     oracles = []
     for i, (m, n) in enumerate(shapes):
@@ -81,13 +105,65 @@ def test_adam_in_the_epilogue(dtype, fused):
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("shape,rank,count", [((130, 1411), 130, 16), ((1411, 130), 130, 16), ((72, 2049), 70, 16)])
 def test_larger_tiles(dtype, shape, rank, count):
-    # 16 tensors: 352 tiles of 128 x 128 (or, with 70 rows, 528 of 128 x 64) in the projection, W in 128 x 64 tiles
-    _steps([shape] * count, rank, dtype, steps=1)
+    # 16 tensors: 384 tiles of 128 x 128 (or, with 70 rows, 528 of 128 x 64) in the projection, W in 128 x 64 tiles
+    shapes = [shape] * count
+    assert _tile(_projection(shapes, rank)) == ((128, 64) if rank == 70 else (128, 128)) and _tile(_update(shapes, rank), update=True) == (128, 64)
+    _steps(shapes, rank, dtype, steps=1)
 
 
 def test_larger_tiles_of_the_weight_update_with_a_long_contraction():
-    # r = 257: more than 350 tiles of 128 x 128 and five K steps, the last of a single element
+    # r = 257: 396 tiles of 128 x 128 and five K steps, the last of a single element
+    assert _tile(_update([(261, 1300)] * 12, 257), update=True) == (128, 128)
     _steps([(261, 1300)] * 12, 257, "bf16", steps=1)
+
+
+# One tensor with enough tiles by itself: rank, short and long side of no multiple of the tile, of the K step or of a 16-byte piece;
+# the tile of its projection (with Adam in the epilogue: whole contractions, more than 64 Ki entries) and of its weight update.
+LONE = [(129, 300, 22531, (128, 128), (128, 64)), (65, 131, 32003, (128, 64), (128, 64)), (130, 203, 21251, (128, 64), (128, 64)),
+        (257, 259, 15002, (128, 128), (128, 128)), (66, 68, 8200, (64, 64), (64, 64))]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("wide", [True, False])
+@pytest.mark.parametrize("rank,k,l,proj,update", LONE)
+def test_every_tile_with_adam_and_weight_update(rank, k, l, proj, update, wide, dtype):
+    shape = (k, l) if wide else (l, k)
+    assert _tile(_projection([shape], rank)) == proj and _tile(_update([shape], rank), update=True) == update
+    _steps([shape], rank, dtype, steps=1, pad=3 if rank == 257 else 0)
+
+
+def _entrywise(got, ref, bound):
+    worst = float(((got.double() - ref).abs() / bound).max())
+    assert worst <= 1.0, worst
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("wide", [True, False])
+@pytest.mark.parametrize("rank,k,l,proj,update", LONE)
+def test_every_tile_of_the_plain_product_and_the_weight_update(rank, k, l, proj, update, wide, dtype):
+    # the stage calls, each entry against 64 bits: K fp32 additions of exact products are off by at most K 2^-24 of the sum of
+    # magnitudes (to first order), a stored bf16 weight (8 significant bits) by another 2^-8 of itself at most
+    m, n = (k, l) if wide else (l, k)
+    assert _tile(_projection([(m, n)], rank)) == proj and _tile(_update([(m, n)], rank), update=True) == update
+    g = torch.Generator(device="cuda").manual_seed(l)
+    tdt = wl.TORCH_DTYPE[dtype]
+    rand = lambda *s: strided(torch.randn(*s, generator=g, device="cuda").to(tdt), 5)
+    G, P = rand(m, n), rand(k, rank)
+    Pt = strided(P.t().contiguous(), 1)
+    Rbuf = torch.full((rank if wide else m, (n if wide else rank) + 2), 7.0, device="cuda")
+    R = Rbuf[:, :-2]
+    gb.galore_project(Pt, G, R)
+    a, b = (P.double().t(), G.double()) if wide else (G.double(), P.double())
+    _entrywise(R, a @ b, (k if wide else n) * 2.0 ** -24 * 1.01 * (a.abs() @ b.abs()))
+    assert bool((Rbuf[:, -2:] == 7.0).all())
+    W, N = rand(m, n), rand(l, rank)
+    a, b = (P.double(), N.double().t()) if wide else (N.double(), P.double().t())
+    lr, scale, decay = f32(1e-2), f32(0.25), f32(0.125)
+    ref = (1 - lr * decay) * W.double() - lr * scale * (a @ b)
+    bound = rank * 2.0 ** -24 * 1.01 * lr * scale * (a.abs() @ b.abs()) + 2.0 ** -22 * (W.double().abs() + ref.abs()) + (2.0 ** -8 if dtype == "bf16" else 0) * ref.abs()
+    gb.galore_project_back(P, N, W, lr, scale, decay)
+    torch.cuda.synchronize()
+    _entrywise(W, ref, bound * 1.01)
 
 
 def test_large_tile_projection_of_a_padded_copy():
@@ -97,3 +173,35 @@ def test_large_tile_projection_of_a_padded_copy():
 
 def test_static_scratch_holds_the_pieces():
     _steps([(1030, 1024), (512, 600)], 40, "bf16", static=True)
+
+
+@pytest.mark.parametrize("m,n,rank,tile", [(300, 22531, 129, (128, 128)), (22531, 300, 129, (64, 64)), (203, 31939, 66, (128, 64)), (200, 8203, 66, (64, 64))])
+def test_products_rounded_in_the_epilogue(m, n, rank, tile):
+    # the two-sided step's T1 = P^T G (r x n) and T2 = Q N^T (n x r) are rounded to bf16 by the product that forms them
+    t1, t2 = (rank, n, m), (n, rank, rank)
+    assert max(_tile([t1]), _tile([t2])) == tile
+    g = torch.Generator(device="cuda").manual_seed(n)
+    rand = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    b16 = lambda x: x.float().to(torch.bfloat16).double()
+    W, G = (0.02 * rand(m, n)).to(torch.bfloat16), rand(m, n).to(torch.bfloat16)
+    opt = gb.GaLoreTwoSided(W, rank, auto_refresh=False, update_gap=1 << 30)
+    opt.P.copy_(torch.linalg.qr(rand(m, rank))[0])
+    opt.Q.copy_(torch.linalg.qr(rand(n, rank))[0])
+    opt.M.copy_(rand(rank, rank))
+    opt.V.fill_(1.0)
+    opt.t = 1000
+    P, Q, M, V, W0 = (x.double().clone() for x in (opt.P, opt.Q, opt.M, opt.V, W))
+    lr = f32(1e-2)
+    opt.step(W, G, lr)
+    torch.cuda.synchronize()
+    b1, b2, k = f32(0.9), f32(0.999), 1001
+    R = b16(P.t() @ G.double()) @ Q
+    M = b1 * M + (1 - b1) * R
+    V = b2 * V + (1 - b2) * R * R
+    N = b16((M / (1 - b1 ** k)) / ((V / (1 - b2 ** k)).sqrt() + 1e-8))
+    T2 = b16(Q @ N.t())
+    ref = W0 - lr * f32(0.25) * (P @ T2.t())
+    # An entry of T1 (N, T2) within fp32 rounding of a boundary of bf16 falls the other way: one in a thousand, by 2^-8, 1.2e-4 in norm
+    assert relF(to64(opt.M), M.cpu().numpy()) <= 5e-4 and relF(to64(opt.V), V.cpu().numpy()) <= 5e-4
+    # every entry of the update to the roundings of N and T2 (2^-8 each at most) and what T1's do to N, the weight to its own
+    _entrywise(W, ref, 1.01 * 2.0 ** -8 * ref.abs() + lr * f32(0.25) * 2.0 ** -6 * (P.abs() @ (Q.abs() @ N.abs().t()).t()))
