@@ -21,17 +21,22 @@ constexpr float kJacobiTol = 1e-5f;  // |b_p.b_q| <= tol |b_p||b_q|: a few times
 // rarely reached although the result has stopped changing.
 constexpr float kJacobiStopTol = 4e-5f;
 // The Cholesky path (below) rotates the rows of a factor L^T of the Rayleigh-Ritz matrix, whose lengths are the square roots of
-// the Ritz values, so the same inner product is twice the angle; and no rotation is accumulated, so tighter levels cost little:
-// 7B layer, neighbouring Ritz values 0.4% apart, median error of a bf16 column (1.62e-3 by its rounding alone) 1.76e-3 at a level of
-// 5e-6, 1.65e-3 at 2e-6, 1.63e-3 at 1e-6, in 14.4, 14.8 and 15.9 ms.
+// the Ritz values, so the same inner product is twice the angle; and no rotation is accumulated, so tighter levels cost little.
+// At levels of 5e-6 / 2e-6 / 1e-6 (stop level five times that): error of a column against 64 bits, root mean square, in units of
+// 2^-24 lambda_1 / (distance to the next Ritz value), r = 64 .. 256: 9 to 19 / 5 to 8 / 3 to 6 (Householder path 10 to 20); a refresh of
+// seven 1024 x 2736 gradients, ms, at r = 256 3.13 / 3.19 / 3.18, at r = 255 6.65 / 6.73 / 7.22.
+// The kernels that stage rows (r of no multiple of 4) have no stop level: a sweep follows while anything rotates.
 constexpr float kFactorTol = 2e-6f;
 constexpr float kFactorStopTol = 1e-5f;
 // Largest rank of the Cholesky path (refresh_chol.hip); higher ranks take Householder QR and Jacobi on the Rayleigh-Ritz matrix itself.
-// The Cholesky path is faster at every rank (7B layer set, r = 1024: 34 ms against 61) and closer to the exact vectors.  But a
-// projector's columns are signed by their largest entry, and with a thousand directions inside a factor of 8 some columns
-// have two entries that tie to 1e-3 or less: there the two paths, each right to its rounding, differ by the signs of about
-// one column in 10^4, which a run that is resumed or compared across versions would see.  At r = 256 (350M) they agree
-// to 8e-4 in norm.
+// The Cholesky path is faster at every rank (7B layer set, r = 1024: 34 ms against 61) and its vectors are closer to those of 64 bits:
+// root mean square error of a column, r directions inside a factor of 8, fp32, k = 2048, Householder / Cholesky: r = 64 4.1e-5 /
+// 2.7e-5, 128 6.9e-5 / 2.7e-5, 256 1.6e-4 / 6.3e-5, 512 3.3e-4 / 1.6e-4, 768 9.4e-4 / 3.5e-4, 1024 1.1e-3 / 5.3e-4.  So accuracy
+// sets no line.  What a change of path can change is the sign of a column whose two largest entries tie to within its error.
+// Columns signed otherwise than in 64 bits, Householder / Cholesky: r up to 128 0 / 0 of 1120, 256 2 / 0 of 1280, 384 0 / 0 of 1920,
+// 512 2 / 1 of 2560, 768 0 / 0 of 1536, 1024 2 / 0 of 2048.  The line stands where the projectors of the two paths still
+// agree to 1e-3 in norm on the layers measured (350M 8e-4, 60M 1e-4), signs included; above it they stay, bit for bit, the Householder
+// path's, for the runs that are resumed or compared with earlier ones.
 constexpr int kCholeskyMaxRank = 256;
 inline bool cholesky_path(int64_t r) { return r <= kCholeskyMaxRank; }
 constexpr int kNB = 8;               // reflectors per Householder panel (block_sum_vec sums 8 values)
