@@ -245,6 +245,7 @@ struct StepItem {
   void* N;
   void* Gpad;    // room for a copy of G with padded rows (see projected_row_length), or nullptr
   int64_t ldr;   // row length of R, set by the projection
+  bool large;    // the launches of the other chains count towards the large-tile kernel as well (count_over_chains)
   int pieces;    // slabs of R: as planned (pieces_of_call), as many as there is room for, then as many as the projection makes
 };
 
@@ -293,6 +294,31 @@ size_t place_transients(const galore_ctx* ctx, std::vector<StepItem>& items, uns
   return off;
 }
 
+long projection_tiles256(const galore_ctx* ctx, const StepItem& it) {
+  const TensorInfo& ti = ctx->tensors[it.tensor];
+  const int r = ctx->hp.rank;
+  return large_projection_eligible(ti.left, ti.kdim, ti.ldim, r, ti.dt) ? (long)(((r + 255) / 256) * ((ti.ldim + 255) / 256)) : 0;
+}
+
+// Chains run at the same time, so where a chunk is divided the launches of all its chains fill the chip together with large
+// tiles.  That pays with tiles that are mostly used and where no tensor of the chunk needs a copy of G; otherwise only what a chain
+// has by itself counts (run_chain).  Three layers in three chains each, us, by the chain / over the chains, repeated passes and (rotating
+// over four states) passes on new data: 4096 / 11008 at r = 256 (193 tiles) 1271 / 1089 and 1330 / 1263, r = 512 (386) 1811 / 1634 and
+// 1891 / 1835, r = 384 (386, 3/4 of their rows used) 1470 / 1456 and 1566 / 1662; 3072 / 8192 at r = 768 (432) 1454 / 1395 and 1624 / 1576;
+// 2560 / 6912 at r = 768 (363) 1100 / 1040 and 1146 / 1180, r = 512 (242) 856 / 832 and 931 / 933; 2048 / 5504 at r = 1024 (392) 976 / 923
+// and 1047 / 1061, r = 512 (196) 623 / 578 and 683 / 700; 2048 / 5461 (copies) at r = 1024 1059 / 1146 and 1205 / 1302.
+void count_over_chains(const galore_ctx* ctx, std::vector<StepItem>& items) {
+  const int r = ctx->hp.rank;
+  bool pays = 10 * r >= 8 * ((r + 255) / 256 * 256);
+  long t256 = 0;
+  for (const StepItem& it : items) {
+    const TensorInfo& ti = ctx->tensors[it.tensor];
+    pays = pays && projected_row_length(ti.left, ti.kdim, ti.ldim, ti.dt) == ti.ldim;
+    t256 += projection_tiles256(ctx, it);
+  }
+  for (StepItem& it : items) it.large = pays && t256 >= kLargeProjectionTiles && projection_tiles256(ctx, it) > 0;
+}
+
 galore_status run_chain(galore_ctx* ctx, std::vector<StepItem>& items, float lr, hipStream_t stream,
                         float* slabs = nullptr, size_t slab_bytes = 0) {
   const galore_hparams& hp = ctx->hp;
@@ -328,17 +354,15 @@ galore_status run_chain(galore_ctx* ctx, std::vector<StepItem>& items, float lr,
       GemmGroup rest[2] = {};       // [0] RIGHT, [1] LEFT: what neither takes (a side of fewer than 8 elements)
       PadGroup pads{};
       long t256 = 0;
-      for (const StepItem& it : items) {
-        const TensorInfo& ti = ctx->tensors[it.tensor];
-        if (ti.dt == dt && large_projection_eligible(ti.left, ti.kdim, ti.ldim, r, dt)) t256 += (long)(((r + 255) / 256) * ((ti.ldim + 255) / 256));
-      }
+      for (const StepItem& it : items)
+        if (ctx->tensors[it.tensor].dt == dt) t256 += projection_tiles256(ctx, it);
       const bool large = t256 >= kLargeProjectionTiles;
       for (int left = 1; left >= 0; --left) {
         for (size_t ii = 0; ii < items.size(); ++ii) {
           StepItem& it = items[ii];
           const TensorInfo& ti = ctx->tensors[it.tensor];
           if (ti.dt != dt || (int)ti.left != left) continue;
-          const bool to_large = large && large_projection_eligible(ti.left, ti.kdim, ti.ldim, r, dt);
+          const bool to_large = it.large || (large && projection_tiles256(ctx, it) > 0);
           const int pieces = it.pieces;
           it.ldr = ti.ldim;
           it.pieces = 1;
@@ -401,7 +425,8 @@ galore_status run_chain(galore_ctx* ctx, std::vector<StepItem>& items, float lr,
           p.slab_stride = (int64_t)p.M * p.ldc;
           // With whole contractions the small-tile kernel can run the update block as well, which saves a launch and the
           // trip of R through memory: always when asked for, and by itself from 64 Ki entries on, where R is traffic (one
-          // 350M layer 61 against 68 us, a 2768 / 7312 layer at r = 272 297 against 313).
+          // 350M layer 61 against 68 us, a 2768 / 7312 layer at r = 272 297 against 313; with the caches flushed before each pass,
+          // three 350M layers 187 against 211, two 1B layers 421 against 502).
           if (it.pieces == 1 && !ti.q8 && (ctx->fused_adam || (int64_t)r * ti.ldim >= 65536)) {
             p.Mo = static_cast<float*>(ti.st.m.data);
             p.Vo = static_cast<float*>(ti.st.v.data);
@@ -588,6 +613,7 @@ galore_status run_step_chunk(galore_ctx* ctx, std::vector<StepItem>& items, floa
   if (lanes <= 1)
     return run_chain(ctx, items, lr, ctx->stream, reinterpret_cast<float*>(ctx->ws + slab_off), slab_avail < kSlabMax ? slab_avail : kSlabMax);
 
+  count_over_chains(ctx, items);
   // Greedy balance by cost (m n, as r is shared): heaviest tensor first, always into the lightest chain.
   std::vector<int> order(items.size());
   for (size_t i = 0; i < items.size(); ++i) order[i] = (int)i;
@@ -909,7 +935,7 @@ galore_status galore_step(galore_ctx* ctx, const galore_tensor* W, const galore_
       const TensorInfo& ti = ctx->tensors[first + pos];
       const size_t need = step_need(ti.left, ti.kdim, ti.ldim, ctx->hp.rank, ti.dt);
       if (!items.empty() && used + need > limit) break;
-      items.push_back(StepItem{first + pos, &W[pos], &G[pos], nullptr, nullptr, nullptr, ti.ldim, pieces[pos]});
+      items.push_back(StepItem{first + pos, &W[pos], &G[pos], nullptr, nullptr, nullptr, ti.ldim, false, pieces[pos]});
       used += need;
       ++pos;
     }
@@ -956,7 +982,7 @@ galore_status galore_step_static(galore_ctx* ctx, const galore_tensor* W, const 
       const TensorInfo& ti = ctx->tensors[first + pos];
       const size_t need = step_need(ti.left, ti.kdim, ti.ldim, r, ti.dt);
       if (used + need > kStaticScratchBytes) break;
-      items.push_back(StepItem{first + pos, &W[pos], &G[pos], nullptr, nullptr, nullptr, ti.ldim, pieces[pos]});
+      items.push_back(StepItem{first + pos, &W[pos], &G[pos], nullptr, nullptr, nullptr, ti.ldim, false, pieces[pos]});
       used += need;
       ++pos;
     }

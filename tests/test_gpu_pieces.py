@@ -46,3 +46,19 @@ def test_chains_workspaces_and_the_static_array_give_the_same_bits(name):
         for i, (a, b) in enumerate(zip(out, results["3 chains"])):
             assert torch.equal(a, b), (variant, i)
     assert not torch.equal(results["1 chain"][0], W0[0])
+
+
+@pytest.mark.parametrize("d,f,rank,large", [(4096, 11008, 512, True), (4096, 11008, 256, True), (4096, 11008, 384, False), (2048, 5504, 512, True), (2048, 5461, 1024, False)])
+def test_forked_chains_count_their_tiles_together(d, f, rank, large):
+    # One layer in three chains of 100 to 130 tiles of 256 x 256 each: together enough for the large-tile kernel (whose Adam runs in
+    # launches of its own here) or not (small tiles, which run Adam in their epilogue), as each is faster
+    shapes = [(d, d)] * 4 + [(d, f)] * 2 + [(f, d)]
+    W = [torch.zeros(m, n, dtype=torch.bfloat16, device="cuda") for m, n in shapes]
+    G = [torch.full((m, n), 0.01, dtype=torch.bfloat16, device="cuda") for m, n in shapes]
+    opt = gb.GaLore(W, rank, update_gap=1 << 30, auto_refresh=False)
+    gb.galore_profile_start(opt.ctx)
+    opt.step(W, G, 1e-3)
+    stages = gb.galore_profile_stop(opt.ctx)
+    assert stages["project_left"][1] == stages["back"][1] == 3   # three chains
+    assert (stages["adam"][1] > 0) == large, stages
+    opt.close()
