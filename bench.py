@@ -29,13 +29,14 @@ PEAK_HBM_GBS = 8000.0
 # cannot be read inside a timed run, so the figures are tied to the kernel sources they were measured on:
 # `sources` is the digest of the files named in TRAFFIC_SOURCES at that time, and roofline.traffic is reported
 # only while the digest still matches (null otherwise: re-run the probe and update both together).
-TRAFFIC_SOURCES = ["gemm_mfma_dl.hpp", "gemm_proj_dl.hpp", "proj.hip", "gemm_mfma.hpp", "gemm_dispatch.hpp", "common.hpp", "adam.hip", "adam_entry.hpp"]
+TRAFFIC_SOURCES = ["gemm_mfma_dl.hpp", "gemm_proj_dl.hpp", "proj.hip", "gemm_mfma.hpp", "gemm_dispatch.hpp", "common.hpp", "adam.hip", "adam_entry.hpp",
+                   "gemm_tile.hpp", "gemm_tile.hip", "api.hip"]  # the last two choose the kernel of a projection and of a weight update
 MEASURED_TRAFFIC_7B = {
-    "sources": "a543e50608c03987",
+    "sources": "2dc30e6a68a2ec3f",
     "bytes": {   # read (2 x FETCH_SIZE KiB x 1024) + written (WRITE_SIZE KiB x 1024)
-        "project_left": (708.0e6 + 219.0e6) + (16.8e6 + 1.0e6),   # the grouped projection launch of both orientations + the sum of the split tiles' slabs
-        "project_left_fused_adam": (1406.1e6 + 637.5e6) + (19.0e6 + 2.6e6),
-        "back": 1192.9e6 + 404.8e6,
+        "project_left": (720.0e6 + 218.9e6) + (16.8e6 + 1.0e6),   # the grouped projection launch of both orientations + the sum of the split tiles' slabs
+        "project_left_fused_adam": (1413.7e6 + 639.8e6) + (19.0e6 + 2.6e6),
+        "back": 1198.5e6 + 404.8e6,
         "adam": (471.9e6 + 135.3e6) + (393.2e6 + 112.7e6),
     },
 }
@@ -132,7 +133,7 @@ def main():
     ap.add_argument("--fused-adam", type=int, choices=[0, 1], default=None,
                     help="1: Adam in the epilogue of the projection GEMM (two kernels per step); 0: separate Adam kernel (three).  Same "
                          "bits either way.  Default: whichever is faster in the stack's schedule (measured): 1 for llama7b, llama350m and "
-                         "llama130m, 0 for llama1b; the fp32 llama60m stack has no fused epilogue")
+                         "llama130m, 0 for llama1b and llama60m (projections on small tiles may take the epilogue by themselves then)")
     ap.add_argument("--in-flight", type=int, choices=[2, 3], default=None,
                     help="overlapped calls: calls in flight (library streams used) on ordinary steps.  Default: 2 for llama7b (measured "
                          "faster than 3 there: the tail of one call's GEMM hides under the next call's, a third call only adds "
@@ -306,9 +307,9 @@ def main():
     else:
         peak = PEAK_BF16_TFLOPS if dtype == "bf16" else PEAK_F32_TFLOPS
         achieved = flops[dominant] / (stage_ms[dominant] * 1e-3) / 1e12
-        # bf16 tensors of these shapes run on the large-tile kernel, fp32 tensors on the general one
-        kname = {"project_left": "proj_dl_kernel/project", "project_right": "gemm_dl_kernel/project_right", "back": "gemm_dl_kernel/back"}
-        roofline = {"kernel": kname[dominant] if dtype == "bf16" else "gemm_group_kernel/" + dominant, "bound": "mfma",
+        # the 7B stack runs on the large-tile kernels throughout; which kernel a launch of the others takes depends on its tiles
+        kname = {"project_left": "proj_dl_kernel/project", "project_right": "gemm_group_kernel/project_right", "back": "gemm_dl_kernel/back"}
+        roofline = {"kernel": kname[dominant] if args.config == "llama7b" else dominant, "bound": "mfma",
                     "achieved": achieved, "peak": peak,
                     "unit": "TFLOP/s", "frac": achieved / peak, "traffic": None}
     roofline["launch_ms"] = stage_ms[dominant]
@@ -330,7 +331,9 @@ def main():
         if prof[k][1]:
             per_stage[k] = {"ms_per_launch": stage_ms[k], "tflops": flops[k] / (stage_ms[k] * 1e-3) / 1e12}
     if prof["adam"][1]:
-        per_stage["adam"] = {"ms_per_launch": stage_ms["adam"], "gbs": adam_bytes / (stage_ms["adam"] * 1e-3) / 1e9}
+        # the rate only where every tensor's Adam ran in these launches: small-tile projections of the other stacks take it into their epilogue
+        whole = args.config == "llama7b" or args.moments == "q8"
+        per_stage["adam"] = {"ms_per_launch": stage_ms["adam"], "gbs": adam_bytes / (stage_ms["adam"] * 1e-3) / 1e9 if whole else None}
 
     # ---- CPU baseline: the fp64 oracle on a bounded sample --------------------------------------------
     cpu = None
@@ -403,7 +406,8 @@ def main():
                                                                                    "per-layer" if LPC == 1 else "%d-layer" % LPC, POOL),
                    "tensors": L * n_per_layer, "rank": r, "update_gap": cfg["update_gap"], "refresh_iters": args.refresh_iters,
                    "adam": ("in the projection GEMM's epilogue" if (args.fused_adam and args.moments == "f32" and dtype == "bf16")
-                            else "separate kernel"),  # the fused epilogue exists for fp32 moments on the large-tile kernel only
+                            else "separate kernel" if args.config == "llama7b" or args.moments == "q8"
+                            else "separate kernel, or in the epilogue of a projection on small tiles"),
                    "schedule": ("consecutive calls overlap on %d library streams (%d on a step with a refresh), one join per step" % (overlap, overlap_refresh)) if overlap else
                                "%d concurrent chains inside each call, joined every call" % args.lanes},
         "roofline": roofline,

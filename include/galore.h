@@ -182,7 +182,7 @@ galore_status galore_step_static(galore_ctx* ctx, const galore_tensor* W, const 
 /* Recompute the projectors of tensors first..first+count-1 from the gradients G
  * (Algorithm 2, refresh branch; Sec. 3.3 SVD equation): the leading r left (LEFT) or right
  * (RIGHT) singular vectors of G, obtained from the Gram matrix of the short side by
- * blocked subspace iteration with Householder QR and a final Rayleigh-Ritz rotation, so
+ * blocked subspace iteration with Householder QR (up to rank 256 Cholesky QR) and a final Rayleigh-Ritz rotation, so
  * columns are ordered by decreasing singular value; each column's sign makes its
  * largest-magnitude entry positive.  Writes state.proj and its transposed copy state.proj_t; M, V, W
  * and t are untouched.
@@ -387,10 +387,10 @@ galore_status galore_adafactor(const galore_tensor* R, const galore_tensor* M, c
  * device time in milliseconds and the number of bracketed launches (arrays of
  * GALORE_STAGE_COUNT entries, host memory).  A refresh counts as one launch per tensor group. */
 typedef enum {
-  GALORE_STAGE_PROJECT_LEFT = 0,   /* the grouped projection launch: R = P^T G, and R = G Q of the tensors that share it
-                                      (bf16 tensors on the large-tile kernel: both orientations in one launch) */
-  GALORE_STAGE_PROJECT_RIGHT = 1,  /* R = G Q of tensors on the general kernel (fp32, odd shapes) */
-  GALORE_STAGE_ADAM = 2,           /* fused low-rank Adam (one launch per orientation) */
+  GALORE_STAGE_PROJECT_LEFT = 0,   /* the grouped projection launches, both orientations: R = P^T G, R = G Q, and Adam of the tensors
+                                      that run it in the epilogue */
+  GALORE_STAGE_PROJECT_RIGHT = 1,  /* R = G Q of tensors on the general kernel (a side of fewer than 8 elements) */
+  GALORE_STAGE_ADAM = 2,           /* low-rank Adam of the other tensors */
   GALORE_STAGE_BACK = 3,           /* W -= lr*alpha*(P N | N Q^T)  (GEMM + weight epilogue) */
   GALORE_STAGE_TRANSPOSE = 4,      /* proj -> proj_t */
   GALORE_STAGE_REFRESH = 5,        /* whole subspace refresh of a tensor group */

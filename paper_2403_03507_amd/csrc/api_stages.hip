@@ -50,7 +50,9 @@ galore_status galore_project(const galore_tensor* proj_t, const galore_tensor* G
     p.M = (int)G->rows; p.N = (int)r; p.K = (int)G->cols;
   }
   p.C = R->data; p.ldc = (int)R->ld;
-  // the kernel galore_step uses for this tensor on its own
+  // The kernels of galore_step, without what needs a workspace: no padded copy of G, and whole contractions.  R has the bits of the
+  // step's wherever that cuts nothing into K pieces, and agrees to fp32 rounding otherwise.  (galore_step also keeps ranks that
+  // fill less than 7/10 of their 256-row tiles off the large-tile kernel; the bits are the same.)
   ProjGroup pg{};
   ProjProblem& q = pg.p[0];
   q.A = p.A; q.B = p.B; q.R = static_cast<float*>(p.C);

@@ -41,8 +41,10 @@ template <class T, int BM, int BN> hipError_t launch(GemmGroup& g, Epilogue epi,
 
 // A larger tile loads fewer bytes per flop through the L2 -> CU path, a smaller one gives more workgroups to hide latency
 // with: the largest that still makes a workgroup and a half per CU (128 x 128) or two (128 x 64).  Whole steps, us, with
-// the projection on 64 x 64 / 128 x 64 / 128 x 128 tiles: one 350M layer (1028 / 514 / 257 tiles) 54.0 / 49.0 / 57.2, one
-// 1B layer (3088 / 1544 / 772) 266 / 244 / 230, one 4096 x 4096 weight at r = 152 (180 / 120 / 60, two K pieces) 65 / 68 / 83.
+// the projection on 64 x 64 / 128 x 64 / 128 x 128 tiles: one 350M layer (772 / 388 / 196 tiles) 54.0 / 49.0 / 57.2, one
+// 1B layer (3088 / 1544 / 772) 266 / 244 / 230, one 3805 x 3805 weight at r = 152 (180 / 120 / 60, two K pieces) 65 / 68 / 83.
+// These are passes repeated on the same tensors; with the caches flushed before each pass, three 350M layers 183 / 190 / 189 (hence
+// 64 x 64 tiles there), two 130M layers 99 / 101 / 108, two 1B layers 502 / 448 / 420.
 // The weight update has more tiles than that and shorter contractions: 128 x 64 unless the contraction is long (r = 54 on
 // a 1105 / 2688 layer: 104 / 100 / 103; r = 401 on 1904 / 3968: 232 / 208 / 194).
 template <class T> hipError_t launch_typed(GemmGroup& g, Epilogue epi, hipStream_t stream) {
@@ -99,7 +101,8 @@ int tile_pieces(long tiles, int64_t K, DType dt) {
 hipError_t launch_weight_update(GemmGroup& g, DType dt, hipStream_t stream) {
   // The persistent 256 x 256 kernel where its tiles come near filling the CUs (W prefetched across tiles): one 350M
   // layer (196 tiles) 54.3 against 55.5 us per step on the small tiles, a 7B layer at r = 128 305 against 346, at
-  // r = 1024 995 against 1290; one 2048 x 2048 weight (64 tiles) 58.2 against 53.5.
+  // r = 1024 995 against 1290; one 2048 x 2048 weight (64 tiles) 58.2 against 53.5.  With the caches flushed before each pass, three
+  // 350M layers 187 against 204, two 1B layers 421 against 448.
   long tiles256 = 0;
   for (int i = 0; i < g.count; ++i) tiles256 += tiles_of(g.p[i], 256, 256);
   GemmGroup large{}, tiles{}, rest{};

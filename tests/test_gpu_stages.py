@@ -239,3 +239,20 @@ def test_more_tiles_than_compute_units_ragged_bf16(shape, r):
     cancel = r * 2.0 ** -24 * (np.abs(to64(W)) + np.abs(W_ref - to64(W)))
     assert np.all(np.abs(to64(Wd) - W_r) <= ulp + cancel)
     assert np.mean(to64(Wd) == W_r) >= 0.98
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("transpose", [False, True])
+def test_adam_on_both_sides_of_the_choice_of_kernel(transpose, dtype):
+    # 256 x 4096 entries, the least that takes the lean kernels, and its two halves, which take the tile kernel: the same bits
+    g = torch.Generator(device="cuda").manual_seed(5)
+    R, M, V = (torch.randn(256, 4096, generator=g, device="cuda") for _ in range(3))
+    V = V.square()
+    new = lambda rows: torch.empty((4096, rows) if transpose else (rows, 4096), dtype=dtype, device="cuda")
+    halves = [(R[a:a + 128].clone(), M[a:a + 128].clone(), V[a:a + 128].clone(), new(128)) for a in (0, 128)]
+    N = new(256)
+    for r, m, v, n in [(R, M, V, N)] + halves:
+        gb.galore_adam(r, m, v, n, transpose, 0.9, 0.999, 1e-8, 3)
+    torch.cuda.synchronize()
+    assert torch.equal(M, torch.cat([h[1] for h in halves])) and torch.equal(V, torch.cat([h[2] for h in halves]))
+    assert torch.equal(N, torch.cat([h[3] for h in halves], dim=1 if transpose else 0))
