@@ -65,6 +65,8 @@ hipError_t launch_tile_group(GemmGroup& g, DType dt, Epilogue epi, hipStream_t s
 constexpr int kMaxTilePieces = 4;
 constexpr long kSplitBelowTiles = 224;  // a launch of as many 64 x 64 tiles keeps its contractions whole
 int tile_pieces(long tiles, int64_t K, DType dt);
+constexpr long kDirectItems = 150;  // 128 x 128 tiles (times K pieces) from which a product may take the direct-load kernel (gemm_tile.hip)
+int direct_pieces(const GemmProblem& p, DType dt, bool b_kcontig, int most);
 // A projection launch with at least this many 256 x 256 tiles takes the 256 x 256 kernel (a 7B layer at r = 256, 193 tiles:
 // 354 against 390 us per step on the small tiles; one 4096 x 11008 weight at r = 1024, 172 tiles: 256 against 283; one
 // 4096 x 4096 weight, 64 tiles: 149 against 102).

@@ -39,6 +39,67 @@ template <class T, int BM, int BN> hipError_t launch(GemmGroup& g, Epilogue epi,
   return hipGetLastError();
 }
 
+// Aligned bf16 operands over whole K steps: the problem may run on DirectTile.
+bool fits_direct(const GemmProblem& p, DType dt) {
+  const bool kc = p.b_kcontig != 0;
+  const uintptr_t at = reinterpret_cast<uintptr_t>(p.A) | reinterpret_cast<uintptr_t>(p.B);
+  return dt == DType::BF16 && at % 16 == 0 && p.lda % 8 == 0 && p.ldb % 8 == 0 && p.K % DirectTile::BK == 0 && (kc || p.N % 8 == 0) &&
+         (int64_t)p.M * p.lda < (1ll << 30) && (kc ? (int64_t)p.N : (int64_t)DirectTile::BK) * p.ldb < (1ll << 30);
+}
+
+template <Epilogue EPI> hipError_t direct_instance(const GemmGroup& g, hipStream_t stream) {
+  auto kern = gemm_tile_kernel<__bf16, 128, 128, EPI, true, true>;
+  static bool attr_set = false;
+  if (!attr_set) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, DirectTile::LDS);
+    if (e != hipSuccess) return e;
+    attr_set = true;
+  }
+  hipLaunchKernelGGL(kern, dim3((unsigned)g.total_tiles), dim3(512), DirectTile::LDS, stream, g);
+  return hipGetLastError();
+}
+
+hipError_t launch_direct(GemmGroup& g, Epilogue epi, hipStream_t stream) {
+  long total = 0;
+  for (int i = 0; i < g.count; ++i) {
+    GemmProblem& p = g.p[i];
+    p.tile_begin = (int32_t)total;
+    p.tiles_m = (p.M + 127) / 128;
+    p.tiles_n = (p.N + 127) / 128;
+    total += tiles_of(p, 128, 128);
+  }
+  if (total > INT32_MAX) return hipErrorInvalidValue;
+  g.total_tiles = (int32_t)total;
+  switch (epi) {
+    case Epilogue::StoreF32: return direct_instance<Epilogue::StoreF32>(g, stream);
+    case Epilogue::ApplyW: return direct_instance<Epilogue::ApplyW>(g, stream);
+    case Epilogue::Adam: return direct_instance<Epilogue::Adam>(g, stream);
+    case Epilogue::StoreBF16: return direct_instance<Epilogue::StoreBF16>(g, stream);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+// One round of DirectTile, a tile per CU, most CUs with a tile: the deeper ring draws 46 GB/s per CU where the register-staged tiles, several a
+// CU, reach 33.  Whole steps, us, on the other tiles / DirectTile: projection of one 350M layer at r = 256 (196 tiles) 51.8 / 48.9, r = 192 (three
+// quarters of the rows used) 44.4 / 46.3, a 4096 x 4096 weight at r = 768 (192) 94.1 / 84.8, 1024 (256) 108.7 / 98.2, 512 (128) 68.1 / 73.5, a 2048
+// / 5504 layer at r = 128 (193) 99.8 / 91.3, r = 96 93.3 / 84.7, a 768 / 2048 layer at r = 256 (144, K = 768) 36.4 / 39.2; in more than one round, 288 tiles
+// 80.1 / 87.2, 258 139.8 / 147.2, 386 140.6 / 130.1 but flushed 162.6 / 161.1, 726 246.6 / 228.6 but flushed 275.9 / 275.7.  Weight update: 2048 x 2048 (256 tiles) at
+// r = 128 22.3 / 21.6 (flushed 28.6 / 29.1), 256 26.5 / 24.9, 512 31.8 / 29.6, 1024 x 2752 (176) at r = 512 28.1 / 26.3; 2560 x 2560 (400) at r = 512 45.8 / 46.4.
+bool direct_pays(const GemmGroup& g, long items128, bool update) {
+  if (items128 > 256 || items128 < (update ? 160 : kDirectItems)) return false;
+  double used = 0;
+  int shortest = INT32_MAX;
+  for (int i = 0; i < g.count; ++i) {
+    const GemmProblem& p = g.p[i];
+    const int S = p.splits > 1 ? p.splits : 1;
+    if (!fits_direct(p, DType::BF16) || (S > 1 && p.K % (128 * S) != 0)) return false;  // pieces end where the other tiles' end
+    used += (double)p.M * p.N * S;
+    shortest = p.K / S < shortest ? p.K / S : shortest;
+  }
+  if (update) return shortest >= 256;
+  return shortest >= 2048 || (shortest >= 1024 && used >= 0.8 * items128 * 128 * 128);
+}
+
 // A larger tile loads fewer bytes per flop through the L2 -> CU path, a smaller one gives more workgroups to hide latency
 // with: the largest that still makes a workgroup and a half per CU (128 x 128) or two (128 x 64).  Whole steps, us, with
 // the projection on 64 x 64 / 128 x 64 / 128 x 128 tiles: one 350M layer (772 / 388 / 196 tiles) 54.0 / 49.0 / 57.2, one
@@ -57,6 +118,7 @@ template <class T> hipError_t launch_typed(GemmGroup& g, Epilogue epi, hipStream
   }
   if (items128 == 0) return hipSuccess;
   const bool update = epi == Epilogue::ApplyW;
+  if (std::is_same<T, __bf16>::value && direct_pays(g, items128, update)) return launch_direct(g, epi, stream);
   if (items128 >= 350 && (!update || longest >= 256)) return launch<T, 128, 128>(g, epi, stream);
   if (items96 >= (update ? 300 : 500)) return launch<T, 128, 64>(g, epi, stream);
   return launch<T, 64, 64>(g, epi, stream);
@@ -84,6 +146,22 @@ hipError_t launch_tile_group(GemmGroup& g, DType dt, Epilogue epi, hipStream_t s
     if (epi == Epilogue::Adam && (!p.Mo || !p.Vo || !p.Nout)) return hipErrorInvalidValue;
   }
   return dt == DType::BF16 ? launch_typed<__bf16>(g, epi, stream) : launch_typed<float>(g, epi, stream);
+}
+
+// Pieces of the contraction of a single product (not tied to others by the promises of galore_set_concurrency) that fill a round of DirectTile;
+// 1 where none do.  `most`: matrices of its size that the caller has room for.
+int direct_pieces(const GemmProblem& p, DType dt, bool b_kcontig, int most) {
+  GemmProblem q = p;
+  q.b_kcontig = b_kcontig;
+  if (!fits_direct(q, dt) || !tile_problem_fits(q, dt, b_kcontig)) return 1;
+  for (int pieces = most < kMaxTilePieces ? most : kMaxTilePieces; pieces > 1; --pieces) {
+    GemmGroup g{};
+    g.count = 1;
+    g.p[0] = q;
+    g.p[0].splits = pieces;
+    if (direct_pays(g, tiles_of(g.p[0], 128, 128), false)) return pieces;
+  }
+  return 1;
 }
 
 // Pieces of the contraction for a launch of `tiles` 64 x 64 tiles: enough for two workgroups per CU where the tiles alone

@@ -20,7 +20,7 @@
 #include <type_traits>
 
 #include "adam_entry.hpp"
-#include "gemm_mfma.hpp"
+#include "gemm_mfma_dl.hpp"
 
 namespace galore {
 
@@ -123,16 +123,31 @@ template <class T, int BM_, int BN_> struct SmallTile {
   }
 };
 
-// AKC: A as [M][K]; else (StoreF32 only) as [K][M]
-template <class T, int BM, int BN_, Epilogue EPI, bool AKC = true>
-__global__ __launch_bounds__(256, 2) void gemm_tile_kernel(const GemmGroup grp) {
+// The 128 x 128 tile of aligned bf16 operands with direct global -> LDS loads: 8 wavefronts, K steps of 64, a ring of 4, so that three
+// steps (96 KB) are on their way to a CU that has one workgroup.  Bound by what a CU draws from L2 (46 GB/s, 2 MB a tile at K = 4096):
+// 1024 x 4096 x 4096 44.8 us against 66.6 on 512 register-staged tiles of 128 x 64, 4096 x 1024 x 1024 15.6 against 21.2; the projection of one 350M
+// layer with Adam in the epilogue 25.6 against 30.0.
+struct DirectTile {
+  static constexpr int BK = 64, STAGES = 4, NW = 8;
+  static constexpr int STAGE_BYTES = 2 * 128 * BK * 2;
+  static constexpr int LDS = STAGES * STAGE_BYTES;
+  static constexpr int LOADS = STAGE_BYTES / 1024 / NW;  // per wavefront and step
+};
+
+// AKC: A as [M][K]; else (StoreF32 only) as [K][M].  DIRECT: see DirectTile; K is a multiple of 64.
+template <class T, int BM, int BN_, Epilogue EPI, bool AKC = true, bool DIRECT = false>
+__global__ __launch_bounds__(DIRECT ? 512 : 256, 2) void gemm_tile_kernel(const GemmGroup grp) {
   using Cfg = SmallTile<T, BM, BN_>;
   using ET = ElemTraits<T>;
-  constexpr int BN = Cfg::BN, BK = Cfg::BK, SP = Cfg::SP, ROWS = Cfg::ROWS;
-  constexpr int WM = BM / 2, WN = BN / 2, TM = WM / 32, TN = WN / 32;
+  constexpr int NT = DIRECT ? 512 : 256;
+  constexpr int BN = Cfg::BN, BK = DIRECT ? DirectTile::BK : Cfg::BK, SP = Cfg::SP, ROWS = Cfg::ROWS;
+  constexpr int WM = BM / 2, WN = BN / (DIRECT ? 4 : 2), TM = WM / 32, TN = WN / 32;
   using AOp = typename Cfg::A;
   using BOp = typename Cfg::B;
-  __shared__ __align__(16) unsigned char smem[Cfg::lds_bytes(EPI == Epilogue::Adam)];
+  static_assert(!DIRECT || (BM == 128 && BN == 128 && AKC && sizeof(T) == 2 && Cfg::STAGE_BYTES + Cfg::NT_BYTES <= DirectTile::LDS), "");
+  __shared__ __align__(16) unsigned char smem_static[DIRECT ? 16 : Cfg::lds_bytes(EPI == Epilogue::Adam)];
+  extern __shared__ __align__(1024) unsigned char smem_direct[];
+  unsigned char* smem = DIRECT ? smem_direct : smem_static;
   T* As = reinterpret_cast<T*>(smem);
   T* Bs = As + AOp::LDS_ELEMS;
 
@@ -167,9 +182,92 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(const GemmGroup grp) 
 
   // W pieces of the weight update: piece q of pass ps is row ps * ROWS + q * RPP + tid / CPW, columns WVEC (tid % CPW) ..
   constexpr int WVEC = ET::VEC;
-  constexpr int CPW = BN / WVEC, RPP = 256 / CPW, NQ = ROWS / RPP, NPASS = BM / ROWS;
+  constexpr int CPW = BN / WVEC, RPP = NT / CPW, NQ = ROWS / RPP, NPASS = BM / ROWS;
   u32x4 wold[EPI == Epilogue::ApplyW ? NPASS * NQ : 1];
   const int wcol = n0 + (tid % CPW) * WVEC;
+
+  auto fetch_w = [&]() {
+    if constexpr (EPI == Epilogue::ApplyW) {
+      const T* W = static_cast<const T*>(pr.C);
+      const int wc = wcol < N - WVEC ? wcol : N - WVEC;
+#pragma unroll
+      for (int q = 0; q < NPASS * NQ; ++q) {
+        const int row = m0 + q * RPP + tid / CPW;
+        __builtin_memcpy(&wold[q], W + (size_t)(row < M ? row : M - 1) * pr.ldc + wc, sizeof(u32x4));
+      }
+    }
+  };
+
+  // fp32 pieces of the epilogue: columns 4 (tid % CPC) ..
+  constexpr int CPC = BN / 4, RPC = NT / CPC, NC = ROWS / RPC;
+  const int pc = (tid % CPC) * 4, col = n0 + pc;
+  // The moments are requested before anything waits for them (N >= 4: see tile_problem_fits): of a pass at its start, or with the last
+  // products where there is one step more to hide them behind (DIRECT).
+  constexpr int HELD = EPI != Epilogue::Adam ? 1 : DIRECT ? NPASS * NC : NC;
+  f32x4 mo[HELD], vo[HELD];
+  auto fetch_moments = [&](int ps) {
+    if constexpr (EPI == Epilogue::Adam) {
+      const int cc = col + 4 <= N ? col : 0;
+#pragma unroll
+      for (int q = 0; q < NC; ++q) {
+        const int row = m0 + ps * ROWS + q * RPC + tid / CPC, at = DIRECT ? ps * NC + q : q;
+        const size_t e = (size_t)(row < M ? row : M - 1) * N + cc;
+        __builtin_memcpy(&mo[at], pr.Mo + e, 16);
+        __builtin_memcpy(&vo[at], pr.Vo + e, 16);
+      }
+    }
+  };
+
+  auto run_direct = [&](auto kc) {
+    constexpr bool BKC = decltype(kc)::value;
+    constexpr int S = DirectTile::STAGES, LOADS = DirectTile::LOADS;
+    using DA = DlOperand<true, 128, DirectTile::BK, DirectTile::NW>;
+    using DB = DlOperand<BKC, 128, DirectTile::BK, DirectTile::NW>;
+    DA da;
+    DB db;
+    da.plan(pr.lda, m0, M, wave, lane);
+    db.plan(pr.ldb, n0, N, wave, lane);
+    const unsigned lds0 = (unsigned)(uintptr_t)smem_direct;
+    const unsigned char* asrc = static_cast<const unsigned char*>(pr.A);
+    const unsigned char* bsrc = static_cast<const unsigned char*>(pr.B);
+    const size_t bstep = BKC ? (size_t)DirectTile::BK * 2 : (size_t)DirectTile::BK * pr.ldb * 2;
+    auto issue = [&](int kt) {
+      const unsigned st = lds0 + ((kt - first) & (S - 1)) * DirectTile::STAGE_BYTES;
+      da.template issue<false>(asrc + (size_t)kt * DirectTile::BK * 2, st, wave);
+      db.template issue<false>(bsrc + kt * bstep, st + DA::TILE_BYTES, wave);
+    };
+    for (int kt = first; kt < last && kt < first + S - 1; ++kt) issue(kt);
+    fetch_w();
+    for (int kt = first; kt < last; ++kt) {
+      // this wavefront's pieces of step kt have landed; its LDS reads of the step before have returned
+      if (kt + 2 < last) wait_vmcnt<2 * LOADS>();
+      else if (kt + 1 < last) wait_vmcnt<LOADS>();
+      else wait_vmcnt<0>();
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      if (kt + S - 1 < last) issue(kt + S - 1);
+      if (kt + 1 == last) {  // earlier, the waits for the tiles would wait for these as well (one 350M layer 52.8 us a step instead of 51.5)
+#pragma unroll
+        for (int ps = 0; ps < NPASS; ++ps) fetch_moments(ps);
+      }
+      const unsigned char* as = smem_direct + ((kt - first) & (S - 1)) * DirectTile::STAGE_BYTES;
+      const unsigned char* bs = as + DA::TILE_BYTES;
+      bf16x8 fa[4][TM], fb[4][TN];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) fa[s][i] = DA::frag(as, wm0 + 32 * i, 16 * s, lane);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) fb[s][j] = DB::frag(bs, wn0 + 32 * j, 16 * s, lane);
+      }
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[s][i], fb[s][j], acc[i][j], 0, 0, 0);
+    }
+    __syncthreads();  // the epilogue takes the ring's place
+  };
 
   auto run = [&](auto kc) {
     constexpr bool BKC = decltype(kc)::value;
@@ -204,21 +302,16 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(const GemmGroup grp) 
     };
     load(ra0, rb0, first);
     if (first + 1 < last) load(ra1, rb1, first + 1);
-    if constexpr (EPI == Epilogue::ApplyW) {
-      const T* W = static_cast<const T*>(pr.C);
-      const int wc = wcol < N - WVEC ? wcol : N - WVEC;
-#pragma unroll
-      for (int q = 0; q < NPASS * NQ; ++q) {
-        const int row = m0 + q * RPP + tid / CPW;
-        __builtin_memcpy(&wold[q], W + (size_t)(row < M ? row : M - 1) * pr.ldc + wc, sizeof(u32x4));
-      }
-    }
+    fetch_w();
     for (int kt = first; kt < last; kt += 2) {
       step(ra0, rb0, kt);
       if (kt + 1 < last) step(ra1, rb1, kt + 1);
     }
   };
-  if constexpr (EPI == Epilogue::ApplyW) {
+  if constexpr (DIRECT) {
+    if (EPI == Epilogue::ApplyW || pr.b_kcontig) run_direct(std::true_type{});
+    else if constexpr (EPI != Epilogue::ApplyW) run_direct(std::false_type{});
+  } else if constexpr (EPI == Epilogue::ApplyW) {
     run(std::true_type{});
   } else if constexpr (!AKC) {
     run(std::false_type{});
@@ -231,22 +324,10 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(const GemmGroup grp) 
   // register v of lane l is element (row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32) of a 32 x 32 block.
   float* st = reinterpret_cast<float*>(smem);
   const int ldc = pr.ldc;
-  constexpr int CPC = BN / 4, RPC = 256 / CPC, NC = ROWS / RPC;  // fp32 pieces: columns 4 (tid % CPC) ..
-  const int pc = (tid % CPC) * 4, col = n0 + pc;
 #pragma unroll
   for (int ps = 0; ps < NPASS; ++ps) {
     if (ps) __syncthreads();
-    f32x4 mo[EPI == Epilogue::Adam ? NC : 1], vo[EPI == Epilogue::Adam ? NC : 1];
-    if constexpr (EPI == Epilogue::Adam) {  // the moments of the pass, requested before anything waits (N >= 4: see tile_problem_fits)
-      const int cc = col + 4 <= N ? col : 0;
-#pragma unroll
-      for (int q = 0; q < NC; ++q) {
-        const int row = m0 + ps * ROWS + q * RPC + tid / CPC;
-        const size_t at = (size_t)(row < M ? row : M - 1) * N + cc;
-        __builtin_memcpy(&mo[q], pr.Mo + at, 16);
-        __builtin_memcpy(&vo[q], pr.Vo + at, 16);
-      }
-    }
+    if constexpr (!DIRECT) fetch_moments(ps);
     if (wm0 / ROWS == ps) {
       const int wr = wm0 % ROWS;
 #pragma unroll
@@ -306,6 +387,8 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(const GemmGroup grp) 
       for (int q = 0; q < NC; ++q) {
         const int lr = q * RPC + tid / CPC, row = m0 + ps * ROWS + lr;
         if (row >= M || col >= N) continue;
+        constexpr bool held = DIRECT;
+        const int mq = held ? ps * NC + q : q;
         const f32x4 g = *reinterpret_cast<const f32x4*>(st + lr * SP + pc);
         float* Mp = pr.Mo + (size_t)row * N + col;
         float* Vp = pr.Vo + (size_t)row * N + col;
@@ -313,12 +396,12 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(const GemmGroup grp) 
         if (col + 4 <= N) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            float me = mo[q][e], ve = vo[q][e];
+            float me = mo[mq][e], ve = vo[mq][e];
             n[e] = (T)adam_entry(g[e], me, ve, grp.beta1, grp.beta2, grp.eps, pr.inv_c1, pr.inv_c2);
-            mo[q][e] = me; vo[q][e] = ve;
+            mo[mq][e] = me; vo[mq][e] = ve;
           }
-          __builtin_memcpy(Mp, &mo[q], 16);
-          __builtin_memcpy(Vp, &vo[q], 16);
+          __builtin_memcpy(Mp, &mo[mq], 16);
+          __builtin_memcpy(Vp, &vo[mq], 16);
         } else {
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
@@ -343,7 +426,7 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(const GemmGroup grp) 
       }
       if (tr) {  // N^T rows: 16-byte pieces along the tile's rows
         __syncthreads();
-        constexpr int LPR = ROWS / WVEC, CPP = 256 / LPR;
+        constexpr int LPR = ROWS / WVEC, CPP = NT / LPR;
 #pragma unroll
         for (int q = 0; q < BN / CPP; ++q) {
           const int jc = q * CPP + tid / LPR, i = (tid % LPR) * WVEC, row = m0 + ps * ROWS + i;
