@@ -19,6 +19,8 @@
 // No atomics and fixed summation orders: results are reproducible bit for bit.
 #include "refresh_common.hpp"
 
+#include <utility>
+
 namespace galore {
 namespace rf {
 namespace {
@@ -105,6 +107,9 @@ __device__ __forceinline__ double lane_value(double x, int lane) {
   return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
 }
 
+// f(0), f(1), .. with the index as a type: a loop that is unrolled whatever its length
+template <class F, int... I> __device__ __forceinline__ void each_index(F f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+
 // 16 x 16 entries at (i0, j0) of a b^T (BT) or a b, both 32 x 32 in LDS; added to acc
 template <bool BT> __device__ __forceinline__ void block_product(d4& acc, const double* a, const double* b, int i0, int j0, int lane) {
   const int i = lane & 15, g = lane >> 4;
@@ -127,11 +132,13 @@ constexpr double kRitzShift = 2.4e-7;    // 2^-22
 //   ritz == 1: Bw (fp32, r x r) <- L^T of the matrix shifted by kRitzShift of its largest diagonal entry.  The shift leaves
 //              the eigenvectors alone and keeps every pivot above the fp32 rounding that the matrix carries anyway; so
 //              does the power of two that brings the entries near one, whatever the scale of the gradient.
-// Bound by latency: about 5 us of block products and 8 us of the serial factorisation per launch.
+// Bound by latency: about 5 us of launch and block products and 6.5 us of the serial factorisation per launch (7 tensors: 11.8 us; 13.2 with all moves through
+// scalar registers and each column's products in the chain of its pivot).
 __global__ __launch_bounds__(256) void chol_step_kernel(const RefreshGroup* __restrict__ gp, int s, int ritz, double dependent) {
   const RefreshGroup& grp = *gp;
   __shared__ double D[kCB * kLP], P[kCB * kLP], Q[kCB * kLP];
   __shared__ double wave_max[4];
+  __shared__ __align__(16) double column[2][64];
   const RefreshTensor& t = grp.t[blockIdx.y];
   const int r = grp.r, nb = (r + kCB - 1) / kCB, rp = nb * kCB;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -262,21 +269,64 @@ __global__ __launch_bounds__(256) void chol_step_kernel(const RefreshGroup* __re
 #pragma unroll
   for (int c = 0; c < kCB; ++c) a[c] = mine ? Q[row * kLP + c] + (row == c ? shift : 0.) : (row == c ? 1. : 0.);
   unsigned bad = 0;
-#pragma unroll
-  for (int c = 0; c < kCB; ++c) {
-    double piv = lane_value(a[c], c);
+  // Column by column: scaled by 1 / sqrt(pivot), then taken out of the columns to its right.  Of the next two that happens at once, with two of
+  // its entries moved from lane to scalar registers; of the others while the column after it is worked on, with its entries as
+  // broadcast reads from LDS that have had that long to arrive.  What bounds a column is the chain from one pivot to the next, some twenty
+  // dependent instructions with the Newton steps of the reciprocal root; the other work is dealt out between them, a part after each.
+  double piv, y, w[2][kCB];
+  bool out;
+  auto pivot = [&](int c) {
+    piv = lane_value(a[c], c);
     const double least = lane_value(low, c);
-    const bool out = !ritz && piv <= least;  // false for NaN, which is passed on
+    out = !ritz && piv <= least;  // false for NaN, which is passed on
     if (ritz && piv < least) piv = least;
-    double y = __builtin_amdgcn_rsq(piv);
-    y = y * (1.5 - 0.5 * piv * y * y);
-    y = y * (1.5 - 0.5 * piv * y * y);
+  };
+  pivot(0);
+  y = __builtin_amdgcn_rsq(piv);
+  y = y * (1.5 - 0.5 * piv * y * y);
+  y = y * (1.5 - 0.5 * piv * y * y);
+  each_index([&](auto index) {
+    constexpr int c = decltype(index)::value;
     if (out) { y = 0.; bad |= 1u << c; }
     a[c] = mine && row == c ? piv * y : a[c] * y;
     if (out) a[c] = 0.;
+    if constexpr (c + 1 < kCB) {
+      column[c & 1][lane] = a[c];   // lanes 32 .. 63: not read
 #pragma unroll
-    for (int e = c + 1; e < kCB; ++e) a[e] -= a[c] * lane_value(a[c], e);
-  }
+      for (int e = c + 3; e < kCB; ++e) w[c & 1][e] = column[c & 1][e];
+      __builtin_amdgcn_sched_barrier(0);
+      a[c + 1] = __builtin_fma(-a[c], lane_value(a[c], c + 1), a[c + 1]);
+      // column c - 1 out of columns c + 2 .. in 7 parts; column c out of column c + 2 after the first
+      constexpr int left = kCB - c - 2;
+      auto part = [&](auto i_t) {
+        constexpr int i = decltype(i_t)::value, first = c + 2 + (left * i + 6) / 7, last = c + 2 + (left * (i + 1) + 6) / 7;
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (c > 0) {
+#pragma unroll
+          for (int e = first; e < last; ++e) a[e] = __builtin_fma(-a[c - 1], w[(c - 1) & 1][e], a[e]);
+        }
+        if constexpr (i == 0 && c + 2 < kCB) a[c + 2] = __builtin_fma(-a[c], lane_value(a[c], c + 2), a[c + 2]);
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      using std::integral_constant;
+      pivot(c + 1);
+      y = __builtin_amdgcn_rsq(piv);
+      const double half = 0.5 * piv;
+      part(integral_constant<int, 0>{});
+      part(integral_constant<int, 1>{});
+      double u = half * y;
+      part(integral_constant<int, 2>{});
+      u = __builtin_fma(-y, u, 1.5);
+      part(integral_constant<int, 3>{});
+      y = y * u;
+      part(integral_constant<int, 4>{});
+      u = half * y;
+      part(integral_constant<int, 5>{});
+      u = __builtin_fma(-y, u, 1.5);
+      part(integral_constant<int, 6>{});
+      y = y * u;
+    }
+  }, std::make_integer_sequence<int, kCB>{});
   double* dnext = t.dinv + (size_t)((s + 1) & 1) * kCB * kCB;
 #pragma unroll
   for (int c = 0; c < kCB; ++c) {
