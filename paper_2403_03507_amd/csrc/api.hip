@@ -193,7 +193,7 @@ size_t step_r_bytes(bool left, int64_t kdim, int64_t ldim, int64_t r, DType dt, 
   return align_up((size_t)pieces * r * projected_row_length(left, kdim, ldim, dt) * 4);
 }
 // The most K pieces that any launch group gives the tensor
-int most_pieces(int64_t kdim, int64_t ldim, int64_t r, DType dt) { return tile_pieces((long)tiles64(ldim, r), kdim, dt); }
+int most_pieces(int64_t kdim, int64_t ldim, int64_t r, DType dt) { return tile_pieces((long)tiles64(ldim, r), kdim, dt, r * ldim); }
 size_t step_n_bytes(int64_t ldim, int64_t r, DType dt) { return align_up((size_t)r * ldim * dtype_size(dt)); }
 size_t step_gpad_bytes(bool left, int64_t kdim, int64_t ldim, DType dt) {
   const int64_t ldp = projected_row_length(left, kdim, ldim, dt);
@@ -247,6 +247,7 @@ struct StepItem {
   void* Gpad;    // room for a copy of G with padded rows (see projected_row_length), or nullptr
   int64_t ldr;   // row length of R, set by the projection
   bool large;    // the launches of the other chains count towards the large-tile kernel as well (count_over_chains)
+  int planned;   // K pieces of the projection (pieces_of_call)
   int pieces;    // slabs of R: as planned (pieces_of_call), as many as there is room for, then as many as the projection makes
 };
 
@@ -263,7 +264,7 @@ std::vector<int> pieces_of_call(const galore_ctx* ctx, int32_t first, int32_t co
     for (int i = a; i < b; ++i) tiles[ctx->tensors[first + i].dt == DType::BF16] += (long)tiles64(ctx->tensors[first + i].ldim, r);
     for (int i = a; i < b; ++i) {
       const TensorInfo& ti = ctx->tensors[first + i];
-      pieces[i] = tile_pieces(tiles[ti.dt == DType::BF16], ti.kdim, ti.dt);
+      pieces[i] = tile_pieces(tiles[ti.dt == DType::BF16], ti.kdim, ti.dt, r * ti.ldim);
     }
   }
   return pieces;
@@ -352,6 +353,8 @@ galore_status run_chain(galore_ctx* ctx, std::vector<StepItem>& items, float lr,
       pgf.beta1 = hp.beta1; pgf.beta2 = hp.beta2; pgf.eps = hp.eps;
       GemmGroup tiles{}, tilesf{};  // small-tile kernel; tilesf: with the update block in the epilogue
       tilesf.beta1 = hp.beta1; tilesf.beta2 = hp.beta2; tilesf.eps = hp.eps;
+      GemmGroup groups{};           // the same in K pieces
+      groups.beta1 = hp.beta1; groups.beta2 = hp.beta2; groups.eps = hp.eps;
       GemmGroup rest[2] = {};       // [0] RIGHT, [1] LEFT: what neither takes (a side of fewer than 8 elements)
       PadGroup pads{};
       long t256 = 0;
@@ -428,14 +431,19 @@ galore_status run_chain(galore_ctx* ctx, std::vector<StepItem>& items, float lr,
           // trip of R through memory: always when asked for, and by itself from 64 Ki entries on, where R is traffic (one
           // 350M layer 61 against 68 us, a 2768 / 7312 layer at r = 272 297 against 313; with the caches flushed before each pass,
           // three 350M layers 187 against 211, two 1B layers 421 against 502).
-          if (it.pieces == 1 && !ti.q8 && (ctx->fused_adam || (int64_t)r * ti.ldim >= 65536)) {
+          const bool whole = it.pieces == 1 && (ctx->fused_adam || (int64_t)r * ti.ldim >= kFuseAdamEntries);
+          // What is cut into K pieces can have them added, and updated, where they were formed: all of them, however many slabs there was room for
+          const bool grouped = k_groups_pay(p, dt, r, it.planned);
+          if (!ti.q8 && (whole || grouped)) {
             p.Mo = static_cast<float*>(ti.st.m.data);
             p.Vo = static_cast<float*>(ti.st.v.data);
             p.Nout = it.N;
             p.n_transposed = left;
             p.inv_c1 = ic1;
             p.inv_c2 = ic2;
-            tilesf.p[tilesf.count++] = p;
+            if (grouped) p.splits = it.planned;
+            GemmGroup& to = grouped ? groups : tilesf;
+            to.p[to.count++] = p;
             adam_done[ii] = 1;
           } else {
             tiles.p[tiles.count++] = p;
@@ -443,12 +451,13 @@ galore_status run_chain(galore_ctx* ctx, std::vector<StepItem>& items, float lr,
         }
       }
       {
-        ProfScope prof(ctx, GALORE_STAGE_PROJECT_LEFT, pg.count + pgf.count + tiles.count + tilesf.count + rest[1].count > 0, stream);
+        ProfScope prof(ctx, GALORE_STAGE_PROJECT_LEFT, pg.count + pgf.count + tiles.count + tilesf.count + groups.count + rest[1].count > 0, stream);
         hipError_t e = launch_pad_rows_group(pads, stream);
         if (e != hipSuccess) return hip_fail(ctx, e, "row padding launch");
         e = launch_proj_group(pgf, slabs, slab_bytes, stream, /*fuse_adam=*/true);
         if (e == hipSuccess) e = launch_proj_group(pg, slabs, slab_bytes, stream);
         if (e == hipSuccess) e = launch_tile_group(tilesf, dt, Epilogue::Adam, stream);
+        if (e == hipSuccess) e = launch_k_groups(groups, stream);
         if (e == hipSuccess) e = launch_tile_group(tiles, dt, Epilogue::StoreF32, stream);
         if (e == hipSuccess) e = launch_gemm_group(rest[1], dt, /*a_kcontig=*/true, /*b_kcontig=*/false, Epilogue::StoreF32, stream);
         if (e != hipSuccess) return hip_fail(ctx, e, "projection GEMM launch");
@@ -939,7 +948,7 @@ galore_status galore_step(galore_ctx* ctx, const galore_tensor* W, const galore_
       const TensorInfo& ti = ctx->tensors[first + pos];
       const size_t need = step_need(ti.left, ti.kdim, ti.ldim, ctx->hp.rank, ti.dt);
       if (!items.empty() && used + need > limit) break;
-      items.push_back(StepItem{first + pos, &W[pos], &G[pos], nullptr, nullptr, nullptr, ti.ldim, false, pieces[pos]});
+      items.push_back(StepItem{first + pos, &W[pos], &G[pos], nullptr, nullptr, nullptr, ti.ldim, false, pieces[pos], pieces[pos]});
       used += need;
       ++pos;
     }
@@ -986,7 +995,7 @@ galore_status galore_step_static(galore_ctx* ctx, const galore_tensor* W, const 
       const TensorInfo& ti = ctx->tensors[first + pos];
       const size_t need = step_need(ti.left, ti.kdim, ti.ldim, r, ti.dt);
       if (used + need > kStaticScratchBytes) break;
-      items.push_back(StepItem{first + pos, &W[pos], &G[pos], nullptr, nullptr, nullptr, ti.ldim, false, pieces[pos]});
+      items.push_back(StepItem{first + pos, &W[pos], &G[pos], nullptr, nullptr, nullptr, ti.ldim, false, pieces[pos], pieces[pos]});
       used += need;
       ++pos;
     }

@@ -63,8 +63,13 @@ hipError_t launch_gemm_group(GemmGroup& g, DType dt, bool a_kcontig, bool b_kcon
 bool tile_problem_fits(const GemmProblem& p, DType dt, bool b_kcontig);
 hipError_t launch_tile_group(GemmGroup& g, DType dt, Epilogue epi, hipStream_t stream);
 constexpr int kMaxTilePieces = 4;
-constexpr long kSplitBelowTiles = 224;  // a launch of as many 64 x 64 tiles keeps its contractions whole
-int tile_pieces(long tiles, int64_t K, DType dt);
+constexpr long kSplitBelowTiles = 224, kSplitBelowTilesF32 = 180;  // a launch of as many 64 x 64 tiles keeps its contractions whole
+constexpr int64_t kFuseAdamEntries = 65536;  // entries of R from which a whole contraction runs the update block by itself
+int tile_pieces(long tiles, int64_t K, DType dt, int64_t entries);
+// The bf16 product in K pieces with the update block of Algorithm 2 on their sum, in one launch: every tile's pieces in one workgroup.  Operands as
+// for Epilogue::Adam of launch_tile_group; the results are those of `splits` slabs and the Adam kernel, to the bit.
+bool k_groups_pay(const GemmProblem& p, DType dt, int rank, int pieces);
+hipError_t launch_k_groups(GemmGroup& g, hipStream_t stream);
 constexpr long kDirectItems = 150;  // 128 x 128 tiles (times K pieces) from which a product may take the direct-load kernel (gemm_tile.hip)
 int direct_pieces(const GemmProblem& p, DType dt, bool b_kcontig, int most);
 // A projection launch with at least this many 256 x 256 tiles takes the 256 x 256 kernel (a 7B layer at r = 256, 193 tiles:

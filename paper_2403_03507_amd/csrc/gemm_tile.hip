@@ -79,6 +79,32 @@ hipError_t launch_direct(GemmGroup& g, Epilogue epi, hipStream_t stream) {
   }
 }
 
+template <int KG> hipError_t k_groups_instance(GemmGroup& g, hipStream_t stream) {
+  using T = __bf16;
+  long total = 0;
+  for (int i = 0; i < g.count; ++i) {
+    GemmProblem& p = g.p[i];
+    p.tile_begin = (int32_t)total;
+    p.tiles_m = (p.M + 63) / 64;
+    p.tiles_n = (p.N + 63) / 64;
+    p.splits = 1;
+    total += tiles_of(p, 64, 64);
+  }
+  if (total > INT32_MAX) return hipErrorInvalidValue;
+  g.total_tiles = (int32_t)total;
+  auto kern = gemm_tile_kernel<T, 64, 64, Epilogue::Adam, true, false, KG>;
+  constexpr int lds = SmallTile<T, 64, 64>::lds_bytes_groups(KG);
+  static_assert(lds <= 160 * 1024, "");
+  static bool attr_set = false;
+  if (!attr_set) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+    attr_set = true;
+  }
+  hipLaunchKernelGGL(kern, dim3((unsigned)total), dim3(256 * KG), lds, stream, g);
+  return hipGetLastError();
+}
+
 // One round of DirectTile, a tile per CU, most CUs with a tile: the deeper ring draws 46 GB/s per CU where the register-staged tiles, several a
 // CU, reach 33.  Whole steps, us, on the other tiles / DirectTile: projection of one 350M layer at r = 256 (196 tiles) 51.8 / 48.9, r = 192 (three
 // quarters of the rows used) 44.4 / 46.3, a 4096 x 4096 weight at r = 768 (192) 94.1 / 84.8, 1024 (256) 108.7 / 98.2, 512 (128) 68.1 / 73.5, a 2048
@@ -168,12 +194,42 @@ int direct_pieces(const GemmProblem& p, DType dt, bool b_kcontig, int most) {
 // leave CUs idle, at most 4 (every piece is another fp32 copy of the product to write and to read).  Contractions under
 // 512 stay whole.  Whole steps, us, with 1 / 2 / 4 / 8 pieces: 3805 x 3805 at r = 152 (180 tiles) 71.6 / 65.4 / 61.8 /
 // 66.9; fp32 512 x 512 at r = 128 (16 tiles) 31.0 / 28.5 / 26.6 / 26.6; 2048 x 2048 at r = 512 (256 tiles) 32.3 / 34.8 / 36.1.
-int tile_pieces(long tiles, int64_t K, DType dt) {
+// fp32, in three pieces / whole with Adam in the epilogue: a 512 / 1376 layer at r = 128 (196 tiles) 43.6 / 39.9, a 1024 / 2736 layer at r = 64 (193)
+// 79.9 / 66.6, 1536 x 4096 at r = 192 (192) 68.4 / 68.4, flushed 77.7 / 76.4; 2048 x 5504 at r = 128 (172) 86.7 / 89.2, 768 x 2048 at r = 256 (128) 36.1 / 38.9;
+// where Adam stays a launch of its own (a 1024 / 2736 layer at r = 32, 193 tiles) 70.7 / 86.7.
+int tile_pieces(long tiles, int64_t K, DType dt, int64_t entries) {
   if (tiles < 1 || tiles >= kSplitBelowTiles || K < 512) return 1;
+  if (dt == DType::F32 && tiles >= kSplitBelowTilesF32 && entries >= kFuseAdamEntries) return 1;
   const int64_t by_k = K / (dt == DType::BF16 ? 256 : 128);
   int64_t pieces = (512 + tiles - 1) / tiles;
   pieces = pieces < by_k ? pieces : by_k;
   return (int)(pieces < kMaxTilePieces ? pieces : kMaxTilePieces);
+}
+
+// bf16 contractions short enough for one CU to draw a tile's operands (256 KB at K = 1024) in about the time of the launch that goes.  Whole steps of
+// one weight, us, slabs / groups, repeated passes and flushed: 512 x 512 at r = 128 15.9 / 11.7, 19.4 / 15.3; 1024 x 1024 at r = 128 16.7 / 12.8, 20.5 / 18.6, 256 18.5 /
+// 13.4, 22.8 / 19.6; 1024 x 2736 at r = 128 22.0 / 16.1, 29.5 / 24.3; 2048 x 2048 at r = 128 21.2 / 19.0, 28.2 / 30.2, 256 25.1 / 21.8, 35.1 / 31.4; 3072 x 3072 at r = 128 29.7 / 31.5.
+// fp32 products are bound by the matrix cores of the CUs that have a tile: 512 x 512 at r = 128 19.3 / 20.7, 1024 x 1024 23.0 / 31.1.
+bool k_groups_pay(const GemmProblem& p, DType dt, int rank, int pieces) {
+  return dt == DType::BF16 && pieces > 1 && pieces <= kMaxTilePieces && tile_problem_fits(p, dt, p.b_kcontig != 0) && (p.K <= 1024 || (p.K <= 2048 && rank > 128));
+}
+
+hipError_t launch_k_groups(GemmGroup& g, hipStream_t stream) {
+  if (g.count > kMaxGroup) return hipErrorInvalidValue;
+  for (int i = 0; i < g.count; ++i) {
+    const GemmProblem& p = g.p[i];
+    if (!tile_problem_fits(p, DType::BF16, p.b_kcontig != 0) || !p.Mo || !p.Vo || !p.Nout || p.splits < 2 || p.splits > kMaxTilePieces) return hipErrorInvalidValue;
+  }
+  for (int pieces = 2; pieces <= kMaxTilePieces; ++pieces) {
+    GemmGroup some{};
+    some.beta1 = g.beta1; some.beta2 = g.beta2; some.eps = g.eps;
+    for (int i = 0; i < g.count; ++i)
+      if (g.p[i].splits == pieces) some.p[some.count++] = g.p[i];
+    if (some.count == 0) continue;
+    const hipError_t e = pieces == 2 ? k_groups_instance<2>(some, stream) : pieces == 3 ? k_groups_instance<3>(some, stream) : k_groups_instance<4>(some, stream);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_weight_update(GemmGroup& g, DType dt, hipStream_t stream) {

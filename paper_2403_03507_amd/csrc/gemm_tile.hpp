@@ -118,6 +118,9 @@ template <class T, int BM_, int BN_> struct SmallTile {
   static constexpr int STAGE_BYTES = ROWS * SP * 4;
   static constexpr int NPITCH = ROWS + 16 / (int)sizeof(T);  // elements per column of the transposed N tile
   static constexpr int NT_BYTES = BN * NPITCH * (int)sizeof(T);
+  static constexpr int lds_bytes_groups(int kg) {  // KG groups with the Adam epilogue
+    return kg * OPERAND_BYTES > kg * STAGE_BYTES + NT_BYTES ? kg * OPERAND_BYTES : kg * STAGE_BYTES + NT_BYTES;
+  }
   static constexpr int lds_bytes(bool adam) {
     return OPERAND_BYTES > STAGE_BYTES + (adam ? NT_BYTES : 0) ? OPERAND_BYTES : STAGE_BYTES + (adam ? NT_BYTES : 0);
   }
@@ -135,25 +138,30 @@ struct DirectTile {
 };
 
 // AKC: A as [M][K]; else (StoreF32 only) as [K][M].  DIRECT: see DirectTile; K is a multiple of 64.
-template <class T, int BM, int BN_, Epilogue EPI, bool AKC = true, bool DIRECT = false>
-__global__ __launch_bounds__(DIRECT ? 512 : 256, 2) void gemm_tile_kernel(const GemmGroup grp) {
+// KG (Adam only): the K pieces of a tile are the work of KG groups of 4 wavefronts of one workgroup, which add their products in LDS, in
+// the order in which the Adam kernel adds slabs.  A launch and the trip of the slabs through memory less, for the rate at which one CU
+// draws the whole contraction's operands.
+template <class T, int BM, int BN_, Epilogue EPI, bool AKC = true, bool DIRECT = false, int KG = 1>
+__global__ __launch_bounds__(DIRECT ? 512 : 256 * KG, KG > 1 ? KG : 2) void gemm_tile_kernel(const GemmGroup grp) {
   using Cfg = SmallTile<T, BM, BN_>;
   using ET = ElemTraits<T>;
-  constexpr int NT = DIRECT ? 512 : 256;
+  constexpr int NT = DIRECT ? 512 : 256 * KG;
+  static_assert(KG == 1 || (EPI == Epilogue::Adam && BM == 64 && !DIRECT), "");
   constexpr int BN = Cfg::BN, BK = DIRECT ? DirectTile::BK : Cfg::BK, SP = Cfg::SP, ROWS = Cfg::ROWS;
   constexpr int WM = BM / 2, WN = BN / (DIRECT ? 4 : 2), TM = WM / 32, TN = WN / 32;
   using AOp = typename Cfg::A;
   using BOp = typename Cfg::B;
   static_assert(!DIRECT || (BM == 128 && BN == 128 && AKC && sizeof(T) == 2 && Cfg::STAGE_BYTES + Cfg::NT_BYTES <= DirectTile::LDS), "");
-  __shared__ __align__(16) unsigned char smem_static[DIRECT ? 16 : Cfg::lds_bytes(EPI == Epilogue::Adam)];
+  __shared__ __align__(16) unsigned char smem_static[DIRECT || KG > 1 ? 16 : Cfg::lds_bytes(EPI == Epilogue::Adam)];
   extern __shared__ __align__(1024) unsigned char smem_direct[];
-  unsigned char* smem = DIRECT ? smem_direct : smem_static;
-  T* As = reinterpret_cast<T*>(smem);
-  T* Bs = As + AOp::LDS_ELEMS;
+  unsigned char* smem = DIRECT || KG > 1 ? smem_direct : smem_static;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm0 = (wave & 1) * WM, wn0 = (wave >> 1) * WN;
+  const int group = KG > 1 ? wave >> 2 : 0, gtid = KG > 1 ? tid & 255 : tid, gwave = KG > 1 ? wave & 3 : wave;
+  const int wm0 = (gwave & 1) * WM, wn0 = (gwave >> 1) * WN;
+  T* As = reinterpret_cast<T*>(smem + group * Cfg::OPERAND_BYTES);
+  T* Bs = As + AOp::LDS_ELEMS;
 
   const int bid = xcd_contiguous_block_id(blockIdx.x, gridDim.x);
   int pi = 0;
@@ -162,12 +170,12 @@ __global__ __launch_bounds__(DIRECT ? 512 : 256, 2) void gemm_tile_kernel(const 
   const GemmProblem& pr = grp.p[pi];
   const int tiles = pr.tiles_m * pr.tiles_n;
   const int item = bid - pr.tile_begin;
-  const int piece = item / tiles;
+  const int slab = KG > 1 ? 0 : item / tiles, piece = KG > 1 ? group : slab;
   int tm, tn;
-  tile_coords(item - piece * tiles, pr.tiles_m, pr.tiles_n, tm, tn);
+  tile_coords(item - slab * tiles, pr.tiles_m, pr.tiles_n, tm, tn);
   const int m0 = tm * BM, n0 = tn * BN;
   const int M = pr.M, N = pr.N, K = pr.K;
-  const int KT = (K + BK - 1) / BK, S = pr.splits > 1 ? pr.splits : 1;
+  const int KT = (K + BK - 1) / BK, S = KG > 1 ? KG : pr.splits > 1 ? pr.splits : 1;
   const int first = (int)((long long)piece * KT / S), last = (int)((long long)(piece + 1) * KT / S);
   const T* __restrict__ A = static_cast<const T*>(pr.A);
   const T* __restrict__ B = static_cast<const T*>(pr.B);
@@ -198,8 +206,9 @@ __global__ __launch_bounds__(DIRECT ? 512 : 256, 2) void gemm_tile_kernel(const 
     }
   };
 
-  // fp32 pieces of the epilogue: columns 4 (tid % CPC) ..
-  constexpr int CPC = BN / 4, RPC = NT / CPC, NC = ROWS / RPC;
+  // fp32 pieces of the epilogue: columns 4 (tid % CPC) .. by EPT threads
+  constexpr int EPT = KG == 3 ? 512 : NT;
+  constexpr int CPC = BN / 4, RPC = EPT / CPC, NC = ROWS / RPC;
   const int pc = (tid % CPC) * 4, col = n0 + pc;
   // The moments are requested before anything waits for them (N >= 4: see tile_problem_fits): of a pass at its start, or with the last
   // products where there is one step more to hide them behind (DIRECT).
@@ -276,14 +285,19 @@ __global__ __launch_bounds__(DIRECT ? 512 : 256, 2) void gemm_tile_kernel(const 
     // two register sets: the pieces of the next two K steps are in flight while one is multiplied
     u32x4 ra0[AOp::PER], rb0[BOp::PER], ra1[AOp::PER], rb1[BOp::PER];
     auto load = [&](u32x4 (&ra)[AOp::PER], u32x4 (&rb)[BOp::PER], int kt) {
-      AOp::template load<AKC>(ra, A, pr.lda, m0, M, kt * BK, K, tid);
-      BOp::template load<BKC>(rb, B, pr.ldb, n0, N, kt * BK, K, tid);
+      AOp::template load<AKC>(ra, A, pr.lda, m0, M, kt * BK, K, gtid);
+      BOp::template load<BKC>(rb, B, pr.ldb, n0, N, kt * BK, K, gtid);
     };
     auto step = [&](u32x4 (&ra)[AOp::PER], u32x4 (&rb)[BOp::PER], int kt) {
       const int k = kt * BK;
       const bool tail = k + BK > K;
-      AOp::template store<AKC>(ra, As, m0, M, k, K, tail || edge_m, tid);
-      BOp::template store<BKC>(rb, Bs, n0, N, k, K, tail || edge_n, tid);
+      if (KG > 1 && kt >= last) {  // a group with a step less keeps the barriers
+        __syncthreads();
+        __syncthreads();
+        return;
+      }
+      AOp::template store<AKC>(ra, As, m0, M, k, K, tail || edge_m, gtid);
+      BOp::template store<BKC>(rb, Bs, n0, N, k, K, tail || edge_n, gtid);
       __syncthreads();
       if (kt + 2 < last) load(ra, rb, kt + 2);
 #pragma unroll
@@ -300,12 +314,13 @@ __global__ __launch_bounds__(DIRECT ? 512 : 256, 2) void gemm_tile_kernel(const 
       }
       __syncthreads();
     };
-    load(ra0, rb0, first);
+    if (KG == 1 || first < last) load(ra0, rb0, first);
     if (first + 1 < last) load(ra1, rb1, first + 1);
     fetch_w();
-    for (int kt = first; kt < last; kt += 2) {
+    const int end = KG > 1 ? first + (KT + KG - 1) / KG : last;
+    for (int kt = first; kt < end; kt += 2) {
       step(ra0, rb0, kt);
-      if (kt + 1 < last) step(ra1, rb1, kt + 1);
+      if (kt + 1 < end) step(ra1, rb1, kt + 1);
     }
   };
   if constexpr (DIRECT) {
@@ -336,7 +351,7 @@ __global__ __launch_bounds__(DIRECT ? 512 : 256, 2) void gemm_tile_kernel(const 
         for (int j = 0; j < TN; ++j)
 #pragma unroll
           for (int v = 0; v < 16; ++v)
-            st[(wr + 32 * i + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * SP + wn0 + 32 * j + (lane & 31)] = acc[i][j][v];
+            st[group * ROWS * SP + (wr + 32 * i + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * SP + wn0 + 32 * j + (lane & 31)] = acc[i][j][v];
     }
     __syncthreads();
     if constexpr (EPI == Epilogue::ApplyW) {
@@ -380,16 +395,18 @@ __global__ __launch_bounds__(DIRECT ? 512 : 256, 2) void gemm_tile_kernel(const 
       }
     } else if constexpr (EPI == Epilogue::Adam) {
       constexpr int NP = Cfg::NPITCH;
-      T* nt = reinterpret_cast<T*>(smem + Cfg::STAGE_BYTES);  // nt[column][row]
+      T* nt = reinterpret_cast<T*>(smem + KG * Cfg::STAGE_BYTES);  // nt[column][row]
       T* Nout = static_cast<T*>(pr.Nout);
       const bool tr = pr.n_transposed != 0;
 #pragma unroll
       for (int q = 0; q < NC; ++q) {
         const int lr = q * RPC + tid / CPC, row = m0 + ps * ROWS + lr;
-        if (row >= M || col >= N) continue;
+        if (row >= M || col >= N || (EPT < NT && tid >= EPT)) continue;
         constexpr bool held = DIRECT;
         const int mq = held ? ps * NC + q : q;
-        const f32x4 g = *reinterpret_cast<const f32x4*>(st + lr * SP + pc);
+        f32x4 g = *reinterpret_cast<const f32x4*>(st + lr * SP + pc);
+#pragma unroll
+        for (int kg = 1; kg < KG; ++kg) g += *reinterpret_cast<const f32x4*>(st + kg * ROWS * SP + lr * SP + pc);
         float* Mp = pr.Mo + (size_t)row * N + col;
         float* Vp = pr.Vo + (size_t)row * N + col;
         T n[4];
@@ -426,11 +443,11 @@ __global__ __launch_bounds__(DIRECT ? 512 : 256, 2) void gemm_tile_kernel(const 
       }
       if (tr) {  // N^T rows: 16-byte pieces along the tile's rows
         __syncthreads();
-        constexpr int LPR = ROWS / WVEC, CPP = NT / LPR;
+        constexpr int LPR = ROWS / WVEC, CPP = EPT / LPR;
 #pragma unroll
-        for (int q = 0; q < BN / CPP; ++q) {
+        for (int q = 0; q < (BN + CPP - 1) / CPP; ++q) {
           const int jc = q * CPP + tid / LPR, i = (tid % LPR) * WVEC, row = m0 + ps * ROWS + i;
-          if (n0 + jc >= N || row >= M) continue;
+          if (n0 + jc >= N || row >= M || jc >= BN || (EPT < NT && tid >= EPT)) continue;
           const u32x4 o = *reinterpret_cast<const u32x4*>(nt + jc * NP + i);
           T* dst = Nout + (size_t)(n0 + jc) * M + row;
           if (row + WVEC <= M) {
@@ -443,7 +460,7 @@ __global__ __launch_bounds__(DIRECT ? 512 : 256, 2) void gemm_tile_kernel(const 
         }
       }
     } else {
-      float* C = static_cast<float*>(pr.C) + (size_t)piece * pr.slab_stride;
+      float* C = static_cast<float*>(pr.C) + (size_t)slab * pr.slab_stride;
 #pragma unroll
       for (int q = 0; q < NC; ++q) {
         const int lr = q * RPC + tid / CPC, row = m0 + ps * ROWS + lr;
