@@ -193,7 +193,7 @@ size_t step_r_bytes(bool left, int64_t kdim, int64_t ldim, int64_t r, DType dt, 
   return align_up((size_t)pieces * r * projected_row_length(left, kdim, ldim, dt) * 4);
 }
 // The most K pieces that any launch group gives the tensor
-int most_pieces(int64_t kdim, int64_t ldim, int64_t r, DType dt) { return tile_pieces((long)tiles64(ldim, r), kdim, dt, r * ldim); }
+int most_pieces(int64_t kdim, int64_t ldim, int64_t r, DType dt) { return tile_pieces((long)tiles64(ldim, r), kdim, dt, /*entries=*/0); }
 size_t step_n_bytes(int64_t ldim, int64_t r, DType dt) { return align_up((size_t)r * ldim * dtype_size(dt)); }
 size_t step_gpad_bytes(bool left, int64_t kdim, int64_t ldim, DType dt) {
   const int64_t ldp = projected_row_length(left, kdim, ldim, dt);
@@ -261,10 +261,16 @@ std::vector<int> pieces_of_call(const galore_ctx* ctx, int32_t first, int32_t co
   for (int a = 0; a < count; a += kMaxGroup) {
     const int b = std::min(a + kMaxGroup, count);
     long tiles[2] = {0, 0};  // by dtype: no launch mixes them
-    for (int i = a; i < b; ++i) tiles[ctx->tensors[first + i].dt == DType::BF16] += (long)tiles64(ctx->tensors[first + i].ldim, r);
+    int64_t entries[2] = {INT64_MAX, INT64_MAX};  // of the smallest R
     for (int i = a; i < b; ++i) {
       const TensorInfo& ti = ctx->tensors[first + i];
-      pieces[i] = tile_pieces(tiles[ti.dt == DType::BF16], ti.kdim, ti.dt, r * ti.ldim);
+      const bool bf16 = ti.dt == DType::BF16;
+      tiles[bf16] += (long)tiles64(ti.ldim, r);
+      entries[bf16] = std::min(entries[bf16], r * ti.ldim);
+    }
+    for (int i = a; i < b; ++i) {
+      const TensorInfo& ti = ctx->tensors[first + i];
+      pieces[i] = tile_pieces(tiles[ti.dt == DType::BF16], ti.kdim, ti.dt, entries[ti.dt == DType::BF16]);
     }
   }
   return pieces;

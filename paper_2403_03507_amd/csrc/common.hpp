@@ -65,7 +65,7 @@ hipError_t launch_tile_group(GemmGroup& g, DType dt, Epilogue epi, hipStream_t s
 constexpr int kMaxTilePieces = 4;
 constexpr long kSplitBelowTiles = 224, kSplitBelowTilesF32 = 180;  // a launch of as many 64 x 64 tiles keeps its contractions whole
 constexpr int64_t kFuseAdamEntries = 65536;  // entries of R from which a whole contraction runs the update block by itself
-int tile_pieces(long tiles, int64_t K, DType dt, int64_t entries);
+int tile_pieces(long tiles, int64_t K, DType dt, int64_t entries);  // entries: of the smallest R that the launches share
 // The bf16 product in K pieces with the update block of Algorithm 2 on their sum, in one launch: every tile's pieces in one workgroup.  Operands as
 // for Epilogue::Adam of launch_tile_group; the results are those of `splits` slabs and the Adam kernel, to the bit.
 bool k_groups_pay(const GemmProblem& p, DType dt, int rank, int pieces);

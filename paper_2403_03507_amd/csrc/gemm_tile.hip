@@ -196,7 +196,8 @@ int direct_pieces(const GemmProblem& p, DType dt, bool b_kcontig, int most) {
 // 66.9; fp32 512 x 512 at r = 128 (16 tiles) 31.0 / 28.5 / 26.6 / 26.6; 2048 x 2048 at r = 512 (256 tiles) 32.3 / 34.8 / 36.1.
 // fp32, in three pieces / whole with Adam in the epilogue: a 512 / 1376 layer at r = 128 (196 tiles) 43.6 / 39.9, a 1024 / 2736 layer at r = 64 (193)
 // 79.9 / 66.6, 1536 x 4096 at r = 192 (192) 68.4 / 68.4, flushed 77.7 / 76.4; 2048 x 5504 at r = 128 (172) 86.7 / 89.2, 768 x 2048 at r = 256 (128) 36.1 / 38.9;
-// where Adam stays a launch of its own (a 1024 / 2736 layer at r = 32, 193 tiles) 70.7 / 86.7.
+// where Adam stays a launch of its own (a 1024 / 2736 layer at r = 32, 193 tiles) 70.7 / 86.7, or does for some (a 512 / 1376 layer at r = 96) 40.7 / 50.2: `entries`
+// are those of the smallest R of the call.
 int tile_pieces(long tiles, int64_t K, DType dt, int64_t entries) {
   if (tiles < 1 || tiles >= kSplitBelowTiles || K < 512) return 1;
   if (dt == DType::F32 && tiles >= kSplitBelowTilesF32 && entries >= kFuseAdamEntries) return 1;
