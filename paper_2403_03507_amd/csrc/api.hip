@@ -463,7 +463,7 @@ galore_status run_chain(galore_ctx* ctx, std::vector<StepItem>& items, float lr,
         e = launch_proj_group(pgf, slabs, slab_bytes, stream, /*fuse_adam=*/true);
         if (e == hipSuccess) e = launch_proj_group(pg, slabs, slab_bytes, stream);
         if (e == hipSuccess) e = launch_tile_group(tilesf, dt, Epilogue::Adam, stream);
-        if (e == hipSuccess) e = launch_k_groups(groups, stream);
+        if (e == hipSuccess) e = launch_k_groups(groups, dt, stream);
         if (e == hipSuccess) e = launch_tile_group(tiles, dt, Epilogue::StoreF32, stream);
         if (e == hipSuccess) e = launch_gemm_group(rest[1], dt, /*a_kcontig=*/true, /*b_kcontig=*/false, Epilogue::StoreF32, stream);
         if (e != hipSuccess) return hip_fail(ctx, e, "projection GEMM launch");

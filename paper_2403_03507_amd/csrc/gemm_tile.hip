@@ -105,6 +105,28 @@ template <int KG> hipError_t k_groups_instance(GemmGroup& g, hipStream_t stream)
   return hipGetLastError();
 }
 
+hipError_t launch_narrow(GemmGroup& g, hipStream_t stream) {
+  long total = 0;
+  for (int i = 0; i < g.count; ++i) {
+    GemmProblem& p = g.p[i];
+    p.tile_begin = (int32_t)total;
+    p.tiles_m = (p.M + NarrowTile::BM - 1) / NarrowTile::BM;
+    p.tiles_n = (p.N + NarrowTile::BN - 1) / NarrowTile::BN;
+    p.splits = 1;
+    total += tiles_of(p, NarrowTile::BM, NarrowTile::BN);
+  }
+  if (total > INT32_MAX) return hipErrorInvalidValue;
+  g.total_tiles = (int32_t)total;
+  static bool attr_set = false;
+  if (!attr_set) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(narrow_adam_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, NarrowTile::LDS);
+    if (e != hipSuccess) return e;
+    attr_set = true;
+  }
+  hipLaunchKernelGGL(narrow_adam_kernel, dim3((unsigned)total), dim3(NarrowTile::NT), NarrowTile::LDS, stream, g);
+  return hipGetLastError();
+}
+
 // One round of DirectTile, a tile per CU, most CUs with a tile: the deeper ring draws 46 GB/s per CU where the register-staged tiles, several a
 // CU, reach 33.  Whole steps, us, on the other tiles / DirectTile: projection of one 350M layer at r = 256 (196 tiles) 51.8 / 48.9, r = 192 (three
 // quarters of the rows used) 44.4 / 46.3, a 4096 x 4096 weight at r = 768 (192) 94.1 / 84.8, 1024 (256) 108.7 / 98.2, 512 (128) 68.1 / 73.5, a 2048
@@ -210,17 +232,25 @@ int tile_pieces(long tiles, int64_t K, DType dt, int64_t entries) {
 // bf16 contractions short enough for one CU to draw a tile's operands (256 KB at K = 1024) in about the time of the launch that goes.  Whole steps of
 // one weight, us, slabs / groups, repeated passes and flushed: 512 x 512 at r = 128 15.9 / 11.7, 19.4 / 15.3; 1024 x 1024 at r = 128 16.7 / 12.8, 20.5 / 18.6, 256 18.5 /
 // 13.4, 22.8 / 19.6; 1024 x 2736 at r = 128 22.0 / 16.1, 29.5 / 24.3; 2048 x 2048 at r = 128 21.2 / 19.0, 28.2 / 30.2, 256 25.1 / 21.8, 35.1 / 31.4; 3072 x 3072 at r = 128 29.7 / 31.5.
-// fp32 products are bound by the matrix cores of the CUs that have a tile: 512 x 512 at r = 128 19.3 / 20.7, 1024 x 1024 23.0 / 31.1.
+// fp32 (NarrowTile), where the call has few enough tiles for 4 slabs: 512 x 512 at r = 128 19.9 / 14.0, 23.4 / 19.1 (in 64 x 64 tiles, bound by the matrix cores of the
+// CUs that have one, 20.7); 768 x 768 at r = 256 23.6 / 19.1, 29.9 / 24.4; 1024 x 1024 at r = 128 22.5 / 17.9, 28.0 / 23.9; 1024 x 2736 at r = 64 28.0 / 22.7, 36.2 / 30.6; 2048 x 2048 at r = 128
+// 39.2 / 37.3, 47.8 / 46.1.  In more than one round of its tiles only short contractions: 768 x 2048 at r = 256 (512) 35.6 / 33.9, 43.6 / 41.6; 1024 x 2736 at r = 192 (516) 47.2 / 51.9,
+// 1536 x 1536 at r = 192 (288) 41.2 / 44.1, 2048 x 5504 at r = 64 (344) 57.3 / 61.7.
 bool k_groups_pay(const GemmProblem& p, DType dt, int rank, int pieces) {
-  return dt == DType::BF16 && pieces > 1 && pieces <= kMaxTilePieces && tile_problem_fits(p, dt, p.b_kcontig != 0) && (p.K <= 1024 || (p.K <= 2048 && rank > 128));
+  if (pieces < 2 || pieces > kMaxTilePieces || !tile_problem_fits(p, dt, p.b_kcontig != 0)) return false;
+  if (dt == DType::F32)
+    return pieces == kMaxTilePieces && (p.K <= 768 || (p.K <= 2048 && (int64_t)((p.M + 31) / 32) * ((p.N + 31) / 32) <= 256));
+  return p.K <= 1024 || (p.K <= 2048 && rank > 128);
 }
 
-hipError_t launch_k_groups(GemmGroup& g, hipStream_t stream) {
+hipError_t launch_k_groups(GemmGroup& g, DType dt, hipStream_t stream) {
+  if (g.count <= 0) return hipSuccess;
   if (g.count > kMaxGroup) return hipErrorInvalidValue;
   for (int i = 0; i < g.count; ++i) {
     const GemmProblem& p = g.p[i];
-    if (!tile_problem_fits(p, DType::BF16, p.b_kcontig != 0) || !p.Mo || !p.Vo || !p.Nout || p.splits < 2 || p.splits > kMaxTilePieces) return hipErrorInvalidValue;
+    if (!tile_problem_fits(p, dt, p.b_kcontig != 0) || !p.Mo || !p.Vo || !p.Nout || p.splits < 2 || p.splits > kMaxTilePieces) return hipErrorInvalidValue;
   }
+  if (dt == DType::F32) return launch_narrow(g, stream);
   for (int pieces = 2; pieces <= kMaxTilePieces; ++pieces) {
     GemmGroup some{};
     some.beta1 = g.beta1; some.beta2 = g.beta2; some.eps = g.eps;

@@ -479,4 +479,150 @@ __global__ __launch_bounds__(DIRECT ? 512 : 256 * KG, KG > 1 ? KG : 2) void gemm
   }
 }
 
+// The fp32 projection of a small weight with the update block: 32 x 32 tiles, and the whole contraction of one in a workgroup of 16 wavefronts
+// that cut it among them (4 groups take a run of K steps each, a wavefront a quarter of every step of its group).  The rate of the fp32 MFMA
+// on the CUs that have a tile bounds 64 x 64 tiles here (7 us at K = 512); a quarter of the tile is a quarter of that.
+struct NarrowTile {
+  static constexpr int BM = 32, BN = 32, BK = 64, KG = 4, NT = 256 * KG;
+  using Operand = TileOperand<float, 32, BK>;
+  static constexpr int GROUP_FLOATS = 2 * Operand::LDS_ELEMS;
+  static constexpr int SP = BN + 4, PART = BM * SP;  // floats of one wavefront's partial tile
+  static constexpr int NP = BM + 4;                  // floats per column of the transposed N tile
+  static constexpr int OPERANDS = KG * GROUP_FLOATS, STAGE = 4 * KG * PART;
+  static constexpr int LDS = (OPERANDS > STAGE ? OPERANDS : STAGE) * 4;
+  static_assert(BN * NP <= PART, "the transposed N tile takes the place of one partial tile");
+};
+
+static __global__ __launch_bounds__(NarrowTile::NT) void narrow_adam_kernel(const GemmGroup grp) {
+  using Op = NarrowTile::Operand;
+  constexpr int BM = NarrowTile::BM, BN = NarrowTile::BN, BK = NarrowTile::BK, KG = NarrowTile::KG, SP = NarrowTile::SP, PART = NarrowTile::PART;
+  extern __shared__ __align__(1024) unsigned char smem_narrow[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int group = wave >> 2, gtid = tid & 255, kk0 = (wave & 3) * (BK / 4);
+  float* As = reinterpret_cast<float*>(smem_narrow) + group * NarrowTile::GROUP_FLOATS;
+  float* Bs = As + Op::LDS_ELEMS;
+
+  const int bid = xcd_contiguous_block_id(blockIdx.x, gridDim.x);
+  int pi = 0;
+  for (int i = 1; i < grp.count; ++i)
+    if (bid >= grp.p[i].tile_begin) pi = i;
+  const GemmProblem& pr = grp.p[pi];
+  int tm, tn;
+  tile_coords(bid - pr.tile_begin, pr.tiles_m, pr.tiles_n, tm, tn);
+  const int m0 = tm * BM, n0 = tn * BN, M = pr.M, N = pr.N, K = pr.K;
+  const int KT = (K + BK - 1) / BK, steps = (KT + KG - 1) / KG;
+  const int first = (int)((long long)group * KT / KG), last = (int)((long long)(group + 1) * KT / KG);
+  const float* __restrict__ A = static_cast<const float*>(pr.A);
+  const float* __restrict__ B = static_cast<const float*>(pr.B);
+
+  f32x16 acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+
+  // the update's four entries of a thread of the first group; the moments are requested before the products (N >= 4: see tile_problem_fits)
+  const int lr = gtid >> 3, pc = (gtid & 7) * 4, row = m0 + lr, col = n0 + pc;
+  f32x4 mo = {0.f, 0.f, 0.f, 0.f}, vo = mo;
+
+  auto run = [&](auto kc) {
+    constexpr bool BKC = decltype(kc)::value;
+    const bool edge_n = !BKC && n0 + BN > N;
+    u32x4 ra0[Op::PER], rb0[Op::PER], ra1[Op::PER], rb1[Op::PER];
+    auto load = [&](u32x4 (&ra)[Op::PER], u32x4 (&rb)[Op::PER], int kt) {
+      Op::load<true>(ra, A, pr.lda, m0, M, kt * BK, K, gtid);
+      Op::load<BKC>(rb, B, pr.ldb, n0, N, kt * BK, K, gtid);
+    };
+    auto step = [&](u32x4 (&ra)[Op::PER], u32x4 (&rb)[Op::PER], int kt) {
+      const int k = kt * BK;
+      const bool tail = k + BK > K, has = kt < last;  // a group with a step less keeps the barriers
+      if (has) {
+        Op::store<true>(ra, As, m0, M, k, K, tail, gtid);
+        Op::store<BKC>(rb, Bs, n0, N, k, K, tail || edge_n, gtid);
+      }
+      __syncthreads();
+      if (has) {
+        if (kt + 2 < last) load(ra, rb, kt + 2);
+#pragma unroll
+        for (int kk = 0; kk < BK / 4; kk += ElemTraits<float>::KSTEP) {
+          Frag<float> fa, fb;
+          Op::frag<true>(fa, As, 0, kk0 + kk, lane);
+          Op::frag<BKC>(fb, Bs, 0, kk0 + kk, lane);
+          Frag<float>::mma(acc, fa, fb);
+        }
+      }
+      __syncthreads();
+    };
+    if (first < last) load(ra0, rb0, first);
+    if (first + 1 < last) load(ra1, rb1, first + 1);
+    if (group == 0) {
+      const size_t e = (size_t)(row < M ? row : M - 1) * N + (col + 4 <= N ? col : 0);
+      __builtin_memcpy(&mo, pr.Mo + e, 16);
+      __builtin_memcpy(&vo, pr.Vo + e, 16);
+    }
+    for (int s = 0; s < steps; s += 2) {
+      step(ra0, rb0, first + s);
+      if (s + 1 < steps) step(ra1, rb1, first + s + 1);
+    }
+  };
+  if (pr.b_kcontig) run(std::true_type{});
+  else run(std::false_type{});
+
+  // the 16 partial tiles, added in the order of the wavefronts
+  float* st = reinterpret_cast<float*>(smem_narrow);
+#pragma unroll
+  for (int v = 0; v < 16; ++v) st[wave * PART + (8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * SP + (lane & 31)] = acc[v];
+  __syncthreads();
+  f32x4 n = {0.f, 0.f, 0.f, 0.f};
+  float* Nout = static_cast<float*>(pr.Nout);
+  const bool tr = pr.n_transposed != 0;
+  if (group == 0 && row < M && col < N) {
+    f32x4 g = *reinterpret_cast<const f32x4*>(st + lr * SP + pc);
+#pragma unroll
+    for (int w = 1; w < 4 * KG; ++w) g += *reinterpret_cast<const f32x4*>(st + w * PART + lr * SP + pc);
+    float* Mp = pr.Mo + (size_t)row * N + col;
+    float* Vp = pr.Vo + (size_t)row * N + col;
+    if (col + 4 <= N) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        float me = mo[e], ve = vo[e];
+        n[e] = adam_entry(g[e], me, ve, grp.beta1, grp.beta2, grp.eps, pr.inv_c1, pr.inv_c2);
+        mo[e] = me; vo[e] = ve;
+      }
+      __builtin_memcpy(Mp, &mo, 16);
+      __builtin_memcpy(Vp, &vo, 16);
+      if (!tr) __builtin_memcpy(Nout + (size_t)row * N + col, &n, 16);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (col + e < N) {
+          float me = Mp[e], ve = Vp[e];
+          n[e] = adam_entry(g[e], me, ve, grp.beta1, grp.beta2, grp.eps, pr.inv_c1, pr.inv_c2);
+          Mp[e] = me; Vp[e] = ve;
+          if (!tr) Nout[(size_t)row * N + col + e] = n[e];
+        }
+    }
+  }
+  if (!tr) return;  // uniform
+  __syncthreads();  // the partial tiles have been read
+  constexpr int NP = NarrowTile::NP;
+  if (group == 0) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) st[(pc + e) * NP + lr] = n[e];
+  }
+  __syncthreads();
+  if (group == 0) {  // N^T rows: 16-byte pieces along the tile's rows
+    const int jc = gtid >> 3, i = (gtid & 7) * 4, r0 = m0 + i;
+    if (n0 + jc >= N || r0 >= M) return;
+    const f32x4 o = *reinterpret_cast<const f32x4*>(st + jc * NP + i);
+    float* dst = Nout + (size_t)(n0 + jc) * M + r0;
+    if (r0 + 4 <= M) {
+      __builtin_memcpy(dst, &o, 16);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (r0 + e < M) dst[e] = o[e];
+    }
+  }
+}
+
 }  // namespace galore

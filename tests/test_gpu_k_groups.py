@@ -37,3 +37,38 @@ def test_pieces_in_one_workgroup(k, r, extra, pad, left):
     assert bool(((W.double() - want).abs() <= 1.02 * (0.5 * ulp + n_err)).all())
     assert not torch.equal(W, W0)
     opt.close()
+
+
+# fp32: 32 x 32 tiles over 16 wavefronts; short sides that end inside a K step, ranks and long sides that end inside a tile
+@pytest.mark.parametrize("k,r", [(512, 64), (513, 33), (575, 8), (640, 128), (1000, 4), (1024, 97)])
+@pytest.mark.parametrize("extra,pad", [(0, 0), (64, 0), (77, 3)])
+@pytest.mark.parametrize("left", [True, False])
+def test_fp32_contraction_in_one_workgroup(k, r, extra, pad, left):
+    g = torch.Generator(device="cuda").manual_seed(k + r + extra)
+    rand = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    m, n = (k, k + extra) if left or not extra else (k + extra, k)
+    W0, G = 0.02 * rand(m, n), rand(m, n)
+    W = strided(W0, pad) if pad else W0.clone()
+    opt = gb.GaLore([W], r, update_gap=1 << 30, beta2=0.99)
+    opt.proj[0].copy_(torch.linalg.qr(rand(k, r))[0])
+    opt.M[0].copy_(0.1 * rand(*opt.M[0].shape))
+    opt.V[0].copy_(0.1 + 0.1 * rand(*opt.V[0].shape).square())
+    opt.set_step(0, 7)
+    M0, V0, P = opt.M[0].double(), opt.V[0].double(), opt.proj[0].double()
+    R = P.t() @ G.double() if m <= n else G.double() @ P
+    opt.step([W], [strided(G, pad) if pad else G], 1e-2)
+    b1, b2 = float(torch.tensor(0.9)), float(torch.tensor(0.99))
+    M, V = b1 * M0 + (1 - b1) * R, b2 * V0 + (1 - b2) * R * R
+    # every entry: k products summed in at most k / 16 + 16 roundings, of 2^-24 of the sum of their absolute values each, and a few of M and V themselves
+    bound = 2.0 ** -24 * (k / 16 + 16) * (P.abs().t() @ G.double().abs() if m <= n else G.double().abs() @ P.abs())
+    dM, dV = (1 - b1) * bound + 2.0 ** -22 * (M0.abs() + R.abs()), (1 - b2) * 2 * R.abs() * bound + 2.0 ** -21 * (V0 + R * R)
+    assert bool(((opt.M[0].double() - M).abs() <= dM).all()) and bool(((opt.V[0].double() - V).abs() <= dV).all())
+    N = (M / (1 - b1 ** 8)) / ((V / (1 - b2 ** 8)).sqrt() + 1e-8)
+    want = W0.double() - 1e-2 * 0.25 * (P @ N if m <= n else N @ P.t())
+    # half an ulp of W where it is stored, what M and V may be off by in N, and r products summed in fp32
+    ulp = 2.0 ** (torch.floor(torch.log2(torch.maximum(want.abs(), W0.double().abs()).clamp_min(2.0 ** -126))) - 23)
+    dN = N.abs() * (dV / V) + dM / (1 - b1 ** 8) / (V / (1 - b2 ** 8)).sqrt() + 2.0 ** -24 * (r + 16) * N.abs()
+    n_err = 1e-2 * 0.25 * (P.abs() @ dN if m <= n else dN @ P.abs().t())
+    assert bool(((W.double() - want).abs() <= 0.51 * ulp + n_err).all())
+    assert not torch.equal(W, W0)
+    opt.close()
