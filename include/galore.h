@@ -203,7 +203,8 @@ galore_status galore_refresh_subspace(galore_ctx* ctx, const galore_tensor* G, i
  * stream and on up to two library-owned streams of default priority, forked from and joined
  * back into the context's stream with events inside the call, so tail waves of one GEMM and the
  * bandwidth-bound Adam pass overlap with another chain's MFMA work (a call whose step takes the chip less time than
- * the forking takes the host runs as one chain).  1 = strictly serial on the
+ * the forking takes the host runs as one chain; fp32 tensors and ranks below 256 run as two at most, where a
+ * third launch at a time only gets in the way of the others).  1 = strictly serial on the
  * context's stream.  W, M, V agree between settings to the fp32 rounding of R, and bit for bit whenever
  * the projection launches cut no tile into K pieces (short sides under 512) or cut the same tiles
  * the same way: a large projection (160 and more tiles of 256 x 256) sums the K range of a tile that does not fill a round
