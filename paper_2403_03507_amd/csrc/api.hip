@@ -248,6 +248,7 @@ struct StepItem {
   int64_t ldr;   // row length of R, set by the projection
   bool large;    // the launches of the other chains count towards the large-tile kernel as well (count_over_chains)
   int planned;   // K pieces of the projection (pieces_of_call)
+  long tiles32;  // 32 x 32 tiles of the projections of its dtype that share the chip with it
   int pieces;    // slabs of R: as planned (pieces_of_call), as many as there is room for, then as many as the projection makes
 };
 
@@ -255,25 +256,28 @@ struct StepItem {
 // tensors of the call, whichever of them share a launch in the end: the chains of a call run at the same time, so their tiles
 // fill the chip together, and the rounding of R is the same for every number of chains, every workspace with room for the
 // pieces, and in galore_step_static.
-std::vector<int> pieces_of_call(const galore_ctx* ctx, int32_t first, int32_t count) {
-  std::vector<int> pieces(count);
+struct PiecePlan { int pieces; long tiles32; };
+std::vector<PiecePlan> pieces_of_call(const galore_ctx* ctx, int32_t first, int32_t count) {
+  std::vector<PiecePlan> plan(count);
   const int r = ctx->hp.rank;
   for (int a = 0; a < count; a += kMaxGroup) {
     const int b = std::min(a + kMaxGroup, count);
-    long tiles[2] = {0, 0};  // by dtype: no launch mixes them
+    long tiles[2] = {0, 0}, tiles32[2] = {0, 0};  // by dtype: no launch mixes them
     int64_t entries[2] = {INT64_MAX, INT64_MAX};  // of the smallest R
     for (int i = a; i < b; ++i) {
       const TensorInfo& ti = ctx->tensors[first + i];
       const bool bf16 = ti.dt == DType::BF16;
       tiles[bf16] += (long)tiles64(ti.ldim, r);
+      tiles32[bf16] += (long)(((int64_t)r + 31) / 32 * ((ti.ldim + 31) / 32));
       entries[bf16] = std::min(entries[bf16], r * ti.ldim);
     }
     for (int i = a; i < b; ++i) {
       const TensorInfo& ti = ctx->tensors[first + i];
-      pieces[i] = tile_pieces(tiles[ti.dt == DType::BF16], ti.kdim, ti.dt, entries[ti.dt == DType::BF16]);
+      const bool bf16 = ti.dt == DType::BF16;
+      plan[i] = PiecePlan{tile_pieces(tiles[bf16], ti.kdim, ti.dt, entries[bf16]), tiles32[bf16]};
     }
   }
-  return pieces;
+  return plan;
 }
 
 // Places R, N and the padded copy of the items, in [off, end) of `base`; returns the end of what is taken.  end - off is at
@@ -439,7 +443,7 @@ galore_status run_chain(galore_ctx* ctx, std::vector<StepItem>& items, float lr,
           // three 350M layers 187 against 211, two 1B layers 421 against 502).
           const bool whole = it.pieces == 1 && (ctx->fused_adam || (int64_t)r * ti.ldim >= kFuseAdamEntries);
           // What is cut into K pieces can have them added, and updated, where they were formed: all of them, however many slabs there was room for
-          const bool grouped = k_groups_pay(p, dt, r, it.planned);
+          const bool grouped = k_groups_pay(p, dt, r, it.planned, it.tiles32);
           if (!ti.q8 && (whole || grouped)) {
             p.Mo = static_cast<float*>(ti.st.m.data);
             p.Vo = static_cast<float*>(ti.st.v.data);
@@ -953,7 +957,7 @@ galore_status galore_step(galore_ctx* ctx, const galore_tensor* W, const galore_
   }
   // with overlapping calls a chunk has to fit one call's share of the workspace
   const size_t limit = ctx->overlap_calls ? workspace_share(ctx) : ctx->ws_bytes;
-  const std::vector<int> pieces = pieces_of_call(ctx, first, count);
+  const std::vector<PiecePlan> plan = pieces_of_call(ctx, first, count);
   int pos = 0;
   while (pos < count) {
     std::vector<StepItem> items;
@@ -962,7 +966,7 @@ galore_status galore_step(galore_ctx* ctx, const galore_tensor* W, const galore_
       const TensorInfo& ti = ctx->tensors[first + pos];
       const size_t need = step_need(ti.left, ti.kdim, ti.ldim, ctx->hp.rank, ti.dt);
       if (!items.empty() && used + need > limit) break;
-      items.push_back(StepItem{first + pos, &W[pos], &G[pos], nullptr, nullptr, nullptr, ti.ldim, false, pieces[pos], pieces[pos]});
+      items.push_back(StepItem{first + pos, &W[pos], &G[pos], nullptr, nullptr, nullptr, ti.ldim, false, plan[pos].pieces, plan[pos].tiles32, plan[pos].pieces});
       used += need;
       ++pos;
     }
@@ -1000,7 +1004,7 @@ galore_status galore_step_static(galore_ctx* ctx, const galore_tensor* W, const 
   }
   // Launch groups of as many consecutive tensors as fit the array, one chain on the context's stream.
   // Stream order protects the array between groups and between calls on this stream.
-  const std::vector<int> pieces = pieces_of_call(ctx, first, count);
+  const std::vector<PiecePlan> plan = pieces_of_call(ctx, first, count);
   int pos = 0;
   while (pos < count) {
     std::vector<StepItem> items;
@@ -1009,7 +1013,7 @@ galore_status galore_step_static(galore_ctx* ctx, const galore_tensor* W, const 
       const TensorInfo& ti = ctx->tensors[first + pos];
       const size_t need = step_need(ti.left, ti.kdim, ti.ldim, r, ti.dt);
       if (used + need > kStaticScratchBytes) break;
-      items.push_back(StepItem{first + pos, &W[pos], &G[pos], nullptr, nullptr, nullptr, ti.ldim, false, pieces[pos], pieces[pos]});
+      items.push_back(StepItem{first + pos, &W[pos], &G[pos], nullptr, nullptr, nullptr, ti.ldim, false, plan[pos].pieces, plan[pos].tiles32, plan[pos].pieces});
       used += need;
       ++pos;
     }

@@ -154,19 +154,26 @@ bool direct_pays(const GemmGroup& g, long items128, bool update) {
 // 1B layer (3088 / 1544 / 772) 266 / 244 / 230, one 3805 x 3805 weight at r = 152 (180 / 120 / 60, two K pieces) 65 / 68 / 83.
 // These are passes repeated on the same tensors; with the caches flushed before each pass, three 350M layers 183 / 190 / 189 (hence
 // 64 x 64 tiles there), two 130M layers 99 / 101 / 108, two 1B layers 502 / 448 / 420.
+// A projection whose rank leaves most of a larger tile's rows (or columns) empty stays on the smaller one (up to half as much again may go to padding: ranks
+// from 129 on): two 3329 / 8824 layers at r = 24 518.8 / 451.5 on 128 x 64 / 64 x 64, two 3328 / 8824 layers 423 / 411.
 // The weight update has more tiles than that and shorter contractions: 128 x 64 unless the contraction is long (r = 54 on
 // a 1105 / 2688 layer: 104 / 100 / 103; r = 401 on 1904 / 3968: 232 / 208 / 194).
 template <class T> hipError_t launch_typed(GemmGroup& g, Epilogue epi, hipStream_t stream) {
-  long items128 = 0, items96 = 0;
+  long items128 = 0, items96 = 0, items64 = 0;
   int longest = 0;
   for (int i = 0; i < g.count; ++i) {
     items128 += tiles_of(g.p[i], 128, 128);
     items96 += tiles_of(g.p[i], 128, 64);
+    items64 += tiles_of(g.p[i], 64, 64);
     longest = g.p[i].K > longest ? g.p[i].K : longest;
   }
   if (items128 == 0) return hipSuccess;
   const bool update = epi == Epilogue::ApplyW;
   if (std::is_same<T, __bf16>::value && direct_pays(g, items128, update)) return launch_direct(g, epi, stream);
+  if (!update) {  // more than half as much again of a larger tile's work for padding: not that tile
+    if (8 * items128 > 3 * items64) items128 = 0;
+    if (4 * items96 > 3 * items64) items96 = 0;
+  }
   if (items128 >= 350 && (!update || longest >= 256)) return launch<T, 128, 128>(g, epi, stream);
   if (items96 >= (update ? 300 : 500)) return launch<T, 128, 64>(g, epi, stream);
   return launch<T, 64, 64>(g, epi, stream);
@@ -235,11 +242,11 @@ int tile_pieces(long tiles, int64_t K, DType dt, int64_t entries) {
 // fp32 (NarrowTile), where the call has few enough tiles for 4 slabs: 512 x 512 at r = 128 19.9 / 14.0, 23.4 / 19.1 (in 64 x 64 tiles, bound by the matrix cores of the
 // CUs that have one, 20.7); 768 x 768 at r = 256 23.6 / 19.1, 29.9 / 24.4; 1024 x 1024 at r = 128 22.5 / 17.9, 28.0 / 23.9; 1024 x 2736 at r = 64 28.0 / 22.7, 36.2 / 30.6; 2048 x 2048 at r = 128
 // 39.2 / 37.3, 47.8 / 46.1.  In more than one round of its tiles only short contractions: 768 x 2048 at r = 256 (512) 35.6 / 33.9, 43.6 / 41.6; 1024 x 2736 at r = 192 (516) 47.2 / 51.9,
-// 1536 x 1536 at r = 192 (288) 41.2 / 44.1, 2048 x 5504 at r = 64 (344) 57.3 / 61.7.
-bool k_groups_pay(const GemmProblem& p, DType dt, int rank, int pieces) {
+// 1536 x 1536 at r = 192 (288) 41.2 / 44.1, 2048 x 5504 at r = 64 (344) 57.3 / 61.7, three 1664 x 1664 at r = 48 in one call (312) 48.0 / 51.0.
+bool k_groups_pay(const GemmProblem& p, DType dt, int rank, int pieces, long tiles32) {
   if (pieces < 2 || pieces > kMaxTilePieces || !tile_problem_fits(p, dt, p.b_kcontig != 0)) return false;
   if (dt == DType::F32)
-    return pieces == kMaxTilePieces && (p.K <= 768 || (p.K <= 2048 && (int64_t)((p.M + 31) / 32) * ((p.N + 31) / 32) <= 256));
+    return pieces == kMaxTilePieces && (p.K <= 768 || (p.K <= 2048 && tiles32 <= 256));
   return p.K <= 1024 || (p.K <= 2048 && rank > 128);
 }
 
