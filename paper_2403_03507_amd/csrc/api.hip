@@ -193,7 +193,7 @@ size_t step_r_bytes(bool left, int64_t kdim, int64_t ldim, int64_t r, DType dt, 
   return align_up((size_t)pieces * r * projected_row_length(left, kdim, ldim, dt) * 4);
 }
 // The most K pieces that any launch group gives the tensor
-int most_pieces(int64_t kdim, int64_t ldim, int64_t r, DType dt) { return tile_pieces((long)tiles64(ldim, r), kdim, dt, /*entries=*/0); }
+int most_pieces(int64_t kdim, int64_t ldim, int64_t r, DType dt) { return tile_pieces((long)tiles64(ldim, r), kdim, dt); }
 size_t step_n_bytes(int64_t ldim, int64_t r, DType dt) { return align_up((size_t)r * ldim * dtype_size(dt)); }
 size_t step_gpad_bytes(bool left, int64_t kdim, int64_t ldim, DType dt) {
   const int64_t ldp = projected_row_length(left, kdim, ldim, dt);
@@ -237,6 +237,13 @@ struct ProfScope {
   }
 };
 
+// The cut of a projection's contraction (pieces_of_call)
+struct PiecePlan {
+  int pieces;     // K pieces
+  bool in_place;  // every workgroup adds the pieces of its tile (launch_pieces_in_place): one R, no slabs
+  long tiles32;   // 32 x 32 tiles of the projections of its dtype that share the chip with it
+};
+
 // ---- one chunk of the step: tensors idx[0..n) with their W, G -------------------------------
 struct StepItem {
   int tensor;
@@ -247,16 +254,14 @@ struct StepItem {
   void* Gpad;    // room for a copy of G with padded rows (see projected_row_length), or nullptr
   int64_t ldr;   // row length of R, set by the projection
   bool large;    // the launches of the other chains count towards the large-tile kernel as well (count_over_chains)
-  int planned;   // K pieces of the projection (pieces_of_call)
-  long tiles32;  // 32 x 32 tiles of the projections of its dtype that share the chip with it
-  int pieces;    // slabs of R: as planned (pieces_of_call), as many as there is room for, then as many as the projection makes
+  PiecePlan plan;
+  int pieces;    // slabs of R: as planned, as many as there is room for, then as many as the projection makes
 };
 
 // The K pieces of every tensor of a call.  The tiles counted are those of the tensor's block of kMaxGroup consecutive
 // tensors of the call, whichever of them share a launch in the end: the chains of a call run at the same time, so their tiles
 // fill the chip together, and the rounding of R is the same for every number of chains, every workspace with room for the
 // pieces, and in galore_step_static.
-struct PiecePlan { int pieces; long tiles32; };
 std::vector<PiecePlan> pieces_of_call(const galore_ctx* ctx, int32_t first, int32_t count) {
   std::vector<PiecePlan> plan(count);
   const int r = ctx->hp.rank;
@@ -274,7 +279,7 @@ std::vector<PiecePlan> pieces_of_call(const galore_ctx* ctx, int32_t first, int3
     for (int i = a; i < b; ++i) {
       const TensorInfo& ti = ctx->tensors[first + i];
       const bool bf16 = ti.dt == DType::BF16;
-      plan[i] = PiecePlan{tile_pieces(tiles[bf16], ti.kdim, ti.dt, entries[bf16]), tiles32[bf16]};
+      plan[i] = PiecePlan{tile_pieces(tiles[bf16], ti.kdim, ti.dt), pieces_fit_in_place(tiles[bf16], ti.dt, entries[bf16]), tiles32[bf16]};
     }
   }
   return plan;
@@ -365,6 +370,8 @@ galore_status run_chain(galore_ctx* ctx, std::vector<StepItem>& items, float lr,
       tilesf.beta1 = hp.beta1; tilesf.beta2 = hp.beta2; tilesf.eps = hp.eps;
       GemmGroup groups{};           // the same in K pieces
       groups.beta1 = hp.beta1; groups.beta2 = hp.beta2; groups.eps = hp.eps;
+      GemmGroup placed{}, placedf{};  // as tiles and tilesf, with the K pieces one after the other in a workgroup
+      placedf.beta1 = hp.beta1; placedf.beta2 = hp.beta2; placedf.eps = hp.eps;
       GemmGroup rest[2] = {};       // [0] RIGHT, [1] LEFT: what neither takes (a side of fewer than 8 elements)
       PadGroup pads{};
       long t256 = 0;
@@ -442,8 +449,9 @@ galore_status run_chain(galore_ctx* ctx, std::vector<StepItem>& items, float lr,
           // 350M layer 61 against 68 us, a 2768 / 7312 layer at r = 272 297 against 313; with the caches flushed before each pass,
           // three 350M layers 187 against 211, two 1B layers 421 against 502).
           const bool whole = it.pieces == 1 && (ctx->fused_adam || (int64_t)r * ti.ldim >= kFuseAdamEntries);
+          if (it.plan.in_place) p.splits = it.plan.pieces;  // one R, as for a whole contraction
           // What is cut into K pieces can have them added, and updated, where they were formed: all of them, however many slabs there was room for
-          const bool grouped = k_groups_pay(p, dt, r, it.planned, it.tiles32);
+          const bool grouped = !it.plan.in_place && k_groups_pay(p, dt, r, it.plan.pieces, it.plan.tiles32);
           if (!ti.q8 && (whole || grouped)) {
             p.Mo = static_cast<float*>(ti.st.m.data);
             p.Vo = static_cast<float*>(ti.st.v.data);
@@ -451,23 +459,26 @@ galore_status run_chain(galore_ctx* ctx, std::vector<StepItem>& items, float lr,
             p.n_transposed = left;
             p.inv_c1 = ic1;
             p.inv_c2 = ic2;
-            if (grouped) p.splits = it.planned;
-            GemmGroup& to = grouped ? groups : tilesf;
+            if (grouped) p.splits = it.plan.pieces;
+            GemmGroup& to = grouped ? groups : it.plan.in_place ? placedf : tilesf;
             to.p[to.count++] = p;
             adam_done[ii] = 1;
           } else {
-            tiles.p[tiles.count++] = p;
+            GemmGroup& to = it.plan.in_place ? placed : tiles;
+            to.p[to.count++] = p;
           }
         }
       }
       {
-        ProfScope prof(ctx, GALORE_STAGE_PROJECT_LEFT, pg.count + pgf.count + tiles.count + tilesf.count + groups.count + rest[1].count > 0, stream);
+        ProfScope prof(ctx, GALORE_STAGE_PROJECT_LEFT, pg.count + pgf.count + tiles.count + tilesf.count + groups.count + placed.count + placedf.count + rest[1].count > 0, stream);
         hipError_t e = launch_pad_rows_group(pads, stream);
         if (e != hipSuccess) return hip_fail(ctx, e, "row padding launch");
         e = launch_proj_group(pgf, slabs, slab_bytes, stream, /*fuse_adam=*/true);
         if (e == hipSuccess) e = launch_proj_group(pg, slabs, slab_bytes, stream);
         if (e == hipSuccess) e = launch_tile_group(tilesf, dt, Epilogue::Adam, stream);
         if (e == hipSuccess) e = launch_k_groups(groups, dt, stream);
+        if (e == hipSuccess) e = launch_pieces_in_place(placedf, Epilogue::Adam, stream);
+        if (e == hipSuccess) e = launch_pieces_in_place(placed, Epilogue::StoreF32, stream);
         if (e == hipSuccess) e = launch_tile_group(tiles, dt, Epilogue::StoreF32, stream);
         if (e == hipSuccess) e = launch_gemm_group(rest[1], dt, /*a_kcontig=*/true, /*b_kcontig=*/false, Epilogue::StoreF32, stream);
         if (e != hipSuccess) return hip_fail(ctx, e, "projection GEMM launch");
@@ -966,7 +977,7 @@ galore_status galore_step(galore_ctx* ctx, const galore_tensor* W, const galore_
       const TensorInfo& ti = ctx->tensors[first + pos];
       const size_t need = step_need(ti.left, ti.kdim, ti.ldim, ctx->hp.rank, ti.dt);
       if (!items.empty() && used + need > limit) break;
-      items.push_back(StepItem{first + pos, &W[pos], &G[pos], nullptr, nullptr, nullptr, ti.ldim, false, plan[pos].pieces, plan[pos].tiles32, plan[pos].pieces});
+      items.push_back(StepItem{first + pos, &W[pos], &G[pos], nullptr, nullptr, nullptr, ti.ldim, false, plan[pos], plan[pos].in_place ? 1 : plan[pos].pieces});
       used += need;
       ++pos;
     }
@@ -1013,7 +1024,7 @@ galore_status galore_step_static(galore_ctx* ctx, const galore_tensor* W, const 
       const TensorInfo& ti = ctx->tensors[first + pos];
       const size_t need = step_need(ti.left, ti.kdim, ti.ldim, r, ti.dt);
       if (used + need > kStaticScratchBytes) break;
-      items.push_back(StepItem{first + pos, &W[pos], &G[pos], nullptr, nullptr, nullptr, ti.ldim, false, plan[pos].pieces, plan[pos].tiles32, plan[pos].pieces});
+      items.push_back(StepItem{first + pos, &W[pos], &G[pos], nullptr, nullptr, nullptr, ti.ldim, false, plan[pos], plan[pos].in_place ? 1 : plan[pos].pieces});
       used += need;
       ++pos;
     }

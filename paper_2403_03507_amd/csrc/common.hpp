@@ -63,9 +63,13 @@ hipError_t launch_gemm_group(GemmGroup& g, DType dt, bool a_kcontig, bool b_kcon
 bool tile_problem_fits(const GemmProblem& p, DType dt, bool b_kcontig);
 hipError_t launch_tile_group(GemmGroup& g, DType dt, Epilogue epi, hipStream_t stream);
 constexpr int kMaxTilePieces = 4;
-constexpr long kSplitBelowTiles = 224, kSplitBelowTilesF32 = 180;  // a launch of as many 64 x 64 tiles keeps its contractions whole
+constexpr long kSplitBelowTiles = 224;  // a launch of as many 64 x 64 tiles keeps its contractions whole
 constexpr int64_t kFuseAdamEntries = 65536;  // entries of R from which a whole contraction runs the update block by itself
-int tile_pieces(long tiles, int64_t K, DType dt, int64_t entries);  // entries: of the smallest R that the launches share
+int tile_pieces(long tiles, int64_t K, DType dt);
+// fp32 in 64 x 64 tiles, StoreF32 or Adam, with the `splits` K pieces of a tile added by the workgroup that forms them: the bits of a slab per piece
+// in one R.  entries: of the smallest R that the launches share.
+bool pieces_fit_in_place(long tiles, DType dt, int64_t entries);
+hipError_t launch_pieces_in_place(GemmGroup& g, Epilogue epi, hipStream_t stream);
 // The product in K pieces with the update block of Algorithm 2 on their sum, in one launch: every tile's pieces in one workgroup.  Operands as
 // for Epilogue::Adam of launch_tile_group.  bf16: the results are those of `splits` slabs and the Adam kernel, to the bit; fp32: the contraction is cut in 16.
 // tiles32: 32 x 32 tiles of the launches that share the chip.

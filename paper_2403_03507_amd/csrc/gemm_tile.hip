@@ -39,6 +39,22 @@ template <class T, int BM, int BN> hipError_t launch(GemmGroup& g, Epilogue epi,
   return hipGetLastError();
 }
 
+template <Epilogue EPI> hipError_t launch_in_place(GemmGroup& g, hipStream_t stream) {
+  long total = 0;
+  for (int i = 0; i < g.count; ++i) {
+    GemmProblem& p = g.p[i];
+    p.tile_begin = (int32_t)total;
+    p.tiles_m = (p.M + 63) / 64;
+    p.tiles_n = (p.N + 63) / 64;
+    if (p.splits < 1) p.splits = 1;
+    total += (long)p.tiles_m * p.tiles_n;
+  }
+  if (total > INT32_MAX) return hipErrorInvalidValue;
+  g.total_tiles = (int32_t)total;
+  hipLaunchKernelGGL((gemm_tile_kernel<float, 64, 64, EPI, true, false, 1, true>), dim3((unsigned)total), dim3(256), 0, stream, g);
+  return hipGetLastError();
+}
+
 // Aligned bf16 operands over whole K steps: the problem may run on DirectTile.
 bool fits_direct(const GemmProblem& p, DType dt) {
   const bool kc = p.b_kcontig != 0;
@@ -223,17 +239,22 @@ int direct_pieces(const GemmProblem& p, DType dt, bool b_kcontig, int most) {
 // leave CUs idle, at most 4 (every piece is another fp32 copy of the product to write and to read).  Contractions under
 // 512 stay whole.  Whole steps, us, with 1 / 2 / 4 / 8 pieces: 3805 x 3805 at r = 152 (180 tiles) 71.6 / 65.4 / 61.8 /
 // 66.9; fp32 512 x 512 at r = 128 (16 tiles) 31.0 / 28.5 / 26.6 / 26.6; 2048 x 2048 at r = 512 (256 tiles) 32.3 / 34.8 / 36.1.
-// fp32, in three pieces / whole with Adam in the epilogue: a 512 / 1376 layer at r = 128 (196 tiles) 43.6 / 39.9, a 1024 / 2736 layer at r = 64 (193)
-// 79.9 / 66.6, 1536 x 4096 at r = 192 (192) 68.4 / 68.4, flushed 77.7 / 76.4; 2048 x 5504 at r = 128 (172) 86.7 / 89.2, 768 x 2048 at r = 256 (128) 36.1 / 38.9;
-// where Adam stays a launch of its own (a 1024 / 2736 layer at r = 32, 193 tiles) 70.7 / 86.7, or does for some (a 512 / 1376 layer at r = 96) 40.7 / 50.2: `entries`
-// are those of the smallest R of the call.
-int tile_pieces(long tiles, int64_t K, DType dt, int64_t entries) {
+int tile_pieces(long tiles, int64_t K, DType dt) {
   if (tiles < 1 || tiles >= kSplitBelowTiles || K < 512) return 1;
-  if (dt == DType::F32 && tiles >= kSplitBelowTilesF32 && entries >= kFuseAdamEntries) return 1;
   const int64_t by_k = K / (dt == DType::BF16 ? 256 : 128);
   int64_t pieces = (512 + tiles - 1) / tiles;
   pieces = pieces < by_k ? pieces : by_k;
   return (int)(pieces < kMaxTilePieces ? pieces : kMaxTilePieces);
+}
+
+// Few enough tiles for pieces (3 here), enough for a workgroup a CU on most CUs: then the launch of the slabs' sum and their trip through memory cost more
+// than the pieces' extra workgroups gain.  Whole steps, us, slabs / in place: a 512 / 1376 layer at r = 128 (196 tiles) 42.7 / 38.6, a 1024 / 2736 layer
+// at r = 64 (193) 79.2 / 66.2, 640 x 5888 at r = 128 (184) 42.8 / 37.4, 11776 x 1024 at r = 64 (184) 60.0 / 55.1; with 8-bit moments, whose update stays a launch
+// of its own, 512 x 12544 at r = 64 60.7 / 48.5, six 1024 x 2048 at r = 32 80.2 / 64.3.  Below 180 tiles: 2048 x 5504 at r = 128 (172) 86.7 / 89.2, 768 x 2048 at
+// r = 256 (128) 36.1 / 38.9.  Where Adam stays a launch of its own for an R that is small (kFuseAdamEntries), as for a 1024 / 2736 layer at r = 32 70.7 / 86.7,
+// a 512 / 1376 layer at r = 96 40.7 / 50.2.
+bool pieces_fit_in_place(long tiles, DType dt, int64_t entries) {
+  return dt == DType::F32 && tiles >= 180 && tiles < kSplitBelowTiles && entries >= kFuseAdamEntries;
 }
 
 // bf16 contractions short enough for one CU to draw a tile's operands (256 KB at K = 1024) in about the time of the launch that goes.  Whole steps of
@@ -248,6 +269,18 @@ bool k_groups_pay(const GemmProblem& p, DType dt, int rank, int pieces, long til
   if (dt == DType::F32)
     return pieces == kMaxTilePieces && (p.K <= 768 || (p.K <= 2048 && tiles32 <= 256));
   return p.K <= 1024 || (p.K <= 2048 && rank > 128);
+}
+
+hipError_t launch_pieces_in_place(GemmGroup& g, Epilogue epi, hipStream_t stream) {
+  if (g.count <= 0) return hipSuccess;
+  if (g.count > kMaxGroup) return hipErrorInvalidValue;
+  for (int i = 0; i < g.count; ++i) {
+    const GemmProblem& p = g.p[i];
+    if (!tile_problem_fits(p, DType::F32, p.b_kcontig != 0) || p.splits > kMaxTilePieces || (p.splits > 1 && p.K < 64 * p.splits)) return hipErrorInvalidValue;
+    if (epi == Epilogue::Adam && (!p.Mo || !p.Vo || !p.Nout)) return hipErrorInvalidValue;
+  }
+  if (epi == Epilogue::Adam) return launch_in_place<Epilogue::Adam>(g, stream);
+  return epi == Epilogue::StoreF32 ? launch_in_place<Epilogue::StoreF32>(g, stream) : hipErrorInvalidValue;
 }
 
 hipError_t launch_k_groups(GemmGroup& g, DType dt, hipStream_t stream) {

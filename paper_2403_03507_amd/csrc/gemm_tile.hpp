@@ -138,15 +138,18 @@ struct DirectTile {
 };
 
 // AKC: A as [M][K]; else (StoreF32 only) as [K][M].  DIRECT: see DirectTile; K is a multiple of 64.
+// IN_PLACE (64 x 64, Adam or StoreF32): a workgroup adds the pr.splits K pieces of its tile itself, one after the other, so that a sum is no longer a
+// chain than with a slab per piece, and has its bits.  Costs 16 registers of a lane and nothing that shows: see gemm_tile.hip.
 // KG (Adam only): the K pieces of a tile are the work of KG groups of 4 wavefronts of one workgroup, which add their products in LDS, in
 // the order in which the Adam kernel adds slabs.  A launch and the trip of the slabs through memory less, for the rate at which one CU
 // draws the whole contraction's operands.
-template <class T, int BM, int BN_, Epilogue EPI, bool AKC = true, bool DIRECT = false, int KG = 1>
+template <class T, int BM, int BN_, Epilogue EPI, bool AKC = true, bool DIRECT = false, int KG = 1, bool IN_PLACE = false>
 __global__ __launch_bounds__(DIRECT ? 512 : 256 * KG, KG > 1 ? KG : 2) void gemm_tile_kernel(const GemmGroup grp) {
   using Cfg = SmallTile<T, BM, BN_>;
   using ET = ElemTraits<T>;
   constexpr int NT = DIRECT ? 512 : 256 * KG;
   static_assert(KG == 1 || (EPI == Epilogue::Adam && BM == 64 && !DIRECT), "");
+  static_assert(!IN_PLACE || (KG == 1 && AKC && BM == 64 && BN_ == 64 && !DIRECT && (EPI == Epilogue::Adam || EPI == Epilogue::StoreF32)), "");
   constexpr int BN = Cfg::BN, BK = DIRECT ? DirectTile::BK : Cfg::BK, SP = Cfg::SP, ROWS = Cfg::ROWS;
   constexpr int WM = BM / 2, WN = BN / (DIRECT ? 4 : 2), TM = WM / 32, TN = WN / 32;
   using AOp = typename Cfg::A;
@@ -170,12 +173,12 @@ __global__ __launch_bounds__(DIRECT ? 512 : 256 * KG, KG > 1 ? KG : 2) void gemm
   const GemmProblem& pr = grp.p[pi];
   const int tiles = pr.tiles_m * pr.tiles_n;
   const int item = bid - pr.tile_begin;
-  const int slab = KG > 1 ? 0 : item / tiles, piece = KG > 1 ? group : slab;
+  const int slab = KG > 1 || IN_PLACE ? 0 : item / tiles, piece = KG > 1 ? group : slab;
   int tm, tn;
   tile_coords(item - slab * tiles, pr.tiles_m, pr.tiles_n, tm, tn);
   const int m0 = tm * BM, n0 = tn * BN;
   const int M = pr.M, N = pr.N, K = pr.K;
-  const int KT = (K + BK - 1) / BK, S = KG > 1 ? KG : pr.splits > 1 ? pr.splits : 1;
+  const int KT = (K + BK - 1) / BK, S = KG > 1 ? KG : !IN_PLACE && pr.splits > 1 ? pr.splits : 1;
   const int first = (int)((long long)piece * KT / S), last = (int)((long long)(piece + 1) * KT / S);
   const T* __restrict__ A = static_cast<const T*>(pr.A);
   const T* __restrict__ B = static_cast<const T*>(pr.B);
@@ -187,6 +190,10 @@ __global__ __launch_bounds__(DIRECT ? 512 : 256 * KG, KG > 1 ? KG : 2) void gemm
     for (int j = 0; j < TN; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+  f32x16 done;  // IN_PLACE: the pieces before the current one; -0 + x is x, also for x = -0
+#pragma unroll
+  for (int v = 0; v < 16; ++v) done[v] = -0.f;
+  int piece_of = 0, piece_end = IN_PLACE ? KT / pr.splits : 0;
 
   // W pieces of the weight update: piece q of pass ps is row ps * ROWS + q * RPP + tid / CPW, columns WVEC (tid % CPW) ..
   constexpr int WVEC = ET::VEC;
@@ -296,6 +303,13 @@ __global__ __launch_bounds__(DIRECT ? 512 : 256 * KG, KG > 1 ? KG : 2) void gemm
         __syncthreads();
         return;
       }
+      if constexpr (IN_PLACE) {
+        if (kt == piece_end) {
+          piece_end = (int)((long long)(++piece_of + 1) * KT / pr.splits);
+#pragma unroll
+          for (int v = 0; v < 16; ++v) { done[v] += acc[0][0][v]; acc[0][0][v] = 0.f; }
+        }
+      }
       AOp::template store<AKC>(ra, As, m0, M, k, K, tail || edge_m, gtid);
       BOp::template store<BKC>(rb, Bs, n0, N, k, K, tail || edge_n, gtid);
       __syncthreads();
@@ -333,6 +347,11 @@ __global__ __launch_bounds__(DIRECT ? 512 : 256 * KG, KG > 1 ? KG : 2) void gemm
   } else {
     if (pr.b_kcontig) run(std::true_type{});
     else run(std::false_type{});
+  }
+
+  if constexpr (IN_PLACE) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[0][0][v] = done[v] + acc[0][0][v];
   }
 
   // Epilogue: ROWS rows at a time through LDS, so that global accesses are 16 contiguous bytes per lane.  Accumulator
