@@ -268,18 +268,18 @@ std::vector<PiecePlan> pieces_of_call(const galore_ctx* ctx, int32_t first, int3
   for (int a = 0; a < count; a += kMaxGroup) {
     const int b = std::min(a + kMaxGroup, count);
     long tiles[2] = {0, 0}, tiles32[2] = {0, 0};  // by dtype: no launch mixes them
-    int64_t entries[2] = {INT64_MAX, INT64_MAX};  // of the smallest R
+    bool in_place[2] = {true, true};
     for (int i = a; i < b; ++i) {
       const TensorInfo& ti = ctx->tensors[first + i];
       const bool bf16 = ti.dt == DType::BF16;
       tiles[bf16] += (long)tiles64(ti.ldim, r);
       tiles32[bf16] += (long)(((int64_t)r + 31) / 32 * ((ti.ldim + 31) / 32));
-      entries[bf16] = std::min(entries[bf16], r * ti.ldim);
+      in_place[bf16] = in_place[bf16] && pieces_add_up_in_place(ti.left, ti.kdim, ti.ldim, r);
     }
     for (int i = a; i < b; ++i) {
       const TensorInfo& ti = ctx->tensors[first + i];
       const bool bf16 = ti.dt == DType::BF16;
-      plan[i] = PiecePlan{tile_pieces(tiles[bf16], ti.kdim, ti.dt), pieces_fit_in_place(tiles[bf16], ti.dt, entries[bf16]), tiles32[bf16]};
+      plan[i] = PiecePlan{tile_pieces(tiles[bf16], ti.kdim, ti.dt), !bf16 && in_place[0] && tiles[0] >= kInPlaceTiles && tiles[0] < kSplitBelowTiles, tiles32[bf16]};
     }
   }
   return plan;

@@ -67,8 +67,9 @@ constexpr long kSplitBelowTiles = 224;  // a launch of as many 64 x 64 tiles kee
 constexpr int64_t kFuseAdamEntries = 65536;  // entries of R from which a whole contraction runs the update block by itself
 int tile_pieces(long tiles, int64_t K, DType dt);
 // fp32 in 64 x 64 tiles, StoreF32 or Adam, with the `splits` K pieces of a tile added by the workgroup that forms them: the bits of a slab per piece
-// in one R.  entries: of the smallest R that the launches share.
-bool pieces_fit_in_place(long tiles, DType dt, int64_t entries);
+// in one R.  Where all fp32 tensors that share the chip suit it (pieces_add_up_in_place) and have kInPlaceTiles to kSplitBelowTiles tiles together.
+constexpr long kInPlaceTiles = 180;
+bool pieces_add_up_in_place(bool left, int64_t K, int64_t ldim, int64_t r);
 hipError_t launch_pieces_in_place(GemmGroup& g, Epilogue epi, hipStream_t stream);
 // The product in K pieces with the update block of Algorithm 2 on their sum, in one launch: every tile's pieces in one workgroup.  Operands as
 // for Epilogue::Adam of launch_tile_group.  bf16: the results are those of `splits` slabs and the Adam kernel, to the bit; fp32: the contraction is cut in 16.

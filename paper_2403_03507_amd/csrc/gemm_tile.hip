@@ -253,8 +253,11 @@ int tile_pieces(long tiles, int64_t K, DType dt) {
 // of its own, 512 x 12544 at r = 64 60.7 / 48.5, six 1024 x 2048 at r = 32 80.2 / 64.3.  Below 180 tiles: 2048 x 5504 at r = 128 (172) 86.7 / 89.2, 768 x 2048 at
 // r = 256 (128) 36.1 / 38.9.  Where Adam stays a launch of its own for an R that is small (kFuseAdamEntries), as for a 1024 / 2736 layer at r = 32 70.7 / 86.7,
 // a 512 / 1376 layer at r = 96 40.7 / 50.2.
-bool pieces_fit_in_place(long tiles, DType dt, int64_t entries) {
-  return dt == DType::F32 && tiles >= 180 && tiles < kSplitBelowTiles && entries >= kFuseAdamEntries;
+// The longer the contraction, the less the launch weighs against the balance of three times as many workgroups, save where every panel of a LEFT
+// tensor's G is read by one workgroup (r <= 64) and the rate of those reads is what counts: K = 1792, r = 128 83.4 / 83.2 (LEFT) and 83.2 / 81.6 (RIGHT), K = 2048
+// 88.2 / 90.0 and 87.9 / 88.1 (r = 100 91.6 / 90.5), K = 3072 120.3 / 127.7 and 120.1 / 125.0 (184 tiles each); r = 64 LEFT K = 2048 127.7 / 97.9, 4096 248.8 / 198.5.
+bool pieces_add_up_in_place(bool left, int64_t K, int64_t ldim, int64_t r) {
+  return r * ldim >= kFuseAdamEntries && (left ? K < 2048 || r <= 64 : K <= 2048);
 }
 
 // bf16 contractions short enough for one CU to draw a tile's operands (256 KB at K = 1024) in about the time of the launch that goes.  Whole steps of

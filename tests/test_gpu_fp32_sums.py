@@ -74,3 +74,25 @@ def test_a_workgroup_adds_pieces_as_slabs_are_added(k, l, rank, left, moments):
     assert adam == ([0, 2] if moments == "f32" else [2, 2])
     assert all(torch.equal(a, b) for a, b in zip(*out))
     assert not torch.equal(out[0][0], W0[0])
+
+
+# short side, rank, side, whether the pieces of 184 tiles add up in place (Adam in that launch) or leave as slabs
+@pytest.mark.parametrize("k,rank,left,in_place", [(2047, 128, True, True), (2048, 128, True, False), (2049, 64, True, True), (3072, 65, True, False),
+                                                  (2048, 128, False, True), (2049, 128, False, False), (3072, 64, False, False)])
+def test_long_contractions_leave_slabs(k, rank, left, in_place):
+    l = 184 // -(-rank // 64) * 64
+    g = torch.Generator(device="cuda").manual_seed(k)
+    rand = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    m, n = (k, l) if left else (l, k)
+    W, G = 0.02 * rand(m, n), rand(m, n)
+    opt = gb.GaLore([W], rank, update_gap=1 << 30, auto_refresh=False)
+    opt.proj[0].copy_(torch.linalg.qr(rand(k, rank))[0])
+    gb.galore_profile_start(opt.ctx)
+    opt.step([W], [G], 1e-3)
+    assert gb.galore_profile_stop(opt.ctx)["adam"][1] == (0 if in_place else 1)
+    a, b = (opt.proj[0].t(), G) if left else (G, opt.proj[0])
+    R, scale = a.double() @ b.double(), a.double().abs() @ b.double().abs()
+    b1 = float(torch.tensor(0.9))
+    # entries of R: a chain of products and the sums of the pieces, 2^-24 of the sum of absolute values each; M in two roundings
+    assert bool(((opt.M[0].double() - (1 - b1) * R).abs() <= (1 - b1) * 2.0 ** -24 * (_chain(k, 3) + 2 + 4) * scale).all())
+    opt.close()
