@@ -591,6 +591,24 @@ bool library_streams_ready(const galore_ctx* ctx) {
   return ctx->fork_ev != nullptr;
 }
 
+// A bf16 step that the chip takes 150 to 190 us for by run_step_chunk's estimate gains from a second chain above rank 256, where one chain's projection
+// leaves most of its second round of 128 x 128 tiles (two a CU) empty, or takes large tiles that two chains would not.  One / two / three chains, us: 2048 / 5504 at
+// r = 257 (579 tiles) 182 / 165 / 164, r = 288 176 / 160 / 159, 1920 / 5120 at r = 320 (540) 139 / 126 / 132, 1600 / 4288 at r = 448 138 / 123 / 130, 1536 / 4096 at
+// r = 512 126 / 118 / 137, two 1280 / 3456 layers at r = 320 134 / 130 / 138, on large tiles in one chain 1792 / 4864 at r = 384 142 / 125 / 132.  Not with one round:
+// 1792 / 4864 at r = 352 (510) 128 / 139 / 142; nor where several chains count as large together: 1664 / 4480 at r = 448 141 / 150 / 148, 1792 / 4864 at r = 448
+// 153 / 158 / 160; nor where a rank of no multiple of 64 keeps the weight update on small tiles too: 1792 / 4864 at r = 400 153 / 163 / 168, 1664 / 4480 at r = 544
+// 166 / 172 / 181; nor at r = 256: 2176 / 5824 125 / 130 / 141.
+bool second_chain_pays(const galore_ctx* ctx, const std::vector<StepItem>& items) {
+  const int r = ctx->hp.rank;
+  long t256 = 0, t128 = 0;
+  for (const StepItem& it : items) {
+    if (it.large) return false;
+    t256 += projection_tiles256(ctx, it);
+    t128 += (long)((r + 127) / 128 * ((ctx->tensors[it.tensor].ldim + 127) / 128));
+  }
+  return r > 256 && (t256 >= kLargeProjectionTiles ? r % 64 == 0 : t128 > 512);
+}
+
 // One chunk of the step: carve the workspace, split the tensors into chains of similar cost and
 // run the chains concurrently.  Chains touch disjoint tensors and disjoint workspace regions.
 galore_status run_step_chunk(galore_ctx* ctx, std::vector<StepItem>& items, float lr) {
@@ -636,11 +654,12 @@ galore_status run_step_chunk(galore_ctx* ctx, std::vector<StepItem>& items, floa
   if (lanes > 1 && !library_streams_ready(ctx)) lanes = 1;
   if ((int)items.size() < 2) lanes = 1;
   // Forking and joining streams costs the host some ten calls into the runtime, and launches that share the chip are shorter of tiles
-  // each: a step that the chip finishes soon runs as one chain.  The estimate: all traffic at 4 TB/s plus all products at 0.8 PFLOP/s (bf16) or 80
+  // each: a step that the chip finishes soon runs as one chain (between 150 and 190: second_chain_pays).  The estimate: all traffic at 4 TB/s plus all products at 0.8 PFLOP/s (bf16) or 80
   // TFLOP/s (fp32).  Whole steps of one layer, us, in 1 / 2 / 3 chains: 2304 / 6144 at r = 128 (estimate 150) 94 / 112 / 117, 2560 / 6912 at r = 64
   // (152) 106 / 114 / 121, r = 128 (186) 112 / 132 / 137, 3072 / 8192 at r = 64 (215) 158 / 152 / 158.
   // Two chains leave each launch more tiles than three: 3072 / 8192 at r = 128 185 / 172 / 183, 4096 / 11008 at r = 64 279 / 273 / 279, r = 128 302 / 292 / 302,
-  // three 2048 / 5504 layers at r = 128 273 / 265 / 277, fp32 2048 / 5504 at r = 64 195 / 197 / 224, 1536 / 4096 at r = 256 318 / 299 / 302.  The third stays for bf16 at
+  // three 2048 / 5504 layers at r = 128 273 / 265 / 277, fp32 2048 / 5504 at r = 64 195 / 197 / 224, 1536 / 4096 at r = 256 318 / 299 / 302 (fp32 from r = 256 on with
+  // short sides up to 1152: two or three within 4 % of each other, either way: 1024 / 2736 at r = 256 158 / 154, r = 320 180 / 183, r = 512 273 / 264).  The third stays for bf16 at
   // higher ranks, where the GEMMs of three chains are in flight most of the time (4096 / 11008 at r = 512 557 / 533 / 536, r = 1024 968 / 964 / 970, with 8-bit
   // moments 988 in two and 980 in three over several states).
   double us = 0;
@@ -648,14 +667,14 @@ galore_status run_step_chunk(galore_ctx* ctx, std::vector<StepItem>& items, floa
     const TensorInfo& ti = ctx->tensors[it.tensor];
     us += (3.0 * ti.rows * ti.cols * dtype_size(ti.dt) + 16.0 * r * ti.ldim) / 4e6 + 4.0 * ti.rows * ti.cols * r / (ti.dt == DType::BF16 ? 8e8 : 8e7);
   }
-  bool two = r < 256;
-  for (const StepItem& it : items) two = two || ctx->tensors[it.tensor].dt == DType::F32;
-  if (lanes > 2 && two) lanes = 2;
-  if (us < 190.0) lanes = 1;
+  bool fp32 = false;
+  for (const StepItem& it : items) fp32 = fp32 || ctx->tensors[it.tensor].dt == DType::F32;
+  count_over_chains(ctx, items);
+  if (lanes > 2 && (r < 256 || fp32 || us < 190.0)) lanes = 2;
+  if (us < 190.0 && (fp32 || us < 150.0 || !second_chain_pays(ctx, items))) lanes = 1;
   if (lanes <= 1)
     return run_chain(ctx, items, lr, ctx->stream, reinterpret_cast<float*>(ctx->ws + slab_off), slab_avail < kSlabMax ? slab_avail : kSlabMax);
 
-  count_over_chains(ctx, items);
   // Greedy balance by cost (m n, as r is shared): heaviest tensor first, always into the lightest chain.
   std::vector<int> order(items.size());
   for (size_t i = 0; i < items.size(); ++i) order[i] = (int)i;

@@ -62,3 +62,39 @@ def test_forked_chains_count_their_tiles_together(d, f, rank, large):
     assert stages["project_left"][1] == stages["back"][1] == 3   # three chains
     assert (stages["adam"][1] > 0) == large, stages
     opt.close()
+
+
+# One layer by estimate between 150 and 190 us: a second chain above rank 256 where one chain leaves a second round of 128 x 128 tiles (512 a round) nearly empty
+# (2048: 579, 1801: 531) or takes large tiles alone (r = 384), not with one round (1792 at r = 352: 510), on large tiles either way (r = 448), with
+# a rank of no multiple of 64 beside large tiles (r = 400), at r = 256, or in fp32
+@pytest.mark.parametrize("d,f,rank,dtype,chains", [(2048, 5504, 288, "bf16", 2), (1801, 4871, 333, "bf16", 2), (1792, 4864, 384, "bf16", 2), (1792, 4864, 352, "bf16", 1),
+                                                   (1664, 4480, 448, "bf16", 1), (1792, 4864, 400, "bf16", 1), (2048, 5504, 256, "bf16", 1), (1024, 2736, 200, "f32", 1)])
+def test_chains_of_a_short_step(d, f, rank, dtype, chains):
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    shapes = [(d, d)] * 4 + [(d, f)] * 2 + [(f, d)]
+    g = torch.Generator(device="cuda").manual_seed(rank)
+    rand = lambda *s: torch.randn(*s, generator=g, device="cuda").to(tdt)
+    W0, G, P = [0.02 * rand(*s) for s in shapes], [rand(*s) for s in shapes], [rand(min(s), rank) / 64 for s in shapes]
+    out, launches = [], []
+    for lanes in (1, 3):
+        W = [w.clone() for w in W0]
+        opt = gb.GaLore(W, rank, update_gap=1 << 30, auto_refresh=False)
+        gb.galore_set_concurrency(opt.ctx, lanes)
+        for i, p in enumerate(P):
+            opt.proj[i].copy_(p)
+            opt.V[i].fill_(1.0)
+            opt.set_step(i, 1000)
+        gb.galore_profile_start(opt.ctx)
+        for _ in range(2):
+            opt.step(W, G, 1e-3)
+        launches.append(gb.galore_profile_stop(opt.ctx)["back"][1])
+        torch.cuda.synchronize()
+        out.append(W + [x.clone() for x in opt.M + opt.V])
+        opt.close()
+    assert launches == [2, 2 * chains]
+    for i, (a, b) in enumerate(zip(*out)):
+        # K pieces of large tiles may differ between the settings (fp32 rounding of R); short sides of no multiple of 64 and ranks that fill no large tile never take them
+        if rank == 384:
+            assert float((a.double() - b.double()).norm() / b.double().norm()) <= (1e-6 if a.dtype == torch.float32 else 1e-4), i
+        else:
+            assert torch.equal(a, b), i
