@@ -653,15 +653,16 @@ galore_status run_step_chunk(galore_ctx* ctx, std::vector<StepItem>& items, floa
   int lanes = ctx->lanes;
   if (lanes > 1 && !library_streams_ready(ctx)) lanes = 1;
   if ((int)items.size() < 2) lanes = 1;
-  // Forking and joining streams costs the host some ten calls into the runtime, and launches that share the chip are shorter of tiles
-  // each: a step that the chip finishes soon runs as one chain (between 150 and 190: second_chain_pays).  The estimate: all traffic at 4 TB/s plus all products at 0.8 PFLOP/s (bf16) or 80
-  // TFLOP/s (fp32).  Whole steps of one layer, us, in 1 / 2 / 3 chains: 2304 / 6144 at r = 128 (estimate 150) 94 / 112 / 117, 2560 / 6912 at r = 64
-  // (152) 106 / 114 / 121, r = 128 (186) 112 / 132 / 137, 3072 / 8192 at r = 64 (215) 158 / 152 / 158.
-  // Two chains leave each launch more tiles than three: 3072 / 8192 at r = 128 185 / 172 / 183, 4096 / 11008 at r = 64 279 / 273 / 279, r = 128 302 / 292 / 302,
-  // three 2048 / 5504 layers at r = 128 273 / 265 / 277, fp32 2048 / 5504 at r = 64 195 / 197 / 224, 1536 / 4096 at r = 256 318 / 299 / 302 (fp32 from r = 256 on with
-  // short sides up to 1152: two or three within 4 % of each other, either way: 1024 / 2736 at r = 256 158 / 154, r = 320 180 / 183, r = 512 273 / 264).  The third stays for bf16 at
-  // higher ranks, where the GEMMs of three chains are in flight most of the time (4096 / 11008 at r = 512 557 / 533 / 536, r = 1024 968 / 964 / 970, with 8-bit
-  // moments 988 in two and 980 in three over several states).
+  // Forking and joining streams costs the host some ten calls into the runtime, and chains that share the chip have launches of fewer tiles each.  The
+  // estimate: all traffic at 4 TB/s plus all products at 0.8 PFLOP/s (bf16) or 80 TFLOP/s (fp32).  Whole steps of one layer, us, in 1 / 2 / 3 chains:
+  //   one under 190        2304 / 6144 at r = 128 (estimate 150) 94 / 112 / 117, 2560 / 6912 at r = 64 (152) 106 / 114 / 121, r = 128 (186) 112 / 132 / 137; 3072 / 8192
+  //                        at r = 64 (215) 158 / 152 / 158; bf16 between 150 and 190: second_chain_pays
+  //   two below r = 256    3072 / 8192 at r = 128 185 / 172 / 183, 4096 / 11008 at r = 64 279 / 273 / 279, r = 128 302 / 292 / 302, three 2048 / 5504 layers at r = 128
+  //                        273 / 265 / 277: they leave each launch more tiles
+  //   two in fp32          2048 / 5504 at r = 64 195 / 197 / 224, 1536 / 4096 at r = 256 318 / 299 / 302 (from r = 256 on with short sides up to 1152 two and three are
+  //                        within 4 % of each other, either way: 1024 / 2736 at r = 256 - / 158 / 154, r = 320 180 / 183, r = 512 273 / 264)
+  //   else three           bf16, where the GEMMs of three are in flight most of the time: 4096 / 11008 at r = 512 557 / 533 / 536, r = 1024 968 / 964 / 970, with 8-bit
+  //                        moments 988 in two and 980 in three over several states
   double us = 0;
   for (const StepItem& it : items) {
     const TensorInfo& ti = ctx->tensors[it.tensor];

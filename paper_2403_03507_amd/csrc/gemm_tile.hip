@@ -144,11 +144,14 @@ hipError_t launch_narrow(GemmGroup& g, hipStream_t stream) {
 }
 
 // One round of DirectTile, a tile per CU, most CUs with a tile: the deeper ring draws 46 GB/s per CU where the register-staged tiles, several a
-// CU, reach 33.  Whole steps, us, on the other tiles / DirectTile: projection of one 350M layer at r = 256 (196 tiles) 51.8 / 48.9, r = 192 (three
-// quarters of the rows used) 44.4 / 46.3, a 4096 x 4096 weight at r = 768 (192) 94.1 / 84.8, 1024 (256) 108.7 / 98.2, 512 (128) 68.1 / 73.5, a 2048
-// / 5504 layer at r = 128 (193) 99.8 / 91.3, r = 96 93.3 / 84.7, a 768 / 2048 layer at r = 256 (144, K = 768) 36.4 / 39.2; in more than one round, 288 tiles
-// 80.1 / 87.2, 258 139.8 / 147.2, 386 140.6 / 130.1 but flushed 162.6 / 161.1, 726 246.6 / 228.6 but flushed 275.9 / 275.7.  Weight update: 2048 x 2048 (256 tiles) at
-// r = 128 22.3 / 21.6 (flushed 28.6 / 29.1), 256 26.5 / 24.9, 512 31.8 / 29.6, 1024 x 2752 (176) at r = 512 28.1 / 26.3; 2560 x 2560 (400) at r = 512 45.8 / 46.4.
+// CU, reach 33.  Whole steps, us, on the other tiles / DirectTile:
+//   256 tiles at most    one 350M layer at r = 256 (196) 51.8 / 48.9, 4096 x 4096 at r = 1024 (256) 108.7 / 98.2; in more than one round, 258 tiles 139.8 / 147.2,
+//                        288 80.1 / 87.2, 386 140.6 / 130.1 but flushed 162.6 / 161.1, 726 246.6 / 228.6 but flushed 275.9 / 275.7
+//   150 at least         4096 x 4096 at r = 768 (192) 94.1 / 84.8, r = 512 (128) 68.1 / 73.5
+//   K of 2048, or 1024   a 2048 / 5504 layer at r = 128 (193) 99.8 / 91.3, r = 96 (three quarters of the rows used) 93.3 / 84.7; a 350M layer (K = 1024) at r = 192 (three
+//   in used tiles        quarters) 44.4 / 46.3; a 768 / 2048 layer (K = 768) at r = 256 36.4 / 39.2
+//   the weight update    from 160 tiles: 1024 x 2752 at r = 512 (176) 28.1 / 26.3, to 256: 2560 x 2560 at r = 512 (400) 45.8 / 46.4; from K = 256: 2048 x 2048 (256) at
+//                        r = 128 22.3 / 21.6 but flushed 28.6 / 29.1, r = 256 26.5 / 24.9, r = 512 31.8 / 29.6
 bool direct_pays(const GemmGroup& g, long items128, bool update) {
   if (items128 > 256 || items128 < (update ? 160 : kDirectItems)) return false;
   double used = 0;
@@ -164,16 +167,16 @@ bool direct_pays(const GemmGroup& g, long items128, bool update) {
   return shortest >= 2048 || (shortest >= 1024 && used >= 0.8 * items128 * 128 * 128);
 }
 
-// A larger tile loads fewer bytes per flop through the L2 -> CU path, a smaller one gives more workgroups to hide latency
-// with: the largest that still makes a workgroup and a half per CU (128 x 128) or two (128 x 64).  Whole steps, us, with
-// the projection on 64 x 64 / 128 x 64 / 128 x 128 tiles: one 350M layer (772 / 388 / 196 tiles) 54.0 / 49.0 / 57.2, one
-// 1B layer (3088 / 1544 / 772) 266 / 244 / 230, one 3805 x 3805 weight at r = 152 (180 / 120 / 60, two K pieces) 65 / 68 / 83.
-// These are passes repeated on the same tensors; with the caches flushed before each pass, three 350M layers 183 / 190 / 189 (hence
-// 64 x 64 tiles there), two 130M layers 99 / 101 / 108, two 1B layers 502 / 448 / 420.
-// A projection whose rank leaves most of a larger tile's rows (or columns) empty stays on the smaller one (up to half as much again may go to padding: ranks
-// from 129 on): two 3329 / 8824 layers at r = 24 518.8 / 451.5 on 128 x 64 / 64 x 64, two 3328 / 8824 layers 423 / 411.
-// The weight update has more tiles than that and shorter contractions: 128 x 64 unless the contraction is long (r = 54 on
-// a 1105 / 2688 layer: 104 / 100 / 103; r = 401 on 1904 / 3968: 232 / 208 / 194).
+// A larger tile loads fewer bytes per flop through the L2 -> CU path, a smaller one gives more workgroups to hide latency with: the largest that
+// still makes a workgroup and a half per CU (128 x 128) or two (128 x 64).  Whole steps, us, with the projection on 64 x 64 / 128 x 64 / 128 x 128 tiles:
+//   500 tiles of 128 x 64    one 350M layer (772 / 388 / 196 tiles) 54.0 / 49.0 / 57.2, flushed three of them 183 / 190 / 189 (hence 64 x 64 there)
+//   350 tiles of 128 x 128   one 1B layer (3088 / 1544 / 772) 266 / 244 / 230, flushed two of them 502 / 448 / 420; 3805 x 3805 at r = 152 (180 / 120 / 60, two K pieces)
+//                            65 / 68 / 83; flushed two 130M layers 99 / 101 / 108
+//   half as much again for   two 3329 / 8824 layers at r = 24 451.5 on 64 x 64, 518.8 on 128 x 64, two 3328 / 8824 layers 411 and 423: what a larger tile
+//   padding at most          adds in empty rows (or columns) is work; ranks from 129 on fit
+//   the weight update        has more tiles and shorter contractions: 128 x 64 from 300 tiles on (r = 54 on a 1105 / 2688 layer 104 / 100 / 103), 128 x 128 from
+//                            K = 256 on (r = 401 on 1904 / 3968 232 / 208 / 194)
+// Flushed: the caches are written over before each pass; the others are passes repeated on the same tensors.
 template <class T> hipError_t launch_typed(GemmGroup& g, Epilogue epi, hipStream_t stream) {
   long items128 = 0, items96 = 0, items64 = 0;
   int longest = 0;
@@ -247,26 +250,27 @@ int tile_pieces(long tiles, int64_t K, DType dt) {
   return (int)(pieces < kMaxTilePieces ? pieces : kMaxTilePieces);
 }
 
-// Few enough tiles for pieces (3 here), enough for a workgroup a CU on most CUs: then the launch of the slabs' sum and their trip through memory cost more
-// than the pieces' extra workgroups gain.  Whole steps, us, slabs / in place: a 512 / 1376 layer at r = 128 (196 tiles) 42.7 / 38.6, a 1024 / 2736 layer
-// at r = 64 (193) 79.2 / 66.2, 640 x 5888 at r = 128 (184) 42.8 / 37.4, 11776 x 1024 at r = 64 (184) 60.0 / 55.1; with 8-bit moments, whose update stays a launch
-// of its own, 512 x 12544 at r = 64 60.7 / 48.5, six 1024 x 2048 at r = 32 80.2 / 64.3.  Below 180 tiles: 2048 x 5504 at r = 128 (172) 86.7 / 89.2, 768 x 2048 at
-// r = 256 (128) 36.1 / 38.9.  Where Adam stays a launch of its own for an R that is small (kFuseAdamEntries), as for a 1024 / 2736 layer at r = 32 70.7 / 86.7,
-// a 512 / 1376 layer at r = 96 40.7 / 50.2.
-// The longer the contraction, the less the launch weighs against the balance of three times as many workgroups, save where every panel of a LEFT
-// tensor's G is read by one workgroup (r <= 64) and the rate of those reads is what counts: K = 1792, r = 128 83.4 / 83.2 (LEFT) and 83.2 / 81.6 (RIGHT), K = 2048
-// 88.2 / 90.0 and 87.9 / 88.1 (r = 100 91.6 / 90.5), K = 3072 120.3 / 127.7 and 120.1 / 125.0 (184 tiles each); r = 64 LEFT K = 2048 127.7 / 97.9, 4096 248.8 / 198.5.
+// The launch that adds the slabs, and their trip through memory, against three times as many workgroups.  Whole steps, us, slabs / in place:
+//   180 tiles at least      a 512 / 1376 layer at r = 128 (196) 42.7 / 38.6, a 1024 / 2736 layer at r = 64 (193) 79.2 / 66.2, 640 x 5888 at r = 128 (184) 42.8 / 37.4,
+//                           11776 x 1024 at r = 64 (184) 60.0 / 55.1; 2048 x 5504 at r = 128 (172) 86.7 / 89.2, 768 x 2048 at r = 256 (128) 36.1 / 38.9
+//   8-bit moments, too      (Adam is a launch of its own either way) 512 x 12544 at r = 64 60.7 / 48.5, six 1024 x 2048 at r = 32 80.2 / 64.3
+//   kFuseAdamEntries        below, Adam would be one as well: a 1024 / 2736 layer at r = 32 70.7 / 86.7, a 512 / 1376 layer at r = 96 40.7 / 50.2
+//   K of 2048               the longer the contraction, the more the balance counts: r = 128, LEFT and RIGHT, K = 1792 83.4 / 83.2, 83.2 / 81.6, K = 2048 88.2 / 90.0,
+//                           87.9 / 88.1 (r = 100 RIGHT 91.6 / 90.5), K = 3072 120.3 / 127.7, 120.1 / 125.0
+//   any K, LEFT, r <= 64    every panel of G has one reader, and the rate of those reads counts: K = 2048 127.7 / 97.9, 4096 248.8 / 198.5; RIGHT 96.3 / 95.7, 187.8 / 193.5
 bool pieces_add_up_in_place(bool left, int64_t K, int64_t ldim, int64_t r) {
   return r * ldim >= kFuseAdamEntries && (left ? K < 2048 || r <= 64 : K <= 2048);
 }
 
-// bf16 contractions short enough for one CU to draw a tile's operands (256 KB at K = 1024) in about the time of the launch that goes.  Whole steps of
-// one weight, us, slabs / groups, repeated passes and flushed: 512 x 512 at r = 128 15.9 / 11.7, 19.4 / 15.3; 1024 x 1024 at r = 128 16.7 / 12.8, 20.5 / 18.6, 256 18.5 /
-// 13.4, 22.8 / 19.6; 1024 x 2736 at r = 128 22.0 / 16.1, 29.5 / 24.3; 2048 x 2048 at r = 128 21.2 / 19.0, 28.2 / 30.2, 256 25.1 / 21.8, 35.1 / 31.4; 3072 x 3072 at r = 128 29.7 / 31.5.
-// fp32 (NarrowTile), where the call has few enough tiles for 4 slabs: 512 x 512 at r = 128 19.9 / 14.0, 23.4 / 19.1 (in 64 x 64 tiles, bound by the matrix cores of the
-// CUs that have one, 20.7); 768 x 768 at r = 256 23.6 / 19.1, 29.9 / 24.4; 1024 x 1024 at r = 128 22.5 / 17.9, 28.0 / 23.9; 1024 x 2736 at r = 64 28.0 / 22.7, 36.2 / 30.6; 2048 x 2048 at r = 128
-// 39.2 / 37.3, 47.8 / 46.1.  In more than one round of its tiles only short contractions: 768 x 2048 at r = 256 (512) 35.6 / 33.9, 43.6 / 41.6; 1024 x 2736 at r = 192 (516) 47.2 / 51.9,
-// 1536 x 1536 at r = 192 (288) 41.2 / 44.1, 2048 x 5504 at r = 64 (344) 57.3 / 61.7, three 1664 x 1664 at r = 48 in one call (312) 48.0 / 51.0.
+// The launch that adds the slabs against one CU that draws a whole contraction's operands (256 KB at K = 1024).  Whole steps of one weight, us, slabs /
+// groups, repeated passes and flushed:
+//   bf16, K of 1024          512 x 512 at r = 128 15.9 / 11.7, 19.4 / 15.3; 1024 x 1024 at r = 128 16.7 / 12.8, 20.5 / 18.6; 1024 x 2736 at r = 128 22.0 / 16.1, 29.5 / 24.3
+//   2048 above rank 128      2048 x 2048 at r = 256 25.1 / 21.8, 35.1 / 31.4; r = 128 21.2 / 19.0 but 28.2 / 30.2; 3072 x 3072 at r = 128 29.7 / 31.5
+//   fp32 (NarrowTile), few   512 x 512 at r = 128 19.9 / 14.0, 23.4 / 19.1 (in 64 x 64 tiles, bound by the matrix cores of the CUs that have one, 20.7); 768 x 768 at r = 256
+//   enough tiles for 4       23.6 / 19.1, 29.9 / 24.4
+//   one round of its tiles   1024 x 1024 at r = 128 22.5 / 17.9, 28.0 / 23.9; 1024 x 2736 at r = 64 28.0 / 22.7, 36.2 / 30.6; 2048 x 2048 at r = 128 39.2 / 37.3, 47.8 / 46.1
+//   more to K = 768          768 x 2048 at r = 256 (512) 35.6 / 33.9, 43.6 / 41.6; 1024 x 2736 at r = 192 (516) 47.2 / 51.9, 1536 x 1536 at r = 192 (288) 41.2 / 44.1,
+//                            2048 x 5504 at r = 64 (344) 57.3 / 61.7, three 1664 x 1664 at r = 48 in one call (312) 48.0 / 51.0
 bool k_groups_pay(const GemmProblem& p, DType dt, int rank, int pieces, long tiles32) {
   if (pieces < 2 || pieces > kMaxTilePieces || !tile_problem_fits(p, dt, p.b_kcontig != 0)) return false;
   if (dt == DType::F32)
