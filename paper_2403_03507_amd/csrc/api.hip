@@ -241,7 +241,7 @@ struct ProfScope {
 struct PiecePlan {
   int pieces;     // K pieces
   bool in_place;  // every workgroup adds the pieces of its tile (launch_pieces_in_place): one R, no slabs
-  long tiles32;   // 32 x 32 tiles of the projections of its dtype that share the chip with it
+  bool grouped;   // all of them in one workgroup, with the update block (launch_k_groups)
 };
 
 // ---- one chunk of the step: tensors idx[0..n) with their W, G -------------------------------
@@ -276,11 +276,28 @@ std::vector<PiecePlan> pieces_of_call(const galore_ctx* ctx, int32_t first, int3
       tiles32[bf16] += (long)(((int64_t)r + 31) / 32 * ((ti.ldim + 31) / 32));
       in_place[bf16] = in_place[bf16] && pieces_add_up_in_place(ti.left, ti.kdim, ti.ldim, r);
     }
+    // K groups save the Adam launch where no other tensor of the dtype needs it, and no launch where they take two of their own (a launch serves one number of
+    // pieces in bf16).  Mixed calls in slabs / with what can in groups, us: bf16 at r = 64 512 x 640 with 768 x 1024 and 1024 x 1024 19.6 / 29.4, 1024 x 1024
+    // with 2304 x 2304 22.9 / 31.7, three 768 x 768 with two 200 x 1000 (small R, whole) 23.8 / 27.5; fp32 at r = 32 1024 x 1024 with 2304 x 2304 35.5 / 46.1.
+    int pieces[2] = {0, 0};
+    bool together[2] = {true, true};
     for (int i = a; i < b; ++i) {
       const TensorInfo& ti = ctx->tensors[first + i];
       const bool bf16 = ti.dt == DType::BF16;
-      plan[i] = PiecePlan{tile_pieces(tiles[bf16], ti.kdim, ti.dt), !bf16 && in_place[0] && tiles[0] >= kInPlaceTiles && tiles[0] < kSplitBelowTiles, tiles32[bf16]};
+      PiecePlan& pl = plan[i];
+      pl.pieces = tile_pieces(tiles[bf16], ti.kdim, ti.dt);
+      pl.in_place = !bf16 && in_place[0] && tiles[0] >= kInPlaceTiles && tiles[0] < kSplitBelowTiles;
+      GemmProblem p{};
+      p.M = ti.left ? r : (int)ti.rows; p.N = ti.left ? (int)ti.cols : r; p.K = (int)ti.kdim;
+      const bool epilogue = !ti.q8 && tile_problem_fits(p, ti.dt, !ti.left);  // Adam can run in its projection
+      pl.grouped = epilogue && !pl.in_place && k_groups_pay(ti.kdim, ti.dt, r, pl.pieces, tiles32[bf16]);
+      if (pl.grouped && bf16) {
+        together[1] = together[1] && (pieces[1] == 0 || pieces[1] == pl.pieces);
+        pieces[1] = pl.pieces;
+      }
+      if (!pl.grouped) together[bf16] = together[bf16] && epilogue && pl.pieces == 1 && r * ti.ldim >= kFuseAdamEntries;
     }
+    for (int i = a; i < b; ++i) plan[i].grouped = plan[i].grouped && together[ctx->tensors[first + i].dt == DType::BF16];
   }
   return plan;
 }
@@ -451,7 +468,7 @@ galore_status run_chain(galore_ctx* ctx, std::vector<StepItem>& items, float lr,
           const bool whole = it.pieces == 1 && (ctx->fused_adam || (int64_t)r * ti.ldim >= kFuseAdamEntries);
           if (it.plan.in_place) p.splits = it.plan.pieces;  // one R, as for a whole contraction
           // What is cut into K pieces can have them added, and updated, where they were formed: all of them, however many slabs there was room for
-          const bool grouped = !it.plan.in_place && k_groups_pay(p, dt, r, it.plan.pieces, it.plan.tiles32);
+          const bool grouped = it.plan.grouped;
           if (!ti.q8 && (whole || grouped)) {
             p.Mo = static_cast<float*>(ti.st.m.data);
             p.Vo = static_cast<float*>(ti.st.v.data);

@@ -74,7 +74,7 @@ hipError_t launch_pieces_in_place(GemmGroup& g, Epilogue epi, hipStream_t stream
 // The product in K pieces with the update block of Algorithm 2 on their sum, in one launch: every tile's pieces in one workgroup.  Operands as
 // for Epilogue::Adam of launch_tile_group.  bf16: the results are those of `splits` slabs and the Adam kernel, to the bit; fp32: the contraction is cut in 16.
 // tiles32: 32 x 32 tiles of the launches that share the chip.
-bool k_groups_pay(const GemmProblem& p, DType dt, int rank, int pieces, long tiles32);
+bool k_groups_pay(int64_t K, DType dt, int rank, int pieces, long tiles32);  // for one tensor; whether a call takes them: pieces_of_call
 hipError_t launch_k_groups(GemmGroup& g, DType dt, hipStream_t stream);
 constexpr long kDirectItems = 150;  // 128 x 128 tiles (times K pieces) from which a product may take the direct-load kernel (gemm_tile.hip)
 int direct_pieces(const GemmProblem& p, DType dt, bool b_kcontig, int most);

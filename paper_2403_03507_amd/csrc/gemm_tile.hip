@@ -271,11 +271,10 @@ bool pieces_add_up_in_place(bool left, int64_t K, int64_t ldim, int64_t r) {
 //   one round of its tiles   1024 x 1024 at r = 128 22.5 / 17.9, 28.0 / 23.9; 1024 x 2736 at r = 64 28.0 / 22.7, 36.2 / 30.6; 2048 x 2048 at r = 128 39.2 / 37.3, 47.8 / 46.1
 //   more to K = 768          768 x 2048 at r = 256 (512) 35.6 / 33.9, 43.6 / 41.6; 1024 x 2736 at r = 192 (516) 47.2 / 51.9, 1536 x 1536 at r = 192 (288) 41.2 / 44.1,
 //                            2048 x 5504 at r = 64 (344) 57.3 / 61.7, three 1664 x 1664 at r = 48 in one call (312) 48.0 / 51.0
-bool k_groups_pay(const GemmProblem& p, DType dt, int rank, int pieces, long tiles32) {
-  if (pieces < 2 || pieces > kMaxTilePieces || !tile_problem_fits(p, dt, p.b_kcontig != 0)) return false;
-  if (dt == DType::F32)
-    return pieces == kMaxTilePieces && (p.K <= 768 || (p.K <= 2048 && tiles32 <= 256));
-  return p.K <= 1024 || (p.K <= 2048 && rank > 128);
+bool k_groups_pay(int64_t K, DType dt, int rank, int pieces, long tiles32) {
+  if (pieces < 2 || pieces > kMaxTilePieces) return false;
+  if (dt == DType::F32) return pieces == kMaxTilePieces && (K <= 768 || (K <= 2048 && tiles32 <= 256));
+  return K <= 1024 || (K <= 2048 && rank > 128);
 }
 
 hipError_t launch_pieces_in_place(GemmGroup& g, Epilogue epi, hipStream_t stream) {

@@ -72,3 +72,29 @@ def test_fp32_contraction_in_one_workgroup(k, r, extra, pad, left):
     assert bool(((W.double() - want).abs() <= 0.51 * ulp + n_err).all())
     assert not torch.equal(W, W0)
     opt.close()
+
+
+# A call takes the groups where they spare its Adam launch: one number of pieces (bf16), nothing in slabs, no R small enough for Adam to stay a launch
+@pytest.mark.parametrize("dtype,rank,shapes,adam", [
+    ("bf16", 32, [(512, 640), (600, 520)], 0), ("bf16", 32, [(512, 640), (768, 1024)], 1), ("bf16", 64, [(1024, 1024), (2304, 2304)], 1),
+    ("bf16", 64, [(768, 768), (200, 1000)], 1), ("bf16", 66, [(768, 768), (200, 1000)], 0), ("bf16", 8, [(768, 768), (7, 40)], 1),
+    ("f32", 32, [(512, 640), (1100, 600)], 0), ("f32", 32, [(512, 640), (2304, 2304)], 1), ("f32", 64, [(512, 640)] + [(1024, 1024)] * 4, 1),
+    ("f32", 64, [(768, 768), (200, 1000)], 1), ("f32", 66, [(768, 768), (200, 1000)], 0)])
+def test_calls_that_take_the_groups(dtype, rank, shapes, adam):
+    rank = min(rank, min(min(s) for s in shapes))
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(rank)
+    rand = lambda *s: torch.randn(*s, generator=g, device="cuda").to(td)
+    W, G = [0.02 * rand(*s) for s in shapes], [rand(*s) for s in shapes]
+    opt = gb.GaLore(W, rank, update_gap=1 << 30, auto_refresh=False)
+    for p in opt.proj:
+        p.copy_(rand(*p.shape) / 16)
+    gb.galore_profile_start(opt.ctx)
+    opt.step(W, G, 1e-3)
+    assert gb.galore_profile_stop(opt.ctx)["adam"][1] == adam
+    for i, (m, n) in enumerate(shapes):
+        a, b = (opt.proj[i].t(), G[i]) if m <= n else (G[i], opt.proj[i])
+        R, scale = a.double() @ b.double(), a.double().abs() @ b.double().abs()
+        # fp32 sums of min(m, n) products, whatever their order
+        assert bool(((opt.M[i].double() - (1 - float(torch.tensor(0.9))) * R).abs() <= 0.1 * 2.0 ** -24 * (min(m, n) + 8) * scale).all()), i
+    opt.close()
