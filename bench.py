@@ -32,11 +32,11 @@ PEAK_HBM_GBS = 8000.0
 TRAFFIC_SOURCES = ["gemm_mfma_dl.hpp", "gemm_proj_dl.hpp", "proj.hip", "gemm_mfma.hpp", "gemm_dispatch.hpp", "common.hpp", "adam.hip", "adam_entry.hpp",
                    "gemm_tile.hpp", "gemm_tile.hip", "api.hip"]  # the last two choose the kernel of a projection and of a weight update
 MEASURED_TRAFFIC_7B = {
-    "sources": "9a514d58f176ceff",
+    "sources": "c63d8c65c01e18a2",
     "bytes": {   # read (2 x FETCH_SIZE KiB x 1024) + written (WRITE_SIZE KiB x 1024)
-        "project_left": (712.6e6 + 218.9e6) + (16.8e6 + 1.0e6),   # the grouped projection launch of both orientations + the sum of the split tiles' slabs
-        "project_left_fused_adam": (1400.6e6 + 637.4e6) + (19.0e6 + 2.6e6),
-        "back": 1200.1e6 + 404.8e6,
+        "project_left": (714.3e6 + 219.0e6) + (16.8e6 + 1.0e6),   # the grouped projection launch of both orientations + the sum of the split tiles' slabs
+        "project_left_fused_adam": (1424.2e6 + 638.3e6) + (19.0e6 + 2.6e6),
+        "back": 1186.7e6 + 404.9e6,
         "adam": (471.9e6 + 135.3e6) + (393.2e6 + 112.7e6),
     },
 }

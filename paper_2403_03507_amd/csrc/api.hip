@@ -608,13 +608,14 @@ bool library_streams_ready(const galore_ctx* ctx) {
   return ctx->fork_ev != nullptr;
 }
 
-// A bf16 step that the chip takes 150 to 190 us for by run_step_chunk's estimate gains from a second chain above rank 256, where one chain's projection
-// leaves most of its second round of 128 x 128 tiles (two a CU) empty, or takes large tiles that two chains would not.  One / two / three chains, us: 2048 / 5504 at
-// r = 257 (579 tiles) 182 / 165 / 164, r = 288 176 / 160 / 159, 1920 / 5120 at r = 320 (540) 139 / 126 / 132, 1600 / 4288 at r = 448 138 / 123 / 130, 1536 / 4096 at
-// r = 512 126 / 118 / 137, two 1280 / 3456 layers at r = 320 134 / 130 / 138, on large tiles in one chain 1792 / 4864 at r = 384 142 / 125 / 132.  Not with one round:
-// 1792 / 4864 at r = 352 (510) 128 / 139 / 142; nor where several chains count as large together: 1664 / 4480 at r = 448 141 / 150 / 148, 1792 / 4864 at r = 448
-// 153 / 158 / 160; nor where a rank of no multiple of 64 keeps the weight update on small tiles too: 1792 / 4864 at r = 400 153 / 163 / 168, 1664 / 4480 at r = 544
-// 166 / 172 / 181; nor at r = 256: 2176 / 5824 125 / 130 / 141.
+// A bf16 step that the chip takes 150 to 190 us for by run_step_chunk's estimate gains from a second chain where one chain's projection
+// leaves most of its second round of 128 x 128 tiles (two a CU) empty, or takes large tiles that two chains would not.  One / two / three chains, us:
+//   more than 512 tiles     2048 / 5504 at r = 257 (579) 182 / 165 / 164, r = 288 176 / 160 / 159, 1920 / 5120 at r = 320 (540) 139 / 126 / 132, two 1536 / 4096 layers at
+//                           r = 160 (576) 163 / 145 / 148, two 1280 / 3456 at r = 320 (726) 134 / 130 / 138, 1536 / 4096 at r = 512 (576) 126 / 118 / 137; not 1792 / 4864 at r = 352 (510)
+//                           128 / 139 / 142, 2176 / 5824 at r = 256 (412) 125 / 130 / 141
+//   large tiles in one      1792 / 4864 at r = 384 142 / 125 / 132, 1536 / 4096 at r = 576 140 / 133 / 150; not in several together (count_over_chains): 1664 / 4480 at
+//   chain only              r = 448 141 / 150 / 148, 1792 / 4864 at r = 448 153 / 158 / 160
+//   ranks of 64s with them  others keep the weight update on small tiles too: 1792 / 4864 at r = 400 153 / 163 / 168, 1664 / 4480 at r = 544 166 / 172 / 181
 bool second_chain_pays(const galore_ctx* ctx, const std::vector<StepItem>& items) {
   const int r = ctx->hp.rank;
   long t256 = 0, t128 = 0;
@@ -623,7 +624,7 @@ bool second_chain_pays(const galore_ctx* ctx, const std::vector<StepItem>& items
     t256 += projection_tiles256(ctx, it);
     t128 += (long)((r + 127) / 128 * ((ctx->tensors[it.tensor].ldim + 127) / 128));
   }
-  return r > 256 && (t256 >= kLargeProjectionTiles ? r % 64 == 0 : t128 > 512);
+  return r > 128 && (t256 >= kLargeProjectionTiles ? r % 64 == 0 : t128 > 512);
 }
 
 // One chunk of the step: carve the workspace, split the tensors into chains of similar cost and

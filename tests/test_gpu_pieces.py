@@ -64,14 +64,15 @@ def test_forked_chains_count_their_tiles_together(d, f, rank, large):
     opt.close()
 
 
-# One layer by estimate between 150 and 190 us: a second chain above rank 256 where one chain leaves a second round of 128 x 128 tiles (512 a round) nearly empty
-# (2048: 579, 1801: 531) or takes large tiles alone (r = 384), not with one round (1792 at r = 352: 510), on large tiles either way (r = 448), with
-# a rank of no multiple of 64 beside large tiles (r = 400), at r = 256, or in fp32
-@pytest.mark.parametrize("d,f,rank,dtype,chains", [(2048, 5504, 288, "bf16", 2), (1801, 4871, 333, "bf16", 2), (1792, 4864, 384, "bf16", 2), (1792, 4864, 352, "bf16", 1),
-                                                   (1664, 4480, 448, "bf16", 1), (1792, 4864, 400, "bf16", 1), (2048, 5504, 256, "bf16", 1), (1024, 2736, 200, "f32", 1)])
-def test_chains_of_a_short_step(d, f, rank, dtype, chains):
+# Steps by estimate between 150 and 190 us: a second chain where one chain leaves a second round of 128 x 128 tiles (512 a round) nearly empty
+# (2048: 579, 1801: 531, two layers of 1536: 576) or takes large tiles alone (r = 384), not with one round (1792 at r = 352: 510, 2048 at r = 256: 386), on large
+# tiles either way (r = 448), with a rank of no multiple of 64 beside large tiles (r = 400), or in fp32
+@pytest.mark.parametrize("layers,d,f,rank,dtype,chains", [
+    (1, 2048, 5504, 288, "bf16", 2), (1, 1801, 4871, 333, "bf16", 2), (2, 1536, 4096, 160, "bf16", 2), (1, 1792, 4864, 384, "bf16", 2), (1, 1792, 4864, 352, "bf16", 1),
+    (1, 1664, 4480, 448, "bf16", 1), (1, 1792, 4864, 400, "bf16", 1), (1, 2048, 5504, 256, "bf16", 1), (1, 1024, 2736, 200, "f32", 1)])
+def test_chains_of_a_short_step(layers, d, f, rank, dtype, chains):
     tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
-    shapes = [(d, d)] * 4 + [(d, f)] * 2 + [(f, d)]
+    shapes = ([(d, d)] * 4 + [(d, f)] * 2 + [(f, d)]) * layers
     g = torch.Generator(device="cuda").manual_seed(rank)
     rand = lambda *s: torch.randn(*s, generator=g, device="cuda").to(tdt)
     W0, G, P = [0.02 * rand(*s) for s in shapes], [rand(*s) for s in shapes], [rand(min(s), rank) / 64 for s in shapes]
