@@ -59,8 +59,9 @@ def test_fp32_contraction_in_one_workgroup(k, r, extra, pad, left):
     opt.step([W], [strided(G, pad) if pad else G], 1e-2)
     b1, b2 = float(torch.tensor(0.9)), float(torch.tensor(0.99))
     M, V = b1 * M0 + (1 - b1) * R, b2 * V0 + (1 - b2) * R * R
-    # every entry: k products summed in at most k / 16 + 16 roundings, of 2^-24 of the sum of their absolute values each, and a few of M and V themselves
-    bound = 2.0 ** -24 * (k / 16 + 16) * (P.abs().t() @ G.double().abs() if m <= n else G.double().abs() @ P.abs())
+    # Every entry: the K steps of 64 are dealt to 4 groups, a wavefront sums 16 products of each of its group's steps, and the 16 sums are added: so many roundings at
+    # most, of 2^-24 of the sum of the products' absolute values each, and a few of M and V themselves
+    bound = 2.0 ** -24 * (16 * -(--(-k // 64) // 4) + 15) * (P.abs().t() @ G.double().abs() if m <= n else G.double().abs() @ P.abs())
     dM, dV = (1 - b1) * bound + 2.0 ** -22 * (M0.abs() + R.abs()), (1 - b2) * 2 * R.abs() * bound + 2.0 ** -21 * (V0 + R * R)
     assert bool(((opt.M[0].double() - M).abs() <= dM).all()) and bool(((opt.V[0].double() - V).abs() <= dV).all())
     N = (M / (1 - b1 ** 8)) / ((V / (1 - b2 ** 8)).sqrt() + 1e-8)
@@ -71,6 +72,38 @@ def test_fp32_contraction_in_one_workgroup(k, r, extra, pad, left):
     n_err = 1e-2 * 0.25 * (P.abs() @ dN if m <= n else dN @ P.abs().t())
     assert bool(((W.double() - want).abs() <= 0.51 * ulp + n_err).all())
     assert not torch.equal(W, W0)
+    opt.close()
+
+
+# short side, rank, pieces: the same bits as the product of each piece, the sums in slab order, Adam and the weight update as calls of their own
+@pytest.mark.parametrize("k,r,pieces", [(512, 64, 2), (700, 33, 2), (768, 128, 3), (1000, 40, 3), (1024, 96, 4), (1100, 200, 4), (2048, 136, 4)])
+@pytest.mark.parametrize("left", [True, False])
+def test_pieces_in_one_workgroup_have_the_bits_of_slabs(k, r, pieces, left):
+    l = k + 65
+    g = torch.Generator(device="cuda").manual_seed(k + r)
+    rand = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    m, n = (k, l) if left else (l, k)
+    W, G = (0.02 * rand(m, n)).to(torch.bfloat16), rand(m, n).to(torch.bfloat16)
+    opt = gb.GaLore([W], r, update_gap=1 << 30, auto_refresh=False)
+    opt.proj[0].copy_(torch.linalg.qr(rand(k, r))[0])
+    opt.M[0].copy_(0.1 * rand(*opt.M[0].shape))
+    opt.V[0].copy_(0.1 + 0.1 * rand(*opt.V[0].shape).square())
+    opt.set_step(0, 7)
+    M, V, W1 = opt.M[0].clone(), opt.V[0].clone(), W.clone()
+    Pt = opt.proj[0].t().contiguous()
+    steps, R = -(-k // 128), None   # K steps of 128
+    for s in range(pieces):
+        part = slice(s * steps // pieces * 128, min((s + 1) * steps // pieces * 128, k))
+        one = torch.empty_like(M)
+        gb.galore_project(Pt[:, part], G[part] if left else G[:, part], one)
+        R = one if R is None else R + one
+    N = torch.empty(l, r, dtype=torch.bfloat16, device="cuda")
+    gb.galore_adam(R, M, V, N, left, 0.9, 0.999, 1e-8, 8)
+    gb.galore_project_back(opt.proj[0], N, W1, 1e-2, 0.25)
+    gb.galore_profile_start(opt.ctx)
+    opt.step([W], [G], 1e-2)
+    assert gb.galore_profile_stop(opt.ctx)["adam"][1] == 0
+    assert torch.equal(opt.M[0], M) and torch.equal(opt.V[0], V) and torch.equal(W, W1)
     opt.close()
 
 

@@ -6,20 +6,27 @@ from paper_2403_03507_amd import binding as gb
 
 pytestmark = pytest.mark.gpu
 
-# rank and tensors (rows, cols, dtype) of one call; short sides of 512 and more, so that contractions may be cut
+# rank and tensors (rows, cols, dtype) of one call, short sides of 512 and more, so that contractions may be cut; weight updates and separate Adam
+# passes of one step by setting of galore_set_concurrency
 CALLS = {
-    # one launch of 512 tiles of 64 x 64, or three of 192, 192 and 128: a call long enough to be divided into chains
-    "eight 4096": (8, [(4096, 4096, torch.bfloat16)] * 8),
-    # 120 tiles, cut into 4 pieces, in one chain
-    "mixed": (40, [(512, 640, torch.float32), (1300, 520, torch.float32), (768, 777, torch.bfloat16), (640, 512, torch.bfloat16), (2050, 600, torch.float32)]),
+    # one launch of 512 tiles of 64 x 64, or two (at this rank never three) of 256: a call long enough to be divided into chains; R of 32 Ki entries
+    "eight 4096": (8, [(4096, 4096, torch.bfloat16)] * 8, {3: (2, 2), 2: (2, 2), 1: (1, 1)}),
+    # three chains, twice, as the workspace takes ten tensors at a time: the other eight are six more of the first block of 16 (whole contractions) and the two of
+    # the next, of 132 and 44 tiles, which are cut, in slabs (K > 2048; the other follows)
+    "eighteen": (256, [(520, 20000, torch.bfloat16)] * 16 + [(2051, 2112, torch.bfloat16), (520, 700, torch.bfloat16)], {3: (6, 2), 2: (4, 2), 1: (2, 1)}),
+    # slabs of both dtypes and both sides
+    "slabs": (33, [(2052, 2100, torch.bfloat16), (2100, 2052, torch.float32), (2300, 2055, torch.bfloat16), (2052, 2112, torch.float32)], {3: (2, 2), 2: (2, 2), 1: (2, 2)}),
+    # one chain: 64 fp32 tiles cut into 4 pieces, in one workgroup each, and 23 of bf16 in 3 and 2, which leave as slabs
+    "mixed": (40, [(512, 640, torch.float32), (1300, 520, torch.float32), (768, 777, torch.bfloat16), (640, 512, torch.bfloat16), (2050, 600, torch.float32)],
+              {3: (2, 1), 2: (2, 1), 1: (2, 1)}),
     # more tensors than a launch takes, both dtypes
-    "twenty": (32, [(512, 2048, torch.float32), (2048, 512, torch.bfloat16)] * 10),
+    "twenty": (32, [(512, 2048, torch.float32), (2048, 512, torch.bfloat16)] * 10, None),
 }
 
 
 @pytest.mark.parametrize("name", list(CALLS))
 def test_chains_workspaces_and_the_static_array_give_the_same_bits(name):
-    rank, tensors = CALLS[name]
+    rank, tensors, launches = CALLS[name]
     g = torch.Generator(device="cuda").manual_seed(17)
     rand = lambda *s: torch.randn(*s, generator=g, device="cuda")
     W0 = [(0.02 * rand(m, n)).to(dt) for m, n, dt in tensors]
@@ -28,7 +35,9 @@ def test_chains_workspaces_and_the_static_array_give_the_same_bits(name):
     results = {}
     for variant in ("3 chains", "2 chains", "1 chain", "fused", "static", "overlap", "workspace x 4"):
         W = [w.clone() for w in W0]
-        opt = gb.GaLore(W, rank, update_gap=1 << 30, workspace_factor=4 if variant in ("overlap", "workspace x 4") else 1)
+        factor = 4 if variant in ("overlap", "workspace x 4") else 1
+        nbytes = factor * 10 * 6 * 256 * 20000 if name == "eighteen" else None   # R and N of ten tensors
+        opt = gb.GaLore(W, rank, update_gap=1 << 30, workspace_bytes=nbytes, workspace_factor=factor)
         for i, p in enumerate(P):
             opt.proj[i].copy_(p)
             opt.set_step(i, 7)
@@ -36,8 +45,14 @@ def test_chains_workspaces_and_the_static_array_give_the_same_bits(name):
             gb.galore_set_concurrency(opt.ctx, int(variant[0]))
         opt.set_fused_adam(variant == "fused")
         opt.set_call_overlap(2 if variant == "overlap" else 0)
-        for _ in range(2):
+        for step in range(2):
+            counted = launches and step == 0 and "chain" in variant
+            if counted:
+                gb.galore_profile_start(opt.ctx)
             (opt.step_static if variant == "static" else opt.step)(W, G, 1e-3)
+            if counted:
+                stages = gb.galore_profile_stop(opt.ctx)
+                assert (stages["back"][1], stages["adam"][1]) == launches[int(variant[0])], variant
         opt.join()
         torch.cuda.synchronize()
         results[variant] = W + [x.clone() for x in opt.M + opt.V]

@@ -19,10 +19,17 @@ def _tile(problems, update=False):
     """The tile of a launch of the small-tile GEMM over problems (M, N, K), as csrc/gemm_tile.hip chooses it (the constants are read
     from there: where the rule takes another form, this has to follow)."""
     src = open(os.path.join(os.path.dirname(gb.__file__), "csrc", "gemm_tile.hip")).read()
+    padding = re.search(r"if \((\d+) \* items128 > (\d+) \* items64\) items128 = 0;\s*if \((\d+) \* items96 > (\d+) \* items64\) items96 = 0;", src)
     rule = re.search(r"if \(items128 >= (\d+) && \(!update \|\| longest >= (\d+)\)\) return launch<T, 128, 128>\(g, epi, stream\);\s*"
                      r"if \(items96 >= \(update \? (\d+) : (\d+)\)\) return launch<T, 128, 64>", src)
     many128, long_k, many96_update, many96 = (int(x) for x in rule.groups())
-    count = lambda bm, bn: sum(-(-m // bm) * -(-n // bn) for m, n, _ in problems)
+    a128, b128, a96, b96 = (int(x) for x in padding.groups())
+    assert all(k % 64 for _, _, k in problems)   # nothing for the tile with direct loads
+
+    def count(bm, bn):
+        n64, items = (sum(-(-m // x) * -(-n // y) for m, n, _ in problems) for x, y in ((64, 64), (bm, bn)))
+        a, b = (a128, b128) if bn == 128 else (a96, b96)
+        return 0 if not update and a * items > b * n64 else items
     if count(128, 128) >= many128 and (not update or max(k for _, _, k in problems) >= long_k):
         return 128, 128
     return (128, 64) if count(128, 64) >= (many96_update if update else many96) else (64, 64)
@@ -36,7 +43,7 @@ def _update(shapes, rank):
     return [(m, n, rank) for m, n in shapes]
 
 
-def _steps(shapes, rank, dtype, steps=2, fused=False, pad=0, static=False):
+def _steps(shapes, rank, dtype, steps=2, fused=False, pad=0, static=False, adam_launches=None):
     # M, V: fp32 sums of at most a few thousand products, 1e-5 as everywhere; fp32 W: 1e-5; bf16 W per entry.
     # fp32 tensors start from moments as earlier steps leave them: from zero moments the first N is R / (|R| + eps), where an entry of R
     # at rounding distance of zero (1e-9 here, against eps = 1e-8) moves W by up to lr alpha |P column| = 2.5e-3, i.e. 3e-4
@@ -64,7 +71,11 @@ def _steps(shapes, rank, dtype, steps=2, fused=False, pad=0, static=False):
         oracles.append(o)
     for step in range(steps):
         G = [s.grad(step) for s in srcs]
+        if adam_launches is not None:
+            gb.galore_profile_start(opt.ctx)
         (opt.step_static if static else opt.step)(Wd, [lay(g.cuda()) for g in G], lr)
+        if adam_launches is not None:
+            assert gb.galore_profile_stop(opt.ctx)["adam"][1] == adam_launches
         torch.cuda.synchronize()
         for i, o in enumerate(oracles):
             o.step(to64(G[i]), lr)
@@ -91,8 +102,16 @@ def test_rows_at_any_element_offset(dtype):
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("shapes,rank", [([(513, 521)], 24), ([(521, 513)], 9), ([(1030, 1024)], 40), ([(512, 600), (1100, 777)], 31)])
 def test_contractions_in_pieces(dtype, shapes, rank):
-    # few tiles and contractions of 512 and more: 2 to 4 pieces, the last one ragged, summed by the Adam kernel
-    _steps(shapes, rank, dtype)
+    # few tiles and contractions of 512 and more: 2 to 4 pieces, the last one ragged, summed by the workgroup that forms them (bf16: 2 and 3 in one call leave as slabs)
+    _steps(shapes, rank, dtype, adam_launches=1 if dtype == "bf16" and len(shapes) == 2 else 0)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("shapes,rank", [([(2052, 2100)], 33), ([(2100, 2052)], 40), ([(2049, 2051)], 130), ([(2060, 2055), (2055, 2300)], 41)])
+@pytest.mark.parametrize("pad", [0, 3])
+def test_pieces_summed_by_the_adam_kernel(dtype, shapes, rank, pad):
+    # contractions above 2048: slabs, whatever the dtype; each R has 64 Ki entries and more, so that Adam would run in the projection were they whole
+    _steps(shapes, rank, dtype, pad=pad, steps=1, adam_launches=1)
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
@@ -171,8 +190,11 @@ def test_large_tile_projection_of_a_padded_copy():
     _steps([(640, 13829)], 640, "bf16", steps=1)
 
 
-def test_static_scratch_holds_the_pieces():
-    _steps([(1030, 1024), (512, 600)], 40, "bf16", static=True)
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_static_scratch_holds_the_pieces(dtype):
+    # slabs for the first two, pieces in one workgroup for the third
+    _steps([(2052, 2100), (2100, 2052), (512, 600)], 40, dtype, adam_launches=1)
+    _steps([(2052, 2100), (2100, 2052), (512, 600)], 40, dtype, static=True)
 
 
 @pytest.mark.parametrize("m,n,rank,tile", [(300, 22531, 129, (128, 128)), (22531, 300, 129, (64, 64)), (203, 31939, 66, (128, 64)), (200, 8203, 66, (64, 64))])

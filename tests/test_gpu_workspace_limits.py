@@ -50,9 +50,10 @@ def _context_in(opt, buf, nbytes):
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("copies", [0, 1.5, 2.9, 8])
 def test_step_whose_k_pieces_get_what_room_there_is(dtype, copies):
-    # 223 tiles of 64 x 64 over a contraction of 512: up to 3 (bf16: 2) pieces of R where the workspace has room for them beside
-    # R and N, else fewer; the results agree to the fp32 rounding of R
-    m, n, r = 512, 14272, 64
+    # Three pieces that leave as slabs of R where the workspace has room for them beside R and N, else fewer; the results agree to the fp32
+    # rounding of R.  fp32: 175 tiles of 64 x 64, too few for a workgroup to add its pieces and too many for 16 pieces in one; bf16:
+    # 223 tiles over a contraction too long for K groups at this rank.  Shapes whose step takes more than their refresh.
+    m, n, r = (512, 11200, 64) if dtype == "f32" else (1027, 14272, 64)
     tdt = torch.float32 if dtype == "f32" else torch.bfloat16
     g = torch.Generator(device="cuda").manual_seed(3)
     W0 = (0.02 * torch.randn(m, n, generator=g, device="cuda")).to(tdt)
@@ -64,6 +65,7 @@ def test_step_whose_k_pieces_get_what_room_there_is(dtype, copies):
     for nbytes in (8 * room, None):
         W = W0.clone()
         opt = gb.GaLore([W], r, update_gap=1000, auto_refresh=False)
+        one = nbytes is None and copies < 1   # room for one R: a whole contraction
         if nbytes is None:
             nbytes = int(least + copies * 4 * r * n) // 256 * 256
         buf = torch.full((nbytes + 4096,), 0x55, dtype=torch.uint8, device="cuda")
@@ -73,13 +75,18 @@ def test_step_whose_k_pieces_get_what_room_there_is(dtype, copies):
         opt.M[0].normal_(generator=torch.Generator(device="cuda").manual_seed(4))
         opt.V[0].fill_(1.0)
         opt.set_step(0, 1000)
+        gb.galore_profile_start(opt.ctx)
         for x in G:
             opt.step([W], [x], 1e-3)
+        stages = gb.galore_profile_stop(opt.ctx)
+        assert stages["adam"][1] == (0 if one else 2)   # an R this large runs Adam in its projection unless its pieces leave as slabs
         torch.cuda.synchronize()
         assert bool((buf[nbytes:] == 0x55).all())
         out.append((to64(W), to64(opt.M[0]), to64(opt.V[0])))
         opt.close()
-    assert relF(out[1][1], out[0][1]) <= 1e-6 and relF(out[1][2], out[0][2]) <= 1e-6   # sums of 512 fp32 terms in another order: 2e-7
+    assert relF(out[1][1], out[0][1]) <= 1e-6 and relF(out[1][2], out[0][2]) <= 1e-6   # sums of 512 (bf16 1027) fp32 terms in another order: 2e-7
+    # all three pieces in either workspace: the same bits; fewer in the smaller one: other roundings somewhere in 900 000 entries
+    assert np.array_equal(out[1][1], out[0][1]) == (copies > 2)
     if dtype == "f32":
         # 1e-6 of an update that is itself under 1e-2 of W, and the rounding of W: half an ulp, 6e-8 at most, in each of two steps
         assert relF(out[1][0], out[0][0]) <= 1.3e-7
