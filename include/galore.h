@@ -203,23 +203,25 @@ galore_status galore_refresh_subspace(galore_ctx* ctx, const galore_tensor* G, i
  * stream and on up to two library-owned streams of default priority, forked from and joined
  * back into the context's stream with events inside the call, so tail waves of one GEMM and the
  * bandwidth-bound Adam pass overlap with another chain's MFMA work (a call whose step takes the chip less time than
- * the forking takes the host runs as one chain; fp32 tensors and ranks below 256 run as two at most, where a
- * third launch at a time only gets in the way of the others).  1 = strictly serial on the
+ * the forking takes the host runs as one chain; fp32 tensors, ranks below 256 and calls shortly above that time run as two at
+ * most, where a third launch at a time only gets in the way of the others).  1 = strictly serial on the
  * context's stream.  W, M, V agree between settings to the fp32 rounding of R, and bit for bit whenever
  * the projection launches cut no tile into K pieces (short sides under 512) or cut the same tiles
  * the same way: a large projection (160 and more tiles of 256 x 256) sums the K range of a tile that does not fill a round
  * of the chip in pieces, and which tiles those are depends on what shares the launch.  (A projection of few
- * tiles is cut into pieces as well; how many depends on the tensors of the call and on galore_workspace_bytes' room
- * for them, not on the setting.)  For one setting and one
+ * tiles is cut into pieces as well; how many depends on the tensors of the call, not on the setting.  Pieces that the
+ * projection adds where it forms them, and runs Adam on, take no room; others are matrices of R's size in the workspace, and
+ * where it lacks the room for all there are fewer.)  For one setting and one
  * sequence of calls results are bit-identical from run to run. */
 galore_status galore_set_concurrency(galore_ctx* ctx, int32_t lanes);
 
 /* Adam inside the projection (off by default; 1 = on).  When on, a tensor with fp32 moments gets the update block of
  * Algorithm 2 (moments, bias correction, N) computed in its projection GEMM's epilogue, on the accumulators: R is never
  * written to memory and read back, and the step of such a tensor is two kernels instead of three.  Exceptions keep the
- * separate Adam kernel: 8-bit moments, a projection whose contraction is cut into pieces (few tiles), a side of fewer
- * than 8 elements.  When off, tensors that share a small launch may still take the epilogue where the library expects
- * it to be faster.  Both paths evaluate the
+ * separate Adam kernel: 8-bit moments, a projection of few tiles whose contraction leaves in pieces (galore_set_concurrency), a
+ * side of fewer than 8 elements.  Whatever the setting, the library uses the epilogue where it expects it to be faster: for
+ * tensors that share a small launch, and for pieces that one workgroup forms and adds (contractions up to 2048; fp32 at any
+ * length at low ranks).  Both paths evaluate the
  * same fp32 expression on the same R: W, M, V are bit-identical between the two settings. */
 galore_status galore_set_fused_adam(galore_ctx* ctx, int32_t on);
 
